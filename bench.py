@@ -319,7 +319,7 @@ def tri_probe(Sampler, torch, n_rep=1024, L=96, sweeps=200):
     return {"config": f"{n_rep} triangular replicas of {L}x{L}, beta_c = ln(3)/4, {sweeps} sweeps",
             "attempts_per_ns": round(sites * sweeps / (ms * 1e6), 1),
             "recorded_attempts_per_ns": round(sites * sweeps / (ms_rec * 1e6), 1),
-            "kernel": "k_nat_resident (lattices in LDS)",
+            "kernel": "k_plane_resident (lattices in LDS)",
             "stream_pass": {"kernel": "k_tri_pass4", "avg_launch_us": round(avg_s * 1e6, 2),
                             "attempts_per_ns": round(per_launch / avg_s / 1e9, 1),
                             "GBs_algorithmic": round(gbs, 1),
@@ -360,7 +360,7 @@ def hc_probe(Sampler, torch, n_rep=256, L=32, sweeps=200):
     return {"config": f"{n_rep} simple-cubic replicas of {L}^3, beta 0.2216546, {sweeps} sweeps",
             "attempts_per_ns": round(sites * sweeps / (ms * 1e6), 1),
             "recorded_attempts_per_ns": round(sites * sweeps / (ms_rec * 1e6), 1),
-            "kernel": "k_nat_resident (lattices in LDS)",
+            "kernel": "k_plane_resident (lattices in LDS)",
             "stream_pass": {"kernel": "k_hc_pass4", "avg_launch_us": round(avg_s * 1e6, 2),
                             "attempts_per_ns": round(sites / 2 / avg_s / 1e9, 1),
                             "GBs_algorithmic": round(gbs, 1),

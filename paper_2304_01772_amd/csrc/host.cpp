@@ -2344,7 +2344,7 @@ TriArgs tri_args(spinmc_ctx* c, int32_t* stats) {
     a.R = c->R;
     a.width = c->width;
     int mb = 0;
-    bool l12 = true, l8 = true;
+    bool l12 = true, l8 = true, even = true;
     a.model = c->reps[0].dev.model;
     for (const HostRep& h : c->reps) {
         l8 = l8 && h.dev.Lx % 8 == 0;
@@ -2353,10 +2353,12 @@ TriArgs tri_args(spinmc_ctx* c, int32_t* stats) {
         else
             mb = std::max(mb, (h.dev.Lx * h.dev.Ly / 3 + 3) / 4);
         l12 = l12 && h.dev.Lx % 12 == 0;
+        even = even && h.dev.Lx % (a.model == kModelIsingHC ? 16 : 24) == 0;
     }
     a.max_blocks = mb;
     a.all_lx12 = l12 ? 1 : 0;
     a.all_lx8 = l8 ? 1 : 0;
+    a.even_blocks = even ? 1 : 0;
     a.max_sites = c->max_sites;
     return a;
 }
@@ -2530,7 +2532,7 @@ int tri_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
             const int rows = re > 0 ? (done + k) / re - done / re : 0;
             const int lds_k = lds + 16 * rows;
             e = timed(c, SPINMC_K_RESIDENT,
-                      [&] { return launch_nat_resident(a, k, done, re, lds_k, c->stream); },
+                      [&] { return launch_plane_resident(a, k, done, re, lds_k, c->stream); },
                       c->stream);
             if (e == hipSuccess) e = launch_advance(c->d_t, (uint64_t)k, c->stream);
             done += k;

@@ -24,6 +24,8 @@ struct TriArgs {
     int32_t all_lx12;         // every Lx a multiple of 12: the span kernel
     int32_t model;            // kModelIsingTri or kModelIsingHC (one per context)
     int32_t all_lx8;          // every Lx a multiple of 8: the chain / cubic span kernel
+    int32_t even_blocks;      // every plane row an even number of Philox blocks (Lx a
+                              // multiple of 24 triangular, 16 chain / cubic)
 };
 
 hipError_t launch_tri_init(const TriArgs& a, hipStream_t s);
@@ -39,7 +41,7 @@ hipError_t launch_tri_observables(const TriArgs& a, double* obs, hipStream_t s);
 // The launch holds sweeps sw0 .. sw0 + n_sweeps - 1 of a call; with re > 0,
 // sweep k re of the call stores its statistics in stats row k - 1 (columns
 // 0..3; the caller zeroes the rows).
-hipError_t launch_nat_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
-                               hipStream_t s);
+hipError_t launch_plane_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
+                                 hipStream_t s);
 
 }  // namespace spinmc

@@ -117,77 +117,6 @@ __device__ __forceinline__ uint64_t keyed_threshold(const uint64_t* tab, int j, 
     return n > k ? 0ull : tab[7 * (1 - neg) + (k + 6) / 2 - n];
 }
 
-// Triangular: S, U, Dn are the 12-byte spans [x0, x0 + 12) of rows y, y - 1,
-// y + 1; the own sites are x0 + xc + 3u.  hl = flags of (y, x0 - 1) and
-// (y + 1, x0 - 1) added, hr = those of (y, x0 + 12) and (y - 1, x0 + 12).
-// Neighbour flags at position o: S[o -+ 1], U[o], U[o + 1], Dn[o], Dn[o - 1],
-// i.e. (S + Dn) moved up one byte position, (S + U) moved down one, U + Dn
-// in place.  A funnel shift by xc bytes brings the own sites to byte
-// positions 0, 3, 6, 9; their flips are shifted back.  Bytes of other
-// positions may read values another lane is writing: they never reach an
-// own site's count.
-__device__ __forceinline__ void tri_span(uint32_t (&S)[3], const uint32_t (&U)[3],
-                                         const uint32_t (&Dn)[3], uint32_t hl, uint32_t hr,
-                                         uint32_t xc, const uint32_t (&w)[4],
-                                         const uint64_t* lt) {
-    uint32_t m[4], A[3], B[3], C[4];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        m[i] = S[i] & kNegFlag;
-        const uint32_t mu = U[i] & kNegFlag, md = Dn[i] & kNegFlag;
-        A[i] = m[i] + md;
-        B[i] = m[i] + mu;
-        C[i] = mu + md;
-    }
-    m[3] = 0u;
-    C[0] += abyte(A[0], hl << 24, 3) + abyte(B[1], B[0], 1);
-    C[1] += abyte(A[1], A[0], 3) + abyte(B[2], B[1], 1);
-    C[2] += abyte(A[2], A[1], 3) + abyte(hr, B[2], 1);
-    C[3] = 0u;
-    // key bytes 2n + 16 [s < 0] with the own sites at bytes 0, 3, 6, 9
-    uint32_t K[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) K[i] = abyte(C[i + 1], C[i], xc) | (abyte(m[i + 1], m[i], xc) << 3);
-    const bool f0 = (uint64_t)w[0] < lt[(K[0] >> 1) & 15u];
-    const bool f1 = (uint64_t)w[1] < lt[(K[0] >> 25) & 15u];
-    const bool f2 = (uint64_t)w[2] < lt[(K[1] >> 17) & 15u];
-    const bool f3 = (uint64_t)w[3] < lt[(K[2] >> 9) & 15u];
-    // a flip negates the byte: s -> -s is s ^ 0xFE for s = +-1
-    const uint32_t F0 = (f0 ? 0xFEu : 0u) | (f1 ? 0xFE000000u : 0u);
-    const uint32_t F1 = f2 ? 0x00FE0000u : 0u;
-    const uint32_t F2 = f3 ? 0x0000FE00u : 0u;
-    if (xc == 0u) {
-        S[0] ^= F0;
-        S[1] ^= F1;
-        S[2] ^= F2;
-    } else {
-        const uint32_t sh = 4u - xc;  // a left shift by xc bytes
-        S[0] ^= abyte(F0, 0u, sh);
-        S[1] ^= abyte(F1, F0, sh);
-        S[2] ^= abyte(F2, F1, sh);
-    }
-}
-
-// Chain / square / cubic in natural layout (the lattice the LDS-resident
-// kernel holds): S the 8-byte span [x0, x0 + 8) of the own row, the own
-// sites x0 + 2u + par; N0, N1 the added flags of the neighbouring rows and
-// planes over the span; hl, hr the flags of (x0 - 1) and (x0 + 8).
-__device__ __forceinline__ void hc_span(uint32_t (&S)[2], uint32_t N0, uint32_t N1, uint32_t hl,
-                                        uint32_t hr, uint32_t par, const uint32_t (&w)[4],
-                                        const uint64_t* lt) {
-    const uint32_t m0 = S[0] & kNegFlag, m1 = S[1] & kNegFlag;
-    const uint32_t K0 = (N0 + abyte(m0, hl << 24, 3) + abyte(m1, m0, 1)) | (m0 << 3);
-    const uint32_t K1 = (N1 + abyte(m1, m0, 3) + abyte(hr, m1, 1)) | (m1 << 3);
-    const uint32_t o0 = 8u * par, o1 = 16u + 8u * par;  // bit offsets of the own bytes
-    const bool f0 = (uint64_t)w[0] < lt[(K0 >> (o0 + 1u)) & 15u];
-    const bool f1 = (uint64_t)w[1] < lt[(K0 >> (o1 + 1u)) & 15u];
-    const bool f2 = (uint64_t)w[2] < lt[(K1 >> (o0 + 1u)) & 15u];
-    const bool f3 = (uint64_t)w[3] < lt[(K1 >> (o1 + 1u)) & 15u];
-    const uint32_t e0 = 0xFEu << o0, e1 = 0xFEu << o1;
-    S[0] ^= (f0 ? e0 : 0u) | (f1 ? e1 : 0u);
-    S[1] ^= (f2 ? e0 : 0u) | (f3 ? e1 : 0u);
-}
-
 // Chain / square / cubic on the colour planes: S the four own bytes (plane
 // bytes j0 .. j0 + 3 of a row, own sites x = 2 j + par), N the added -1 flags
 // of the vertical partners (the other plane's rows y +- 1 and z +- 1, same
@@ -496,228 +425,388 @@ __global__ void k_tri_observables(TriArgs a, double* obs) {
     o[3] = M / N;
 }
 
-// All n_sweeps unrecorded sweeps in one launch, one workgroup per replica
-// with its lattice in LDS in natural order (converted from the colour planes
-// of global memory when loaded, and back when stored) and a barrier after
+// ------------------------------------------------ LDS-resident colour planes
+// All sweeps of a call in one launch, one workgroup per replica, its colour
+// planes in LDS in the order they have in global memory and a barrier after
 // every colour pass: the same decisions as the streamed passes, without the
-// per-pass launches and lattice round trips.  Needs Lx % 12 == 0 for the
-// triangular lattice (the four sites of a Philox block in one row) and
-// Lx % 8 == 0 for the chain / cubic lattices.
-// The statistics of k_tri_stats / k_hc_stats ([M, B1, B2, B3]) of an LDS
-// lattice, this thread's share: four sites per 32-bit word.  A -1 byte has
-// bit 7 set, so M = sites - 2 popc(v & 0x80808080); two +-1 bytes differ
-// iff their xor is 0xFE (7 bits), so a bond sum is sites - 2 popc(v ^ w) / 7
-// with w the word of the bond partners (byte funnel shifts for the x + 1
-// and, on the triangular lattice, the down-left partners).
-// The four sites (z, y, x0 .. x0 + 3) of natural index i = row Lx + x0
-// (x0 % 4 == 0, Lx % 8 == 0) as one natural-order word, and back: sites x0
-// and x0 + 2 are bytes (row, x0 / 2) and (row, x0 / 2 + 1) of plane
-// (x0 + y + z) & 1, sites x0 + 1 and x0 + 3 the same bytes of the other plane.
-__device__ __forceinline__ uint32_t hc_natural_word(const int8_t* lat, int i, int Lx, int Ly,
-                                                    int Lz) {
-    const int row = i / Lx, x0 = i - row * Lx, z = row / Ly, y = row - z * Ly;
-    const size_t psz = (size_t)Ly * Lz * (Lx >> 1);
-    const size_t pa = hc_byte(z, y, x0, Lx, Ly, Lz);
-    const size_t pb = ((x0 + y + z) & 1) ? pa - psz : pa + psz;
-    const uint32_t A = *reinterpret_cast<const uint16_t*>(lat + pa);
-    const uint32_t B = *reinterpret_cast<const uint16_t*>(lat + pb);
-    return __builtin_amdgcn_perm(B, A, 0x05010400u);  // bytes A0 B0 A1 B1
-}
+// per-pass launches and lattice round trips.  A spin is one byte, 1 for -1
+// and 0 for +1, so that sums of neighbour words need no masks.
+//
+// A lane owns NI items for the whole launch; an item is NB consecutive Philox
+// blocks of a plane row, 4 NB bytes at the same place of every plane, read as
+// one LDS access.  Their offsets are worked out once per launch (they are the
+// same in every pass), which leaves a pass the Philox rounds (57 of about 85
+// lane-cycles a block), the neighbour words and one table lookup and compare
+// per site.  (In natural order, where a 12- or 8-byte span holds four own
+// sites, the same passes took about 45 lane-instructions a site: 1024 x 96^2
+// triangular, 200 sweeps with every tenth recorded, 2705 us; 256 x 32^3, 100
+// sweeps and one measurement, 1000 us; now 1205 and 568.)
+//
+// NB = 2 where every row holds an even number of blocks (half the LDS
+// accesses and offsets per site), else 1; NI = 1 up to 1024 items (any number
+// of waves, several workgroups to a CU), else up to 8 / NB.
+template <int NB>
+struct Words {
+    uint32_t v[NB];
+};
 
-__device__ __forceinline__ void hc_store_natural_word(int8_t* lat, int i, uint32_t v, int Lx,
-                                                      int Ly, int Lz) {
-    const int row = i / Lx, x0 = i - row * Lx, z = row / Ly, y = row - z * Ly;
-    const size_t psz = (size_t)Ly * Lz * (Lx >> 1);
-    const size_t pa = hc_byte(z, y, x0, Lx, Ly, Lz);
-    const size_t pb = ((x0 + y + z) & 1) ? pa - psz : pa + psz;
-    *reinterpret_cast<uint16_t*>(lat + pa) = (uint16_t)__builtin_amdgcn_perm(0u, v, 0x0C0C0200u);
-    *reinterpret_cast<uint16_t*>(lat + pb) = (uint16_t)__builtin_amdgcn_perm(0u, v, 0x0C0C0301u);
-}
-
-// The same for the triangular planes: sites (y, x0 .. x0 + 3), byte by byte.
-__device__ __forceinline__ uint32_t tri_natural_word(const int8_t* lat, int i, int Lx, int Ly) {
-    const int y = i / Lx, x0 = i - y * Lx;
-    uint32_t v = 0u;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v |= (uint32_t)(uint8_t)lat[tri_byte(y, x0 + u, Lx, Ly)] << (8 * u);
-    return v;
-}
-
-__device__ __forceinline__ void tri_store_natural_word(int8_t* lat, int i, uint32_t v, int Lx,
-                                                       int Ly) {
-    const int y = i / Lx, x0 = i - y * Lx;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) lat[tri_byte(y, x0 + u, Lx, Ly)] = (int8_t)(v >> (8 * u));
-}
-
-template <int MODEL>
-__device__ __forceinline__ int4 nat_stats(const int8_t* ls, int Lx, int Ly, int Lz) {
-    const int plane = Lx * Ly, nq = (plane * Lz) >> 2;
-    int cnt = 0;
-    uint32_t pm = 0, p1 = 0, p2 = 0, p3 = 0;
-    for (int q = threadIdx.x; q < nq; q += blockDim.x) {
-        const int i = 4 * q;
-        const int row = qdiv(i, Lx, true), x0 = i - row * Lx;  // i < 2^16
-        const uint32_t v = ld32(ls + i);
-        const uint32_t nx = ld32(ls + row * Lx + (x0 + 4 == Lx ? 0 : x0 + 4));
-        pm += __popc(v & 0x80808080u);
-        p1 += __popc(v ^ abyte(nx, v, 1));
-        if (MODEL == kModelIsingTri) {
-            const int yd = row + 1 == Ly ? 0 : row + 1;
-            const uint32_t d = ld32(ls + yd * Lx + x0);
-            const uint32_t dp = ld32(ls + yd * Lx + (x0 == 0 ? Lx - 4 : x0 - 4));
-            p2 += __popc(v ^ d);
-            p3 += __popc(v ^ abyte(d, dp, 3));
-        } else {
-            const int z = qdiv(row, Ly, true), y = row - z * Ly;
-            if (Ly > 1) p2 += __popc(v ^ ld32(ls + (z * Ly + (y + 1 == Ly ? 0 : y + 1)) * Lx + x0));
-            if (Lz > 1) p3 += __popc(v ^ ld32(ls + (z + 1 == Lz ? 0 : z + 1) * plane + y * Lx + x0));
-        }
-        cnt += 4;
+template <int NB>
+__device__ __forceinline__ Words<NB> ldw(const int8_t* p) {
+    Words<NB> r;
+    if (NB == 2) {
+        const uint2 t = *reinterpret_cast<const uint2*>(p);
+        r.v[0] = t.x;
+        r.v[NB - 1] = t.y;
+    } else {
+        r.v[0] = *reinterpret_cast<const uint32_t*>(p);
     }
-    const bool has2 = MODEL == kModelIsingTri || Ly > 1, has3 = MODEL == kModelIsingTri || Lz > 1;
-    return make_int4(cnt - 2 * (int)pm, cnt - 2 * (int)(p1 / 7), has2 ? cnt - 2 * (int)(p2 / 7) : 0,
-                     has3 ? cnt - 2 * (int)(p3 / 7) : 0);
+    return r;
 }
 
-// REC (re > 0): after sweep sw0 + sw + 1 = k re of the call the statistics
-// of the LDS lattice go to stats row k - 1 (columns 0..3; the caller zeroes
-// the rows).  The rows of the launch gather in LDS behind the lattice (LDS
-// atomics of the waves) and are stored once at its end, so no sweep waits
-// for global memory.
-template <int MODEL, bool REC>
-__global__ void __launch_bounds__(1024) k_nat_resident(TriArgs a, int n_sweeps, int sw0, int re) {
+template <int NB>
+__device__ __forceinline__ void stw(int8_t* p, const Words<NB>& w) {
+    if (NB == 2)
+        *reinterpret_cast<uint2*>(p) = make_uint2(w.v[0], w.v[NB - 1]);
+    else
+        *reinterpret_cast<uint32_t*>(p) = w.v[0];
+}
+
+__device__ __forceinline__ uint32_t lbyte(const int8_t* p) { return (uint32_t)(uint8_t)*p; }
+
+// Bytes moved by one place within a row: up takes byte i + 1 (h, its low
+// byte, follows the last word) where sh = 1, and leaves w where sh = 0; down
+// takes byte i - 1 (h << 24 precedes the first word) under the selector
+// kDown, and leaves w under kKeep.
+constexpr uint32_t kDown = 0x06050403u, kKeep = 0x07060504u;
+
+template <int NB>
+__device__ __forceinline__ Words<NB> bytes_up(const Words<NB>& w, uint32_t h, uint32_t sh) {
+    Words<NB> r;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) r.v[k] = abyte(k + 1 < NB ? w.v[k + 1] : h, w.v[k], sh);
+    return r;
+}
+
+template <int NB>
+__device__ __forceinline__ Words<NB> bytes_down(const Words<NB>& w, uint32_t h, uint32_t sel) {
+    Words<NB> r;
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+        r.v[k] = __builtin_amdgcn_perm(w.v[k], k > 0 ? w.v[k - 1] : h << 24, sel);
+    return r;
+}
+
+// An item's place: off the offset of its first byte within a plane, ou / od
+// the same bytes of rows y - 1 / y + 1, ozu / ozd of planes z - 1 / z + 1
+// (chain / cubic), dl / dr from off to the bytes left and right of it (row
+// ends wrap), ph its row's phase (y mod 3, or (y + z) mod 2).
+struct PlaneItem {
+    uint32_t off, ou, od, ozu, ozd;
+    int dl, dr;
+    uint32_t ph;
+};
+
+// The same in four registers (a plane of an LDS-resident lattice is at most
+// 32 KiB, so every offset fits 15 bits): what a lane keeps of each item when
+// it owns several.
+struct PackedItem {
+    uint32_t a, b, c, d;
+};
+
+__device__ __forceinline__ PackedItem pack_item(const PlaneItem& t) {
+    return PackedItem{t.off | (t.ph << 16), t.ou | (t.od << 16), t.ozu | (t.ozd << 16),
+                      ((uint32_t)t.dl & 0xFFFFu) | ((uint32_t)t.dr << 16)};
+}
+
+__device__ __forceinline__ PlaneItem unpack_item(PackedItem p) {
+    // opaque here, so that the unpacked values of all items are not kept
+    // over the whole sweep loop
+    asm volatile("" : "+v"(p.a), "+v"(p.b), "+v"(p.c), "+v"(p.d));
+    PlaneItem t;
+    t.off = p.a & 0xFFFFu;
+    t.ph = p.a >> 16;
+    t.ou = p.b & 0xFFFFu;
+    t.od = p.b >> 16;
+    t.ozu = p.c & 0xFFFFu;
+    t.ozd = p.c >> 16;
+    t.dl = (int)(int16_t)(p.d & 0xFFFFu);
+    t.dr = (int)p.d >> 16;
+    return t;
+}
+
+template <int MODEL, int NB>
+__device__ __forceinline__ PlaneItem plane_item(int i, int Lx, int Ly, int Lz) {
+    PlaneItem t;
+    const int W = MODEL == kModelIsingTri ? Lx / 3 : Lx >> 1, G = W / (4 * NB);
+    const int row = i / G, j = 4 * NB * (i - row * G);
+    const int z = row / Ly, y = row - z * Ly;
+    const int yu = y == 0 ? Ly - 1 : y - 1, yd = y + 1 == Ly ? 0 : y + 1;
+    t.off = (uint32_t)(row * W + j);
+    t.ou = (uint32_t)((z * Ly + yu) * W + j);
+    t.od = (uint32_t)((z * Ly + yd) * W + j);
+    t.ozu = (uint32_t)(((z == 0 ? Lz - 1 : z - 1) * Ly + y) * W + j);
+    t.ozd = (uint32_t)(((z + 1 == Lz ? 0 : z + 1) * Ly + y) * W + j);
+    t.dl = j == 0 ? W - 1 : -1;
+    t.dr = j + 4 * NB == W ? -j : 4 * NB;
+    t.ph = MODEL == kModelIsingTri ? (uint32_t)(y % 3) : (uint32_t)((y + z) & 1);
+    return t;
+}
+
+// The six neighbours of the item's colour-c sites (see k_tri_pass4): row
+// phase rr = (c + y) mod 3 decides which of the words move by a byte.
+template <int NB>
+struct TriWords {
+    Words<NB> S, sa, fb, sc, sd, fe, sf;
+};
+
+template <int NB, bool ALL>
+__device__ __forceinline__ TriWords<NB> tri_words(const int8_t* ls, uint32_t psz, int c,
+                                                  const PlaneItem& t) {
+    const int cp = c == 2 ? 0 : c + 1, cm = c == 0 ? 2 : c - 1;
+    const int8_t* own = ls + (uint32_t)c * psz;
+    const int8_t* pp = ls + (uint32_t)cp * psz;
+    const int8_t* pm = ls + (uint32_t)cm * psz;
+    const uint32_t r = t.ph + (uint32_t)c, rr = r >= 3u ? r - 3u : r;
+    const bool up = rr == 2u, dn = rr == 0u;
+    const uint32_t sh = up ? 1u : 0u, sel = dn ? kDown : kKeep;
+    TriWords<NB> w;
+    w.S = ldw<NB>(own + t.off);
+    const Words<NB> fa = ldw<NB>(pp + t.off), fc = ldw<NB>(pp + t.od);
+    w.fe = ldw<NB>(pm + t.od);
+    const uint32_t h1 = lbyte(pp + (up ? t.off + (uint32_t)t.dr : t.od + (uint32_t)t.dl));
+    w.sa = bytes_up<NB>(fa, h1, sh);
+    w.sc = bytes_down<NB>(fc, h1, sel);
+    if (ALL) {
+        w.fb = ldw<NB>(pp + t.ou);
+        const Words<NB> fd = ldw<NB>(pm + t.off), ff = ldw<NB>(pm + t.ou);
+        const uint32_t h2 = lbyte(pm + (up ? t.ou + (uint32_t)t.dr : t.off + (uint32_t)t.dl));
+        w.sd = bytes_down<NB>(fd, h2, sel);
+        w.sf = bytes_up<NB>(ff, h2, sh);
+    }
+    return w;
+}
+
+// The horizontal neighbours of the item's colour-c sites: the other plane's
+// own bytes M and those moved towards the side of the row's parity.
+template <int NB>
+__device__ __forceinline__ void hc_words(const int8_t* oth, int c, const PlaneItem& t,
+                                         Words<NB>& M, Words<NB>& H) {
+    const bool par = ((t.ph + (uint32_t)c) & 1u) != 0u;
+    M = ldw<NB>(oth + t.off);
+    const uint32_t h = lbyte(oth + (t.off + (uint32_t)(par ? t.dr : t.dl)));
+    // byte i + 1 (par) or i - 1: the neighbouring word on that side, one perm
+    const uint32_t sel = par ? 0x00070605u : kDown;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        const uint32_t nx = k + 1 < NB ? M.v[k + 1] : h, pv = k > 0 ? M.v[k - 1] : h << 24;
+        H.v[k] = __builtin_amdgcn_perm(M.v[k], par ? nx : pv, sel);
+    }
+}
+
+// Four sites of one Philox block: own bytes S, neighbour counts N (-1
+// neighbours per byte); lt holds T - 1 by n + 8 [s = -1] (W < T as a 32-bit
+// compare), zero the bits of the entries with T = 0, which never accept.
+__device__ __forceinline__ uint32_t plane_decide(uint32_t S, uint32_t N, const uint32_t (&w)[4],
+                                                 const uint32_t* lt, uint32_t zero) {
+    const uint32_t K = (S << 3) + N, K4 = K << 2;
+    const uint8_t* tb = reinterpret_cast<const uint8_t*>(lt);
+    uint32_t F = 0u;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        F |= w[u] <= *reinterpret_cast<const uint32_t*>(tb + ((K4 >> (8 * u)) & 0xFFu)) ? 1u << (8 * u)
+                                                                                        : 0u;
+    if (zero != 0u) {  // uniform over the workgroup
+        uint32_t k = K;
+        asm volatile("" : "+v"(k));  // keeps this out of the common path
+        for (int u = 0; u < 4; ++u)
+            if ((zero >> ((k >> (8 * u)) & 15u)) & 1u) F &= ~(1u << (8 * u));
+    }
+    return S ^ F;
+}
+
+// re > 0: after sweep sw0 + sw + 1 = k re of the call the statistics of the
+// lattice go to stats row k - 1 (columns 0..3; the caller zeroes the rows).
+// They are counts of unequal bonds (and of -1 spins) from the planes, four
+// sites a word: triangular from every site's three forward bonds, chain /
+// cubic from both ends' directions of the colour-1 sites (every bond has one
+// colour-1 end).  The counts of the launch's rows gather in LDS behind the
+// lattice and are stored once at its end, so no sweep waits for global
+// memory.
+template <int MODEL, int NB, int NI>
+__global__ void __launch_bounds__(1024) k_plane_resident(TriArgs a, int n_sweeps, int sw0, int re) {
     extern __shared__ __align__(16) int8_t ls[];
-    __shared__ uint64_t lt[16];
-    const int r = blockIdx.x;
+    __shared__ uint32_t lt[16];
+    __shared__ uint32_t lzero;
+    constexpr bool TRI = MODEL == kModelIsingTri;
+    constexpr int ncol = TRI ? 3 : 2;
+    const int r = blockIdx.x, tid = (int)threadIdx.x, nthr = (int)blockDim.x;
     const RepDev D = a.reps[r];
-    const int Lx = D.Lx, Ly = D.Ly, Lz = MODEL == kModelIsingHC ? D.q : 1;
+    const int Lx = D.Lx, Ly = D.Ly, Lz = TRI ? 1 : D.q;
     const int n = Lx * Ly * Lz;
-    int8_t* lat = a.lat + D.lat_off;
-    if (threadIdx.x < 16)
-        lt[threadIdx.x] = keyed_threshold(
-            a.tab + (size_t)r * kTriClasses, threadIdx.x,
-            MODEL == kModelIsingHC ? 2 + 2 * (Ly > 1) + 2 * (Lz > 1) : 6);
-    for (int i = threadIdx.x; i < n / 4; i += blockDim.x)
-        reinterpret_cast<uint32_t*>(ls)[i] = MODEL == kModelIsingHC
-                                                 ? hc_natural_word(lat, 4 * i, Lx, Ly, Lz)
-                                                 : tri_natural_word(lat, 4 * i, Lx, Ly);
+    const uint32_t psz = (uint32_t)(n / ncol);
+    uint32_t* lat = reinterpret_cast<uint32_t*>(a.lat + D.lat_off);
+    if (tid == 0) lzero = 0u;
+    __syncthreads();
+    if (tid < 16) {
+        const int k = TRI ? 6 : 2 + 2 * (Ly > 1) + 2 * (Lz > 1);
+        const uint64_t T = keyed_threshold(a.tab + (size_t)r * kTriClasses, tid, k);
+        lt[tid] = (uint32_t)(T - 1u);
+        if (T == 0u && (tid & 7) <= k) atomicOr(&lzero, 1u << tid);
+    }
+    for (int i = tid; i < n / 4; i += nthr)
+        reinterpret_cast<uint32_t*>(ls)[i] = (lat[i] >> 1) & 0x01010101u;
     // recorded rows rec0 .. rec0 + n_rows - 1 (1-based) of this launch
     int* lrec = reinterpret_cast<int*>(ls + ((n + 15) & ~15));
-    const int rec0 = REC ? sw0 / re + 1 : 0;
-    const int n_rows = REC ? (sw0 + n_sweeps) / re - sw0 / re : 0;
-    for (int i = threadIdx.x; i < 4 * n_rows; i += blockDim.x) lrec[i] = 0;
+    const int rec0 = re > 0 ? sw0 / re + 1 : 0;
+    const int n_rows = re > 0 ? (sw0 + n_sweeps) / re - sw0 / re : 0;
+    for (int i = tid; i < 4 * n_rows; i += nthr) lrec[i] = 0;
+    const int items = (int)(psz / (4 * NB));
+    PlaneItem it0;
+    PackedItem itp[NI];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        it0 = plane_item<MODEL, NB>(min(tid + k * nthr, items - 1), Lx, Ly, Lz);
+        itp[k] = pack_item(it0);
+    }
     __syncthreads();
+    const uint32_t zero = __builtin_amdgcn_readfirstlane(lzero);
     const uint64_t t0 = *a.t_base;
-    constexpr int ncol = MODEL == kModelIsingHC ? 2 : 3;
-    const int nb = MODEL == kModelIsingHC ? n / 8 : n / 12;  // Philox blocks per pass
-    const int plane = Lx * Ly;
+    int next = re > 0 ? rec0 * re - sw0 : 0;  // sweeps to the next recorded one
     for (int sw = 0; sw < n_sweeps; ++sw) {
         const uint64_t t = t0 + (uint64_t)sw;
         for (int c = 0; c < ncol; ++c) {
             const uint32_t p = (uint32_t)((uint64_t)ncol * t + (uint64_t)c);
-            for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-                uint32_t w[4];
-                philox4x32_10((uint32_t)b, p, D.rid, kTriTagMain, a.key0, a.key1, w);
-                if (MODEL == kModelIsingTri) {
-                    const int G = Lx / 12;
-                    const int y = qdiv(b, G, true), x0 = 12 * (b - y * G);  // b < 2^16
-                    const int yu = y == 0 ? Ly - 1 : y - 1, yd = y + 1 == Ly ? 0 : y + 1;
-                    const int xl = x0 == 0 ? Lx - 1 : x0 - 1, xr = x0 + 12 == Lx ? 0 : x0 + 12;
-                    int8_t* row = ls + y * Lx;
-                    const int8_t* up = ls + yu * Lx;
-                    const int8_t* dn = ls + yd * Lx;
-                    uint32_t S[3] = {ld32(row + x0), ld32(row + x0 + 4), ld32(row + x0 + 8)};
-                    const uint32_t U[3] = {ld32(up + x0), ld32(up + x0 + 4), ld32(up + x0 + 8)};
-                    const uint32_t Dn[3] = {ld32(dn + x0), ld32(dn + x0 + 4), ld32(dn + x0 + 8)};
-                    const uint32_t hl = negflag(row + xl) + negflag(dn + xl);
-                    const uint32_t hr = negflag(row + xr) + negflag(up + xr);
-                    tri_span(S, U, Dn, hl, hr, (uint32_t)((c + y) % 3), w, lt);
-                    uint32_t* rw = reinterpret_cast<uint32_t*>(row + x0);
-                    rw[0] = S[0];
-                    rw[1] = S[1];
-                    rw[2] = S[2];
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                const int i = tid + k * nthr;
+                if (i >= items) break;
+                const PlaneItem q = NI == 1 ? it0 : unpack_item(itp[k]);
+                Words<NB> S, N;
+                int8_t* own = ls + (uint32_t)c * psz;
+                if (TRI) {
+                    const TriWords<NB> w = tri_words<NB, true>(ls, psz, c, q);
+                    S = w.S;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        N.v[b] = w.sa.v[b] + w.fb.v[b] + w.sc.v[b] + w.sd.v[b] + w.fe.v[b] + w.sf.v[b];
                 } else {
-                    const int row = qdiv(8 * b, Lx, true);  // 8 b < 2^16
-                    const int z = qdiv(row, Ly, true), y = row - z * Ly;
-                    const int x0 = 8 * b - row * Lx;
-                    int8_t* own = ls + row * Lx + x0;
-                    const uint2 S2 = ld64(own);
-                    uint32_t S[2] = {S2.x, S2.y};
-                    const uint32_t hl = negflag(ls + row * Lx + (x0 == 0 ? Lx - 1 : x0 - 1));
-                    const uint32_t hr = negflag(ls + row * Lx + (x0 + 8 == Lx ? 0 : x0 + 8));
-                    uint32_t N0 = 0u, N1 = 0u;
+                    const int8_t* oth = ls + (uint32_t)(1 - c) * psz;
+                    Words<NB> M, H;
+                    hc_words<NB>(oth, c, q, M, H);
+                    S = ldw<NB>(own + q.off);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) N.v[b] = M.v[b] + H.v[b];
                     if (Ly > 1) {
-                        const uint2 vu = ld64(ls + (z * Ly + (y == 0 ? Ly - 1 : y - 1)) * Lx + x0);
-                        const uint2 vd = ld64(ls + (z * Ly + (y + 1 == Ly ? 0 : y + 1)) * Lx + x0);
-                        N0 += (vu.x & kNegFlag) + (vd.x & kNegFlag);
-                        N1 += (vu.y & kNegFlag) + (vd.y & kNegFlag);
+                        const Words<NB> u = ldw<NB>(oth + q.ou), d = ldw<NB>(oth + q.od);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) N.v[b] += u.v[b] + d.v[b];
                     }
                     if (Lz > 1) {
-                        const int ip = y * Lx + x0;
-                        const uint2 vu = ld64(ls + (z == 0 ? Lz - 1 : z - 1) * plane + ip);
-                        const uint2 vd = ld64(ls + (z + 1 == Lz ? 0 : z + 1) * plane + ip);
-                        N0 += (vu.x & kNegFlag) + (vd.x & kNegFlag);
-                        N1 += (vu.y & kNegFlag) + (vd.y & kNegFlag);
+                        const Words<NB> u = ldw<NB>(oth + q.ozu), d = ldw<NB>(oth + q.ozd);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) N.v[b] += u.v[b] + d.v[b];
                     }
-                    hc_span(S, N0, N1, hl, hr, (uint32_t)((c + y + z) & 1), w, lt);
-                    *reinterpret_cast<uint2*>(own) = make_uint2(S[0], S[1]);
                 }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    uint32_t w[4];
+                    philox4x32_10((uint32_t)(NB * i + b), p, D.rid, kTriTagMain, a.key0, a.key1, w);
+                    S.v[b] = plane_decide(S.v[b], N.v[b], w, lt, zero);
+                }
+                stw<NB>(own + q.off, S);
             }
             __syncthreads();
         }
-        if (REC && (sw0 + sw + 1) % re == 0) {
-            int4 st = nat_stats<MODEL>(ls, Lx, Ly, Lz);
-            // wave sums over the active lanes (every wave of the workgroup is
-            // full and has reconverged after the loop)
-            st.x = __ockl_wfred_add_i32(st.x);
-            st.y = __ockl_wfred_add_i32(st.y);
-            st.z = __ockl_wfred_add_i32(st.z);
-            st.w = __ockl_wfred_add_i32(st.w);
-            if ((threadIdx.x & 63) == 0) {
-                int* row = lrec + 4 * ((sw0 + sw + 1) / re - rec0);
-                atomicAdd(&row[0], st.x);
-                atomicAdd(&row[1], st.y);
-                atomicAdd(&row[2], st.z);
-                atomicAdd(&row[3], st.w);
+        if (re > 0 && sw + 1 == next) {
+            int cnt[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                if (tid + k * nthr >= items) break;
+                const PlaneItem q = NI == 1 ? it0 : unpack_item(itp[k]);
+                if (TRI) {
+                    for (int c = 0; c < 3; ++c) {
+                        const TriWords<NB> w = tri_words<NB, false>(ls, psz, c, q);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) {
+                            const uint32_t s = w.S.v[b];
+                            cnt[0] += __popc(s);
+                            cnt[1] += __popc(s ^ w.sa.v[b]);
+                            cnt[2] += __popc(s ^ w.fe.v[b]);
+                            cnt[3] += __popc(s ^ w.sc.v[b]);
+                        }
+                    }
+                } else {
+                    Words<NB> M, H;
+                    hc_words<NB>(ls, 1, q, M, H);
+                    const Words<NB> S = ldw<NB>(ls + psz + q.off);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        cnt[0] += __popc(S.v[b]) + __popc(M.v[b]);
+                        cnt[1] += __popc(S.v[b] ^ M.v[b]) + __popc(S.v[b] ^ H.v[b]);
+                    }
+                    if (Ly > 1) {
+                        const Words<NB> u = ldw<NB>(ls + q.ou), d = ldw<NB>(ls + q.od);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            cnt[2] += __popc(S.v[b] ^ u.v[b]) + __popc(S.v[b] ^ d.v[b]);
+                    }
+                    if (Lz > 1) {
+                        const Words<NB> u = ldw<NB>(ls + q.ozu), d = ldw<NB>(ls + q.ozd);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            cnt[3] += __popc(S.v[b] ^ u.v[b]) + __popc(S.v[b] ^ d.v[b]);
+                    }
+                }
             }
+            // wave sums (every wave is full and has reconverged)
+            int* row = lrec + 4 * ((sw0 + sw + 1) / re - rec0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                cnt[j] = __ockl_wfred_add_i32(cnt[j]);
+                if ((tid & 63) == 0) atomicAdd(&row[j], cnt[j]);
+            }
+            next += re;
             __syncthreads();  // the next sweep writes the lattice
         }
     }
-    if (REC)
-        for (int i = threadIdx.x; i < 4 * n_rows; i += blockDim.x)
-            a.stats[((size_t)(rec0 - 1 + (i >> 2)) * a.R + r) * a.width + (i & 3)] = lrec[i];
-    for (int i = threadIdx.x; i < n / 4; i += blockDim.x) {
-        const uint32_t v = reinterpret_cast<const uint32_t*>(ls)[i];
-        if (MODEL == kModelIsingHC)
-            hc_store_natural_word(lat, 4 * i, v, Lx, Ly, Lz);
-        else
-            tri_store_natural_word(lat, 4 * i, v, Lx, Ly);
+    // counts to sums: n - 2 x (-1 spins, unequal bonds); 0 for an absent dimension
+    for (int i = tid; i < 4 * n_rows; i += nthr) {
+        const int j = i & 3;
+        const bool has = TRI || j < 2 || (j == 2 ? Ly > 1 : Lz > 1);
+        a.stats[((size_t)(rec0 - 1 + (i >> 2)) * a.R + r) * a.width + j] = has ? n - 2 * lrec[i] : 0;
     }
+    for (int i = tid; i < n / 4; i += nthr)
+        lat[i] = reinterpret_cast<const uint32_t*>(ls)[i] * 0xFEu + 0x01010101u;
 }
 
-hipError_t launch_nat_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
-                               hipStream_t s) {
-    const bool hc = a.model == kModelIsingHC, rec = re > 0;
-    const void* fn = hc ? (rec ? (const void*)k_nat_resident<kModelIsingHC, true>
-                               : (const void*)k_nat_resident<kModelIsingHC, false>)
-                        : (rec ? (const void*)k_nat_resident<kModelIsingTri, true>
-                               : (const void*)k_nat_resident<kModelIsingTri, false>);
+namespace {
+const void* plane_resident_fn(bool hc, int nb, int ni) {
+    if (hc)
+        return nb == 2 ? (ni == 1 ? (const void*)k_plane_resident<kModelIsingHC, 2, 1>
+                                  : (const void*)k_plane_resident<kModelIsingHC, 2, 4>)
+                       : (ni == 1 ? (const void*)k_plane_resident<kModelIsingHC, 1, 1>
+                                  : (const void*)k_plane_resident<kModelIsingHC, 1, 8>);
+    return nb == 2 ? (ni == 1 ? (const void*)k_plane_resident<kModelIsingTri, 2, 1>
+                              : (const void*)k_plane_resident<kModelIsingTri, 2, 4>)
+                   : (ni == 1 ? (const void*)k_plane_resident<kModelIsingTri, 1, 1>
+                              : (const void*)k_plane_resident<kModelIsingTri, 1, 8>);
+}
+}  // namespace
+
+hipError_t launch_plane_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
+                                 hipStream_t s) {
+    const bool hc = a.model == kModelIsingHC;
+    const int nb = a.even_blocks ? 2 : 1;
+    const int items = (a.max_blocks + nb - 1) / nb;
+    const int ni = (items + 1023) / 1024;
+    if (ni > 8 / nb) return hipErrorInvalidValue;  // lattices above 64 KiB
+    const int threads = ((items + ni - 1) / ni + 63) & ~63;
+    const void* fn = plane_resident_fn(hc, nb, ni);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
-    if (hc && rec)
-        hipLaunchKernelGGL((k_nat_resident<kModelIsingHC, true>), dim3(a.R), dim3(1024), lds_bytes,
-                           s, a, n_sweeps, sw0, re);
-    else if (hc)
-        hipLaunchKernelGGL((k_nat_resident<kModelIsingHC, false>), dim3(a.R), dim3(1024),
-                           lds_bytes, s, a, n_sweeps, sw0, re);
-    else if (rec)
-        hipLaunchKernelGGL((k_nat_resident<kModelIsingTri, true>), dim3(a.R), dim3(1024),
-                           lds_bytes, s, a, n_sweeps, sw0, re);
-    else
-        hipLaunchKernelGGL((k_nat_resident<kModelIsingTri, false>), dim3(a.R), dim3(1024),
-                           lds_bytes, s, a, n_sweeps, sw0, re);
-    return hipGetLastError();
+    TriArgs b = a;
+    void* args[] = {&b, &n_sweeps, &sw0, &re};
+    return hipLaunchKernel(fn, dim3(a.R), dim3(threads), args, lds_bytes, s);
 }
 
 hipError_t launch_tri_init(const TriArgs& a, hipStream_t s) {

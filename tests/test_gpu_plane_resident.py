@@ -1,0 +1,58 @@
+"""The LDS-resident triangular and chain / cubic kernel at the edges of its
+forms, bit for bit against the oracle: one or two Philox blocks per item
+(plane rows of an odd or even number of blocks), one item or several per lane
+(up to the 64 KiB limit), a ragged last workgroup wave, absent and two-site
+dimensions, thresholds that underflow to 0, and recorded sweeps that do not
+start or end with the call."""
+import numpy as np
+import pytest
+
+from oracle import chain as orc
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _check(reps, run, seed=0x77_0000_0031, n=7, every=3):
+    from paper_2304_01772_amd.sampler import Sampler
+    smp = Sampler(reps, seed, init=True)
+    init = [smp.get_state(r) for r in range(len(reps))]
+    smp.sweep(2)
+    st = smp.sweep(n, every).cpu().numpy()
+    for r, d in enumerate(reps):
+        s1, _ = run(init[r], d, seed, 0, 2, 0)
+        s2, ost = run(s1, d, seed, 2, n, every)
+        assert np.array_equal(smp.get_state(r), s2), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
+
+
+@pytest.mark.parametrize("Ly,Lx,n_rep,beta", [
+    (3, 12, 1, 0.27),      # one block a row
+    (9, 36, 3, 0.27),      # three blocks a row (one per item)
+    (6, 24, 2, 0.27),      # two blocks a row (two per item)
+    (102, 120, 2, 0.27),   # two per item, 510 items: a ragged wave
+    (180, 192, 2, 0.27),   # two per item, several items a lane
+    (243, 252, 2, 0.27),   # one per item, several items a lane
+    (27, 2424, 1, 0.27),   # near the 64 KiB limit, long rows
+    (12, 24, 2, 90.0),     # T = 0 for the largest energy changes
+])
+def test_triangular(Ly, Lx, n_rep, beta):
+    reps = [dict(model=3, Lx=Lx, Ly=Ly, Jx=1.0 - 0.5 * r, Jy=1.0 - 0.5 * r, h=0.05, beta=beta,
+                 rid=40 + r) for r in range(n_rep)]
+    _check(reps, lambda s, d, seed, t, n, e: orc.tri_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
+                                                         t, n, e))
+
+
+@pytest.mark.parametrize("Lz,Ly,Lx,beta", [
+    (1, 1, 8, 0.4), (1, 1, 48, 0.4), (1, 1, 4104, 0.4),
+    (1, 2, 16, 0.4), (2, 2, 8, 0.3), (1, 66, 72, 0.4), (4, 1, 16, 0.3),
+    (34, 30, 32, 0.22),    # two blocks per item, several items a lane
+    (34, 38, 40, 0.22),    # one per item, several items a lane
+    (2, 4, 16, 130.0),     # T = 0 for the largest energy changes
+])
+def test_chain_square_cubic(Lz, Ly, Lx, beta):
+    reps = [dict(model=4, Lx=Lx, Ly=Ly, Lz=Lz, Jx=1.0 - 0.7 * r, Jy=1.0 - 0.7 * r, h=-0.03,
+                 beta=beta, rid=50 + r) for r in range(2)]
+    _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
+                                                        t, n, e))
