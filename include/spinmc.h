@@ -393,6 +393,13 @@ int spinmc_mlp_act_floats(int32_t B);
 int spinmc_mlp_forward(const void *dev_params, const void *dev_x, int32_t B, void *dev_y,
                        void *dev_act, void *hip_stream);
 
+/* The network on physical inputs in one call: y = MLP(2 (x - x_lo) /
+ * (x_hi - x_lo) - 1) * y_sd + y_mu in FP32 (that order of operations), x
+ * [B][4] and y [B][3], x_lo, x_hi [4] and y_mu, y_sd [3], all device FP32.  */
+int spinmc_mlp_predict(const void *dev_params, const void *dev_x, int32_t B, const void *dev_x_lo,
+                       const void *dev_x_hi, const void *dev_y_mu, const void *dev_y_sd,
+                       void *dev_y, void *hip_stream);
+
 /* Gradients of L = (1/B) sum_b sum_j w_j (y_bj - t_bj)^2 with respect to the
  * parameters (dev_grad, FP32, same layout as the parameters) and optionally
  * the inputs (dev_dx [B][4], may be NULL).  dev_act from the forward call of

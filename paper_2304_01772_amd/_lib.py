@@ -74,6 +74,8 @@ SIGNATURES = {
     "spinmc_mlp_act_floats": (C.c_int, [C.c_int32]),
     "spinmc_mlp_forward": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
                                      C.c_void_p]),
+    "spinmc_mlp_predict": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
+                                     C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "spinmc_mlp_workspace_floats": (C.c_int, [C.c_int32]),
     "spinmc_mlp_backward": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                       C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,

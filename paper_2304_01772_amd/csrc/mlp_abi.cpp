@@ -32,6 +32,15 @@ int spinmc_mlp_forward(const void* params, const void* x, int32_t B, void* y, vo
                                      (float*)act, (hipStream_t)stream));
 }
 
+int spinmc_mlp_predict(const void* params, const void* x, int32_t B, const void* x_lo,
+                       const void* x_hi, const void* y_mu, const void* y_sd, void* y,
+                       void* stream) {
+    if (!params || !x || !x_lo || !x_hi || !y_mu || !y_sd || !y || B < 1) return SPINMC_E_INVALID;
+    return status(launch_mlp_predict((const float*)params, (const float*)x, B, (const float*)x_lo,
+                                     (const float*)x_hi, (const float*)y_mu, (const float*)y_sd,
+                                     (float*)y, (hipStream_t)stream));
+}
+
 int spinmc_mlp_backward(const void* params, const void* x, const void* act, const void* t,
                         const void* w, int32_t B, void* grad, void* dx, void* loss,
                         void* workspace, void* stream) {

@@ -121,65 +121,232 @@ __device__ __forceinline__ float4v out_layer(const uint16_t* h2, const uint16_t*
 }  // namespace
 
 // --------------------------------------------------------------- forward
-__global__ void __launch_bounds__(256) k_mlp_fwd(const float* P, const float* x, int B, float* y,
-                                                 float* act) {
-    __shared__ __align__(16) uint16_t w1[kH * kS1];
-    __shared__ __align__(16) uint16_t w2[kH * kS2];
-    __shared__ __align__(16) uint16_t w3[16 * kS2];
-    __shared__ __align__(16) uint16_t xa[4][16 * kS1];
-    __shared__ __align__(16) uint16_t h1[4][16 * kS2];
-    __shared__ __align__(16) uint16_t h2[4][16 * kS2];
-    stage_weights(P, w1, w2, w3, true);
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int s0 = blockIdx.x * kSamplesPerWG + wave * 16;
-    for (int i = l; i < 16 * kK1; i += 64) {
-        const int r = i / kK1, k = i % kK1;
-        const int s = s0 + r;
-        xa[wave][r * kS1 + k] = (k < kIn && s < B) ? f2bf(x[(size_t)s * kIn + k]) : (uint16_t)0;
-    }
-    __syncthreads();
-    const int col = l & 15, rb = 4 * (l >> 4);
-    // layer 1 (K = 4, zero-padded to 32)
+namespace {
+
+// SiLU with the reciprocal as v_rcp_f32 and one Newton step (correct to an
+// ulp, three instructions for the ten of an IEEE division); the maximum turns
+// the step's inf * 0 at an overflowed exponential into the quotient's 0.
+__device__ __forceinline__ float sigm_fast(float z) {
+    const float d = 1.0f + __expf(-z);
+    const float r = __builtin_amdgcn_rcpf(d);
+    return fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), 0.0f);
+}
+__device__ __forceinline__ float silu_fast(float z) { return z * sigm_fast(z); }
+
+// two values as BF16 in one word (v_cvt_pk_bf16_f32, nearest even), a low
+__device__ __forceinline__ uint32_t pk_bf(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    bf16x2 v;
+    v[0] = (__bf16)a;
+    v[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+__device__ __forceinline__ bf16x8 as_frag(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// Weights in LDS as whole MFMA A operands: 64 lanes x 16 bytes each, so that
+// a wave reads one with a conflict-free ds_read_b128.  Rows of A are output
+// neurons, columns of B samples, and row 4 g + i of row tile nt is neuron
+// tile_neuron(nt, g) + i, so that a result lane (g = lane / 16) holds, of the
+// tiles 2 kt and 2 kt + 1, the neurons 32 kt + 8 g .. + 7 of one sample:
+// packed as BF16 they are its B operand of k tile kt in the next layer.
+// Activations never leave registers.
+struct FwdWeights {
+    uint4 w1[8 * 64];       // row tile nt, k = the 4 inputs (lanes g = 0), rest 0
+    uint4 w2[8 * 4 * 64];   // row tile nt, k tile kt
+    uint4 w3[4 * 64];       // k tile kt, rows 0..2, rest 0
+    float4 b1[32], b2[32];  // biases by four neurons
+};
+
+__device__ __forceinline__ uint4 pk8(const float4& u, const float4& v) {
+    return make_uint4(pk_bf(u.x, u.y), pk_bf(u.z, u.w), pk_bf(v.x, v.y), pk_bf(v.z, v.w));
+}
+
+__device__ __forceinline__ int tile_neuron(int nt, int g) {
+    return 32 * (nt >> 1) + 8 * g + 4 * (nt & 1);
+}
+// neuron of row r of row tile nt
+__device__ __forceinline__ int row_neuron(int nt, int r) { return tile_neuron(nt, r >> 2) + (r & 3); }
+
+__device__ __forceinline__ void stage_fwd(const float* P, FwdWeights& S) {
+    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+    const float4* W2 = reinterpret_cast<const float4*>(P + oW2);
+    // all of a thread's loads of W2 before its conversions
+    constexpr int kU = 8;
+    for (int d0 = tid; d0 < 2048; d0 += kU * nthr) {
+        float4 u[kU], v[kU];
 #pragma unroll
-    for (int nt = 0; nt < kH / 16; ++nt) {
-        float4v acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma(frag(xa[wave], kS1, 0), frag(w1 + nt * 16 * kS1, kS1, 0), acc);
-        const int n = nt * 16 + col;
+        for (int j = 0; j < kU; ++j) {
+            const int d = d0 + j * nthr;
+            if (d < 2048) {
+                const int f = d >> 6, l = d & 63;
+                const int n = row_neuron(f >> 2, l & 15), q = 8 * (f & 3) + 2 * (l >> 4);
+                u[j] = W2[n * 32 + q];
+                v[j] = W2[n * 32 + q + 1];
+            }
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float z = acc[i] + P[ob1 + n];
-            const int s = s0 + rb + i;
-            if (act && s < B) act[(size_t)s * 2 * kH + n] = z;
-            h1[wave][(rb + i) * kS2 + n] = f2bf(silu(z));
+        for (int j = 0; j < kU; ++j) {
+            const int d = d0 + j * nthr;
+            if (d < 2048) S.w2[d] = pk8(u[j], v[j]);
         }
     }
-    __syncthreads();
-    // layer 2 (K = 128)
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int d = tid; d < 512; d += nthr) {
+        const int l = d & 63;
+        const bool in = l < 16;
+        S.w1[d] = pk8(in ? reinterpret_cast<const float4*>(P + oW1)[row_neuron(d >> 6, l)] : zero, zero);
+    }
+    for (int d = tid; d < 256; d += nthr) {
+        const int l = d & 63, n = l & 15, q = 8 * (d >> 6) + 2 * (l >> 4);
+        const float4* W3 = reinterpret_cast<const float4*>(P + oW3);
+        const bool in = n < kOut;
+        S.w3[d] = pk8(in ? W3[n * 32 + q] : zero, in ? W3[n * 32 + q + 1] : zero);
+    }
+    for (int d = tid; d < 64; d += nthr)
+        (d < 32 ? S.b1 : S.b2)[d & 31] =
+            reinterpret_cast<const float4*>(P + (d < 32 ? ob1 : ob2))[d & 31];
+}
+
+// Input and output scaling of spinmc_mlp_predict (null pointers: none).
+struct Affine {
+    const float *lo, *hi, *mu, *sd;
+};
+
+__device__ __forceinline__ float4 load_x(const float* x, size_t s, bool vec) {
+    const float* p = x + 4 * s;
+    return vec ? *reinterpret_cast<const float4*>(p) : make_float4(p[0], p[1], p[2], p[3]);
+}
+
+__device__ __forceinline__ void store_act(float* p, const float4v& z, bool vec) {
+    if (vec) {
+        *reinterpret_cast<float4v*>(p) = z;
+    } else {
 #pragma unroll
-    for (int nt = 0; nt < kH / 16; ++nt) {
-        float4v acc = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 4; ++i) p[i] = z[i];
+    }
+}
+
+__device__ __forceinline__ float4v plus(const float4v& z, const float4& b) {
+    return float4v{z[0] + b.x, z[1] + b.y, z[2] + b.z, z[3] + b.w};
+}
+
+// Both hidden layers for C tiles of 16 samples (lane l of tile c: sample
+// s[c], neurons tile_neuron(nt, l / 16) + i): the pre-activations go to act if it
+// is given, h2 receives the B operands of the output layer.
+template <int C>
+__device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (&xb)[C],
+                                              const size_t (&s)[C], int B, float* act, bool vec,
+                                              uint32_t (&h2)[C][16]) {
+    const int l = (int)threadIdx.x & 63, g = l >> 4;
+    uint32_t h1[C][16];
 #pragma unroll
-        for (int kt = 0; kt < kH / 32; ++kt)
-            acc = mfma(frag(h1[wave], kS2, 32 * kt), frag(w2 + nt * 16 * kS2, kS2, 32 * kt), acc);
-        const int n = nt * 16 + col;
+    for (int nt = 0; nt < 8; ++nt) {
+        const int n0 = tile_neuron(nt, g);
+        const float4 b = S.b1[n0 >> 2];
+        const bf16x8 w = as_frag(S.w1[nt * 64 + l]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float z = acc[i] + P[ob2 + n];
-            const int s = s0 + rb + i;
-            if (act && s < B) act[(size_t)s * 2 * kH + kH + n] = z;
-            h2[wave][(rb + i) * kS2 + n] = f2bf(silu(z));
+        for (int c = 0; c < C; ++c) {
+            const float4v z = plus(mfma(w, as_frag(xb[c]), float4v{0.f, 0.f, 0.f, 0.f}), b);
+            if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + n0, z, vec);
+            h1[c][2 * nt] = pk_bf(silu_fast(z[0]), silu_fast(z[1]));
+            h1[c][2 * nt + 1] = pk_bf(silu_fast(z[2]), silu_fast(z[3]));
         }
     }
-    __syncthreads();
-    if (!y) return;  // training steps keep only the pre-activations
-    const float4v o = out_layer(h2[wave], w3);
-    if (col < kOut) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = s0 + rb + i;
-            if (s < B) y[(size_t)s * kOut + col] = o[i] + P[ob3 + col];
+    for (int nt = 0; nt < 8; ++nt) {
+        const int n0 = tile_neuron(nt, g);
+        const float4 b = S.b2[n0 >> 2];
+        float4v z[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) z[c] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+            const bf16x8 w = as_frag(S.w2[(nt * 4 + kt) * 64 + l]);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                z[c] = mfma(w, as_frag(make_uint4(h1[c][4 * kt], h1[c][4 * kt + 1], h1[c][4 * kt + 2],
+                                                  h1[c][4 * kt + 3])), z[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            z[c] = plus(z[c], b);
+            if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + kH + n0, z[c], vec);
+            h2[c][2 * nt] = pk_bf(silu_fast(z[c][0]), silu_fast(z[c][1]));
+            h2[c][2 * nt + 1] = pk_bf(silu_fast(z[c][2]), silu_fast(z[c][3]));
         }
     }
+}
+
+// Output layer: lanes 0..15 hold the three outputs of their sample.
+__device__ __forceinline__ float4v output_layer(const FwdWeights& S, const uint32_t (&h2)[16]) {
+    const int l = (int)threadIdx.x & 63;
+    float4v y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+        y = mfma(as_frag(S.w3[kt * 64 + l]),
+                 as_frag(make_uint4(h2[4 * kt], h2[4 * kt + 1], h2[4 * kt + 2], h2[4 * kt + 3])), y);
+    return y;
+}
+
+}  // namespace
+
+// A wave takes C tiles of 16 samples at a time, tile groups strided over the
+// launch's waves, so that the weights are staged once per workgroup.  Bound
+// by the VALU work of the SiLUs (256 a sample, about 60 lane-cycles each,
+// half of it the quarter-rate exponential and reciprocal); the matrix
+// products take a sixth of that.  10^5 points: 82 us with a
+// workgroup (and its own staging and conversion of the weights) per 64
+// samples, activations through LDS and IEEE divisions; now 20.
+template <int C, bool AFF>
+__global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x, int B, float* y,
+                                                 float* act, Affine af) {
+    __shared__ FwdWeights S;
+    stage_fwd(P, S);
+    const int waves = (int)blockDim.x >> 6, l = (int)threadIdx.x & 63, g = l >> 4;
+    const bool vec = ((uintptr_t)x & 15u) == 0, avec = ((uintptr_t)act & 15u) == 0;
+    const float bo[3] = {P[ob3], P[ob3 + 1], P[ob3 + 2]};
+    __syncthreads();
+    const int groups = (B + 16 * C - 1) / (16 * C);
+    // one tile a wave (C = 1) needs no loop: the grid covers the samples
+    int q = (int)blockIdx.x * waves + ((int)threadIdx.x >> 6);
+    if (q >= groups) return;
+    do {
+        uint4 xb[C];
+        size_t s[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            s[c] = (size_t)(q * C + c) * 16 + (l & 15);
+            xb[c] = make_uint4(0u, 0u, 0u, 0u);
+            if (g == 0 && s[c] < (size_t)B) {
+                float4 v = load_x(x, s[c], vec);
+                if (AFF) {
+                    v.x = 2.0f * (v.x - af.lo[0]) / (af.hi[0] - af.lo[0]) - 1.0f;
+                    v.y = 2.0f * (v.y - af.lo[1]) / (af.hi[1] - af.lo[1]) - 1.0f;
+                    v.z = 2.0f * (v.z - af.lo[2]) / (af.hi[2] - af.lo[2]) - 1.0f;
+                    v.w = 2.0f * (v.w - af.lo[3]) / (af.hi[3] - af.lo[3]) - 1.0f;
+                }
+                xb[c].x = pk_bf(v.x, v.y);
+                xb[c].y = pk_bf(v.z, v.w);
+            }
+        }
+        uint32_t h2[C][16];
+        hidden_layers<C>(S, xb, s, B, act, avec, h2);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (!y) break;  // training steps keep only the pre-activations
+            const float4v o = output_layer(S, h2[c]);
+            if (g == 0 && s[c] < (size_t)B) {
+#pragma unroll
+                for (int j = 0; j < kOut; ++j) {
+                    float v = o[j] + bo[j];
+                    if (AFF) v = v * af.sd[j] + af.mu[j];
+                    y[s[c] * kOut + j] = v;
+                }
+            }
+        }
+        q += (int)gridDim.x * waves;
+    } while (C > 1 && q < groups);
 }
 
 // -------------------------------------------------------------- backward
@@ -438,13 +605,37 @@ __global__ void k_mlp_reduce_adam(const float* part, int n_wg, float* grad, floa
     p[i] -= lr * mh / (sqrtf(vh) + eps);
 }
 
+// Few samples: one tile a wave, four waves a workgroup, as many workgroups as
+// the samples need (the chip is not filled and latency counts).  From 32768
+// samples (two such workgroups on every CU) two tiles a wave share each
+// weight operand read from LDS, and 512 workgroups of eight waves stride over
+// the samples.
+static hipError_t launch_fwd(const float* params, const float* x, int B, float* y, float* act,
+                             const Affine* af, hipStream_t s) {
+    const Affine none{nullptr, nullptr, nullptr, nullptr};
+    if (B < 32768) {
+        const dim3 g((B + 63) / 64), b(256);
+        if (af)
+            hipLaunchKernelGGL((k_mlp_fwd<1, true>), g, b, 0, s, params, x, B, y, act, *af);
+        else
+            hipLaunchKernelGGL((k_mlp_fwd<1, false>), g, b, 0, s, params, x, B, y, act, none);
+    } else {
+        const int64_t need = ((int64_t)B + 255) / 256;
+        const dim3 g((unsigned)(need < 512 ? need : 512)), b(512);
+        if (af)
+            hipLaunchKernelGGL((k_mlp_fwd<2, true>), g, b, 0, s, params, x, B, y, act, *af);
+        else
+            hipLaunchKernelGGL((k_mlp_fwd<2, false>), g, b, 0, s, params, x, B, y, act, none);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_mlp_train_step(float* params, const float* x, const float* t, const float* w,
                                  int B, float* grad, float* m, float* v, int step, float lr,
                                  float b1, float b2, float eps, float* loss, float* act,
                                  float* scratch, hipStream_t s) {
     const int g = (B + kSamplesPerWG - 1) / kSamplesPerWG;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(g), dim3(256), 0, s, params, x, B, (float*)nullptr, act);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_fwd(params, x, B, nullptr, act, nullptr, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mlp_bwd, dim3(g), dim3(256), 0, s, params, x, act, t, w, B, scratch,
                        (float*)nullptr);
@@ -459,9 +650,14 @@ hipError_t launch_mlp_train_step(float* params, const float* x, const float* t, 
 
 hipError_t launch_mlp_forward(const float* params, const float* x, int B, float* y, float* act,
                               hipStream_t s) {
-    const int g = (B + kSamplesPerWG - 1) / kSamplesPerWG;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(g), dim3(256), 0, s, params, x, B, y, act);
-    return hipGetLastError();
+    return launch_fwd(params, x, B, y, act, nullptr, s);
+}
+
+hipError_t launch_mlp_predict(const float* params, const float* x, int B, const float* xlo,
+                              const float* xhi, const float* ymu, const float* ysd, float* y,
+                              hipStream_t s) {
+    const Affine af{xlo, xhi, ymu, ysd};
+    return launch_fwd(params, x, B, y, nullptr, &af, s);
 }
 
 hipError_t launch_mlp_backward(const float* params, const float* x, const float* act,

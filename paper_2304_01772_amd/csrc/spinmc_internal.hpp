@@ -206,6 +206,10 @@ hipError_t launch_cpm_area_recount(const CpmArgs& a, int n_tiles, int total_cell
 // Surrogate MLP
 hipError_t launch_mlp_forward(const float* params, const float* x, int B, float* y, float* act,
                               hipStream_t s);
+// forward on physical inputs: x' = 2 (x - xlo) / (xhi - xlo) - 1, y' = y ysd + ymu
+hipError_t launch_mlp_predict(const float* params, const float* x, int B, const float* xlo,
+                              const float* xhi, const float* ymu, const float* ysd, float* y,
+                              hipStream_t s);
 hipError_t launch_mlp_backward(const float* params, const float* x, const float* act,
                                const float* t, const float* w, int B, float* grad, float* dx,
                                float* loss, float* scratch, hipStream_t s);

@@ -148,3 +148,53 @@ def test_train_step_equals_the_separate_calls(L):
         _, bg, _ = mlp.magnitude_bounds(p_before, x.cpu().numpy(), t.cpu().numpy(),
                                         w.cpu().numpy())
         _close(b["g"].cpu().numpy(), go, bg)
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 63, 65, 32767, 32768, 131073])
+def test_forward_sizes_and_alignment(L, B):
+    """The forward at the edges of its sample tiles and of its two launch
+    forms (from 32768 samples on two tiles a wave), on an input at a 4-byte
+    offset from any vector boundary too: outputs and pre-activations against
+    the oracle, and the same bits from both alignments."""
+    rng = np.random.default_rng(B)
+    dev = torch.device("cuda")
+    P = mlp.init_params(rng)
+    P[512:640] = rng.normal(size=128).astype(np.float32) * 0.1
+    x = rng.uniform(-1, 1, size=(B, 4)).astype(np.float32)
+    Pt = torch.tensor(P, device=dev)
+    s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    outs = []
+    for off in (0, 1):
+        flat = torch.zeros(4 * B + 4, device=dev)
+        flat[off:off + 4 * B] = torch.tensor(x.reshape(-1), device=dev)
+        n_act = L.spinmc_mlp_act_floats(B)
+        act = torch.full((n_act + 4,), float("nan"), device=dev)
+        y = torch.full((B + 1, 3), float("nan"), device=dev)
+        assert L.spinmc_mlp_forward(_p(Pt), _p(flat[off:]), B, _p(y), _p(act[off:]), s) == 0
+        torch.cuda.synchronize()
+        assert torch.isnan(y[B]).all() and torch.isnan(act[off + n_act:]).all()
+        outs.append((y[:B].cpu().numpy(), act[off:off + n_act].cpu().numpy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    pick = np.unique(np.linspace(0, B - 1, min(B, 2000)).astype(int))
+    yo, cache = mlp.forward(P, x[pick])
+    by, _, _ = mlp.magnitude_bounds(P, x[pick], np.zeros((len(pick), 3), np.float32),
+                                    np.ones(3, np.float32))
+    _close(outs[0][0][pick], yo, by)
+
+
+@pytest.mark.parametrize("B", [1, 100, 40000])
+def test_predict_is_the_scaled_forward(L, B):
+    """predict() in one kernel equals scaling, forward and scaling as
+    separate tensor operations, bit for bit, and an input that is not a
+    contiguous float32 tensor takes those operations."""
+    from paper_2304_01772_amd.surrogate import BOX_HI, BOX_LO, SurrogateMLP
+    net = SurrogateMLP(seed=3)
+    net.y_mu = torch.tensor([0.3, -1.0, 2.0], device="cuda")
+    net.y_sd = torch.tensor([0.7, 1.3, 5.0], device="cuda")
+    g = np.random.default_rng(B)
+    x = torch.tensor(BOX_LO + (BOX_HI - BOX_LO) * g.random((B, 4)), dtype=torch.float32).cuda()
+    want = net.forward_normalised(net.normalise_x(x)) * net.y_sd + net.y_mu
+    assert torch.equal(net.predict(x), want)
+    strided = torch.zeros((B, 8), device="cuda")[:, ::2]
+    strided.copy_(x)
+    assert torch.equal(net.predict(strided), want)
