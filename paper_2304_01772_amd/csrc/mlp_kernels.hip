@@ -27,27 +27,10 @@ constexpr int oW1 = 0, ob1 = oW1 + kH * kIn, oW2 = ob1 + kH, ob2 = oW2 + kH * kH
               oW3 = ob2 + kH, ob3 = oW3 + kOut * kH, kNP = ob3 + kOut;
 constexpr int kSamplesPerWG = 64;
 constexpr int kPadK = 8;             // LDS row padding (bf16 elements) against bank conflicts
-constexpr int kK1 = 32;              // layer-1 K (4 inputs, zero-padded to one MFMA step)
-constexpr int kS1 = kK1 + kPadK;     // row stride of layer-1 tiles
-constexpr int kS2 = kH + kPadK;      // row stride of K=128 tiles
 constexpr int kST = kSamplesPerWG + kPadK;  // row stride of sample-major transposed tiles
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-
-__device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + __expf(-z)); }
-__device__ __forceinline__ float silu(float z) { return z * sigm(z); }
-__device__ __forceinline__ float dsilu(float z) {
-    const float s = sigm(z);
-    return s * (1.0f + z * (1.0f - s));
-}
 
 // Operand fragment of a 16 x 32 tile (rows r, k in [k0, k0 + 32)) from a
 // row-major bf16 tile: lane l holds row l % 16, k0 + 8 (l / 16) .. + 7, one
@@ -60,62 +43,6 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* base, int stride, int k0)
 
 __device__ __forceinline__ float4v mfma(bf16x8 a, bf16x8 b, float4v c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// Weights into LDS as BF16, [out][in] rows (B^T layout of the matrix cores).
-// 16-byte loads, all of a thread's loads issued before their conversions.
-__device__ void stage_weights(const float* P, uint16_t* w1, uint16_t* w2, uint16_t* w3,
-                              bool need_w2) {
-    // W1: 128 x 4 -> rows of kK1 (k >= 4 zero); one float4 per row
-    for (int n = threadIdx.x; n < kH; n += blockDim.x) {
-        const float4 v = *reinterpret_cast<const float4*>(P + oW1 + n * kIn);
-        uint16_t* r = w1 + n * kS1;
-        r[0] = f2bf(v.x);
-        r[1] = f2bf(v.y);
-        r[2] = f2bf(v.z);
-        r[3] = f2bf(v.w);
-#pragma unroll
-        for (int k = kIn; k < kK1; ++k) r[k] = 0;
-    }
-    if (need_w2) {
-        constexpr int kV = kH * kH / 4;  // float4 of W2
-        const float4* src = reinterpret_cast<const float4*>(P + oW2);
-        for (int i0 = threadIdx.x; i0 < kV; i0 += 16 * blockDim.x) {
-            float4 v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int i = i0 + u * (int)blockDim.x;
-                v[u] = i < kV ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int i = i0 + u * (int)blockDim.x;
-                if (i >= kV) break;
-                const int n = (4 * i) >> 7, k = (4 * i) & 127;
-                const uint32_t lo = (uint32_t)f2bf(v[u].x) | ((uint32_t)f2bf(v[u].y) << 16);
-                const uint32_t hi = (uint32_t)f2bf(v[u].z) | ((uint32_t)f2bf(v[u].w) << 16);
-                *reinterpret_cast<uint2*>(w2 + n * kS2 + k) = make_uint2(lo, hi);
-            }
-        }
-    }
-    // W3: 3 x 128 -> 16 rows (rows >= 3 zero)
-    for (int i = threadIdx.x; i < 16 * kH / 4; i += blockDim.x) {
-        const int n = (4 * i) >> 7, k = (4 * i) & 127;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (n < kOut) v = *reinterpret_cast<const float4*>(P + oW3 + n * kH + k);
-        const uint32_t lo = (uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16);
-        const uint32_t hi = (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16);
-        *reinterpret_cast<uint2*>(w3 + n * kS2 + k) = make_uint2(lo, hi);
-    }
-}
-
-// Output layer for the wave's 16 samples from h2 (bf16 tile): lane holds
-// y[row = 4(l/16)+i][col = l%16] (cols >= 3 are padding).
-__device__ __forceinline__ float4v out_layer(const uint16_t* h2, const uint16_t* w3) {
-    float4v acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kt = 0; kt < kH / 32; ++kt) acc = mfma(frag(h2, kS2, 32 * kt), frag(w3, kS2, 32 * kt), acc);
-    return acc;
 }
 
 }  // namespace
@@ -278,6 +205,31 @@ __device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (
     }
 }
 
+// The same for one tile with the pre-activations kept.
+__device__ __forceinline__ void hidden_layers_z(const FwdWeights& S, const uint4& xb, float4v (&z1)[8],
+                                                float4v (&z2)[8], uint32_t (&h1)[16],
+                                                uint32_t (&h2)[16]) {
+    const int l = (int)threadIdx.x & 63, g = l >> 4;
+#pragma unroll
+    for (int nt = 0; nt < 8; ++nt) {
+        z1[nt] = plus(mfma(as_frag(S.w1[nt * 64 + l]), as_frag(xb), float4v{0.f, 0.f, 0.f, 0.f}),
+                      S.b1[tile_neuron(nt, g) >> 2]);
+        h1[2 * nt] = pk_bf(silu_fast(z1[nt][0]), silu_fast(z1[nt][1]));
+        h1[2 * nt + 1] = pk_bf(silu_fast(z1[nt][2]), silu_fast(z1[nt][3]));
+    }
+#pragma unroll
+    for (int nt = 0; nt < 8; ++nt) {
+        float4v z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+            z = mfma(as_frag(S.w2[(nt * 4 + kt) * 64 + l]),
+                     as_frag(make_uint4(h1[4 * kt], h1[4 * kt + 1], h1[4 * kt + 2], h1[4 * kt + 3])), z);
+        z2[nt] = plus(z, S.b2[tile_neuron(nt, g) >> 2]);
+        h2[2 * nt] = pk_bf(silu_fast(z2[nt][0]), silu_fast(z2[nt][1]));
+        h2[2 * nt + 1] = pk_bf(silu_fast(z2[nt][2]), silu_fast(z2[nt][3]));
+    }
+}
+
 // Output layer: lanes 0..15 hold the three outputs of their sample.
 __device__ __forceinline__ float4v output_layer(const FwdWeights& S, const uint32_t (&h2)[16]) {
     const int l = (int)threadIdx.x & 63;
@@ -334,7 +286,6 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x,
         hidden_layers<C>(S, xb, s, B, act, avec, h2);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            if (!y) break;  // training steps keep only the pre-activations
             const float4v o = output_layer(S, h2[c]);
             if (g == 0 && s[c] < (size_t)B) {
 #pragma unroll
@@ -350,134 +301,219 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x,
 }
 
 // -------------------------------------------------------------- backward
-// Per-workgroup partial gradients into part[wg][kNP + 1] (last: loss), and
-// input gradients dx (optional).
-__global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x, const float* act,
+namespace {
+
+// FP32 buffer of one value per (sample, neuron): row stride 144, so that the
+// 16 neurons x 4 samples of an FP32 MFMA operand read 64 different banks.
+constexpr int kSF = kH + 16;
+
+struct BwdShared {
+    union {
+        FwdWeights f;
+        float h2[kSamplesPerWG * kSF];  // after the forward: bf16(silu z2) as FP32
+    };
+    uint4 w2t[8 * 4 * 64];                   // W2^T operands (rows: layer-1 neurons)
+    float4 w3[kOut][kH / 4];                 // bf16(W3) as FP32
+    float ba[kSamplesPerWG][16];             // [bf16(x) (4) | 1 | dY (3) | 0 ...]
+    uint16_t h1t[kH * kST], dz2t[kH * kST];  // [neuron][sample] as BF16
+    float dz[kSamplesPerWG * kSF];           // dz2, then dz1
+    float loss[4];
+};
+
+__device__ __forceinline__ void stage_w2t(const float* P, uint4* w2t) {
+    const float4* W2 = reinterpret_cast<const float4*>(P + oW2);
+    // task: layer-1 neurons 4 m .. + 3 against layer-2 neurons 8 o8 .. + 7
+    for (int q = (int)threadIdx.x; q < 32 * 16; q += (int)blockDim.x) {
+        const int m = q & 31, o8 = q >> 5;
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = W2[(8 * o8 + j) * 32 + m];
+        const int kt = o8 >> 2, g = o8 & 3;
+        const int nt = 2 * (m >> 3) + (m & 1), r = 4 * ((m >> 1) & 3);
+        uint4* d = w2t + (nt * 4 + kt) * 64 + r + 16 * g;
+        d[0] = make_uint4(pk_bf(v[0].x, v[1].x), pk_bf(v[2].x, v[3].x), pk_bf(v[4].x, v[5].x),
+                          pk_bf(v[6].x, v[7].x));
+        d[1] = make_uint4(pk_bf(v[0].y, v[1].y), pk_bf(v[2].y, v[3].y), pk_bf(v[4].y, v[5].y),
+                          pk_bf(v[6].y, v[7].y));
+        d[2] = make_uint4(pk_bf(v[0].z, v[1].z), pk_bf(v[2].z, v[3].z), pk_bf(v[4].z, v[5].z),
+                          pk_bf(v[6].z, v[7].z));
+        d[3] = make_uint4(pk_bf(v[0].w, v[1].w), pk_bf(v[2].w, v[3].w), pk_bf(v[4].w, v[5].w),
+                          pk_bf(v[6].w, v[7].w));
+    }
+}
+
+__device__ __forceinline__ float bf_lo(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+
+__device__ __forceinline__ float dsilu_fast(float z) {
+    const float s = sigm_fast(z);
+    return s * (1.0f + z * (1.0f - s));
+}
+
+// Sums over the workgroup's 64 samples of v[sample][neuron] ba[sample][col]
+// for the wave's neuron tile, on FP32 matrix instructions: lane l holds
+// neurons 16 tile + 4 (l / 16) + i of column l % 16.
+__device__ __forceinline__ float4v sample_sums(const float* v, const float (&ba)[16], int tile) {
+    const int l = (int)threadIdx.x & 63;
+    const float* p = v + (l >> 4) * kSF + 16 * tile + (l & 15);
+    float4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(p[4 * k * kSF], ba[k], acc, 0, 0, 0);
+    return acc;
+}
+
+}  // namespace
+
+// Partial gradients of 64 samples into part[wg][kNP + 1] (last: loss) and
+// input gradients dx (optional).  FWD: the forward of the same samples first
+// (a training step's one pass: pre-activations stay in registers and go to
+// act on the side); otherwise they come from act.  Four waves, 16 samples
+// each, in the forward's layout (a lane: one sample, eight groups of four
+// neurons): dz2 packed as BF16 is its own operand of dH1 = W2^T dz2; only
+// dW2, whose sum runs over samples, needs [neuron][sample] copies in LDS, and
+// the sums that stay FP32 (dW1, dW3 and the biases) run on FP32 matrix
+// instructions against one [sample][x | 1 | dY] table.  A step of 1024
+// samples is 16 workgroups, one chain of latencies each: forward and backward
+// as two launches with VALU sums and LDS activations 17.2 + 31.9 us, now 19.5.
+template <bool FWD>
+__global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x, float* act,
                                                  const float* t, const float* w, int B,
                                                  float* part, float* dx) {
-    __shared__ __align__(16) uint16_t w2t[kH * kS2];      // W2^T: [in][out]
-    __shared__ __align__(16) uint16_t w3[16 * kS2];
-    __shared__ __align__(16) uint16_t w1[kH * kS1];
-    __shared__ __align__(16) uint16_t h1t[kH * kST];      // h1^T: [neuron][sample]
-    __shared__ __align__(16) uint16_t dz2t[kH * kST];     // dz2b^T: [neuron][sample]
-    __shared__ __align__(16) uint16_t dz2[kSamplesPerWG * kS2];  // dz2b: [sample][neuron]
-    __shared__ __align__(16) uint16_t h2[4][16 * kS2];
-    constexpr int kSZ = kH + 4;
-    __shared__ __align__(16) float dz1[kSamplesPerWG * kSZ];
-    __shared__ float dY[kSamplesPerWG][4];
-    __shared__ float xs[kSamplesPerWG][kIn];  // bf16-rounded inputs, as float
-    __shared__ float red[256];
-    stage_weights(P, w1, nullptr, w3, false);
-    {
-        constexpr int kV = kH * kH / 4;
-        const float4* src = reinterpret_cast<const float4*>(P + oW2);
-        for (int i0 = threadIdx.x; i0 < kV; i0 += 16 * blockDim.x) {
-            float4 v[16];
+    __shared__ BwdShared S;
+    const int tid = (int)threadIdx.x, wave = tid >> 6, l = tid & 63, g = l >> 4, sl = l & 15;
+    const int base = (int)blockIdx.x * kSamplesPerWG;
+    const bool vec = ((uintptr_t)x & 15u) == 0, avec = ((uintptr_t)act & 15u) == 0;
+    const int row = 16 * wave + sl;  // the lane's sample within the workgroup
+    const size_t s[1] = {(size_t)base + row};
+    const bool in = s[0] < (size_t)B;
+    float4 xv = make_float4(0.f, 0.f, 0.f, 0.f);
+    float tv[kOut] = {0.f, 0.f, 0.f}, wv[kOut], bo[kOut];
+    if (in) {
+        xv = load_x(x, s[0], vec);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int i = i0 + u * (int)blockDim.x;
-                v[u] = i < kV ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int i = i0 + u * (int)blockDim.x;
-                if (i >= kV) break;
-                const int o = (4 * i) >> 7, in = (4 * i) & 127;
-                w2t[(in + 0) * kS2 + o] = f2bf(v[u].x);
-                w2t[(in + 1) * kS2 + o] = f2bf(v[u].y);
-                w2t[(in + 2) * kS2 + o] = f2bf(v[u].z);
-                w2t[(in + 3) * kS2 + o] = f2bf(v[u].w);
-            }
-        }
+        for (int j = 0; j < kOut; ++j) tv[j] = t[s[0] * kOut + j];
     }
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int base = blockIdx.x * kSamplesPerWG;
-    for (int i = threadIdx.x; i < kSamplesPerWG * kIn; i += blockDim.x) {
-        const int gs = base + i / kIn;
-        xs[i / kIn][i % kIn] = gs < B ? bf2f(f2bf(x[(size_t)gs * kIn + i % kIn])) : 0.f;
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+        wv[j] = w[j];
+        bo[j] = P[ob3 + j];
     }
-    // h1 (transposed) and h2 from the stored pre-activations
-    {
-        constexpr int kV = kSamplesPerWG * kH / 4;  // float4 per layer
-        static_assert(kV % 256 == 0, "act staging assumes 256 threads");
-        float4 z1[kV / 256], z2[kV / 256];
-#pragma unroll
-        for (int u = 0; u < kV / 256; ++u) {
-            const int i = threadIdx.x + 256 * u;
-            const int sm = (4 * i) >> 7, n = (4 * i) & 127;
-            const int gs = base + sm;
-            z1[u] = z2[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gs < B) {
-                z1[u] = *reinterpret_cast<const float4*>(act + (size_t)gs * 2 * kH + n);
-                z2[u] = *reinterpret_cast<const float4*>(act + (size_t)gs * 2 * kH + kH + n);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kV / 256; ++u) {
-            const int i = threadIdx.x + 256 * u;
-            const int sm = (4 * i) >> 7, n = (4 * i) & 127;
-            const bool in_b = base + sm < B;
-            const float a1[4] = {z1[u].x, z1[u].y, z1[u].z, z1[u].w};
-            const float a2[4] = {z2[u].x, z2[u].y, z2[u].z, z2[u].w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                h1t[(n + c) * kST + sm] = in_b ? f2bf(silu(a1[c])) : (uint16_t)0;
-                h2[sm >> 4][(sm & 15) * kS2 + n + c] = in_b ? f2bf(silu(a2[c])) : (uint16_t)0;
-            }
-        }
+    stage_fwd(P, S.f);
+    stage_w2t(P, S.w2t);
+    for (int d = tid; d < kOut * kH / 4; d += 256) {
+        const float4 v = reinterpret_cast<const float4*>(P + oW3)[d];
+        const uint32_t a = pk_bf(v.x, v.y), b = pk_bf(v.z, v.w);
+        (&S.w3[0][0])[d] = make_float4(bf_lo(a), bf_hi(a), bf_lo(b), bf_hi(b));
     }
     __syncthreads();
-    // recompute y for the wave's samples, then dY and the loss
-    const int col = l & 15, rb = 4 * (l >> 4);
-    const int s0 = wave * 16;
-    const float4v o = out_layer(h2[wave], w3);
-    float lossp = 0.f;
-    if (col < 4) {
+    // pre-activations of both layers, neurons tile_neuron(nt, g) + i
+    float4v z1[8], z2[8];
+    uint32_t h1[16], h2[16];
+    const uint32_t xa = pk_bf(xv.x, xv.y), xc = pk_bf(xv.z, xv.w);
+    if (FWD) {
+        const uint4 xb[1] = {g == 0 ? make_uint4(xa, xc, 0u, 0u) : make_uint4(0u, 0u, 0u, 0u)};
+        hidden_layers_z(S.f, xb[0], z1, z2, h1, h2);
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) {
+            if (!in) break;
+            store_act(act + s[0] * 2 * kH + tile_neuron(nt, g), z1[nt], avec);
+            store_act(act + s[0] * 2 * kH + kH + tile_neuron(nt, g), z2[nt], avec);
+        }
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) {
+            z1[nt] = z2[nt] = float4v{0.f, 0.f, 0.f, 0.f};
+            if (in) {
+                z1[nt] = *reinterpret_cast<const float4v*>(act + s[0] * 2 * kH + tile_neuron(nt, g));
+                z2[nt] = *reinterpret_cast<const float4v*>(act + s[0] * 2 * kH + kH + tile_neuron(nt, g));
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) {
+            h1[2 * nt] = pk_bf(silu_fast(z1[nt][0]), silu_fast(z1[nt][1]));
+            h1[2 * nt + 1] = pk_bf(silu_fast(z1[nt][2]), silu_fast(z1[nt][3]));
+            h2[2 * nt] = pk_bf(silu_fast(z2[nt][0]), silu_fast(z2[nt][1]));
+            h2[2 * nt + 1] = pk_bf(silu_fast(z2[nt][2]), silu_fast(z2[nt][3]));
+        }
+    }
+    if (!in) {  // samples past B: nothing to add
+#pragma unroll
+        for (int k = 0; k < 16; ++k) h1[k] = h2[k] = 0u;
+    }
+    // outputs (lanes g = 0), dY and the loss
+    const float4v o = output_layer(S.f, h2);
+    float dY[kOut], lossp = 0.f;
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+        const float e = (o[j] + bo[j]) - tv[j];
+        if (g == 0 && in) lossp += wv[j] * e * e;
+        const float d = in ? 2.0f * wv[j] * e / (float)B : 0.f;
+        dY[j] = __shfl(d, sl, 64);  // the sample's lane of g = 0
+    }
+    for (int k = 8; k >= 1; k >>= 1) lossp += __shfl_xor(lossp, k, 64);
+    if (l == 0) S.loss[wave] = lossp;
+    if (g == 0) {
+        float4* r = reinterpret_cast<float4*>(S.ba[row]);
+        r[0] = make_float4(bf_lo(xa), bf_hi(xa), bf_lo(xc), bf_hi(xc));
+        r[1] = make_float4(1.0f, dY[0], dY[1], dY[2]);
+        r[2] = r[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();  // the forward's operands are free from here
+    // dz2 = (W3b^T dY) silu'(z2)
+    uint32_t dzb[16];
+#pragma unroll
+    for (int nt = 0; nt < 8; ++nt) {
+        const int n0 = tile_neuron(nt, g);
+        float4 v[kOut];
+#pragma unroll
+        for (int j = 0; j < kOut; ++j) v[j] = S.w3[j][n0 >> 2];
+        float4v d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int s = s0 + rb + i, gs = base + s;
-            float d = 0.f;
-            if (col < kOut && gs < B) {
-                const float yv = o[i] + P[ob3 + col];
-                const float e = yv - t[(size_t)gs * kOut + col];
-                lossp += w[col] * e * e;
-                d = 2.0f * w[col] * e / (float)B;
-            }
-            dY[s][col] = d;
+            float dh = 0.f;
+#pragma unroll
+            for (int j = 0; j < kOut; ++j)
+                dh += dY[j] * (i == 0 ? v[j].x : (i == 1 ? v[j].y : (i == 2 ? v[j].z : v[j].w)));
+            d[i] = in ? dh * dsilu_fast(z2[nt][i]) : 0.f;
         }
-    }
-    red[threadIdx.x] = lossp;
-    __syncthreads();
-    // dH2 = W3b^T dY, dz2 = dH2 silu'(z2); eight pre-activations per lane
-    // loaded before their use
-    static_assert((kSamplesPerWG * kH) % (8 * 256) == 0, "dz2 batches assume 256 threads");
-    for (int i0 = threadIdx.x; i0 < kSamplesPerWG * kH; i0 += 8 * 256) {
-        float z2v[8];
+        *reinterpret_cast<float4v*>(S.dz + row * kSF + n0) = d;
+        dzb[2 * nt] = pk_bf(d[0], d[1]);
+        dzb[2 * nt + 1] = pk_bf(d[2], d[3]);
+        *reinterpret_cast<float4*>(S.h2 + row * kSF + n0) =
+            make_float4(bf_lo(h2[2 * nt]), bf_hi(h2[2 * nt]), bf_lo(h2[2 * nt + 1]),
+                        bf_hi(h2[2 * nt + 1]));
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + 256 * u;
-            const int gs = base + (i >> 7);
-            z2v[u] = gs < B ? act[(size_t)gs * 2 * kH + kH + (i & 127)] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + 256 * u;
-            const int s = i >> 7, n = i & 127;
-            float d = 0.f;
-            if (base + s < B) {
-                float dh = 0.f;
-#pragma unroll
-                for (int j = 0; j < kOut; ++j) dh += dY[s][j] * bf2f(w3[j * kS2 + n]);
-                d = dh * dsilu(z2v[u]);
-            }
-            const uint16_t db = f2bf(d);
-            dz2t[n * kST + s] = db;
-            dz2[s * kS2 + n] = db;
-            dz1[s * kSZ + n] = d;  // unrounded dz2, for db2 (dz1 is computed later)
+        for (int i = 0; i < 4; ++i) {
+            const int sh = 16 * (i & 1);
+            S.h1t[(n0 + i) * kST + row] = (uint16_t)(h1[2 * nt + (i >> 1)] >> sh);
+            S.dz2t[(n0 + i) * kST + row] = (uint16_t)(dzb[2 * nt + (i >> 1)] >> sh);
         }
     }
     __syncthreads();
     float* pg = part + (size_t)blockIdx.x * (kNP + 1);
+    float ba[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) ba[k] = S.ba[4 * k + g][sl];
+    // dW3 (columns 5..7 against h2), db2 (column 4 against dz2)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int tile = 2 * wave + m;
+        const float4v a3 = sample_sums(S.h2, ba, tile), a2 = sample_sums(S.dz, ba, tile);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n = 16 * tile + 4 * g + i;
+            if (sl >= 5 && sl < 8) pg[oW3 + (sl - 5) * kH + n] = a3[i];
+            if (sl == 4) pg[ob2 + n] = a2[i];
+        }
+    }
+    if (wave == 0) {  // db3: columns 5..7 against ones
+        float4v a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, ba[k], a, 0, 0, 0);
+        if (g == 0 && sl >= 5 && sl < 8) pg[ob3 + sl - 5] = a[0];
+    }
     // dW2 = dz2b^T h1 (M = out neuron, N = in neuron, K = 64 samples): wave
     // owns out-tiles 2*wave, 2*wave+1
     for (int mt = 2 * wave; mt < 2 * wave + 2; ++mt) {
@@ -486,84 +522,88 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
             float4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < kSamplesPerWG / 32; ++kt)
-                acc = mfma(frag(dz2t + mt * 16 * kST, kST, 32 * kt),
-                           frag(h1t + nt * 16 * kST, kST, 32 * kt), acc);
+                acc = mfma(frag(S.dz2t + mt * 16 * kST, kST, 32 * kt),
+                           frag(S.h1t + nt * 16 * kST, kST, 32 * kt), acc);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                pg[oW2 + (mt * 16 + rb + i) * kH + nt * 16 + col] = acc[i];
+                pg[oW2 + (mt * 16 + 4 * g + i) * kH + nt * 16 + sl] = acc[i];
         }
     }
-    // dW3, db3 (VALU): out j, neuron n
-    for (int i = threadIdx.x; i < kOut * kH; i += blockDim.x) {
-        const int j = i >> 7, n = i & 127;
-        float s = 0.f;
-        for (int q = 0; q < kSamplesPerWG; ++q) s += dY[q][j] * bf2f(h2[q >> 4][(q & 15) * kS2 + n]);
-        pg[oW3 + j * kH + n] = s;
-    }
-    if (threadIdx.x < kOut) {
-        float s = 0.f;
-        for (int q = 0; q < kSamplesPerWG; ++q) s += dY[q][threadIdx.x];
-        pg[ob3 + threadIdx.x] = s;
-    }
-    // db2 = sum of the unrounded dz2 (zero for samples past B)
-    if (threadIdx.x < kH) {
-        const int n = threadIdx.x;
-        float s = 0.f;
-        for (int q = 0; q < kSamplesPerWG; ++q) s += dz1[q * kSZ + n];
-        pg[ob2 + n] = s;
-    }
-    __syncthreads();
-    // dH1 = dz2b W2b (the wave's 16 samples), dz1 = dH1 silu'(z1)
+    // dH1 = W2b^T dz2b, dz1 = dH1 silu'(z1)
+    float4v d1[8];
 #pragma unroll
-    for (int nt = 0; nt < kH / 16; ++nt) {
+    for (int nt = 0; nt < 8; ++nt) {
         float4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kt = 0; kt < kH / 32; ++kt)
-            acc = mfma(frag(dz2 + s0 * kS2, kS2, 32 * kt), frag(w2t + nt * 16 * kS2, kS2, 32 * kt),
-                       acc);
-        const int n = nt * 16 + col;
+        for (int kt = 0; kt < 4; ++kt)
+            acc = mfma(as_frag(S.w2t[(nt * 4 + kt) * 64 + l]),
+                       as_frag(make_uint4(dzb[4 * kt], dzb[4 * kt + 1], dzb[4 * kt + 2],
+                                          dzb[4 * kt + 3])), acc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = s0 + rb + i, gs = base + s;
-            dz1[s * kSZ + n] = gs < B ? acc[i] * dsilu(act[(size_t)gs * 2 * kH + n]) : 0.f;
-        }
-    }
-    __syncthreads();
-    // dW1, db1 (VALU) and dx
-    for (int i = threadIdx.x; i < kH * (kIn + 1); i += blockDim.x) {
-        const int n = i / (kIn + 1), k = i % (kIn + 1);
-        float s = 0.f;
-        for (int q = 0; q < kSamplesPerWG; ++q)  // dz1 is zero for samples past B
-            s += dz1[q * kSZ + n] * (k < kIn ? xs[q][k] : 1.0f);
-        if (k < kIn)
-            pg[oW1 + n * kIn + k] = s;
-        else
-            pg[ob1 + n] = s;
+        for (int i = 0; i < 4; ++i) d1[nt][i] = in ? acc[i] * dsilu_fast(z1[nt][i]) : 0.f;
     }
     if (dx) {
-        for (int i = threadIdx.x; i < kSamplesPerWG * kIn; i += blockDim.x) {
-            const int q = i >> 2, k = i & 3;
-            const int gs = base + q;
-            if (gs >= B) continue;
-            float s = 0.f;
-            for (int n = 0; n < kH; ++n) s += dz1[q * kSZ + n] * bf2f(w1[n * kS1 + k]);
-            dx[(size_t)gs * kIn + k] = s;
+        // each lane its 32 neurons, then the four lanes of the sample
+        float v[kIn] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 q = reinterpret_cast<const float4*>(P + oW1)[tile_neuron(nt, g) + i];
+                const uint32_t a = pk_bf(q.x, q.y), b = pk_bf(q.z, q.w);
+                v[0] += d1[nt][i] * bf_lo(a);
+                v[1] += d1[nt][i] * bf_hi(a);
+                v[2] += d1[nt][i] * bf_lo(b);
+                v[3] += d1[nt][i] * bf_hi(b);
+            }
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            v[k] += __shfl_xor(v[k], 16, 64);
+            v[k] += __shfl_xor(v[k], 32, 64);
+            if (g == 0 && in) dx[s[0] * kIn + k] = v[k];
         }
     }
-    // loss partial
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
+    __syncthreads();  // every wave has read dz2
+#pragma unroll
+    for (int nt = 0; nt < 8; ++nt)
+        *reinterpret_cast<float4v*>(S.dz + row * kSF + tile_neuron(nt, g)) = d1[nt];
+    __syncthreads();
+    // dW1 (columns 0..3), db1 (column 4)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int tile = 2 * wave + m;
+        const float4v a1 = sample_sums(S.dz, ba, tile);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n = 16 * tile + 4 * g + i;
+            if (sl < kIn) pg[oW1 + n * kIn + sl] = a1[i];
+            if (sl == 4) pg[ob1 + n] = a1[i];
+        }
     }
-    if (threadIdx.x == 0) pg[kNP] = red[0] / (float)B;
+    if (tid == 0) pg[kNP] = (S.loss[0] + S.loss[1] + S.loss[2] + S.loss[3]) / (float)B;
+}
+
+// Sum of the per-workgroup partials of entry i in their order, 16 loads in
+// flight at a time.
+__device__ __forceinline__ float partial_sum(const float* part, int n_wg, int i) {
+    float s = 0.f;
+    for (int g0 = 0; g0 < n_wg; g0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            v[u] = g0 + u < n_wg ? part[(size_t)(g0 + u) * (kNP + 1) + i] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (g0 + u < n_wg) s += v[u];
+    }
+    return s;
 }
 
 // Fixed-order sum of the per-workgroup partials.
 __global__ void k_mlp_reduce(const float* part, int n_wg, float* grad, float* loss) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i > kNP) return;
-    float s = 0.f;
-    for (int g = 0; g < n_wg; ++g) s += part[(size_t)g * (kNP + 1) + i];
+    const float s = partial_sum(part, n_wg, i);
     if (i < kNP)
         grad[i] = s;
     else if (loss)
@@ -590,8 +630,7 @@ __global__ void k_mlp_reduce_adam(const float* part, int n_wg, float* grad, floa
                                   float eps, float c1, float c2) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i > kNP) return;
-    float gi = 0.f;
-    for (int g = 0; g < n_wg; ++g) gi += part[(size_t)g * (kNP + 1) + i];
+    const float gi = partial_sum(part, n_wg, i);
     if (i == kNP) {
         if (loss) *loss = gi;
         return;
@@ -635,11 +674,9 @@ hipError_t launch_mlp_train_step(float* params, const float* x, const float* t, 
                                  float b1, float b2, float eps, float* loss, float* act,
                                  float* scratch, hipStream_t s) {
     const int g = (B + kSamplesPerWG - 1) / kSamplesPerWG;
-    hipError_t e = launch_fwd(params, x, B, nullptr, act, nullptr, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_bwd, dim3(g), dim3(256), 0, s, params, x, act, t, w, B, scratch,
+    hipLaunchKernelGGL(k_mlp_bwd<true>, dim3(g), dim3(256), 0, s, params, x, act, t, w, B, scratch,
                        (float*)nullptr);
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float c1 = (float)(1.0 - std::pow((double)b1, (double)step));
     const float c2 = (float)(1.0 - std::pow((double)b2, (double)step));
@@ -664,7 +701,8 @@ hipError_t launch_mlp_backward(const float* params, const float* x, const float*
                                const float* t, const float* w, int B, float* grad, float* dx,
                                float* loss, float* scratch, hipStream_t s) {
     const int g = (B + kSamplesPerWG - 1) / kSamplesPerWG;
-    hipLaunchKernelGGL(k_mlp_bwd, dim3(g), dim3(256), 0, s, params, x, act, t, w, B, scratch, dx);
+    hipLaunchKernelGGL(k_mlp_bwd<false>, dim3(g), dim3(256), 0, s, params, x, const_cast<float*>(act),
+                       t, w, B, scratch, dx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mlp_reduce, dim3((kNP + 1 + 255) / 256), dim3(256), 0, s, scratch, g,

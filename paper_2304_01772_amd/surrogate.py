@@ -101,7 +101,7 @@ class SurrogateMLP:
         return y * self.y_sd + self.y_mu
 
     def train_step(self, xn, tn, w, lr=1e-3):
-        """Forward, backward and Adam in one library call (three launches)."""
+        """Forward, backward and Adam in one library call (two launches)."""
         B = xn.shape[0]
         b = self._buffers(B)
         self.step_no += 1

@@ -198,3 +198,46 @@ def test_predict_is_the_scaled_forward(L, B):
     strided = torch.zeros((B, 8), device="cuda")[:, ::2]
     strided.copy_(x)
     assert torch.equal(net.predict(strided), want)
+
+
+@pytest.mark.parametrize("B", [1, 16, 63, 64, 65, 1040])
+def test_train_step_gradient_at_workgroup_edges(L, B):
+    """One training step from zero moments at the edges of the 64-sample
+    workgroups and 16-sample tiles, x and act 4 bytes off any vector boundary:
+    the gradient, the pre-activations and the loss against the oracle, nothing
+    written past the workspace, and a second run with the same bits."""
+    rng = np.random.default_rng(300 + B)
+    dev = torch.device("cuda")
+    P = mlp.init_params(rng)
+    P[512:640] = rng.normal(size=128).astype(np.float32) * 0.1
+    x = rng.normal(size=(B, 4)).astype(np.float32)
+    t = rng.normal(size=(B, 3)).astype(np.float32)
+    w = np.array([1.0, 0.5, 2.0], np.float32)
+    s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    n_ws = L.spinmc_mlp_workspace_floats(B)
+    runs = []
+    for _ in range(2):
+        p = torch.tensor(P, device=dev)
+        xf = torch.zeros(4 * B + 1, device=dev)
+        xf[1:] = torch.tensor(x.reshape(-1), device=dev)
+        m, v, g = (torch.zeros(mlp.NP, device=dev) for _ in range(3))
+        act = torch.empty(L.spinmc_mlp_act_floats(B) + 1, device=dev)
+        ws = torch.full((n_ws + 8,), 7.0, device=dev)
+        loss = torch.empty(1, device=dev)
+        tt, wt = torch.tensor(t, device=dev), torch.tensor(w, device=dev)
+        assert L.spinmc_mlp_train_step(_p(p), _p(xf[1:]), _p(tt), _p(wt), B, _p(g), _p(m), _p(v), 1,
+                                       1e-3, 0.9, 0.999, 1e-8, _p(loss), _p(act[1:]), _p(ws), s) == 0
+        torch.cuda.synchronize()
+        assert (ws[n_ws:] == 7.0).all()
+        runs.append([a.cpu().numpy() for a in (g, p, loss, act[1:])])
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+    g, _, loss, act = runs[0]
+    go, _, losso = mlp.backward(P, x, t, w)
+    _, bg, _ = mlp.magnitude_bounds(P, x, t, w)
+    _close(g, go, bg)
+    assert abs(float(loss[0]) - losso) <= 2.0 ** -6 * losso + 1e-6
+    y = torch.empty((B, 3), device=dev)
+    act2 = torch.empty(L.spinmc_mlp_act_floats(B), device=dev)
+    Pt, xt = torch.tensor(P, device=dev), torch.tensor(x, device=dev)
+    assert L.spinmc_mlp_forward(_p(Pt), _p(xt), B, _p(y), _p(act2), s) == 0
+    assert np.array_equal(act2.cpu().numpy(), act)
