@@ -470,10 +470,431 @@ __global__ void __launch_bounds__(256) k_dmc_gather(DmcArgs a, int c, float* gs,
     gs[off + d.i] += acc;
 }
 
+// ---- resident chain ----------------------------------------------------------
+// All passes of a call in one launch, one workgroup per replica.  A lane owns
+// NI consecutive rows (NI even, from a row that NI divides, so that every
+// row's parity is known at compile time) of an 8-column span for the whole
+// launch and keeps their couplings in registers -- eight bonds and the one
+// left of the span per row, the vertical bonds of its rows and of the row
+// above -- while the spins sit in LDS as two colour planes.  A pass reads the
+// other plane, writes its own and ends at a barrier, so that global memory
+// sees the inputs once, the saved spins (which the gradient needs) and the
+// result: 8 B per attempt at most instead of the 32 (forward) and 76
+// (backward) of a launch per pass, which re-reads spins and couplings.  Bound
+// by VALU work: two exponentials, a division and Philox, about 90
+// lane-instructions an attempt forward, 130 backward.
+namespace {
+
+struct ResLane {
+    int y0, j, G, W;      // first row, span, spans per row, plane row length
+    int o, ou, od;        // plane offsets of the span in rows y0, y0 - 1, y0 + NI
+    int dL, dR;           // from a span to the columns left and right of it
+    bool in;
+
+    // Opaque offsets: a row's addresses are a few additions from these, and
+    // worked out in the row; kept over the loop of passes instead, those of
+    // all rows and passes would take the registers that the rows' state needs.
+    __device__ __forceinline__ ResLane here() const {
+        ResLane l = *this;
+        asm volatile("" : "+v"(l.o), "+v"(l.ou), "+v"(l.od), "+v"(l.dL), "+v"(l.dR));
+        return l;
+    }
+};
+
+template <int NI>
+__device__ __forceinline__ ResLane res_lane(const DmcArgs& a) {
+    ResLane L;
+    L.G = a.Lx >> 3;
+    L.W = a.Lx >> 1;
+    const int rows = a.Ly / NI;
+    L.in = (int)threadIdx.x < rows * L.G;
+    const int t = L.in ? (int)threadIdx.x : 0;
+    const int rg = t / L.G;
+    L.j = t - rg * L.G;
+    L.y0 = rg * NI;
+    L.o = L.y0 * L.W + 4 * L.j;
+    L.ou = (L.y0 == 0 ? a.Ly - 1 : L.y0 - 1) * L.W + 4 * L.j;
+    L.od = (L.y0 + NI == a.Ly ? 0 : L.y0 + NI) * L.W + 4 * L.j;
+    L.dL = L.j == 0 ? L.W - 1 : -1;
+    L.dR = L.j + 1 == L.G ? -4 * L.j : 4;
+    return L;
+}
+
+__device__ __forceinline__ void unpack8(const Row8& r, float* v) {
+    v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
+    v[4] = r.b.x; v[5] = r.b.y; v[6] = r.b.z; v[7] = r.b.w;
+}
+
+__device__ __forceinline__ void store8(float* p, const float* v) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+}
+
+// jx[r][0] the bond left of the span, jx[r][1 + x] bond x
+template <int NI>
+__device__ __forceinline__ void res_jx(const DmcArgs& a, const ResLane& L, size_t off,
+                                       float (&jx)[NI][9]) {
+    const float* Jx = a.Jx + off;
+    const int x0 = 8 * L.j, xl = L.j == 0 ? a.Lx - 1 : x0 - 1;
+#pragma unroll
+    for (int r = 0; r < NI; ++r) {
+        const uint32_t row = (uint32_t)(L.y0 + r) * a.Lx;
+        jx[r][0] = Jx[row + xl];
+        unpack8(ld8(Jx + row + x0), &jx[r][1]);
+    }
+}
+
+// jy[r] the bonds above row y0 + r
+template <int NI>
+__device__ __forceinline__ void res_jy(const DmcArgs& a, const ResLane& L, size_t off,
+                                       float (&jy)[NI + 1][8]) {
+    const float* Jy = a.Jy + off;
+    const int x0 = 8 * L.j;
+#pragma unroll
+    for (int r = 0; r < NI; ++r)
+        unpack8(ld8(Jy + (uint32_t)(L.y0 + r) * a.Lx + x0), &jy[r + 1][0]);
+    const uint32_t up = (uint32_t)(L.y0 == 0 ? a.Ly - 1 : L.y0 - 1) * a.Lx;
+    unpack8(ld8(Jy + up + x0), &jy[0][0]);
+}
+
+// The lane's rows of a natural-order lattice into the planes and back
+template <int NI>
+__device__ __forceinline__ void res_load(const float* s, int Lx, const ResLane& L, float* sp,
+                                         int plane) {
+#pragma unroll
+    for (int r = 0; r < NI; ++r) {
+        const Row8 v = ld8(s + (uint32_t)(L.y0 + r) * Lx + 8 * L.j);
+        float* q = sp + L.o + r * L.W;
+        *reinterpret_cast<float4*>(q + (r & 1) * plane) = make_float4(v.a.x, v.a.z, v.b.x, v.b.z);
+        *reinterpret_cast<float4*>(q + (1 - (r & 1)) * plane) =
+            make_float4(v.a.y, v.a.w, v.b.y, v.b.w);
+    }
+}
+
+template <int NI>
+__device__ __forceinline__ void res_store(float* s, int Lx, const ResLane& L, const float* sp,
+                                          int plane) {
+#pragma unroll
+    for (int r = 0; r < NI; ++r) {
+        const float* q = sp + L.o + r * L.W;
+        const float4 e = *reinterpret_cast<const float4*>(q + (r & 1) * plane);
+        const float4 o = *reinterpret_cast<const float4*>(q + (1 - (r & 1)) * plane);
+        float* d = s + (uint32_t)(L.y0 + r) * Lx + 8 * L.j;
+        *reinterpret_cast<float4*>(d) = make_float4(e.x, o.x, e.y, o.y);
+        *reinterpret_cast<float4*>(d + 4) = make_float4(e.z, o.z, e.w, o.w);
+    }
+}
+
+// A row's values in the other plane around its four own sites: row y itself
+// with the value beyond the span on the side PAR reaches, rows y + 1 and
+// y - 1
+struct ResNb {
+    float m[4], e, d[4], u[4];
+};
+
+template <int NI, int PAR, int R>
+__device__ __forceinline__ ResNb res_nb(const float* p, const ResLane& L) {
+    ResNb n;
+    const int o = L.o + R * L.W;
+    const float4 m = *reinterpret_cast<const float4*>(p + o);
+    const float4 u = *reinterpret_cast<const float4*>(p + (R == 0 ? L.ou : o - L.W));
+    const float4 d = *reinterpret_cast<const float4*>(p + (R == NI - 1 ? L.od : o + L.W));
+    n.e = p[o + (PAR ? L.dR : L.dL)];
+    n.m[0] = m.x; n.m[1] = m.y; n.m[2] = m.z; n.m[3] = m.w;
+    n.u[0] = u.x; n.u[1] = u.y; n.u[2] = u.z; n.u[3] = u.w;
+    n.d[0] = d.x; n.d[1] = d.y; n.d[2] = d.z; n.d[3] = d.w;
+    return n;
+}
+
+// horizontal neighbours of own site u (column 2u + PAR of the span)
+template <int PAR>
+__device__ __forceinline__ float nb_left(const ResNb& n, int u) {
+    return PAR ? n.m[u] : (u == 0 ? n.e : n.m[u > 0 ? u - 1 : 0]);
+}
+template <int PAR>
+__device__ __forceinline__ float nb_right(const ResNb& n, int u) {
+    return PAR ? (u == 3 ? n.e : n.m[u < 3 ? u + 1 : 3]) : n.m[u];
+}
+
+template <int NI, int C, int R>
+__device__ __forceinline__ void res_fwd_row(const DmcArgs& a, const ResLane& L, float* sp, int plane,
+                                            uint32_t p, uint32_t rid, float* save,
+                                            const float (&jx)[NI][9], const float (&jy)[NI + 1][8]) {
+    constexpr int PAR = (R + C) & 1;
+    const int o = L.o + R * L.W, b = o >> 2;  // Philox block: within-colour index / 4
+    float* own = sp + C * plane + o;
+    const ResNb n = res_nb<NI, PAR, R>(sp + (1 - C) * plane, L);
+    const float4 so = *reinterpret_cast<const float4*>(own);
+    uint32_t w[4];
+    philox4x32_10((uint32_t)b, p, rid, kTagDmc, a.key0, a.key1, w);
+    float snew[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = 2 * u + PAR;
+        const float sv = el4(so, u);
+        const DmcUpd Q = dmc_update(sv, jx[R][x + 1], nb_right<PAR>(n, u), jx[R][x],
+                                    nb_left<PAR>(n, u), jy[R + 1][x], n.d[u], jy[R][x], n.u[u],
+                                    a.beta, a.alpha, a.h, w[u]);
+        snew[u] = sv * (1.0f - 2.0f * Q.q);
+    }
+    *reinterpret_cast<float4*>(save + o) = so;
+    *reinterpret_cast<float4*>(own) = make_float4(snew[0], snew[1], snew[2], snew[3]);
+}
+
+template <int NI, int C>
+__device__ __forceinline__ void res_fwd_pass(const DmcArgs& a, const ResLane& L, float* sp, int plane,
+                                             uint32_t p, uint32_t rid, float* save,
+                                             const float (&jx)[NI][9], const float (&jy)[NI + 1][8]) {
+    res_fwd_row<NI, C, 0>(a, L, sp, plane, p, rid, save, jx, jy);
+    res_fwd_row<NI, C, 1>(a, L, sp, plane, p, rid, save, jx, jy);
+    if constexpr (NI == 4) {
+        res_fwd_row<NI, C, 2>(a, L, sp, plane, p, rid, save, jx, jy);
+        res_fwd_row<NI, C, 3>(a, L, sp, plane, p, rid, save, jx, jy);
+    }
+}
+
+// What a lane carries through the replay: the horizontal couplings, the
+// gradients of all its bonds (those left of the span and above the first row
+// are shares that go to the lanes that own the bonds at the end) and the
+// adjoints g.  (The vertical couplings too would be 40 more registers of the
+// 256 a lane of eight waves has at NI = 4: they sit in LDS, in colour planes
+// like the spins.)
+template <int NI>
+struct ResGrad {
+    float jx[NI][9], gx[NI][9], gy[NI + 1][8], g[NI][8];
+};
+
+template <int NI, int C, int R>
+__device__ __forceinline__ void res_bwd_row(const DmcArgs& a, const ResLane& L0, float* sp,
+                                            const float* jp, const float* tp, int plane, uint32_t p,
+                                            uint32_t rid, bool first, const float4& sold4,
+                                            float (&tv)[NI][4], ResGrad<NI>& S) {
+    constexpr int PAR = (R + C) & 1;
+    const ResLane L = L0.here();
+    const int o = L.o + R * L.W, b = o >> 2;
+    const ResNb n = res_nb<NI, PAR, R>(sp + (1 - C) * plane, L);
+    const ResNb t4 = res_nb<NI, PAR, R>(tp, L);
+    const float4 jd4 = *reinterpret_cast<const float4*>(jp + C * plane + o);
+    const float4 ju4 =
+        *reinterpret_cast<const float4*>(jp + (1 - C) * plane + (R == 0 ? L.ou : o - L.W));
+    uint32_t w[4];
+    philox4x32_10((uint32_t)b, p, rid, kTagDmc, a.key0, a.key1, w);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = 2 * u + PAR;
+        const float sv = el4(sold4, u);
+        const float jr = S.jx[R][x + 1], jl = S.jx[R][x], jd = el4(jd4, u), ju = el4(ju4, u);
+        const float sr = nb_right<PAR>(n, u), sl = nb_left<PAR>(n, u);
+        const DmcUpd Q = dmc_update(sv, jr, sr, jl, sl, jd, n.d[u], ju, n.u[u], a.beta, a.alpha,
+                                    a.h, w[u]);
+        float av = S.g[R][x];
+        if (!first)
+            av += jr * nb_right<PAR>(t4, u) + jl * nb_left<PAR>(t4, u) + jd * t4.d[u] + ju * t4.u[u];
+        const float wq = 4.0f * a.alpha * a.beta * Q.q * (1.0f - Q.q) * Q.P;
+        S.g[R][x] = av * ((1.0f - 2.0f * Q.q) + wq * sv * Q.hloc);
+        const float t = av * wq * sv * sv;
+        tv[R][u] = t;
+        S.gx[R][x + 1] += t * sr;
+        S.gx[R][x] += t * sl;
+        S.gy[R + 1][x] += t * n.d[u];
+        S.gy[R][x] += t * n.u[u];
+    }
+    *reinterpret_cast<float4*>(sp + C * plane + o) = sold4;
+    // rows stay in sequence: interleaved, their temporaries do not fit
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// One pass of the replay; nx holds the saved spins of its first row on entry
+// and those of the next pass's first row on exit (each row's load is issued a
+// row ahead), next the saved plane of the next pass (or this one's, if none).
+template <int NI, int C>
+__device__ __forceinline__ void res_bwd_pass(const DmcArgs& a, const ResLane& L, float* sp,
+                                             const float* jp, const float* tp, int plane, uint32_t p,
+                                             uint32_t rid, bool first, const float* save,
+                                             const float* next, float4& nx, float (&tv)[NI][4],
+                                             ResGrad<NI>& S) {
+    const int o = L.o, st = L.W;
+    float4 c = nx;
+    nx = *reinterpret_cast<const float4*>(save + o + st);
+    res_bwd_row<NI, C, 0>(a, L, sp, jp, tp, plane, p, rid, first, c, tv, S);
+    c = nx;
+    nx = *reinterpret_cast<const float4*>(NI == 4 ? save + o + 2 * st : next + o);
+    res_bwd_row<NI, C, 1>(a, L, sp, jp, tp, plane, p, rid, first, c, tv, S);
+    if constexpr (NI == 4) {
+        c = nx;
+        nx = *reinterpret_cast<const float4*>(save + o + 3 * st);
+        res_bwd_row<NI, C, 2>(a, L, sp, jp, tp, plane, p, rid, first, c, tv, S);
+        c = nx;
+        nx = *reinterpret_cast<const float4*>(next + o);
+        res_bwd_row<NI, C, 3>(a, L, sp, jp, tp, plane, p, rid, first, c, tv, S);
+    }
+}
+
+// The t of a pass into its plane: one plane serves both colours, since a pass
+// has read the previous one's (a barrier apart) before it writes its own.
+template <int NI>
+__device__ __forceinline__ void res_put_t(const ResLane& L, float* tp, const float (&tv)[NI][4]) {
+#pragma unroll
+    for (int r = 0; r < NI; ++r)
+        *reinterpret_cast<float4*>(tp + L.o + r * L.W) =
+            make_float4(tv[r][0], tv[r][1], tv[r][2], tv[r][3]);
+}
+
+// the t J terms of the last replayed pass (colour 0) on the colour-1 sites
+template <int NI, int R>
+__device__ __forceinline__ void res_gather_row(const DmcArgs& a, const ResLane& L, const float* jp,
+                                               const float* tp, int plane, ResGrad<NI>& S) {
+    constexpr int PAR = (R + 1) & 1;
+    const int o = L.o + R * L.W;
+    const ResNb t4 = res_nb<NI, PAR, R>(tp, L);
+    const float4 jd4 = *reinterpret_cast<const float4*>(jp + plane + o);
+    const float4 ju4 = *reinterpret_cast<const float4*>(jp + (R == 0 ? L.ou : o - L.W));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = 2 * u + PAR;
+        S.g[R][x] += S.jx[R][x + 1] * nb_right<PAR>(t4, u) + S.jx[R][x] * nb_left<PAR>(t4, u) +
+                     el4(jd4, u) * t4.d[u] + el4(ju4, u) * t4.u[u];
+    }
+}
+
+}  // namespace
+
+template <int NI>
+__global__ void __launch_bounds__(1024) k_dmc_resident_fwd(DmcArgs a, uint32_t p0, int n_sweeps,
+                                                           float* save) {
+    extern __shared__ __align__(16) float lds[];
+    const int plane = a.Ly * (a.Lx >> 1);
+    const int r = (int)blockIdx.x;
+    const size_t off = (size_t)r * a.Lx * a.Ly, step = (size_t)a.R * plane;
+    const ResLane L = res_lane<NI>(a);
+    const uint32_t rid = a.rid0 + (uint32_t)r;
+    float jx[NI][9], jy[NI + 1][8];
+    res_jx<NI>(a, L, off, jx);
+    res_jy<NI>(a, L, off, jy);
+    if (L.in) res_load<NI>(a.s + off, a.Lx, L, lds, plane);
+    __syncthreads();
+    float* sv = save + (size_t)r * plane;
+    for (int i = 0; i < n_sweeps; ++i) {
+        const uint32_t p = p0 + 2u * (uint32_t)i;
+        if (L.in) res_fwd_pass<NI, 0>(a, L, lds, plane, p, rid, sv, jx, jy);
+        __syncthreads();
+        if (L.in) res_fwd_pass<NI, 1>(a, L, lds, plane, p + 1u, rid, sv + step, jx, jy);
+        __syncthreads();
+        sv += 2 * step;
+    }
+    if (L.in) res_store<NI>(a.s + off, a.Lx, L, lds, plane);
+}
+
+// Dynamic LDS: two planes of the spins, two of the vertical couplings, one of
+// t = dL/dhloc.
+template <int NI>
+__global__ void __launch_bounds__(512) k_dmc_resident_bwd(DmcArgs a, uint32_t p0, int n_sweeps,
+                                                          const float* save, float* gs, float* gJx,
+                                                          float* gJy) {
+    extern __shared__ __align__(16) float lds[];
+    const int plane = a.Ly * (a.Lx >> 1), Lx = a.Lx;
+    float* jp = lds + 2 * plane;
+    float* tp = lds + 4 * plane;
+    const int r = (int)blockIdx.x;
+    const size_t off = (size_t)r * Lx * a.Ly, step = (size_t)a.R * plane;
+    const ResLane L = res_lane<NI>(a);
+    const uint32_t rid = a.rid0 + (uint32_t)r;
+    ResGrad<NI> S;
+    res_jx<NI>(a, L, off, S.jx);
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+        const uint32_t o = (uint32_t)(L.y0 + q) * Lx + 8 * L.j;
+        S.gx[q][0] = 0.f;
+        unpack8(ld8(gJx + off + o), &S.gx[q][1]);
+        unpack8(ld8(gJy + off + o), &S.gy[q + 1][0]);
+        unpack8(ld8(gs + off + o), &S.g[q][0]);
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) S.gy[0][x] = 0.f;
+    if (L.in) {
+        res_load<NI>(a.s + off, Lx, L, lds, plane);
+        res_load<NI>(a.Jy + off, Lx, L, jp, plane);
+    }
+    const float* sv = save + (size_t)(2 * n_sweeps - 1) * step + (size_t)r * plane;
+    float4 nx = *reinterpret_cast<const float4*>(sv + L.o);
+    float tv[NI][4];
+    __syncthreads();
+    for (int i = n_sweeps - 1; i >= 0; --i) {
+        const uint32_t p = p0 + 2u * (uint32_t)i;
+        if (L.in)
+            res_bwd_pass<NI, 1>(a, L, lds, jp, tp, plane, p + 1u, rid, i == n_sweeps - 1, sv,
+                                sv - step, nx, tv, S);
+        __syncthreads();
+        if (L.in) res_put_t<NI>(L, tp, tv);
+        __syncthreads();
+        sv -= step;
+        if (L.in)
+            res_bwd_pass<NI, 0>(a, L, lds, jp, tp, plane, p, rid, false, sv,
+                                i > 0 ? sv - step : sv, nx, tv, S);
+        __syncthreads();
+        if (L.in) res_put_t<NI>(L, tp, tv);
+        __syncthreads();
+        sv -= step;
+    }
+    if (L.in) {
+        res_gather_row<NI, 0>(a, L, jp, tp, plane, S);
+        res_gather_row<NI, 1>(a, L, jp, tp, plane, S);
+        if constexpr (NI == 4) {
+            res_gather_row<NI, 2>(a, L, jp, tp, plane, S);
+            res_gather_row<NI, 3>(a, L, jp, tp, plane, S);
+        }
+        res_store<NI>(a.s + off, Lx, L, lds, plane);
+    }
+    __syncthreads();  // the planes are free: shares of other lanes' bonds
+    const int lane = (int)threadIdx.x;
+    if (L.in) {
+        store8(lds + 8 * lane, S.gy[0]);
+#pragma unroll
+        for (int q = 0; q < NI; ++q) tp[NI * lane + q] = S.gx[q][0];
+    }
+    __syncthreads();
+    if (!L.in) return;
+    const int rows = a.Ly / NI, rg = L.y0 / NI;
+    const int below = (rg + 1 == rows ? 0 : rg + 1) * L.G + L.j;
+    const int right = rg * L.G + (L.j + 1 == L.G ? 0 : L.j + 1);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) S.gy[NI][x] += lds[8 * below + x];
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+        const uint32_t o = (uint32_t)(L.y0 + q) * Lx + 8 * L.j;
+        S.gx[q][8] += tp[NI * right + q];
+        store8(gJx + off + o, &S.gx[q][1]);
+        store8(gJy + off + o, &S.gy[q + 1][0]);
+        store8(gs + off + o, &S.g[q][0]);
+    }
+}
+
 namespace {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
+// Lanes of the resident form with NI rows a lane, or 0 where it does not fit.
+// Lattices up to 2^14 sites (8-column spans; the aligned buffers of the span
+// kernels).  Forward: 2 rows a lane, up to 1024 lanes.  Backward: 2 rows up to
+// 512 lanes (2^13 sites), 4 above, where the state of a lane fills 256
+// registers; that form's passes of one workgroup take 10 us, so it pays from
+// 24 replicas on (128 x 128, 10 sweeps: 213 us against 314 for a launch per
+// pass at 64 replicas, 203 against 198 at 16).  256 replicas of 128 x 128, 10
+// sweeps: forward 297 -> 95 us, backward 811 -> 203; 64 x 64, 4 replicas,
+// with the calls around it: forward 126 -> 60, backward 212 -> 103.
+int res_lanes(const DmcArgs& a, int NI, int max_lanes) {
+    if (a.Ly % NI != 0) return 0;
+    const int64_t lanes = (int64_t)(a.Ly / NI) * (a.Lx >> 3);
+    return lanes <= max_lanes ? (int)lanes : 0;
+}
+
+template <class F>
+hipError_t res_launch(F fn, const DmcArgs& a, int lanes, size_t lds, void** args, hipStream_t s) {
+    hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    return hipLaunchKernel((const void*)fn, dim3(a.R), dim3((lanes + 63) & ~63), args, lds, s);
+}
 
 }  // namespace
 
@@ -483,6 +904,12 @@ hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float
     const bool v8 = (a.Lx & 7) == 0 && aligned16(a.s) && aligned16(a.Jx) && aligned16(a.Jy) &&
                     aligned16(save);
     const int n_blocks = (n_sites + 3) >> 2;
+    if (const int lanes = v8 ? res_lanes(a, 2, 1024) : 0) {
+        DmcArgs b = a;
+        uint32_t p0 = (uint32_t)(2 * t0);
+        void* args[] = {&b, &p0, &n_sweeps, &save};
+        return res_launch(k_dmc_resident_fwd<2>, a, lanes, (size_t)8 * n_sites, args, s);
+    }
     const dim3 grid((n_blocks + 255) / 256, a.R), block(256);
     for (int i = 0; i < n_sweeps; ++i)
         for (int c = 0; c < 2; ++c) {
@@ -504,6 +931,15 @@ hipError_t launch_dmc_backward(const DmcArgs& a, uint64_t t0, int n_sweeps, cons
                     aligned16(save) && aligned16(gs) && aligned16(gJx) && aligned16(gJy) &&
                     aligned16(work);
     const int n_blocks = (n_sites + 3) >> 2;
+    {
+        const int l2 = v8 && n_sweeps > 0 ? res_lanes(a, 2, 512) : 0;
+        const int l4 = v8 && n_sweeps > 0 && l2 == 0 && a.R >= 24 ? res_lanes(a, 4, 512) : 0;
+        DmcArgs b = a;
+        uint32_t p0 = (uint32_t)(2 * t0);
+        void* args[] = {&b, &p0, &n_sweeps, &save, &gs, &gJx, &gJy};
+        if (l2) return res_launch(k_dmc_resident_bwd<2>, a, l2, (size_t)20 * n_sites, args, s);
+        if (l4) return res_launch(k_dmc_resident_bwd<4>, a, l4, (size_t)20 * n_sites, args, s);
+    }
     const dim3 grid((n_blocks + 255) / 256, a.R), gridg((n_sites + 255) / 256, a.R), block(256);
     // pass m = 2 i + c writes its t to plane m & 1 and folds in the t of
     // pass m + 1 from the other plane

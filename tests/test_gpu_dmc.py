@@ -187,3 +187,28 @@ def test_gradient_size_peaks_at_an_intermediate_temperature():
         want = float(torch.cat([jx.grad.abs().flatten(), jy.grad.abs().flatten()]).mean())
         got = sizes[Ts.index(T)]
         assert abs(got - want) <= 1e-3 * want + 1e-7, (T, got, want)
+
+
+# the LDS-resident forms at their edges: one row pair, one span a row, 510 of
+# 512 lanes (two rows a lane), the first size with four rows a lane (24
+# replicas), the largest lattice, and just past it (a launch per pass); 66 rows
+# of 136 have too many pairs for two rows a lane and do not divide by four
+@pytest.mark.parametrize("R,Ly,Lx,n", [
+    (2, 2, 8, 3), (1, 4, 16, 1), (3, 60, 8, 2), (2, 60, 136, 2), (24, 64, 136, 1), (24, 4, 4096, 1),
+    (25, 128, 128, 2), (24, 66, 136, 1), (3, 128, 128, 1), (24, 130, 128, 1)])
+def test_resident_chain_at_its_limits(R, Ly, Lx, n):
+    from paper_2304_01772_amd.dmc import relaxed_ising
+    s0, Jx, Jy, g = _case(R * 7 + Lx + Ly, R, Ly, Lx)
+    beta, alpha, h = 0.5, 6.0, float(np.float32(-0.02))
+    pick = sorted({0, R // 2, R - 1})
+    s0t, jx, jy = (torch.tensor(v, device="cuda", requires_grad=True) for v in (s0, Jx, Jy))
+    s = relaxed_ising(s0t, jx, jy, beta, alpha, h, n, 99, 3, 5)
+    (s * torch.tensor(g, device="cuda")).sum().backward()
+    want, gs0, gJx, gJy, _ = odmc.forward_backward(s0[pick], Jx[pick], Jy[pick], h, beta, alpha, 99,
+                                                   [5 + r for r in pick], 3, n, g[pick])
+    np.testing.assert_allclose(s.detach().cpu().numpy()[pick], want, rtol=0, atol=2e-5)
+    for got, ref in ((s0t.grad, gs0), (jx.grad, gJx), (jy.grad, gJy)):
+        got = got.cpu().numpy()
+        assert np.all(np.isfinite(got))
+        scale = max(1.0, float(np.abs(ref).max()))
+        np.testing.assert_allclose(got[pick], ref, rtol=0, atol=2e-4 * scale)
