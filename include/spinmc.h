@@ -298,9 +298,11 @@ int spinmc_thresholds(const spinmc_ctx *ctx, int32_t replica, uint64_t *host_T, 
  *   divide the lattice or cannot all be resident at once, the streamed passes
  *   run instead.  A barrier wait past its bound poisons the context as above.
  * Invalid values return SPINMC_E_INVALID.  CPM contexts: mode 2 keeps every
- * step on streamed passes; any other mode lets the unrecorded steps of
- * lattices whose ids and tables fit 64 KiB of LDS run resident (one
- * workgroup per replica).  tile_rows is rounded down to whole periods of
+ * step on streamed passes; any other mode lets the steps, recorded or not, of
+ * lattices whose ids (4 bytes a site, with a one- or two-cell halo), tables
+ * and attempt queues fit 156 KiB of LDS run resident (one workgroup per
+ * replica); with SPINMC_SCHED_PERSIST unrecorded steps of 3x3 lattices
+ * above 16384 sites run tiled instead.  tile_rows is rounded down to whole periods of
  * the colouring (2 rows, or 6 with the 5x5 neighbourhood).  wg_threads of
  * a streamed 3x3 pass where every Lx is a multiple of 8: 0 = one site per
  * lane in workgroups of 1024 (tiles of about 8192 sites by default), 512 =

@@ -4,15 +4,20 @@
 
 namespace spinmc {
 
-// LDS bytes of the resident kernel: thresholds, per-cell tables of cell_cap
-// entries, and the ids of the largest replica.
-size_t cpm_resident_lds_bytes(int tab_lds_bytes, int cell_cap, int max_sites);
+// LDS bytes of the resident kernel: thresholds, five per-cell arrays of
+// cell_cap entries, the waves' queues, and the ids with their halo (max_padded
+// sites for the largest replica); SIZE_MAX where a queue entry cannot hold a
+// within-colour index.
+size_t cpm_resident_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int max_sites,
+                              int max_padded);
 
-// n_steps unrecorded Monte Carlo steps of every replica in one launch, one
-// workgroup per replica (range 1 with every Lx % 8 == 0, or range 2; the LDS
-// above at most 64 KiB); the device step counter is not advanced.
-hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int tab_lds_bytes, int cell_cap,
-                               int max_sites, hipStream_t s);
+// n_steps Monte Carlo steps of every replica in one launch, one workgroup per
+// replica (range 1 with every Lx % 8 == 0, or range 2); the device step
+// counter is not advanced.  The launch holds steps sw0 .. sw0 + n_steps - 1 of
+// a call; with re > 0, step k re of the call stores its statistics (the whole
+// row) in stats row k - 1.
+hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int sw0, int re, int tab_lds_bytes,
+                               int cell_cap, int max_sites, int max_padded, hipStream_t s);
 
 // Tiled persistent passes (range 1, Lx % 8 == 0, TH | Ly, TW | Lx, TH even,
 // TW % 8 == 0): n_steps unrecorded Monte Carlo steps, one 256-thread

@@ -369,52 +369,6 @@ __device__ __forceinline__ void cpm_stage(const CpmArgs& a, const RepDev& R, con
 }
 
 
-// The copy attempt of site (y, x) of colour pass p, word u of Philox block kq
-// (the quad of four consecutive same-colour sites of the row): its Moore
-// window from ids, the decision, and on acceptance the id and area updates.
-__device__ __forceinline__ void cpm_moore_site(const CpmArgs& a, const RepDev& R, int32_t* ids,
-                                               int32_t* area, int y, int x, uint32_t kq, int u,
-                                               uint32_t p, const uint32_t* qthr,
-                                               const int32_t* lsa, const int8_t* lty,
-                                               const int32_t* ljs) {
-    const int Lx = R.Lx, Ly = R.Ly;
-    const int yu = y == 0 ? Ly - 1 : y - 1, yd = y + 1 == Ly ? 0 : y + 1;
-    const int xl = x == 0 ? Lx - 1 : x - 1, xr = x + 1 == Lx ? 0 : x + 1;
-    // int offsets: a replica holds fewer than 2^31 sites
-    const int32_t* ru = ids + yu * Lx;
-    const int32_t* ry = ids + y * Lx;
-    const int32_t* rd = ids + yd * Lx;
-    const int nb[8] = {ru[xl], ru[x], ru[xr], ry[xl], ry[xr], rd[xl], rd[x], rd[xr]};
-    const int s = ry[x];
-    uint32_t w[4];
-    philox4x32_10(kq, p, R.rid, kTagMain, a.key0, a.key1, w);
-    const uint32_t word = (u & 2) ? ((u & 1) ? w[3] : w[2]) : ((u & 1) ? w[1] : w[0]);
-    const int tg = cpm_decide(a, R, nb, s, word, 4u * kq + (uint32_t)u, p, qthr, lsa, lty, ljs);
-    if (tg >= 0) {
-        ids[y * Lx + x] = tg;
-        atomicAdd(&area[tg], 1);
-        atomicAdd(&area[s], -1);
-    }
-}
-
-// The colour-c sites of rows y0 .. y0 + rows - 1 (rows even), one per thread
-// of the loop: site j is word j & 3 of quad j >> 2.  (Streamed from global
-// memory the quad form is faster: its window loads serve four sites.)
-__device__ __forceinline__ void cpm_sites(const CpmArgs& a, const RepDev& R, int32_t* ids,
-                                          int32_t* area, int y0, int rows, int c, uint32_t p,
-                                          const uint32_t* qthr, const int32_t* lsa,
-                                          const int8_t* lty, const int32_t* ljs) {
-    const int Q = R.Lx >> 3, cy = c >> 1, cx = c & 1;
-    const int n = (rows >> 1) * (R.Lx >> 1);
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const int it = j >> 2, u = j & 3;
-        const int r = it / Q, qi = it - r * Q;
-        const int y = y0 + 2 * r + cy, x = 8 * qi + 2 * u + cx;
-        cpm_moore_site(a, R, ids, area, y, x, (uint32_t)((y >> 1) * Q + qi), u, p, qthr, lsa,
-                       lty, ljs);
-    }
-}
-
 // One quad's inputs: its 3 x 9 id window (rows y - 1, y, y + 1; the halo
 // column on the side of colour CX) and its Philox block.
 struct QuadIn {
@@ -639,74 +593,421 @@ __global__ void __launch_bounds__(1024) k_cpm_pass_site(CpmArgs a, int c, int sw
         site_pass<0>(a, c, sweep_off, qthr, lsa, lty, ljs, ldel);
 }
 
-// All n_steps unrecorded Monte Carlo steps of every replica in one launch:
-// one 1024-thread workgroup per replica with its ids, areas, cell tables and
-// thresholds in LDS.  Per pass the snapshot (area minus target) is taken in
-// LDS; then one site per thread.  Range 1 (Lx % 8 == 0): the four lanes of a
-// quad (four consecutive same-colour sites of a row, one Philox block)
-// compute the block alike and take one word each; range 2: the attempt of
-// the streamed 5x5 pass on the LDS ids.  A replica has 16 waves to hide the
-// latency of its table lookups; accepted copies update the areas with LDS
-// atomics, and a barrier closes the pass.  The same
-// decisions as the streamed passes; ids and areas are written back at the
-// end (the stored snapshot equals the areas then).
+// ------------------------------------------------------- two-phase attempts
+// Most attempts end at once: the chosen neighbour holds the site's own id.
+// A wave therefore works in two phases.  The first takes one Philox block of
+// four attempts per lane, looks at nothing but the two ids, and queues the
+// attempts that have to be decided (in LDS, in the wave's own segment, so
+// that no barrier lies between); the second decides the queued ones, one per
+// lane, so that no lane waits through a decision it does not have.  (One
+// attempt per lane, decided in place, ran every wave that held one boundary
+// site through the whole decision and computed each block four times.)
+namespace {
+
+// Queue entry: the attempt's accept prefix (bits 16..31), its within-colour
+// index and the chosen neighbour (range 1: index in bits 3..15, neighbour in
+// 0..2; range 2: index in bits 5..15, neighbour in 0..4).
 template <int RANGE>
-__global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps,
-                                                       int tab_lds_bytes, int cell_cap) {
-    // dynamic LDS: [T hi | T lo] (tab_lds_bytes) | snap - A | area | A (int32 [cell_cap] each)
-    // | type (int8 [cell_cap], padded to 16) | ids (int32 [Ly Lx])
-    extern __shared__ __align__(16) uint8_t dyn[];
-    uint32_t* qthr = reinterpret_cast<uint32_t*>(dyn);
-    int32_t* lsa = reinterpret_cast<int32_t*>(dyn + tab_lds_bytes);
-    int32_t* larea = lsa + cell_cap;
-    int32_t* lA = larea + cell_cap;
-    int8_t* lty = reinterpret_cast<int8_t*>(lA + cell_cap);
-    int32_t* lids = reinterpret_cast<int32_t*>(lty + ((cell_cap + 15) & ~15));
-    __shared__ int32_t ljs[kMaxCpmTypes * kMaxCpmTypes];
-    const RepDev R = a.reps[blockIdx.x];
-    const int Lx = R.Lx, Ly = R.Ly;
-    const int ncell = R.q + 1, n = Lx * Ly, nthr = (int)blockDim.x;
-    int32_t* gids = a.lat + R.lat_off;
-    int32_t* garea = a.area + R.cell_off;
-    for (int i = threadIdx.x; i < 2 * R.tab_n; i += nthr) qthr[i] = a.tab[R.tab_off + i];
-    for (int i = threadIdx.x; i < R.n_types * R.n_types; i += nthr) ljs[i] = a.js[R.js_off + i];
-    for (int i = threadIdx.x; i < ncell; i += nthr) {
-        larea[i] = garea[i];
-        lA[i] = a.target[R.cell_off + i];
-        lty[i] = a.ctype[R.cell_off + i];
+struct Entry {
+    static constexpr int kShift = RANGE == 1 ? 3 : 5;
+    static __device__ __forceinline__ uint32_t make(uint32_t word, uint32_t k, uint32_t jn) {
+        return (word & 0xFFFF0000u) | (k << kShift) | jn;
     }
-    for (int i = threadIdx.x; i < n / 4; i += nthr)
-        reinterpret_cast<int4*>(lids)[i] = reinterpret_cast<const int4*>(gids)[i];
-    __syncthreads();
-    const uint64_t t0 = *a.t_base;
-    constexpr int ncol = RANGE == 2 ? 9 : 4;
-    const int n_sites = n / ncol;  // sites of one colour
-    const auto sa = [=](int i) -> int64_t { return (int64_t)lsa[i]; };
-    for (int st = 0; st < n_steps; ++st) {
-        for (int c = 0; c < ncol; ++c) {
-            for (int i = threadIdx.x; i < ncell; i += nthr) lsa[i] = larea[i] - lA[i];
-            __syncthreads();
-            const uint32_t p = (uint32_t)(ncol * (t0 + (uint64_t)st) + (uint64_t)c);
-            if (RANGE == 2) {
-                // the 3x3 sublattice: colour c = 3 (y mod 3) + (x mod 3)
-                const int cy = c / 3, cx = c - 3 * cy, Wc = Lx / 3;
-                for (int j = threadIdx.x; j < n_sites; j += nthr) {
-                    const int r = j / Wc, i = j - r * Wc;
-                    cpm5_attempt(a, R, lids, larea, 3 * r + cy, 3 * i + cx, (uint32_t)j, p, qthr,
-                                 lty, ljs, sa);
-                }
-                __syncthreads();
-                continue;
+    static __device__ __forceinline__ uint32_t k(uint32_t e) { return (e & 0xFFFFu) >> kShift; }
+    static __device__ __forceinline__ uint32_t jn(uint32_t e) { return e & ((1u << kShift) - 1u); }
+};
+
+// Ids carry their cell's type, times eight, in the top byte: a type count is
+// one shift-and-add, and ids compare as whole words.
+__device__ __forceinline__ int id_of(uint32_t v) { return (int)(v & 0xFFFFFFu); }
+
+// Adhesion change for all pairs (type of the present id, type of the copied
+// one): d[t] = J[new][t] - J[old][t] per neighbour type, and the two diagonal
+// terms J[new][new], J[old][old] of neighbours that hold the id itself.
+struct PairTab {
+    int4 d[16];
+    int2 diag[16];
+};
+
+__device__ __forceinline__ void stage_pairs(const CpmArgs& a, const RepDev& R, PairTab* T, int tid) {
+    if (tid >= 16) return;
+    const int ts = tid >> 2, tt = tid & 3, nt = R.n_types;
+    const int32_t* js = a.js + R.js_off;
+    int v[4] = {0, 0, 0, 0};
+    int2 dg = make_int2(0, 0);
+    if (ts < nt && tt < nt) {
+        for (int t = 0; t < nt; ++t) v[t] = js[tt * nt + t] - js[ts * nt + t];
+        dg = make_int2(js[tt * nt + tt], js[ts * nt + ts]);
+    }
+    T->d[tid] = make_int4(v[0], v[1], v[2], v[3]);
+    T->diag[tid] = dg;
+}
+
+// The decision of one attempt: old id s, copied id tg (packed with types),
+// cnt the neighbours' type counts (a byte each), nt / ns how many neighbours
+// hold tg / s; da / db the pass-start area minus target of tg and s (not used
+// for the medium; R.small_areas is uniform).  Prefix r of W from the entry; the low half from the
+// fallback block of k.
+__device__ __forceinline__ bool cpm_accept(const CpmArgs& a, const RepDev& R, uint32_t s, uint32_t tg,
+                                           uint32_t cnt, int nt, int ns, const PairTab* T, int da,
+                                           int db, const uint32_t* thr, uint32_t r, uint32_t k,
+                                           uint32_t p) {
+    const int pi = (int)((s >> 27) * 4u + (tg >> 27));
+    const int4 d = T->d[pi];
+    const int2 dg = T->diag[pi];
+    const int kadh = __mul24((int)(cnt & 0xFFu), d.x) + __mul24((int)((cnt >> 8) & 0xFFu), d.y) +
+                     __mul24((int)((cnt >> 16) & 0xFFu), d.z) + __mul24((int)(cnt >> 24), d.w) -
+                     __mul24(nt, dg.x) + __mul24(ns, dg.y);
+    const bool ct = id_of(tg) != 0, cs = id_of(s) != 0;
+    const int xa = ct ? da : 0, xb = cs ? db : 0;
+    int64_t kk;
+    if (R.small_areas)  // the area term fits 32 bits, lambda S always does
+        kk = (int64_t)kadh + (int64_t)(int32_t)R.LS * (int64_t)(2 * (xa - xb) + ct + cs);
+    else
+        kk = (int64_t)kadh + R.LS * (2 * ((int64_t)xa - (int64_t)xb) + ct + cs);
+    if (kk <= 0) return true;
+    if (kk >= R.K0) return false;
+    uint32_t hi = 0u, lo = 1u;  // T = 1 for K1 <= k < K0
+    const bool tab = kk < (int64_t)R.K1;
+    if (tab) hi = thr[kk - 1];
+    if (r != hi) return r < hi;
+    if (tab) lo = thr[R.tab_n + kk - 1];
+    if (lo == 0u) return false;
+    uint32_t f[4];
+    philox4x32_10(k, p, R.rid, kTagFallback, a.key0, a.key1, f);
+    return (f[0] & 0xFFFFu) < lo;
+}
+
+// The wave's queued attempts (act[u] per word u) into its segment, by the
+// lanes' prefix counts; returns their number (uniform over the wave).
+__device__ __forceinline__ int queue_put(uint32_t* queue, const bool (&act)[4],
+                                         const uint32_t (&e)[4]) {
+    int total = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint64_t m = __ballot(act[u]);
+        if (act[u])
+            queue[__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)total))] =
+                e[u];
+        total += __popcll(m);
+    }
+    // the other lanes of the wave read the entries
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return total;
+}
+
+// The neighbour's offset for neighbour j of a lattice of row stride st.
+// Moore (range 1): the table holds offset + st + 1 for the eight neighbours,
+// low and high bytes apart, so that two byte permutes look it up.
+struct MooreTab {
+    uint32_t lo0, lo1, hi0, hi1;
+};
+__device__ __forceinline__ MooreTab moore_tab(int st) {
+    const int o[8] = {0, 1, 2, st, st + 2, 2 * st, 2 * st + 1, 2 * st + 2};
+    MooreTab t = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        t.lo0 |= (uint32_t)(o[j] & 255) << (8 * j);
+        t.hi0 |= (uint32_t)(o[j] >> 8) << (8 * j);
+        t.lo1 |= (uint32_t)(o[j + 4] & 255) << (8 * j);
+        t.hi1 |= (uint32_t)(o[j + 4] >> 8) << (8 * j);
+    }
+    return t;
+}
+__device__ __forceinline__ int moore_offset(const MooreTab& t, uint32_t word) {
+    const uint32_t sel = (word & 7u) | 0x0C0C0C00u;
+    return (int)(__builtin_amdgcn_perm(t.lo1, t.lo0, sel) |
+                 (__builtin_amdgcn_perm(t.hi1, t.hi0, sel) << 8));
+}
+// 5x5 (range 2): neighbour j of 24 in row-major order without the centre
+__device__ __forceinline__ int offset5(uint32_t j, int st) {
+    const uint32_t jj = j < 12u ? j : j + 1u;
+    const uint32_t dy = __umul24(jj, 13u) >> 6;  // jj / 5 for jj < 25
+    return (int)(__umul24(dy, (uint32_t)st) + jj - __umul24(dy, 5u));
+}
+
+// exact quotient b / d for b < 2^16 from m = floor((2^32 - 1) / d) + 1 (d > 1)
+__device__ __forceinline__ int mdiv(int b, uint32_t m) { return (int)__umulhi((uint32_t)b, m); }
+__device__ __forceinline__ uint32_t mdiv_of(int d) { return 0xFFFFFFFFu / (uint32_t)d + 1u; }
+
+// The statistics of k_cpm_stats and k_cpm_area_energy from the LDS lattice
+// (row stride st, the first site at o0): boundary bonds by type pair into
+// lpair, the fixed-point energy into lH; sa + da is area minus target.
+template <int RANGE>
+__device__ __forceinline__ void cpm_lds_stats(const CpmArgs& a, const RepDev& R, const uint32_t* lids,
+                                              int o0, int st, uint32_t mL, const int32_t* sa,
+                                              const int32_t* da, int* lpair,
+                                              unsigned long long* lH) {
+    const int Lx = R.Lx, n = Lx * R.Ly, nt = R.n_types;
+    const int32_t* js = a.js + R.js_off;
+    long long H = 0;
+    for (int it = (int)threadIdx.x; it < n; it += (int)blockDim.x) {
+        const int y = mdiv(it, mL), x = it - y * Lx;
+        const uint32_t* q = lids + o0 + y * st + x;
+        const uint32_t s = q[0];
+        constexpr int kN = RANGE == 2 ? 12 : 4;  // forward half of the neighbourhood
+        const int dy[12] = {0, 1, 1, 1, 0, 1, 1, 2, 2, 2, 2, 2};
+        const int dx[12] = {1, 0, 1, -1, 2, -2, 2, -2, -1, 0, 1, 2};
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            const uint32_t m = q[dy[j] * st + dx[j]];
+            if (m == s) continue;
+            const int ts = (int)(s >> 27), tm = (int)(m >> 27);
+            H += js[ts * nt + tm];
+            if (j < 2) {  // von Neumann bonds
+                const int p0 = min(ts, tm), p1 = max(ts, tm);
+                atomicAdd(&lpair[p0 * nt - p0 * (p0 - 1) / 2 + (p1 - p0)], 1);
             }
-            cpm_sites(a, R, lids, larea, 0, Ly, c, p, qthr, lsa, lty, ljs);
-            __syncthreads();
         }
     }
-    for (int i = threadIdx.x; i < n / 4; i += nthr)
-        reinterpret_cast<int4*>(gids)[i] = reinterpret_cast<const int4*>(lids)[i];
-    for (int i = threadIdx.x; i < ncell; i += nthr) {
-        garea[i] = larea[i];
-        a.snap[R.cell_off + i] = larea[i];
+    for (int i = 1 + (int)threadIdx.x; i <= R.q; i += (int)blockDim.x) {
+        const long long d = (long long)(sa[i] + da[i]);
+        H += R.LS * d * d;
+    }
+    for (int o = 32; o > 0; o >>= 1) H += __shfl_xor(H, o, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(lH, (unsigned long long)H);
+}
+
+}  // namespace
+
+namespace {
+
+// The four attempts of block b in pass p from their random words: queue
+// entries e and the chosen neighbours' offsets off in the padded lattice,
+// from the window's first id.
+template <int RANGE>
+__device__ __forceinline__ void cpm_draw(const CpmArgs& a, const RepDev& R, const MooreTab& moore,
+                                         int st, int b, uint32_t p, uint32_t (&e)[4],
+                                         uint32_t (&off)[4]) {
+    uint32_t w[4];
+    philox4x32_10((uint32_t)b, p, R.rid, kTagMain, a.key0, a.key1, w);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t k = 4u * (uint32_t)b + (uint32_t)u;
+        uint32_t jn;
+        if (RANGE == 1) {
+            jn = w[u] & 7u;
+            off[u] = (uint32_t)moore_offset(moore, jn);
+        } else {
+            // 24 neighbours: Lemire's multiply-shift of the low 16 bits,
+            // redrawn from the fallback block on rejection
+            const uint32_t l = __umul24(w[u] & 0xFFFFu, 24u);
+            jn = l >> 16;
+            if ((l & 0xFFFFu) < 16u) {
+                uint32_t f[4];
+                philox4x32_10(k, p, R.rid, kTagFallback, a.key0, a.key1, f);
+                jn = (uint32_t)(((uint64_t)f[1] * 24u) >> 32);
+            }
+            off[u] = (uint32_t)offset5(jn, st);
+        }
+        e[u] = Entry<RANGE>::make(w[u], k, jn);
+    }
+}
+
+}  // namespace
+
+// All n_steps Monte Carlo steps of every replica in one launch: one workgroup
+// per replica with its ids (with a halo of the neighbourhood's width, so that
+// no neighbour wraps), areas, cell tables and thresholds in LDS, one barrier a
+// pass.  Range 1 (Lx % 8 == 0): a block's four sites are consecutive
+// same-colour sites of a row; range 2 (5x5, nine colours): four consecutive
+// within-colour indices; groups of eight blocks go round the waves, so that
+// the cells' boundaries spread over them.  Areas minus targets rotate as in
+// the streamed passes: pass P reads S[P & 1] + D[(P - 1) % 3] and adds its
+// changes into D[P % 3] with LDS atomics, S and D of pass P + 1 are prepared
+// on the side.  GEN (lattices of up to 512 blocks a pass): as many waves again
+// draw the next pass's attempts into LDS and rotate the areas meanwhile, so
+// that the deciding waves' chain holds only reads of ids and decisions;
+// otherwise every wave draws its own.  re > 0: after step sw0 + st + 1 = j re
+// of the call the statistics go to stats row j - 1.
+// Bound by the chain of LDS reads and dependent instructions of a pass's few
+// waves per SIMD: 256 replicas of 64 x 64 with 36 cells took 7.5 us a step
+// with one attempt per lane decided in place, 6.7 with two phases around a
+// barrier and a branch per site, 6.0 without those, 5.6 with the drawing
+// waves.
+template <int RANGE, bool GEN>
+__global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, int sw0, int re,
+                                                       int tab_lds_bytes, int cell_cap,
+                                                       int queue_words) {
+    // dynamic LDS: [T hi | T lo] (tab_lds_bytes) | S[2], D[3] (int32 [cell_cap]
+    // each) | queue (256 words per deciding wave) | GEN: drawn entries (uint4)
+    // and offsets (four 16-bit) per deciding lane, two passes | ids with halo
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ PairTab pairs;
+    __shared__ int lpair[10];
+    __shared__ unsigned long long lH;
+    constexpr int ncol = RANGE == 2 ? 9 : 4, P = RANGE == 2 ? 3 : 2;  // colours, period
+    constexpr int h = RANGE;                                         // halo
+    uint32_t* qthr = reinterpret_cast<uint32_t*>(dyn);
+    int32_t* lS = reinterpret_cast<int32_t*>(dyn + tab_lds_bytes);
+    int32_t* lD = lS + 2 * cell_cap;
+    const RepDev R = a.reps[blockIdx.x];
+    const int Lx = R.Lx, Ly = R.Ly, st = Lx + 2 * h;
+    const int ncell = R.q + 1, nthr = (int)blockDim.x, tid = (int)threadIdx.x;
+    const int ndec = GEN ? nthr >> 1 : nthr;  // deciding lanes
+    const bool gen = GEN && tid >= ndec;      // uniform over a wave
+    const int dt = gen ? tid - ndec : tid;    // the lane's place among its kind
+    const int wave = dt >> 6, lane = tid & 63, nw = ndec >> 6;
+    uint32_t* queue0 = reinterpret_cast<uint32_t*>(lD + 3 * cell_cap);
+    uint32_t* queue = queue0 + 256 * wave;
+    uint4* gE = reinterpret_cast<uint4*>(queue0 + queue_words);
+    uint2* gO = reinterpret_cast<uint2*>(gE + 2 * ndec);
+    uint32_t* lids = GEN ? reinterpret_cast<uint32_t*>(gO + 2 * ndec) : queue0 + queue_words;
+    uint32_t* gids = reinterpret_cast<uint32_t*>(a.lat + R.lat_off);
+    int32_t* garea = a.area + R.cell_off;
+    const int32_t* gA = a.target + R.cell_off;
+    const int8_t* ty = a.ctype + R.cell_off;
+    for (int i = tid; i < 2 * R.tab_n; i += nthr) qthr[i] = a.tab[R.tab_off + i];
+    stage_pairs(a, R, &pairs, tid);
+    const uint64_t t0 = *a.t_base;
+    // rotating areas for the first pass P0 = ncol t0
+    int sp = (int)((ncol * t0) & 1u), dp = (int)((ncol * t0) % 3u);  // P & 1, P % 3
+    for (int i = tid; i < ncell; i += nthr) {
+        lS[sp * cell_cap + i] = garea[i] - gA[i];
+        lD[i] = lD[cell_cap + i] = lD[2 * cell_cap + i] = 0;
+    }
+    for (int i = tid; i < st * (Ly + 2 * h); i += nthr) {
+        const int y = i / st, x = i - y * st;
+        const uint32_t v = gids[wrapc(y - h, Ly) * Lx + wrapc(x - h, Lx)];
+        lids[i] = v | ((uint32_t)ty[v] << 27);
+    }
+    const int Wc = Lx / P, n_sites = (Ly / P) * Wc;  // sites per colour row and colour
+    const int n_blk = (n_sites + 3) >> 2;
+    const uint32_t mW = mdiv_of(Wc), mL = mdiv_of(Lx);
+    const MooreTab moore = moore_tab(st);
+    // block of the lane in round j: eight consecutive ones per eight lanes,
+    // the groups of eight dealt out to the waves
+    const int b0 = ((lane >> 3) * nw + wave) * 8 + (lane & 7);
+    uint32_t e[4], off[4];
+    const auto put = [&](int buf) {
+        gE[buf * ndec + dt] = make_uint4(e[0], e[1], e[2], e[3]);
+        gO[buf * ndec + dt] = make_uint2(off[0] | (off[1] << 16), off[2] | (off[3] << 16));
+    };
+    if (gen) {
+        cpm_draw<RANGE>(a, R, moore, st, b0, (uint32_t)(ncol * t0), e, off);
+        put(sp);
+    }
+    __syncthreads();
+    int next = re > 0 ? (sw0 / re + 1) * re - sw0 : 0;  // steps to the next recorded one
+    for (int step = 0; step < n_steps; ++step) {
+        for (int c = 0; c < ncol; ++c) {
+            const uint32_t p = (uint32_t)(ncol * (t0 + (uint64_t)step) + (uint64_t)c);
+            const int cy = c / P, cx = c - P * cy;
+            const int dq = dp == 0 ? 2 : dp - 1, dn = dp == 2 ? 0 : dp + 1;
+            const int32_t* S0 = lS + sp * cell_cap;
+            const int32_t* D0 = lD + dq * cell_cap;
+            int32_t* D1 = lD + dp * cell_cap;
+            if (!GEN || gen) {
+                for (int i = GEN ? dt : tid; i < ncell; i += ndec) {
+                    lS[(sp ^ 1) * cell_cap + i] = S0[i] + D0[i];
+                    lD[dn * cell_cap + i] = 0;
+                }
+            }
+            if (gen) {
+                cpm_draw<RANGE>(a, R, moore, st, b0, p + 1u, e, off);
+                put(sp ^ 1);
+            }
+            // offset of the colour's site (0, 0), one row and column up-left
+            // of it for the neighbour tables
+            const int oc = (cy + h) * st + cx + h, on = oc - h * st - h;
+            // every lane takes part (ballots); blocks past the end queue nothing
+            for (int g = 0; g < n_blk && !gen; g += ndec) {
+                const int b = g + b0;
+                if (GEN) {
+                    const uint4 ev = gE[sp * ndec + dt];
+                    const uint2 ov = gO[sp * ndec + dt];
+                    e[0] = ev.x; e[1] = ev.y; e[2] = ev.z; e[3] = ev.w;
+                    off[0] = ov.x & 0xFFFFu; off[1] = ov.x >> 16;
+                    off[2] = ov.y & 0xFFFFu; off[3] = ov.y >> 16;
+                } else {
+                    cpm_draw<RANGE>(a, R, moore, st, b, p, e, off);
+                }
+                bool act[4];
+                int r = mdiv(4 * b, mW), i = 4 * b - (int)__umul24((uint32_t)r, (uint32_t)Wc);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = RANGE == 1 ? b < n_blk : 4 * b + u < n_sites;
+                    const int o = in ? P * ((int)__umul24((uint32_t)r, (uint32_t)st) + i) : 0;
+                    // (no branch around the reads: all of the block's together)
+                    act[u] = (lids[oc + o] != lids[on + o + (int)off[u]]) & in;
+                    // the block's next site (range 1: of the same row)
+                    ++i;
+                    if (RANGE == 2 && i == Wc) {
+                        i = 0;
+                        ++r;
+                    }
+                }
+                const int cnt_q = queue_put(queue, act, e);
+                for (int q = lane; q < cnt_q; q += 64) {
+                    const uint32_t v = queue[q], k = Entry<RANGE>::k(v), jn = Entry<RANGE>::jn(v);
+                    const int r2 = mdiv((int)k, mW);
+                    const int i2 = (int)k - (int)__umul24((uint32_t)r2, (uint32_t)Wc);
+                    const int o = P * ((int)__umul24((uint32_t)r2, (uint32_t)st) + i2);
+                    const uint32_t* nb = lids + on + o;  // the window's first id
+                    const uint32_t s = nb[h * st + h];
+                    const uint32_t tg =
+                        nb[RANGE == 1 ? moore_offset(moore, jn) : offset5(jn, st)];
+                    uint32_t cnt = 0u;
+                    int nt = 0, ns = 0;
+#pragma unroll
+                    for (int dy = 0; dy <= 2 * h; ++dy)
+#pragma unroll
+                        for (int dx = 0; dx <= 2 * h; ++dx) {
+                            if (dy == h && dx == h) continue;  // the site itself
+                            const uint32_t m = nb[dy * st + dx];
+                            cnt += 1u << (m >> 24);
+                            nt += m == tg;
+                            ns += m == s;
+                        }
+                    const int it = id_of(tg), is = id_of(s);
+                    if (cpm_accept(a, R, s, tg, cnt, nt, ns, &pairs, S0[it] + D0[it],
+                                   S0[is] + D0[is], qthr, v >> 16, k, p)) {
+                        const int y = P * r2 + cy, x = P * i2 + cx;
+                        uint32_t* d = lids + oc + o;
+                        *d = tg;
+                        // the halo's copies
+                        const int xe = x < h ? Lx : (x >= Lx - h ? -Lx : 0);
+                        const int ye = (y < h ? Ly : (y >= Ly - h ? -Ly : 0)) * st;
+                        if (xe != 0) d[xe] = tg;
+                        if (ye != 0) d[ye] = tg;
+                        if (xe != 0 && ye != 0) d[xe + ye] = tg;
+                        atomicAdd(&D1[it], 1);
+                        atomicAdd(&D1[is], -1);
+                    }
+                }
+                // the queue is read before the next round's entries
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            sp ^= 1;
+            dp = dn;
+            __syncthreads();
+        }
+        if (re > 0 && step + 1 == next) {
+            next += re;
+            if (tid < 10) lpair[tid] = 0;
+            if (tid == 0) lH = 0ull;
+            __syncthreads();
+            cpm_lds_stats<RANGE>(a, R, lids, h * st + h, st, mL, lS + sp * cell_cap,
+                                 lD + (dp == 0 ? 2 : dp - 1) * cell_cap, lpair, &lH);
+            __syncthreads();
+            int32_t* row = a.stats + ((size_t)((sw0 + step + 1) / re - 1) * a.R + blockIdx.x) * a.width;
+            for (int i = tid; i < a.width; i += nthr)
+                row[i] = i < 10 ? lpair[i]
+                                : (i == 10 ? (int32_t)(uint32_t)lH
+                                           : (i == 11 ? (int32_t)(uint32_t)(lH >> 32) : 0));
+        }
+    }
+    for (int i = tid; i < Lx * Ly; i += nthr) {
+        const int y = i / Lx, x = i - y * Lx;
+        gids[i] = (uint32_t)id_of(lids[(y + h) * st + x + h]);
+    }
+    for (int i = tid; i < ncell; i += nthr) {
+        const int v = lS[sp * cell_cap + i] + lD[(dp == 0 ? 2 : dp - 1) * cell_cap + i] + gA[i];
+        garea[i] = v;
+        a.snap[R.cell_off + i] = v;
     }
 }
 
@@ -912,24 +1213,39 @@ hipError_t launch_cpm_tiled(const CpmArgs& a, int n_steps, int TH, int TW, int t
     return hipGetLastError();
 }
 
-size_t cpm_resident_lds_bytes(int tab_lds_bytes, int cell_cap, int max_sites) {
-    return (size_t)tab_lds_bytes + (size_t)12 * cell_cap + (size_t)((cell_cap + 15) & ~15) +
-           (size_t)4 * max_sites;
+namespace {
+// Deciding lanes: one per Philox block of a pass, whole waves; as many drawing
+// lanes beside them up to 512.
+int cpm_resident_lanes(int range, int max_sites) {
+    const int blk = (max_sites / (range == 2 ? 9 : 4) + 3) / 4;
+    return blk >= 1024 ? 1024 : (blk + 63) & ~63;
+}
+}  // namespace
+
+size_t cpm_resident_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int max_sites,
+                              int max_padded) {
+    if (max_sites / (range == 2 ? 9 : 4) > (range == 2 ? 2048 : 8192)) return SIZE_MAX;
+    const int lanes = cpm_resident_lanes(range, max_sites);
+    return (size_t)tab_lds_bytes + (size_t)20 * cell_cap +
+           (size_t)(lanes <= 512 ? 16 + 48 : 16) * lanes + (size_t)4 * max_padded;
 }
 
-hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int tab_lds_bytes, int cell_cap,
-                               int max_sites, hipStream_t s) {
-    const size_t lds = cpm_resident_lds_bytes(tab_lds_bytes, cell_cap, max_sites);
-    const void* fn = a.range == 2 ? (const void*)k_cpm_resident<2> : (const void*)k_cpm_resident<1>;
+hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int sw0, int re, int tab_lds_bytes,
+                               int cell_cap, int max_sites, int max_padded, hipStream_t s) {
+    const size_t lds =
+        cpm_resident_lds_bytes(a.range, tab_lds_bytes, cell_cap, max_sites, max_padded);
+    const int lanes = cpm_resident_lanes(a.range, max_sites);
+    const bool gen = lanes <= 512;
+    const void* fn = a.range == 2 ? (gen ? (const void*)k_cpm_resident<2, true>
+                                         : (const void*)k_cpm_resident<2, false>)
+                                  : (gen ? (const void*)k_cpm_resident<1, true>
+                                         : (const void*)k_cpm_resident<1, false>);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (a.range == 2)
-        hipLaunchKernelGGL(k_cpm_resident<2>, dim3(a.R), dim3(1024), lds, s, a, n_steps,
-                           tab_lds_bytes, cell_cap);
-    else
-        hipLaunchKernelGGL(k_cpm_resident<1>, dim3(a.R), dim3(1024), lds, s, a, n_steps,
-                           tab_lds_bytes, cell_cap);
-    return hipGetLastError();
+    int queue_words = 4 * lanes;
+    CpmArgs b = a;
+    void* args[] = {&b, &n_steps, &sw0, &re, &tab_lds_bytes, &cell_cap, &queue_words};
+    return hipLaunchKernel(fn, dim3(a.R), dim3(gen ? 2 * lanes : lanes), args, lds, s);
 }
 
 __global__ void k_cpm_copy(const int32_t* src, int32_t* dst, int n) {

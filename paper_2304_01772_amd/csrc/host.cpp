@@ -51,6 +51,7 @@ constexpr size_t kResidentLdsBudget = 150 * 1024;
 // cache between passes: their own-plane traffic goes nontemporal by default.
 constexpr size_t kNtAutoBytes = 192ull << 20;
 constexpr int kCpmLdsCells = 16384;  // cells (medium included) per replica in LDS tables
+constexpr size_t kCpmResidentLdsMax = 156 * 1024;  // dynamic LDS of the resident CPM kernel
 constexpr size_t kCpmQuadLdsMax = 160 * 1024;  // LDS of one workgroup of the quad pass
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1988,6 +1989,9 @@ int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
         r.LS = f.LS;
         r.K1 = f.K1;
         r.K0 = f.K0;
+        r.small_areas = (int64_t)r.Lx * r.Ly <= (1 << 26);
+        for (int32_t t : h.target)
+            if (t > (1 << 26) || t < -(1 << 26)) r.small_areas = 0;
         h.lat_bytes = (size_t)r.Lx * r.Ly * 4;
         r.lat_off = (int64_t)(lat_off / 4);  // int32 elements
         lat_off = align_up(lat_off + h.lat_bytes, kAlign);
@@ -2225,16 +2229,23 @@ int cpm_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
         c->cpm_lds_reserved = true;
     }
     hipError_t e = hipSuccess;
-    // unrecorded steps of lattices whose ids and tables fit 64 KiB of LDS (the
-    // 3x3 neighbourhood with every Lx % 8 == 0, or the 5x5 one): the resident
-    // kernel, one launch per chunk of at most 500 steps (the step counter
-    // advances after each), unless streamed passes are requested
-    if (re == 0 && !c->prof && (c->cpm_quad || c->cpm_range == 2) && c->sched.mode != 2 &&
-        cpm_resident_lds_bytes((int)tab_bytes, c->cpm_cell_cap, c->max_sites) <= 64 * 1024) {
+    // steps of lattices whose ids, tables and queue fit the LDS of a compute
+    // unit (the 3x3 neighbourhood with every Lx % 8 == 0, or the 5x5 one),
+    // recorded or not: the resident kernel, one launch per chunk of at most
+    // 500 steps (the step counter advances after each), unless streamed passes
+    // or, for lattices above 64 KiB of ids, tiled ones are requested
+    const bool tiled = re == 0 && (c->sched.flags & SPINMC_SCHED_PERSIST) && c->cpm_range == 1 &&
+                       (size_t)4 * c->max_sites > 64 * 1024;
+    int max_padded = 0;
+    for (const HostRep& h : c->reps)
+        max_padded = std::max(max_padded, (h.dev.Lx + 2 * c->cpm_range) * (h.dev.Ly + 2 * c->cpm_range));
+    if (!c->prof && (c->cpm_quad || c->cpm_range == 2) && c->sched.mode != 2 && !tiled &&
+        cpm_resident_lds_bytes(c->cpm_range, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
+                               max_padded) <= kCpmResidentLdsMax) {
         for (int done = 0; done < n && e == hipSuccess;) {
             const int k = std::min(500, n - done);
-            e = launch_cpm_resident(a, k, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
-                                    c->stream);
+            e = launch_cpm_resident(a, k, done, re, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
+                                    max_padded, c->stream);
             if (e == hipSuccess) e = launch_advance(c->d_t, (uint64_t)k, c->stream);
             done += k;
         }

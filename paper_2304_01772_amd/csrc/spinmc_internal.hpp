@@ -38,7 +38,7 @@ struct RepDev {
     int32_t K1;                   // CPM: k in [1,K1) from the table (entry k-1); [K1,K0) T=1
     int32_t js_off;               // CPM: fixed-point adhesion table offset (int32)
     int32_t S;                    // CPM: fixed-point scale
-    int32_t pad2;
+    int32_t small_areas;          // CPM: sites and |target areas| at most 2^26
     int64_t K0;                   // CPM: k >= K0 has T = 0 (never accepted)
     int64_t LS;                   // CPM: lambda * S
     float Jx, Jy, h, pad1;

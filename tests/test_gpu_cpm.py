@@ -422,3 +422,41 @@ def test_autotune_keeps_the_chain(S):
         want, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 10.0, 15, 80 + r, 0, 9)
         assert np.array_equal(smp.get_state(r), want), (r, chosen)
     smp.close()
+
+
+@pytest.mark.parametrize("cpm_range,shapes,n_types,n,re", [
+    # one and two Philox blocks a lane, the largest lattice the queue's index
+    # and the LDS admit, and one past it (streamed)
+    (1, [((2, 8), 2), ((16, 24), 9)], 3, 9, 4),
+    (1, [((136, 128), 60)], 3, 4, 2),
+    (1, [((168, 168), 90)], 2, 2, 1),
+    (1, [((200, 168), 90)], 3, 2, 1),
+    # blocks across rows and a ragged last block; the largest index
+    (2, [((6, 6), 2), ((18, 30), 9)], 4, 9, 4),
+    (2, [((132, 132), 60)], 4, 2, 1),
+    (2, [((138, 138), 60)], 3, 2, 1),
+    # recorded across the launch boundary of 500 steps
+    (1, [((16, 16), 5)], 3, 511, 7),
+    (2, [((12, 18), 5)], 3, 511, 7),
+])
+def test_recorded_steps_resident(S, cpm_range, shapes, n_types, n, re):
+    """Recorded steps in one workgroup per replica at the edges of its forms:
+    states and every recorded row equal the oracle's, after unrecorded steps
+    of the same context."""
+    rng = np.random.default_rng(n_types)
+    J = rng.integers(0, 17, size=(n_types, n_types)).astype(np.float32)
+    J = np.triu(J) + np.triu(J, 1).T
+    cases = [_random_case(700 + r, sh, nc, n_types) for r, (sh, nc) in enumerate(shapes)]
+    reps = [dict(_rep(ids, J, ct, A, 1.0, 12.0, 60 + r), cpm_range=cpm_range)
+            for r, (ids, ct, A) in enumerate(cases)]
+    smp = S(reps, 19, init=False)
+    for r, (ids, _, _) in enumerate(cases):
+        smp.set_state(r, ids)
+    smp.sweep(3)
+    st = smp.sweep(n, re).cpu().numpy()
+    for r, (ids, ct, A) in enumerate(cases):
+        s1, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 19, 60 + r, 0, 3, nrange=cpm_range)
+        want, _, ost = orc.cpm_run(s1, J, ct, A, 1.0, 12.0, 19, 60 + r, 3, n, re, nrange=cpm_range)
+        assert np.array_equal(smp.get_state(r), want), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
