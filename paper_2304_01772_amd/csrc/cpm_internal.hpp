@@ -19,6 +19,22 @@ size_t cpm_resident_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int ma
 hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int sw0, int re, int tab_lds_bytes,
                                int cell_cap, int max_sites, int max_padded, hipStream_t s);
 
+// A tile of the streamed two-phase pass: rows y0 .. y0 + rows - 1 (even), columns
+// x0 .. x0 + cols - 1 (multiples of 8) of the replica whose record it carries
+// (one dependent load less than a tile and then its replica).
+struct CpmTile {
+    RepDev R;
+    int32_t y0, rows, x0, cols;
+};
+size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols);
+hipError_t cpm_tile_reserve_lds(size_t lds_bytes);
+// One colour pass (range 1, every Lx % 8 == 0; at most 8192 sites of a colour
+// per tile, rows x cols / 4; cell_cap a multiple of 16; threads a multiple of
+// 64 up to 512; lds_bytes for the largest tile).
+hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
+                                int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
+                                size_t lds_bytes, hipStream_t s);
+
 // Tiled persistent passes (range 1, Lx % 8 == 0, TH | Ly, TW | Lx, TH even,
 // TW % 8 == 0): n_steps unrecorded Monte Carlo steps, one 256-thread
 // workgroup per tile of every replica (n_blocks = R x tiles per replica, the

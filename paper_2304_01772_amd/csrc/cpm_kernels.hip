@@ -1011,6 +1011,171 @@ __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, i
     }
 }
 
+// ------------------------------------------------------ streamed, two phases
+// One colour pass over tiles of rows x columns (range 1, every Lx % 8 == 0):
+// the tile's ids with a halo come into LDS in 16-byte loads, together with the
+// thresholds and the cells' tables -- one round of global loads, none of them
+// waiting for another but for the tile's record -- and the attempts run on the
+// LDS ids in the two phases of the resident kernel.  Accepted ids go straight
+// to the lattice; area changes gather in LDS and go to the pass's change
+// buffer as one atomic per touched cell.  Bound by latencies: launch, the tile
+// record, the loads, the chain of LDS reads, the stores.  8 x 512^2, 1000
+// cells: 9.0 us a pass with one attempt per lane on a register window,
+// 6.5 now.
+__global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile* tiles, int c,
+                                                       int sweep_off, int tab_lds_bytes,
+                                                       int cell_cap) {
+    // dynamic LDS: [T hi | T lo] (tab_lds_bytes) | snap - A, area changes (int32
+    // [cell_cap] each) | 8 x type (int8 [cell_cap]) | queue (256 words per wave)
+    // | ids: (rows + 2) x (cols + 8), four halo columns on either side
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ PairTab pairs;
+    const CpmTile& T = tiles[blockIdx.x];
+    const RepDev R = T.R;
+    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x, lane = tid & 63;
+    uint32_t* qthr = reinterpret_cast<uint32_t*>(dyn);
+    int32_t* lsa = reinterpret_cast<int32_t*>(dyn + tab_lds_bytes);
+    int32_t* ldel = lsa + cell_cap;
+    uint8_t* lty = reinterpret_cast<uint8_t*>(ldel + cell_cap);
+    uint32_t* queue0 = reinterpret_cast<uint32_t*>(lty + cell_cap);
+    uint32_t* queue = queue0 + 256 * (tid >> 6);
+    uint32_t* lids = queue0 + 4 * nthr;
+    const int Lx = R.Lx, Ly = R.Ly, y0 = T.y0, x0 = T.x0, rows = T.rows, cols = T.cols;
+    const int st = cols + 8, cw = st >> 2, nch = (rows + 2) * cw;  // 16-byte chunks
+    int32_t* gids = a.lat + R.lat_off;
+    const uint64_t P = 4 * (*a.t_base + (uint64_t)sweep_off) + (uint64_t)c;
+    const uint32_t p = (uint32_t)P;
+    const PassAreas pa = pass_areas(a, P, R.cell_off);
+    const int ncell = R.q + 1, ntab = 2 * R.tab_n;
+    const uint32_t mC = mdiv_of(cw);
+    // every thread's first loads of each kind before any is used
+    constexpr int kU = 5;
+    int4 v[kU];
+    const auto chunk = [&](int i) {
+        const int r = mdiv(i, mC), j = i - r * cw;
+        int gx = x0 - 4 + 4 * j;
+        gx = gx < 0 ? gx + Lx : (gx >= Lx ? gx - Lx : gx);
+        return *reinterpret_cast<const int4*>(gids + (size_t)wrapc(y0 + r - 1, Ly) * Lx + gx);
+    };
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+        if (tid + u * nthr < nch) v[u] = chunk(tid + u * nthr);
+    constexpr int kC = 2;
+    int32_t sv[kC], av[kC];
+    uint8_t tv[kC];
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+        const int i = tid + u * nthr;
+        if (i < ncell) {
+            sv[u] = pa.s_rd[i] + pa.d_rd[i];
+            av[u] = a.target[R.cell_off + i];
+            tv[u] = (uint8_t)a.ctype[R.cell_off + i];
+        }
+    }
+    for (int i = tid; i < ntab; i += nthr) qthr[i] = a.tab[R.tab_off + i];
+    stage_pairs(a, R, &pairs, tid);
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+        const int i = tid + u * nthr;
+        if (i < ncell) {
+            lsa[i] = sv[u] - av[u];
+            lty[i] = (uint8_t)(8 * tv[u]);
+            ldel[i] = 0;
+        }
+    }
+    for (int i = tid + kC * nthr; i < ncell; i += nthr) {
+        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - a.target[R.cell_off + i];
+        lty[i] = (uint8_t)(8 * a.ctype[R.cell_off + i]);
+        ldel[i] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+        if (tid + u * nthr < nch) reinterpret_cast<int4*>(lids)[tid + u * nthr] = v[u];
+    for (int i = tid + kU * nthr; i < nch; i += nthr) reinterpret_cast<int4*>(lids)[i] = chunk(i);
+    pass_rotate(a, P);
+    __syncthreads();
+    const int cy = c >> 1, cx = c & 1;
+    const int Gt = cols >> 3, G = Lx >> 3, nq = (rows >> 1) * Gt;  // quads of the tile's colour
+    const uint32_t mG = Gt > 1 ? mdiv_of(Gt) : 0u;
+    const auto qrow = [&](int b) { return Gt > 1 ? mdiv(b, mG) : b; };
+    const MooreTab moore = moore_tab(st);
+    const int oc = (cy + 1) * st + cx + 4, on = oc - st - 1;
+    // every lane takes part (ballots); quads past the end queue nothing
+    for (int g = 0; g < nq; g += nthr) {
+        const int b = g + tid;
+        const bool in = b < nq;
+        const int r = in ? qrow(b) : 0, j = in ? b - (int)__umul24((uint32_t)r, (uint32_t)Gt) : 0;
+        const uint32_t kq = (uint32_t)((y0 >> 1) + r) * (uint32_t)G + (uint32_t)((x0 >> 3) + j);
+        uint32_t w[4];
+        philox4x32_10(kq, p, R.rid, kTagMain, a.key0, a.key1, w);
+        const int o = 2 * (int)__umul24((uint32_t)r, (uint32_t)st) + 8 * j;
+        bool act[4];
+        uint32_t e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            // (no branch around the reads: all of the quad's together)
+            act[u] = (lids[oc + o + 2 * u] !=
+                      lids[on + o + 2 * u + moore_offset(moore, w[u])]) & in;
+            e[u] = Entry<1>::make(w[u], (uint32_t)(4 * b + u) & 0x1FFFu, w[u] & 7u);
+        }
+        const int cnt_q = queue_put(queue, act, e);
+        for (int q = lane; q < cnt_q; q += 64) {
+            const uint32_t ev = queue[q], kl = Entry<1>::k(ev), jn = Entry<1>::jn(ev);
+            const int b2 = (int)(kl >> 2), r2 = qrow(b2);
+            const int j2 = b2 - (int)__umul24((uint32_t)r2, (uint32_t)Gt);
+            const int o2 = 2 * (int)__umul24((uint32_t)r2, (uint32_t)st) + 8 * j2 + 2 * (int)(kl & 3u);
+            const uint32_t* nb = lids + on + o2;
+            const uint32_t s = nb[st + 1], tg = nb[moore_offset(moore, jn)];
+            uint32_t cnt = 0u;
+            int nt = 0, ns = 0;
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    if (dy == 1 && dx == 1) continue;
+                    const uint32_t m = nb[dy * st + dx];
+                    cnt += 1u << lty[m];
+                    nt += m == tg;
+                    ns += m == s;
+                }
+            const uint32_t k = 4u * ((uint32_t)((y0 >> 1) + r2) * (uint32_t)G +
+                                     (uint32_t)((x0 >> 3) + j2)) + (kl & 3u);
+            if (cpm_accept(a, R, s | ((uint32_t)lty[s] << 24), tg | ((uint32_t)lty[tg] << 24), cnt, nt,
+                           ns, &pairs, lsa[tg], lsa[s], qthr, ev >> 16, k, p)) {
+                gids[(size_t)(y0 + 2 * r2 + cy) * Lx + x0 + 8 * j2 + 2 * (int)(kl & 3u) + cx] = (int)tg;
+                atomicAdd(&ldel[tg], 1);
+                atomicAdd(&ldel[s], -1);
+            }
+        }
+        // the queue is read before the next round's entries
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (int i = tid; i < ncell; i += nthr) {
+        const int d = ldel[i];
+        if (d != 0) atomicAdd(&pa.d_wr[i], d);
+    }
+}
+
+size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols) {
+    return (size_t)tab_lds_bytes + (size_t)9 * cell_cap + (size_t)16 * threads +
+           (size_t)4 * (rows + 2) * (cols + 8);
+}
+
+hipError_t cpm_tile_reserve_lds(size_t lds_bytes) {
+    return hipFuncSetAttribute((const void*)k_cpm_pass_tile,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+}
+
+hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
+                                int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
+                                size_t lds_bytes, hipStream_t s) {
+    hipLaunchKernelGGL(k_cpm_pass_tile, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles, c,
+                       sweep_off, tab_lds_bytes, cell_cap);
+    return hipGetLastError();
+}
+
 // ------------------------------------------- tiled persistent streamed passes
 // All 4 G colour passes of G unrecorded Monte Carlo steps in one launch for
 // lattices too large for one workgroup's LDS (range 1, Lx % 8 == 0): every
@@ -1281,16 +1446,38 @@ __global__ void k_cpm_pass_final(CpmArgs a, int sweep_off) {
         a.area[i] = s_rd[i] + d_rd[i];
 }
 
-// Areas from the lattice (after set_state): per tile, atomics into area
-// (which the caller cleared).
-__global__ void k_cpm_area_count(CpmArgs a) {
+// Areas from the lattice (after set_state), added into area, which the caller
+// cleared: per tile in LDS (cell_cap entries), the medium by wave ballots, then
+// one atomic per cell of the tile.  cell_cap = 0 (more cells than LDS holds):
+// one atomic per site.  (8 x 512^2, 1000 cells: one atomic per site 1890 us,
+// almost all on the medium's word; now 13.)
+__global__ void k_cpm_area_count(CpmArgs a, int cell_cap) {
+    extern __shared__ int32_t lcnt[];
     const TileDev T = a.tiles[blockIdx.x];
     const RepDev R = a.reps[T.rep];
     const int32_t* ids = a.lat + R.lat_off;
     int32_t* area = a.area + R.cell_off;
     const int n = T.rows * R.Lx;
     const size_t base = (size_t)T.y0 * R.Lx;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&area[ids[base + i]], 1);
+    if (cell_cap == 0) {
+        for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&area[ids[base + i]], 1);
+        return;
+    }
+    for (int i = threadIdx.x; i <= R.q; i += blockDim.x) lcnt[i] = 0;
+    __syncthreads();
+    int medium = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int id = ids[base + i];
+        if (id == 0)
+            ++medium;
+        else
+            atomicAdd(&lcnt[id], 1);
+    }
+    medium = __ockl_wfred_add_i32(medium);
+    if ((threadIdx.x & 63) == 0 && medium != 0) atomicAdd(&lcnt[0], medium);
+    __syncthreads();
+    for (int i = threadIdx.x; i <= R.q; i += blockDim.x)
+        if (lcnt[i] != 0) atomicAdd(&area[i], lcnt[i]);
 }
 
 // Statistics: boundary bonds by type pair (von Neumann, right and down) and
@@ -1435,10 +1622,12 @@ hipError_t launch_cpm_pass_final(const CpmArgs& a, int sweep_off, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_cpm_area_recount(const CpmArgs& a, int n_tiles, int total_cells, hipStream_t s) {
+hipError_t launch_cpm_area_recount(const CpmArgs& a, int n_tiles, int total_cells, int cell_cap,
+                                   hipStream_t s) {
     hipError_t e = launch_fill_i32(a.area, (size_t)total_cells, 0, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cpm_area_count, dim3(n_tiles), dim3(256), 0, s, a);
+    const int cap = cell_cap <= 16384 ? cell_cap : 0;
+    hipLaunchKernelGGL(k_cpm_area_count, dim3(n_tiles), dim3(256), (size_t)4 * cap, s, a, cap);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_cpm_snapshot(a, total_cells, s);

@@ -191,6 +191,10 @@ struct spinmc_ctx {
     long long* d_cov_part = nullptr;  // chunk sums of the split covariance estimator
     size_t cov_part_n = 0;
     int cpm_cell_cap = 0;
+    // tiles of the streamed two-phase CPM pass (null where it does not fit)
+    CpmTile* d_ctiles = nullptr;
+    int n_ctiles = 0, ctile_threads = 0;
+    size_t ctile_lds = 0;
     uint32_t* d_cpm_bar = nullptr;  // tiled persistent CPM passes: [0] abort word, [1 .. R] barriers
     bool cpm_tiled_used = false;
     // kernel timing
@@ -258,6 +262,8 @@ void free_all(spinmc_ctx* c) {
     hipFree(c->d_dbuf);
     hipFree(c->d_cpm_bar);
     c->d_cpm_bar = nullptr;
+    hipFree(c->d_ctiles);
+    c->d_ctiles = nullptr;
     c->d_sbuf = nullptr;
     c->d_dbuf = nullptr;
     hipFree(c->d_js);
@@ -1913,6 +1919,50 @@ int cpm_pass_threads(const spinmc_ctx* c) {
     return w > 0 ? std::min(w, 256) : 256;
 }
 
+// Tiles of the streamed two-phase pass (wg_threads 0): up to 512 columns by
+// the schedule's rows or as many as make 8192 sites (a quad of a pass's colour
+// per lane), 4096 where that leaves compute units without a tile (8 x 256^2:
+// 5.3 against 5.8 us a pass; 8 x 512^2: 6.5 with 8192, 7.2 with 4096; in
+// workgroups of 256 lanes 8.1 at best); fewer where the LDS asks for it.
+int cpm_build_ctiles(spinmc_ctx* c) {
+    hipFree(c->d_ctiles);
+    c->d_ctiles = nullptr;
+    c->n_ctiles = 0;
+    if (c->cpm_range != 1 || !c->cpm_quad || c->sched.wg_threads != 0) return SPINMC_OK;
+    const int tab = (int)align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
+    const int threads = 512;
+    std::vector<CpmTile> tiles;
+    size_t lds = 0, sites = 0;
+    for (const HostRep& h : c->reps) sites += (size_t)h.dev.Lx * h.dev.Ly;
+    const int per = sites / 8192 < 256 ? 4096 : 8192;
+    for (const HostRep& h : c->reps) {
+        const int Lx = h.dev.Lx, Ly = h.dev.Ly;
+        const int cols = std::min(Lx, 512);
+        int rows = c->sched.tile_rows > 0 ? c->sched.tile_rows & ~1 : per / cols & ~1;
+        rows = std::max(2, std::min(rows, Ly));
+        while (rows > 2 &&
+               (rows * cols > 4 * 8192 ||
+                cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols) > kCpmResidentLdsMax))
+            rows -= 2;
+        const size_t need = cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols);
+        if (need > kCpmResidentLdsMax) return SPINMC_OK;
+        lds = std::max(lds, need);
+        for (int y0 = 0; y0 < Ly; y0 += rows)
+            for (int x0 = 0; x0 < Lx; x0 += cols)
+                tiles.push_back(CpmTile{h.dev, y0, std::min(rows, Ly - y0), x0,
+                                        std::min(cols, Lx - x0)});
+    }
+    hipError_t e = hipMalloc((void**)&c->d_ctiles, sizeof(CpmTile) * tiles.size());
+    if (e == hipSuccess)
+        e = hipMemcpy(c->d_ctiles, tiles.data(), sizeof(CpmTile) * tiles.size(),
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = cpm_tile_reserve_lds(lds);
+    c->n_ctiles = (int)tiles.size();
+    c->ctile_threads = threads;
+    c->ctile_lds = lds;
+    return check_dev(c, e, "CPM tiles");
+}
+
 // Row tiles: whole periods of the colouring (2 rows for the 2x2 sublattice,
 // 6 for the 3x3 one, which also keeps them even); by default about 4096
 // sites a tile, 8192 for the one-site-per-lane quad pass.
@@ -1943,7 +1993,8 @@ int cpm_build_tiles(spinmc_ctx* c) {
     c->n_tiles = (int)tiles.size();
     c->tiles_rows = c->sched.tile_rows;
     c->tiles_threads = cpm_pass_threads(c);
-    return check_dev(c, e, "CPM tiles");
+    if (e != hipSuccess) return check_dev(c, e, "CPM tiles");
+    return cpm_build_ctiles(c);
 }
 
 int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
@@ -2066,7 +2117,7 @@ int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
     int rc = cpm_build_tiles(c);
     if (rc == SPINMC_OK) {
         CpmArgs a = cpm_args(c, nullptr);
-        e = launch_cpm_area_recount(a, c->n_tiles, c->total_cells, c->stream);
+        e = launch_cpm_area_recount(a, c->n_tiles, c->total_cells, c->cpm_cell_cap, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         rc = check_dev(c, e, "create: area count");
     }
@@ -2100,7 +2151,7 @@ int cpm_set_state(spinmc_ctx* c, int r, const void* host, size_t bytes) {
 int cpm_recount_if_dirty(spinmc_ctx* c) {
     if (!c->cpm_areas_dirty) return SPINMC_OK;
     CpmArgs a = cpm_args(c, nullptr);
-    hipError_t e = launch_cpm_area_recount(a, c->n_tiles, c->total_cells, c->stream);
+    hipError_t e = launch_cpm_area_recount(a, c->n_tiles, c->total_cells, c->cpm_cell_cap, c->stream);
     if (e == hipSuccess) c->cpm_areas_dirty = false;
     return check_dev(c, e, "area count");
 }
@@ -2175,6 +2226,9 @@ hipError_t cpm_enqueue_pass(spinmc_ctx* c, const CpmArgs& a, int i, int col, hip
     return timed(c, SPINMC_K_CPM_PASS, [&] {
         if (c->cpm_range == 2)
             return launch_cpm_pass5(a, c->n_tiles, col, i, threads, tab_bytes, s);
+        if (c->d_ctiles)
+            return launch_cpm_pass_tile(a, c->d_ctiles, c->n_ctiles, col, i, c->ctile_threads,
+                                        (int)tab_bytes, c->cpm_cell_cap, c->ctile_lds, s);
         if (c->cpm_quad)
             return launch_cpm_pass_quad(a, c->n_tiles, col, i, threads, (int)tab_bytes,
                                         c->cpm_cell_cap, s);

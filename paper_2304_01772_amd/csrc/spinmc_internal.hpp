@@ -201,7 +201,9 @@ hipError_t launch_cpm_pass_init(const CpmArgs& a, int sweep_off, hipStream_t s);
 // snapshot pass P would read.
 hipError_t launch_cpm_pass_final(const CpmArgs& a, int sweep_off, hipStream_t s);
 hipError_t launch_cpm_stats(const CpmArgs& a, int n_tiles, int rec_row, hipStream_t s);
-hipError_t launch_cpm_area_recount(const CpmArgs& a, int n_tiles, int total_cells, hipStream_t s);
+// cell_cap: at least the largest replica's cells plus one
+hipError_t launch_cpm_area_recount(const CpmArgs& a, int n_tiles, int total_cells, int cell_cap,
+                                   hipStream_t s);
 
 // Surrogate MLP
 hipError_t launch_mlp_forward(const float* params, const float* x, int B, float* y, float* act,

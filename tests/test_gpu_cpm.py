@@ -460,3 +460,30 @@ def test_recorded_steps_resident(S, cpm_range, shapes, n_types, n, re):
         assert np.array_equal(smp.get_state(r), want), r
         assert np.array_equal(st[:, r], ost), r
     smp.close()
+
+
+# the streamed tile pass: one quad a row, two column tiles (the second of eight
+# columns), three, ragged last rows, more quads than lanes, the largest tile,
+# and cell tables that leave no room for a tile (one site per lane)
+@pytest.mark.parametrize("shape,n_cells,n_types,tile_rows", [
+    ((2, 8), 3, 2, 0), ((38, 8), 9, 3, 0), ((6, 520), 40, 3, 0), ((10, 1032), 60, 4, 4),
+    ((34, 136), 30, 3, 32), ((66, 512), 200, 3, 64), ((40, 48), 11000, 3, 0),
+    ((32, 40), 16000, 3, 0)])
+def test_streamed_tile_pass_matches_oracle(S, shape, n_cells, n_types, tile_rows):
+    rng = np.random.default_rng(n_cells)
+    J = rng.integers(0, 17, size=(n_types, n_types)).astype(np.float32)
+    J = np.triu(J) + np.triu(J, 1).T
+    cases = [_random_case(500 + r, shape, n_cells, n_types) for r in range(2)]
+    reps = [_rep(ids, J, ct, A, 1.0, 12.0, 30 + r) for r, (ids, ct, A) in enumerate(cases)]
+    smp = S(reps, 23, init=False)
+    smp.set_schedule(mode="stream", tile_rows=tile_rows)
+    for r, (ids, _, _) in enumerate(cases):
+        smp.set_state(r, ids)
+    smp.sweep(2)
+    st = smp.sweep(3, 1).cpu().numpy()
+    for r, (ids, ct, A) in enumerate(cases):
+        s1, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 23, 30 + r, 0, 2)
+        want, _, ost = orc.cpm_run(s1, J, ct, A, 1.0, 12.0, 23, 30 + r, 2, 3, 1)
+        assert np.array_equal(smp.get_state(r), want), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
