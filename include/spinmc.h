@@ -116,7 +116,9 @@ enum spinmc_status {
  * a Metropolis chain.  A context of G groups reports 32 G replicas to
  * spinmc_num_replicas / sweep / measure (replica 32 g + b, statistics
  * [M, Bx, By] as for SPINMC_ISING); spinmc_get_state / set_state move the
- * uint32 words of group g (Ly Lx * 4 bytes).  Only groups in a context.     */
+ * uint32 words of group g (Ly Lx * 4 bytes).  Only groups in a context.
+ * Groups of up to 256 x 256 run resident, one workgroup a group (schedule
+ * mode 2 forces streamed passes; few groups of the largest stay streamed).  */
 
 /* Hamiltonian parameters of one replica (Eq. (1), Eq. (2), Eq. (3)).
  * Signs: Ising H = -Jx sum_h s s' - Jy sum_v s s' - h sum s with s = +-1;

@@ -1450,7 +1450,7 @@ __global__ void k_cpm_pass_final(CpmArgs a, int sweep_off) {
 // cleared: per tile in LDS (cell_cap entries), the medium by wave ballots, then
 // one atomic per cell of the tile.  cell_cap = 0 (more cells than LDS holds):
 // one atomic per site.  (8 x 512^2, 1000 cells: one atomic per site 1890 us,
-// almost all on the medium's word; now 13.)
+// almost all on the medium's word; now 14.)
 __global__ void k_cpm_area_count(CpmArgs a, int cell_cap) {
     extern __shared__ int32_t lcnt[];
     const TileDev T = a.tiles[blockIdx.x];

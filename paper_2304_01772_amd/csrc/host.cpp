@@ -187,6 +187,7 @@ struct spinmc_ctx {
     uint64_t* d_tab64 = nullptr;  // [R][14] thresholds ([G][18] multispin-coded)
     // multispin-coded Ising: reps holds the G groups, R = 32 G
     bool msc = false;
+    int msc_mode = kMscAny;
     RepDev* d_reps_obs = nullptr;  // one square-lattice Ising entry per replica
     long long* d_cov_part = nullptr;  // chunk sums of the split covariance estimator
     size_t cov_part_n = 0;
@@ -2644,6 +2645,23 @@ void msc_thresholds(const spinmc_replica_desc& d, std::vector<uint64_t>& T) {
             }
 }
 
+// The rule of k_msc_pass4 / k_msc_resident that a group's thresholds allow.
+int msc_mode(const std::vector<uint64_t>& T) {
+    const uint64_t always = (uint64_t)1 << 32;
+    const uint64_t* F = T.data() + 9;  // s = +1: agreement counts 3 i + j
+    bool iso = true;
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            if (F[3 * i + j] != T[3 * (2 - i) + (2 - j)]) return kMscAny;
+            // the class of n = i + j agreeing neighbours: (0, n) or (n - 2, 2)
+            iso = iso && F[3 * i + j] == (i + j <= 2 ? F[i + j] : F[3 * (i + j - 2) + 2]);
+        }
+    // n = 0 .. 4 is F[0], F[1], F[2], F[5], F[8]
+    const bool up = F[0] == always && F[1] == always && F[5] < always && F[8] < always;
+    const bool down = F[8] == always && F[5] == always && F[1] < always && F[0] < always;
+    return iso && F[2] == always && (up || down) ? kMscIso : kMscSym;
+}
+
 MscArgs msc_args(spinmc_ctx* c, int32_t* stats) {
     MscArgs a{};
     a.reps = c->d_reps;
@@ -2659,6 +2677,7 @@ MscArgs msc_args(spinmc_ctx* c, int32_t* stats) {
     for (const HostRep& h : c->reps) mb = std::max(mb, h.dev.Lx * h.dev.Ly / 8);
     a.max_blocks = mb;
     a.max_sites = c->max_sites;
+    a.mode = c->msc_mode;
     return a;
 }
 
@@ -2675,10 +2694,12 @@ int create_msc(const spinmc_replica_desc* d, int n, uint64_t seed, int init, voi
     std::vector<uint64_t> tab((size_t)n * kMscClasses);
     std::vector<RepDev> rd(n), robs((size_t)32 * n);
     size_t lat_off = 0;
+    c->msc_mode = kMscIso;
     for (int i = 0; i < n; ++i) {
         HostRep& h = c->reps[i];
         h.d = d[i];
         msc_thresholds(d[i], h.T);
+        c->msc_mode = std::max(c->msc_mode, msc_mode(h.T));
         std::copy(h.T.begin(), h.T.end(), tab.begin() + (size_t)i * kMscClasses);
         RepDev& r = h.dev;
         r.model = kModelIsingMsc;
@@ -2741,11 +2762,58 @@ int create_msc(const spinmc_replica_desc* d, int n, uint64_t seed, int init, voi
     return SPINMC_OK;
 }
 
+// Resident schedule: rows of a lane and lanes of a workgroup.  The fewest rows
+// that fit 1024 lanes: more waves hide a pass's latency (64 x 64: 0.57 us).
+// A resident pass takes about 0.15 / 0.30 / 0.48 ns a word of the plane (ISO,
+// SYM, ANY rule) in each of ceil(G / 256) turns of the compute units, a streamed
+// one 2.5 us to launch and 2 ns for 1000 words of the context: few groups of
+// large lattices stay streamed (256 x 256, ISO: 32 groups 5.0 us resident, 3.8
+// streamed; 128 groups 5.0 and 9.0).
+bool msc_resident_ok(const spinmc_ctx* c, int* rows, int* lanes) {
+    if (c->sched.mode == 2) return false;  // streamed passes requested
+    double total = 0.0, largest = 0.0;
+    for (const HostRep& h : c->reps) {
+        const double words = 0.5 * h.dev.Lx * h.dev.Ly;
+        total += words;
+        largest = std::max(largest, words);
+    }
+    const double turns = std::ceil((double)c->reps.size() / 256.0);
+    const double ns = c->msc_mode == kMscIso ? 0.15 : c->msc_mode == kMscSym ? 0.30 : 0.48;
+    if (turns * ns * largest > 2500.0 + 0.002 * total) return false;
+    for (int nr = 2; nr <= 8; nr *= 2) {
+        int need = 0;
+        bool ok = true;
+        for (const HostRep& h : c->reps) {
+            need = std::max(need, h.dev.Lx / 8 * ((h.dev.Ly + nr - 1) / nr));
+            ok = ok && h.dev.Ly >= nr;
+        }
+        if (!ok || need > 1024) continue;
+        *rows = nr;
+        *lanes = (int)align_up(need, 64);
+        return true;
+    }
+    return false;
+}
+
 int msc_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     MscArgs a = msc_args(c, stats);
     hipError_t e = hipSuccess;
     const int n_rec = re > 0 ? n / re : 0;
     if (n_rec > 0) e = launch_fill_i32(stats, (size_t)n_rec * c->R * c->width, 0, c->stream);
+    int rows = 0, lanes = 0;
+    if (msc_resident_ok(c, &rows, &lanes)) {
+        // chunks of at most 1000 sweeps per launch (statistics recorded inside);
+        // the counter advances after each
+        for (int done = 0; done < n && e == hipSuccess;) {
+            const int k = std::min(1000, n - done);
+            e = timed(c, SPINMC_K_RESIDENT,
+                      [&] { return launch_msc_resident(a, rows, lanes, k, done, re, c->stream); },
+                      c->stream);
+            if (e == hipSuccess) e = launch_advance(c->d_t, (uint64_t)k, c->stream);
+            done += k;
+        }
+        return check_dev(c, e, "sweep");
+    }
     for (int i = 0; i < n && e == hipSuccess; ++i) {
         for (int col = 0; col < 2 && e == hipSuccess; ++col)
             e = timed(c, SPINMC_K_MSC_PASS, [&] { return launch_msc_pass(a, col, i, c->stream); },

@@ -66,3 +66,51 @@ def test_msc_set_state_and_thresholds():
     smp.close()
     with pytest.raises(Exception):
         Sampler([_grp(4, 12, 1.0, 1.0, 0.0, 0.5, 0)], 1)  # Lx not a multiple of 8
+
+
+# (Jx, Jy, h, beta): the rules of two, nine and eighteen compares, each with
+# classes that always flip on either side, and thresholds of 0 and 2^32
+_RULES = [(1.0, 1.0, 0.0, 0.44), (-0.8, -0.8, 0.0, 0.6), (0.9, -0.4, 0.0, 0.7),
+          (0.8, 0.8, 0.1, 0.5), (1.0, 1.0, 0.0, 40.0), (1.0, 1.0, 0.0, 0.0)]
+
+
+@pytest.mark.parametrize("schedule", ["auto", "stream"])
+@pytest.mark.parametrize("rules", [[0, 1, 4], [2, 1, 0], [3, 0, 5], [5, 0, 0]])
+def test_msc_rules_match_oracle(rules, schedule):
+    from paper_2304_01772_amd.sampler import Sampler
+    shapes = [(10, 16), (4, 8), (34, 72)]
+    groups = [_grp(Ly, Lx, *_RULES[k], 70 + k) for k, (Ly, Lx) in zip(rules, shapes)]
+    smp = Sampler(groups, 99, init=True)
+    smp.set_schedule(mode=schedule)
+    init = [smp.get_state(g) for g in range(3)]
+    st = smp.sweep(7, 2).cpu().numpy()
+    for g, k in enumerate(rules):
+        w, want = orc.msc_run(init[g], *_RULES[k], 99, 70 + k, 0, 7, 2)
+        assert np.array_equal(smp.get_state(g), w), g
+        assert np.array_equal(st[:, 32 * g:32 * g + 32], want), g
+    smp.close()
+
+
+# rows a lane 2, 4 and 8 with whole and ragged last chunks, the most lanes of a
+# workgroup, one lane, and one quad a row next to a larger lattice
+@pytest.mark.parametrize("shapes", [
+    [(2, 8)], [(128, 128)], [(6, 8), (126, 256)], [(128, 256)], [(250, 256), (250, 256)],
+    [(256, 256)], [(8, 8192)],
+])
+def test_msc_resident_at_its_limits(shapes):
+    from paper_2304_01772_amd.sampler import Sampler
+    par = (1.0, 1.0, 0.0, 0.44)
+    # (enough groups that large lattices are resident; the later ones repeat the last)
+    shapes = shapes + shapes[-1:] * (64 if np.prod(shapes[0]) > 32768 else 0)
+    smp = Sampler([_grp(Ly, Lx, *par, 9 + g) for g, (Ly, Lx) in enumerate(shapes)], 5, init=True)
+    init = [smp.get_state(g) for g in range(len(shapes))]
+    smp.sweep(1)
+    st = smp.sweep(2, 1).cpu().numpy()
+    obs = smp.measure()[0].cpu().numpy()
+    for g in [*range(min(2, len(shapes))), len(shapes) - 1]:
+        w, _ = orc.msc_run(init[g], *par, 5, 9 + g, 0, 1)
+        w, want = orc.msc_run(w, *par, 5, 9 + g, 1, 2, 1)
+        assert np.array_equal(smp.get_state(g), w), g
+        assert np.array_equal(st[:, 32 * g:32 * g + 32], want), g
+        assert np.array_equal(obs[32 * g:32 * g + 32], want[-1]), g
+    smp.close()
