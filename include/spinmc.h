@@ -273,7 +273,8 @@ int spinmc_thresholds(const spinmc_ctx *ctx, int32_t replica, uint64_t *host_T, 
  * sweeps of a call on side streams forked from and joined into the call's
  * stream, concurrently with the streamed work.
  * tile_rows: rows of a plane per streamed unit (even; 0 = about 16 KiB);
- * wg_threads: 256 or 512 (0 = default);
+ * wg_threads: 256 or 512 (0 = default; a resident Ising workgroup takes up to
+ * 1024 lanes by default and never fewer than half its row pairs of 16 columns);
  * flags: 0, SPINMC_SCHED_NT_ON or SPINMC_SCHED_NT_OFF: streamed passes load
  *   and store their own colour plane with nontemporal hints (bypassing the
  *   caches, for lattice sets that do not fit the 256 MB last-level cache).

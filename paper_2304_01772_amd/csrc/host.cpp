@@ -149,7 +149,7 @@ struct spinmc_ctx {
     // resident workgroup groups (replicas of one shape packed rpb per workgroup)
     bool nt_ising = false, nt_potts = false;  // nontemporal own-plane access per model
     struct ResGroup {
-        int off, count, rpb, threads, model;
+        int off, count, rpb, threads, model, items;
         bool chunk;
         size_t slot;
     };
@@ -1475,7 +1475,7 @@ int plan_persist(spinmc_ctx* c, int mode) {
         auto& P = c->pplan[m];
         P = spinmc_ctx::PersistPlan{};
         if (by_model[m].empty()) continue;
-        P.slot_words = (int)align_up((size_t)2 * c->max_tab_n + 18, 4);
+        P.slot_words = m == 0 ? kIsingTabWords : (int)align_up((size_t)2 * c->max_tab_n + 18, 4);
         const int items_cap = std::max(1, std::min(16, 8192 / (4 * P.slot_words)));
         P.lds = (size_t)items_cap * P.slot_words * 4;
         const bool nt = m == 0 ? c->nt_ising : c->nt_potts;
@@ -1610,13 +1610,19 @@ int prepare(spinmc_ctx* c, int mode) {
         for (auto& kv : shapes) {
             const HostRep& h = c->reps[kv.second[0]];
             const int items = pass == 0 ? (h.dev.Ly / 2) * (h.dev.W / 16) : h.dev.Ly * h.dev.W;
-            const size_t slot = align_up((size_t)8 * c->max_tab_n, 16) + align_up(h.lat_bytes, 16);
+            // Ising chunks: their own table, at most two items a lane (of up to 1024)
+            const bool ising = pass == 0 && h.dev.model == SPINMC_ISING;
+            const size_t slot = (ising ? (size_t)4 * kIsingTabWords
+                                       : align_up((size_t)8 * c->max_tab_n, 16)) +
+                                align_up(h.lat_bytes, 16);
             const int n = (int)kv.second.size();
+            const int tcap = ising && c->sched.wg_threads == 0 ? 1024 : tmax;
             int P = 1;
             if (c->sched.rpb > 0) {
                 // forced packing: at most rpb, within the LDS budget, one
                 // wave per replica at least, and no more than the group holds
                 while (P * 2 <= c->sched.rpb && P * 2 <= kMaxRpb && P * 2 * 64 <= tmax &&
+                       (!ising || P * 2 * items <= 2048) &&
                        (size_t)(P * 2) * slot <= kResidentLdsBudget && P * 2 <= n)
                     P *= 2;
             } else {
@@ -1626,8 +1632,9 @@ int prepare(spinmc_ctx* c, int mode) {
             }
             // forced packing gives every replica a wave at least (64 P <= tmax)
             int threads = c->sched.rpb > 0 ? 64 * P : 64;
-            while (threads < tmax && threads < P * items) threads *= 2;
-            c->res_groups.push_back({(int)buf.size(), n, P, threads, std::get<0>(kv.first),
+            while (threads < tcap && threads < P * items) threads *= 2;
+            while (ising && 2 * threads < P * items) threads *= 2;
+            c->res_groups.push_back({(int)buf.size(), n, P, threads, std::get<0>(kv.first), items,
                                      pass == 0, slot});
             buf.insert(buf.end(), kv.second.begin(), kv.second.end());
         }
@@ -1706,7 +1713,7 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
         a.rpb = g.rpb;
         a.res_slot_bytes = (int)g.slot;
         e = timed(c, SPINMC_K_RESIDENT, [&] {
-            return launch_resident(a, g.count, g.model, g.chunk, g.threads, g.slot * g.rpb, side);
+            return launch_resident(a, g.count, g.model, g.chunk, g.items, g.threads, g.slot * g.rpb, side);
         }, side);
     }
     return e;

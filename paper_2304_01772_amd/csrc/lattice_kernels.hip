@@ -12,7 +12,8 @@
 // The fast ("chunk") path gives each lane 16 consecutive bytes of a plane row
 // (one dwordx4 load per plane row), builds neighbour sums with byte-SWAR
 // arithmetic, and consumes one 16-bit Philox prefix per site for the
-// Metropolis test of Algorithm 1 (Ising: 8 sites per Philox4x32-10 call;
+// Metropolis test of Algorithm 1 (Ising: 8 sites per Philox4x32-10 call, two
+// sites a lookup and compare;
 // Potts: 16-bit proposal + 16-bit accept prefix, 4 sites per call).  The low
 // 16 bits of the uniform word are drawn from the fallback stream only when
 // the prefix ties the threshold's high half (probability 2^-16), so the
@@ -125,19 +126,11 @@ struct ChunkOff {
     }
 };
 
-// PAR = (y + c) & 1 selects which horizontal neighbour the shifted byte
-// stream supplies.  thr: LDS [18 hi | 18 lo].
-template <int PAR, bool REC, bool NT>
-__device__ __forceinline__ void ising_compute(const ChunkIn& in, uint8_t* own, uint32_t oo,
-                                              uint32_t p, uint32_t rid, uint32_t k0, uint32_t k1,
-                                              const uint32_t* thr, IsingAcc& acc) {
-    const uint32_t e = in.e;
-    const uint32_t ov[4] = {in.o.x, in.o.y, in.o.z, in.o.w};
-    const uint32_t mv[4] = {in.m.x, in.m.y, in.m.z, in.m.w};
-    const uint32_t Uv[4] = {in.U.x, in.U.y, in.U.z, in.U.w};
-    const uint32_t Dv[4] = {in.D.x, in.D.y, in.D.z, in.D.w};
-    uint32_t sv[4];
-    if (PAR == 0) {
+// The shifted byte stream: the horizontal neighbour that the other plane's same
+// row does not hold at the own column, left (par 0) or right (par 1).
+__device__ __forceinline__ void side_bytes(int par, const uint32_t (&mv)[4], uint32_t e,
+                                           uint32_t (&sv)[4]) {
+    if (par == 0) {
         sv[0] = __builtin_amdgcn_alignbyte(mv[0], e, 3);
         sv[1] = __builtin_amdgcn_alignbyte(mv[1], mv[0], 3);
         sv[2] = __builtin_amdgcn_alignbyte(mv[2], mv[1], 3);
@@ -148,64 +141,146 @@ __device__ __forceinline__ void ising_compute(const ChunkIn& in, uint8_t* own, u
         sv[2] = __builtin_amdgcn_alignbyte(mv[3], mv[2], 1);
         sv[3] = __builtin_amdgcn_alignbyte(e, mv[3], 1);
     }
-    // class 9u + 3nx + ny per byte (< 18), times 4: the byte offset of its
-    // threshold in LDS (< 72, still one byte)
-    uint32_t idx4[4];
+}
+
+typedef short s16x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const uint32_t* lds_u32_t;
+
+// Two sites at a time.  The table in LDS holds, for each pair of classes
+// (c0, c1), the high halves of both thresholds as signed 16-bit numbers,
+// min(T_hi, 65535) - 32768, in one dword: entry 18 c0 + c1, whose byte offset
+// 72 c0 + 4 c1 is one byte dot product.  Against the prefixes with their top
+// bit flipped one saturating packed subtraction decides both: negative accepts,
+// zero is a tie (or T_hi = 65536 at r = 65535) that the exact rule below
+// resolves, positive rejects.  The thresholds themselves, [18 hi | 18 lo], lie
+// behind the pairs.
+constexpr int kIsingPairs = kIsingClasses * kIsingClasses;
+static_assert(kIsingTabWords == kIsingPairs + 2 * kIsingClasses, "table layout");
+
+__device__ __forceinline__ void load_ising_table(const uint32_t* tab, const RepDev& R, uint32_t* l,
+                                                 int tid, int nthr) {
+    const uint32_t* t = tab + R.tab_off;
+    for (int i = tid; i < kIsingTabWords; i += nthr) {
+        if (i < kIsingPairs) {
+            const int c0 = i / kIsingClasses, c1 = i - c0 * kIsingClasses;
+            l[i] = (min(t[c0], 65535u) | (min(t[c1], 65535u) << 16)) ^ 0x80008000u;
+        } else {
+            l[i] = t[i - kIsingPairs];
+        }
+    }
+}
+
+// The ties of a chunk (bit j of tie: site j), decided by the low halves.
+__device__ __forceinline__ uint32_t ising_ties(uint32_t tie, const uint32_t* tab, uint32_t i0,
+                                            uint32_t i1, uint32_t i2, uint32_t i3, uint32_t kb,
+                                            uint32_t p, uint32_t rid, uint32_t k0, uint32_t k1) {
+    uint32_t acc = 0u;
+    while (tie != 0u) {
+        const uint32_t j = (uint32_t)__builtin_ctz(tie);
+        tie &= tie - 1u;
+        const uint32_t iw = j < 8u ? (j < 4u ? i0 : i1) : (j < 12u ? i2 : i3);
+        const uint32_t cls = (iw >> (8u * (j & 3u))) & 0xFFu;
+        const uint32_t hi = tab[kIsingPairs + cls], lo = tab[kIsingPairs + kIsingClasses + cls];
+        bool ok = hi > 65535u;  // T = 2^32
+        if (!ok && lo != 0u) {
+            uint32_t f[4];
+            philox4x32_10(kb + j, p, rid, kTagFallback, k0, k1, f);
+            ok = (f[0] & 0xFFFFu) < lo;
+        }
+        acc |= ok ? 1u << j : 0u;
+    }
+    return acc;
+}
+
+// The new own bytes nv of a 16-site chunk, within-colour index kb of its first
+// site, and the side neighbours sv.  par = (y + c) & 1, a constant at each call.
+// About 165 VALU slots a chunk, 108 of them the two Philox blocks; a lookup and
+// a 32-bit compare for every site took 213.
+__device__ __forceinline__ void ising_core(int par, const uint4& o, const uint4& m, const uint4& U,
+                                           const uint4& D, uint32_t e, uint32_t kb, uint32_t p,
+                                           uint32_t rid, uint32_t k0, uint32_t k1,
+                                           const uint32_t* tab, uint32_t (&nv)[4],
+                                           uint32_t (&sv)[4]) {
+    const uint32_t ov[4] = {o.x, o.y, o.z, o.w};
+    const uint32_t mv[4] = {m.x, m.y, m.z, m.w};
+    const uint32_t Uv[4] = {U.x, U.y, U.z, U.w};
+    const uint32_t Dv[4] = {D.x, D.y, D.z, D.w};
+    side_bytes(par, mv, e, sv);
+    // class 9u + 3nx + ny per byte (< 18)
+    uint32_t idx[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t nx = mv[k] + sv[k];
-        const uint32_t ny = Uv[k] + Dv[k];
-        idx4[k] = ((ov[k] << 3) + ov[k] + (nx << 1) + nx + ny) << 2;
+        idx[k] = ((ov[k] << 3) + ov[k]) + ((nx << 1) + nx) + (Uv[k] + Dv[k]);
     }
-    const uint32_t kb = oo;  // within-colour index of the first site
     uint32_t w[8];
-    philox4x32_10(kb >> 3, p, rid, kTagMain, k0, k1, &w[0]);
-    philox4x32_10((kb >> 3) + 1u, p, rid, kTagMain, k0, k1, &w[4]);
-    // d = r - T_hi as unsigned: bit 31 set iff r < T_hi (accept on the prefix),
-    // d == 0 iff the prefix ties; the smallest d flags a tie anywhere.
-    const uint8_t* thb = reinterpret_cast<const uint8_t*>(thr);
-    uint32_t d[16];
-    uint32_t dmin = 0xFFFFFFFFu;
+    philox4x32_10<0x80008000u>(kb >> 3, p, rid, kTagMain, k0, k1, &w[0]);
+    philox4x32_10<0x80008000u>((kb >> 3) + 1u, p, rid, kTagMain, k0, k1, &w[4]);
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_u32_t)tab;
+    s16x2_t d[8];
+    u16x2_t dmin = {0xFFFF, 0xFFFF};
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const uint32_t off = (idx4[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-        const uint32_t r = (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-        d[j] = r - *reinterpret_cast<const uint32_t*>(thb + off);
-        dmin = min(dmin, d[j]);
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t at =
+            __builtin_amdgcn_udot4(idx[i >> 1], (i & 1) ? 0x04480000u : 0x00000448u, base, false);
+        const uint32_t T = *(lds_u32_t)(uintptr_t)at;
+        d[i] = __builtin_elementwise_sub_sat(__builtin_bit_cast(s16x2_t, w[i]),
+                                             __builtin_bit_cast(s16x2_t, T));
+        dmin = __builtin_elementwise_min(dmin, __builtin_bit_cast(u16x2_t, d[i]));
     }
-    uint32_t flip[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) flip[k] = sign_bytes(d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]) & 0x01010101u;
-    if (dmin == 0u) {
-        // The prefix equals the threshold's high half: the low halves decide.
-        for (int j = 0; j < 16; ++j) {
-            if (d[j] != 0u) continue;
-            const uint32_t cls = ((idx4[j >> 2] >> (8 * (j & 3))) & 0xFFu) >> 2;
-            const uint32_t lo = thr[kIsingClasses + cls];
-            if (lo == 0u) continue;
-            uint32_t f[4];
-            philox4x32_10(kb + (uint32_t)j, p, rid, kTagFallback, k0, k1, f);
-            if ((f[0] & 0xFFFFu) < lo) flip[j >> 2] |= 1u << (8 * (j & 3));
-        }
+    for (int k = 0; k < 4; ++k) {
+        // v_perm_b32 selectors 8 .. 11: the signs of the four 16-bit halves
+        const uint32_t f = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, d[2 * k + 1]),
+                                                 __builtin_bit_cast(uint32_t, d[2 * k]), 0x0B0A0908u);
+        nv[k] = ov[k] ^ (f & 0x01010101u);
     }
-    uint32_t nv[4];
+    if (min((uint32_t)dmin.x, (uint32_t)dmin.y) == 0u) {
+        uint32_t tie = 0u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) nv[k] = ov[k] ^ flip[k];
+        for (int i = 0; i < 8; ++i)
+            tie |= (d[i].x == 0 ? 1u << (2 * i) : 0u) | (d[i].y == 0 ? 2u << (2 * i) : 0u);
+        const uint32_t acc =
+            ising_ties(tie, tab, idx[0], idx[1], idx[2], idx[3], kb, p, rid, k0, k1);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) nv[j >> 2] ^= ((acc >> j) & 1u) << (8 * (j & 3));
+    }
+}
+
+// Adds a chunk of a recorded sweep's colour-1 pass to byte-wise counts: up
+// spins of both colours, unequal horizontal and vertical bonds (every bond has
+// exactly one colour-1 end).  At most 8 a byte and call.
+__device__ __forceinline__ void ising_count(const uint32_t (&nv)[4], const uint32_t (&mv)[4],
+                                            const uint32_t (&sv)[4], const uint32_t (&Uv)[4],
+                                            const uint32_t (&Dv)[4], uint32_t& up, uint32_t& dx,
+                                            uint32_t& dy) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        up = nv[k] + mv[k] + up;
+        dx = (nv[k] ^ mv[k]) + dx;
+        dx = (nv[k] ^ sv[k]) + dx;
+        dy = (nv[k] ^ Uv[k]) + dy;
+        dy = (nv[k] ^ Dv[k]) + dy;
+    }
+}
+
+template <int PAR, bool REC, bool NT>
+__device__ __forceinline__ void ising_compute(const ChunkIn& in, uint8_t* own, uint32_t oo,
+                                              uint32_t p, uint32_t rid, uint32_t k0, uint32_t k1,
+                                              const uint32_t* tab, IsingAcc& acc) {
+    uint32_t nv[4], sv[4];
+    ising_core(PAR, in.o, in.m, in.U, in.D, in.e, oo, p, rid, k0, k1, tab, nv, sv);
     store_own<NT>(own + oo, nv[0], nv[1], nv[2], nv[3]);
     if (REC) {
-        // Colour-1 pass of a recorded sweep: every bond has exactly one
-        // colour-1 end, so summing over the updated sites counts each once.
+        const uint32_t mv[4] = {in.m.x, in.m.y, in.m.z, in.m.w};
+        const uint32_t Uv[4] = {in.U.x, in.U.y, in.U.z, in.U.w};
+        const uint32_t Dv[4] = {in.D.x, in.D.y, in.D.z, in.D.w};
         uint32_t up = 0u, dx = 0u, dy = 0u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            up = sad_u8(nv[k], up);
-            up = sad_u8(mv[k], up);
-            dx = sad_u8((nv[k] ^ mv[k]) + (nv[k] ^ sv[k]), dx);
-            dy = sad_u8((nv[k] ^ Uv[k]) + (nv[k] ^ Dv[k]), dy);
-        }
-        acc.M += 2 * (int)up - 32;
-        acc.Bx += 32 - 2 * (int)dx;
-        acc.By += 32 - 2 * (int)dy;
+        ising_count(nv, mv, sv, Uv, Dv, up, dx, dy);
+        acc.M += 2 * (int)sad_u8(up, 0u) - 32;
+        acc.Bx += 32 - 2 * (int)sad_u8(dx, 0u);
+        acc.By += 32 - 2 * (int)sad_u8(dy, 0u);
     }
 }
 
@@ -459,11 +534,10 @@ __device__ __forceinline__ void run_tile_potts(uint8_t* planes, int W, int Ly, i
     }
 }
 
-// Ising rows [y0, y0+rows) of plane c.  DUAL: each lane takes one chunk of
-// each row parity per iteration and issues both chunks' loads before
-// computing (latency hiding for the HBM stream); otherwise one chunk per
-// iteration, parity by parity (fewer registers for the LDS-resident path).
-template <bool REC, bool DUAL, bool NT>
+// Ising rows [y0, y0+rows) of plane c.  Each lane takes one chunk of each row
+// parity per iteration and issues both chunks' loads before computing (latency
+// hiding for the HBM stream).
+template <bool REC, bool NT>
 __device__ __forceinline__ void run_tile_ising(uint8_t* planes, int W, int Ly, int y0, int rows,
                                                int c, uint32_t p, uint32_t rid, uint32_t k0,
                                                uint32_t k1, const uint32_t* thr, IsingAcc& ia,
@@ -482,49 +556,23 @@ __device__ __forceinline__ void run_tile_ising(uint8_t* planes, int W, int Ly, i
     const uint32_t Wb = (uint32_t)W, W2 = 2u * Wb;
     const uint32_t last = (uint32_t)(Ly - 1) * Wb;
     const uint32_t dro = (uint32_t)dr * W2, dj0 = (uint32_t)dj << 4;
-    if (DUAL) {
-        // ra: row of parity 0, ra + db: the row of parity 1 in the same pair
-        const int db = yb - ya;  // +1 or -1
-        const uint32_t ra_end = (uint32_t)(ya + rows) * Wb;
-        uint32_t ra = (uint32_t)(ya + 2 * r0) * Wb, j0 = (uint32_t)jc0 << 4;
-        for (; ra < ra_end;) {
-            const uint32_t rb = ra + (uint32_t)db * Wb;
-            const ChunkOff<0> fa(ra, j0, Wb, last);
-            const ChunkOff<1> fb(rb, j0, Wb, last);
-            const ChunkIn A = chunk_load<NT>(own, oth, fa.oo, fa.uo, fa.dof, fa.eo);
-            const ChunkIn B = chunk_load<NT>(own, oth, fb.oo, fb.uo, fb.dof, fb.eo);
-            ising_compute<0, REC, NT>(A, own, fa.oo, p, rid, k0, k1, thr, ia);
-            ising_compute<1, REC, NT>(B, own, fb.oo, p, rid, k0, k1, thr, ia);
-            ra += dro;
-            j0 += dj0;
-            if (j0 >= Wb) {
-                j0 -= Wb;
-                ra += W2;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int par = 0; par < 2; ++par) {
-            const int yf = par == 0 ? ya : yb;
-            const uint32_t ro_end = (uint32_t)(yf + rows) * Wb;
-            uint32_t ro = (uint32_t)(yf + 2 * r0) * Wb, j0 = (uint32_t)jc0 << 4;
-            for (; ro < ro_end;) {
-                if (par == 0) {
-                    const ChunkOff<0> f(ro, j0, Wb, last);
-                    const ChunkIn A = chunk_load<NT>(own, oth, f.oo, f.uo, f.dof, f.eo);
-                    ising_compute<0, REC, NT>(A, own, f.oo, p, rid, k0, k1, thr, ia);
-                } else {
-                    const ChunkOff<1> f(ro, j0, Wb, last);
-                    const ChunkIn B = chunk_load<NT>(own, oth, f.oo, f.uo, f.dof, f.eo);
-                    ising_compute<1, REC, NT>(B, own, f.oo, p, rid, k0, k1, thr, ia);
-                }
-                ro += dro;
-                j0 += dj0;
-                if (j0 >= Wb) {
-                    j0 -= Wb;
-                    ro += W2;
-                }
-            }
+    // ra: row of parity 0, ra + db: the row of parity 1 in the same pair
+    const int db = yb - ya;  // +1 or -1
+    const uint32_t ra_end = (uint32_t)(ya + rows) * Wb;
+    uint32_t ra = (uint32_t)(ya + 2 * r0) * Wb, j0 = (uint32_t)jc0 << 4;
+    for (; ra < ra_end;) {
+        const uint32_t rb = ra + (uint32_t)db * Wb;
+        const ChunkOff<0> fa(ra, j0, Wb, last);
+        const ChunkOff<1> fb(rb, j0, Wb, last);
+        const ChunkIn A = chunk_load<NT>(own, oth, fa.oo, fa.uo, fa.dof, fa.eo);
+        const ChunkIn B = chunk_load<NT>(own, oth, fb.oo, fb.uo, fb.dof, fb.eo);
+        ising_compute<0, REC, NT>(A, own, fa.oo, p, rid, k0, k1, thr, ia);
+        ising_compute<1, REC, NT>(B, own, fb.oo, p, rid, k0, k1, thr, ia);
+        ra += dro;
+        j0 += dj0;
+        if (j0 >= Wb) {
+            j0 -= Wb;
+            ra += W2;
         }
     }
 }
@@ -588,8 +636,12 @@ __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, 
                                                  uint32_t* lthr9, int* lhist, int* lred) {
     const TileDev T = a.tiles[tile0 + logical_block(n)];
     const RepDev R = a.reps[T.rep];
-    load_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
-    if (MODEL == kModelPotts) load_table9(a.tab, R, lthr9, threadIdx.x);
+    if (MODEL == kModelPotts) {
+        load_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
+        load_table9(a.tab, R, lthr9, threadIdx.x);
+    } else {
+        load_ising_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
+    }
     const bool rec = (rec_row >= 0) && (c == 1);
     if (MODEL == kModelPotts && rec)
         for (int i = threadIdx.x; i < R.q; i += blockDim.x) lhist[i] = 0;
@@ -601,10 +653,10 @@ __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, 
     PottsAcc pa{0, 0, 0};
     if (MODEL == kModelIsing) {
         if (rec)
-            run_tile_ising<true, true, NT>(planes, R.W, R.Ly, T.y0, T.rows, c, p, R.rid, a.key0, a.key1,
+            run_tile_ising<true, NT>(planes, R.W, R.Ly, T.y0, T.rows, c, p, R.rid, a.key0, a.key1,
                                  lthr, ia, threadIdx.x, blockDim.x);
         else
-            run_tile_ising<false, true, NT>(planes, R.W, R.Ly, T.y0, T.rows, c, p, R.rid, a.key0, a.key1,
+            run_tile_ising<false, NT>(planes, R.W, R.Ly, T.y0, T.rows, c, p, R.rid, a.key0, a.key1,
                                   lthr, ia, threadIdx.x, blockDim.x);
     } else {
         if (rec)
@@ -641,11 +693,10 @@ __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, 
 template <bool NT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6, 8)))
 k_stream_pass_ising(SweepArgs a, int tile0, int n, int c, int sweep_off, int rec_row) {
-    extern __shared__ uint32_t lthr[];  // [2 * tab_n] thresholds of this tile's replica
-    __shared__ uint32_t lthr9[18];
-    __shared__ int lhist[kMaxPottsQ];
+    __shared__ uint32_t tab[kIsingTabWords];  // thresholds of this tile's replica
     __shared__ int lred[64];
-    stream_pass_body<kModelIsing, NT>(a, tile0, n, c, sweep_off, rec_row, lthr, lthr9, lhist, lred);
+    stream_pass_body<kModelIsing, NT>(a, tile0, n, c, sweep_off, rec_row, tab, nullptr, nullptr,
+                                      lred);
 }
 
 template <bool NT>
@@ -724,8 +775,12 @@ __device__ __forceinline__ void persist_body(const SweepArgs& a, const PersistIt
     for (int k = i0; k < i1; ++k) {
         const RepDev R = a.reps[items[k].rep];
         uint32_t* t = lds + (k - i0) * slot_words;
-        load_table(a.tab, R, t, threadIdx.x, blockDim.x);
-        if (MODEL == kModelPotts) load_table9(a.tab, R, t + slot_words - 18, threadIdx.x);
+        if (MODEL == kModelPotts) {
+            load_table(a.tab, R, t, threadIdx.x, blockDim.x);
+            load_table9(a.tab, R, t + slot_words - 18, threadIdx.x);
+        } else {
+            load_ising_table(a.tab, R, t, threadIdx.x, blockDim.x);
+        }
     }
     __syncthreads();
     const uint64_t t0 = *a.t_base + (uint64_t)a.sweep_off;
@@ -745,7 +800,7 @@ __device__ __forceinline__ void persist_body(const SweepArgs& a, const PersistIt
                 uint8_t* planes = a.lat + R.lat_off;
                 if (MODEL == kModelIsing) {
                     IsingAcc ia{0, 0, 0};
-                    run_tile_ising<false, true, NT>(planes, R.W, R.Ly, it.y0, it.rows, c, p, R.rid,
+                    run_tile_ising<false, NT>(planes, R.W, R.Ly, it.y0, it.rows, c, p, R.rid,
                                                     a.key0, a.key1, tab, ia, threadIdx.x,
                                                     blockDim.x);
                 } else {
@@ -892,10 +947,9 @@ __device__ __forceinline__ void lattice_stats(int model, const uint8_t* planes, 
 // Resident kernel: a workgroup owns a.rpb replicas of one shape for the
 // whole call, each with its thresholds and both planes in LDS, and
 // blockDim/rpb threads; colour passes are separated by workgroup barriers.
-// KIND selects the path: kResIsing / kResPotts run the 16-byte SWAR chunks
-// (W % 16 == 0, every replica of the launch of that model), kResGeneric the
-// per-site code for any model and width.  Separate instantiations keep the
-// Ising path's register count (and so its waves per SIMD) free of Potts's.
+// KIND selects the path: kResPotts runs the 16-byte SWAR chunks (W % 16 == 0,
+// every replica of the launch of that model), kResGeneric the per-site code for
+// any model and width.  Ising chunks have k_resident_ising.
 template <int KIND>
 __device__ __forceinline__ void resident_body(const SweepArgs& a) {
     constexpr bool CHUNK = KIND != kResGeneric;
@@ -904,7 +958,6 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
     __shared__ uint32_t lthr9[kMaxRpb][18];
     __shared__ int lhist[kMaxPottsQ];
     __shared__ int lred[64];
-    __shared__ int lsum[kMaxRpb][3];  // Ising: per-slot (M, Bx, By) of a recorded sweep
     const int P = a.rpb;
     const int nt = blockDim.x / P;
     const int g = threadIdx.x / nt, lt = threadIdx.x - g * nt;
@@ -936,26 +989,8 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
         const bool rec = a.record_every > 0 && ((sw + 1) % a.record_every) == 0;
         for (int c = 0; c < 2; ++c) {
             const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
-            if (KIND == kResIsing && rec && c == 1) {
-                if (threadIdx.x < 3 * kMaxRpb) (&lsum[0][0])[threadIdx.x] = 0;
-                __syncthreads();
-            }
             if (active) {
-                if (KIND == kResIsing) {
-                    IsingAcc ia{0, 0, 0};
-                    if (rec && c == 1) {
-                        // statistics fused into the colour-1 pass: every bond has
-                        // exactly one colour-1 end
-                        run_tile_ising<true, false, false>(lds, R.W, R.Ly, 0, R.Ly, c, p, R.rid,
-                                                           a.key0, a.key1, lthr, ia, lt, nt);
-                        atomicAdd(&lsum[g][0], ia.M);
-                        atomicAdd(&lsum[g][1], ia.Bx);
-                        atomicAdd(&lsum[g][2], ia.By);
-                    } else {
-                        run_tile_ising<false, false, false>(lds, R.W, R.Ly, 0, R.Ly, c, p, R.rid,
-                                                            a.key0, a.key1, lthr, ia, lt, nt);
-                    }
-                } else if (KIND == kResPotts) {
+                if (KIND == kResPotts) {
                     PottsAcc pa{0, 0, 0};
                     potts_tile<false, false>(R, lds, 0, R.Ly, c, p, a.key0, a.key1, lthr, lthr9[g], pa,
                                       lhist, lt, nt);
@@ -967,16 +1002,7 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
             }
             __syncthreads();
         }
-        if (KIND == kResIsing && rec) {
-            if (active && lt == 0) {
-                int32_t* row =
-                    a.stats + ((size_t)((sw + 1) / a.record_every - 1) * a.R + rep) * a.width;
-                row[0] = lsum[g][0];
-                row[1] = lsum[g][1];
-                row[2] = lsum[g][2];
-                for (int k = 3; k < a.width; ++k) row[k] = 0;
-            }
-        } else if (rec) {
+        if (rec) {
             // statistics of each replica of the workgroup, all threads per replica
             for (int gg = 0; gg < P && first + gg < a.n_list; ++gg) {
                 const int rg = a.rep_list[first + gg];
@@ -1019,9 +1045,197 @@ __global__ void __launch_bounds__(512) k_resident_generic(SweepArgs a) {
     resident_body<kResGeneric>(a);
 }
 
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6, 8)))
-k_resident_ising(SweepArgs a) {
-    resident_body<kResIsing>(a);
+// ------------------------------------------------ resident Ising chunks
+namespace {
+
+// Sum of v over groups of n lanes (a power of two up to 64, uniform).
+__device__ __forceinline__ int group_sum(int v, int n) {
+    // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
+    if (n > 1) v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
+    if (n > 2) v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
+    if (n > 4) v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
+    if (n > 8) v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
+    if (n > 16) v += __shfl_xor(v, 16, 64);
+    if (n > 32) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
+// The lanes of one replica meet: a barrier, or where a replica has at most a
+// wave's lanes only an order of its LDS accesses (a wave's are served in order).
+__device__ __forceinline__ void replica_sync(bool waves) {
+    if (waves) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+__device__ __forceinline__ void arr(const uint4& v, uint32_t (&o)[4]) {
+    o[0] = v.x;
+    o[1] = v.y;
+    o[2] = v.z;
+    o[3] = v.w;
+}
+
+}  // namespace
+
+// A workgroup owns a.rpb replicas of one shape for the whole call, blockDim /
+// rpb = nt lanes each.  A lane owns NI items of a replica: 16 columns of two
+// adjacent rows of both planes, in registers for the whole call; the planes in
+// LDS carry them to the neighbours (two 16-byte and two 4-byte reads and two
+// 16-byte writes an item and pass).  Everything that depends on the lane alone
+// is computed once: a lane has one item in most shapes, and the index
+// arithmetic of a pass used to cost as much as half a chunk.
+// UNI: nt is a multiple of 64, so a wave's replica is uniform (scalar loads,
+// Philox keys and counters in scalar registers).
+// Bound by VALU operations where the chip is full (4096 lattices of 64 x 64, 100
+// sweeps and 200 recorded ones: 2.59 -> 1.55 ms, 3.1e12 attempts/s), by one
+// wave's latency for single small lattices.
+template <int NI, bool UNI>
+__global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
+    // dynamic LDS: rpb slots of [thresholds (kIsingTabWords) | plane 0 | plane 1]
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ int lsum[kMaxRpb][3];  // per-slot counts of a recorded sweep
+    const int P = a.rpb;
+    const int nt = blockDim.x / P;
+    int g = threadIdx.x / nt;
+    const int lt = threadIdx.x - g * nt;
+    if (UNI) g = __builtin_amdgcn_readfirstlane(g);
+    const int first = blockIdx.x * P;
+    const bool active = first + g < a.n_list;
+    const int rep = a.rep_list[active ? first + g : first];
+    const RepDev& R = a.reps[rep];
+    const int W = R.W, Ly = R.Ly, cpr = W >> 4;
+    const uint32_t plane = (uint32_t)(Ly * W), rid = R.rid;
+    uint8_t* slot = dyn + (size_t)(active ? g : 0) * a.res_slot_bytes;
+    uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
+    uint8_t* lds = slot + 4 * kIsingTabWords;
+    uint8_t* gmem = a.lat + R.lat_off;
+    const int n_items = active ? (Ly >> 1) * cpr : 0;
+    if (active) load_ising_table(a.tab, R, tab, lt, nt);
+    // per item: byte offset in a plane of the even row's chunk, of the rows
+    // above it and below its odd row, and of the halo dwords of the even row
+    uint32_t oo[NI], uo[NI], dof[NI], le[NI], re[NI];
+    uint4 V[2][2][NI];  // [plane][row][item]
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        const int it = lt + k * nt;
+        const int r = it < n_items ? it / cpr : 0;
+        const uint32_t j0 = it < n_items ? (uint32_t)(it - r * cpr) << 4 : 0u;
+        const uint32_t ro = (uint32_t)(2 * r * W), last = plane - (uint32_t)W;
+        oo[k] = ro + j0;
+        uo[k] = (r == 0 ? last : ro - (uint32_t)W) + j0;
+        dof[k] = (2 * r + 2 == Ly ? 0u : ro + 2u * (uint32_t)W) + j0;
+        le[k] = ro + (j0 == 0u ? (uint32_t)W : j0) - 4u;
+        re[k] = ro + (j0 + 16u == (uint32_t)W ? 0u : j0 + 16u);
+        if (it < n_items) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    const uint32_t at = c * plane + oo[k] + (uint32_t)(o * W);
+                    V[c][o][k] = *reinterpret_cast<const uint4*>(gmem + at);
+                    *reinterpret_cast<uint4*>(lds + at) = V[c][o][k];
+                }
+        }
+    }
+    if (threadIdx.x < 3 * kMaxRpb) (&lsum[0][0])[threadIdx.x] = 0;
+    __syncthreads();
+    const bool waves = nt > 64;
+    const uint64_t t0 = *a.t_base;
+    for (int i = 0; i < a.n_sweeps; ++i) {
+        const int sw = a.sweep_off + i;  // sweep index within the call
+        const uint64_t t = t0 + (uint64_t)sw;
+        const bool rec = a.record_every > 0 && ((sw + 1) % a.record_every) == 0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
+            uint8_t* own = lds + c * plane;
+            const uint8_t* oth = lds + (1 - c) * plane;
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                if (lt + k * nt >= n_items) continue;
+                // even row: parity c; odd row: parity 1 - c (left halo for parity 0)
+                const uint4 U = *reinterpret_cast<const uint4*>(oth + uo[k]);
+                const uint4 D = *reinterpret_cast<const uint4*>(oth + dof[k]);
+                const uint32_t e0 =
+                    *reinterpret_cast<const uint32_t*>(oth + (c == 0 ? le[k] : re[k]));
+                const uint32_t e1 =
+                    *reinterpret_cast<const uint32_t*>(oth + W + (c == 0 ? re[k] : le[k]));
+                uint32_t nv[4], sv[4];
+                ising_core(c, V[c][0][k], V[1 - c][0][k], U, V[1 - c][1][k], e0, oo[k], p, rid,
+                              a.key0, a.key1, tab, nv, sv);
+                V[c][0][k] = make_uint4(nv[0], nv[1], nv[2], nv[3]);
+                *reinterpret_cast<uint4*>(own + oo[k]) = V[c][0][k];
+                ising_core(1 - c, V[c][1][k], V[1 - c][1][k], V[1 - c][0][k], D, e1,
+                                  oo[k] + (uint32_t)W, p, rid, a.key0, a.key1, tab, nv, sv);
+                V[c][1][k] = make_uint4(nv[0], nv[1], nv[2], nv[3]);
+                *reinterpret_cast<uint4*>(own + oo[k] + W) = V[c][1][k];
+            }
+            if (c == 0) replica_sync(waves);
+        }
+        if (rec) {
+            // colour 1 just written, colour 0 (in LDS) before the next pass writes it
+            uint32_t up = 0u, dx = 0u, dy = 0u;
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                if (lt + k * nt >= n_items) continue;
+                uint32_t nv[2][4], mv[2][4], sv[4], Uv[4], Dv[4];
+                arr(V[1][0][k], nv[0]);
+                arr(V[1][1][k], nv[1]);
+                arr(V[0][0][k], mv[0]);
+                arr(V[0][1][k], mv[1]);
+                arr(*reinterpret_cast<const uint4*>(lds + uo[k]), Uv);
+                arr(*reinterpret_cast<const uint4*>(lds + dof[k]), Dv);
+                side_bytes(1, mv[0], *reinterpret_cast<const uint32_t*>(lds + re[k]), sv);
+                ising_count(nv[0], mv[0], sv, Uv, mv[1], up, dx, dy);
+                side_bytes(0, mv[1], *reinterpret_cast<const uint32_t*>(lds + W + le[k]), sv);
+                ising_count(nv[1], mv[1], sv, mv[0], Dv, up, dx, dy);
+            }
+            // at most 16 NI a byte, 8192 a wave: the bonds in one word
+            const int n = nt < 64 ? nt : 64;
+            const int su = group_sum((int)sad_u8(up, 0u), n);
+            const int sb = group_sum((int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16)), n);
+            int cu = su, cx = sb & 0xFFFF, cy = (int)((uint32_t)sb >> 16);
+            if (waves) {
+                if ((lt & 63) == 0) {
+                    atomicAdd(&lsum[g][0], cu);
+                    atomicAdd(&lsum[g][1], cx);
+                    atomicAdd(&lsum[g][2], cy);
+                }
+                __syncthreads();
+                if (lt == 0) {  // cleared for the next row, a barrier away
+                    cu = lsum[g][0];
+                    cx = lsum[g][1];
+                    cy = lsum[g][2];
+                    lsum[g][0] = lsum[g][1] = lsum[g][2] = 0;
+                }
+            } else {
+                replica_sync(false);
+            }
+            if (active && lt == 0) {
+                const int N = 2 * (int)plane;
+                int32_t* row =
+                    a.stats + ((size_t)((sw + 1) / a.record_every - 1) * a.R + rep) * a.width;
+                row[0] = 2 * cu - N;
+                row[1] = N - 2 * cx;
+                row[2] = N - 2 * cy;
+                for (int k = 3; k < a.width; ++k) row[k] = 0;
+            }
+        } else {
+            replica_sync(waves);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NI; ++k)
+        if (lt + k * nt < n_items)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+                    *reinterpret_cast<uint4*>(gmem + c * plane + oo[k] + (uint32_t)(o * W)) =
+                        V[c][o][k];
 }
 
 __global__ void __launch_bounds__(512) k_resident_potts(SweepArgs a) {
@@ -1130,24 +1344,34 @@ hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* 
 }
 
 hipError_t resident_reserve_lds(size_t lds_bytes) {
-    const void* fns[3] = {(const void*)k_resident_generic, (const void*)k_resident_ising,
-                          (const void*)k_resident_potts};
+    const void* fns[] = {(const void*)k_resident_generic, (const void*)k_resident_potts,
+                         (const void*)k_resident_ising<1, false>,
+                         (const void*)k_resident_ising<2, false>,
+                         (const void*)k_resident_ising<1, true>,
+                         (const void*)k_resident_ising<2, true>};
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 3 && e == hipSuccess; ++i)
-        e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    for (const void* f : fns)
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     return e;
 }
 
-hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int threads,
-                           size_t lds_bytes, hipStream_t s) {
+hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int items,
+                           int threads, size_t lds_bytes, hipStream_t s) {
     if (n_list <= 0) return hipSuccess;
-    const int blocks = (n_list + a.rpb - 1) / a.rpb;
-    if (!chunk)
-        hipLaunchKernelGGL(k_resident_generic, dim3(blocks), dim3(threads), lds_bytes, s, a);
-    else if (model == kModelIsing)
-        hipLaunchKernelGGL(k_resident_ising, dim3(blocks), dim3(threads), lds_bytes, s, a);
-    else
-        hipLaunchKernelGGL(k_resident_potts, dim3(blocks), dim3(threads), lds_bytes, s, a);
+    const dim3 g((n_list + a.rpb - 1) / a.rpb), b(threads);
+    if (!chunk) {
+        hipLaunchKernelGGL(k_resident_generic, g, b, lds_bytes, s, a);
+    } else if (model == kModelIsing) {
+        const int nt = threads / a.rpb;
+        if (items > 2 * nt) return hipErrorInvalidValue;
+        auto* k = nt % 64 == 0 ? (items > nt ? k_resident_ising<2, true> : k_resident_ising<1, true>)
+                               : (items > nt ? k_resident_ising<2, false>
+                                             : k_resident_ising<1, false>);
+        hipLaunchKernelGGL(k, g, b, lds_bytes, s, a);
+    } else {
+        hipLaunchKernelGGL(k_resident_potts, g, b, lds_bytes, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1158,11 +1382,11 @@ hipError_t launch_stream_pass(const SweepArgs& a, int model, int tile0, int n_ti
     const dim3 g(n_tiles), b(threads);
     if (model == kModelIsing) {
         if (nt)
-            hipLaunchKernelGGL(k_stream_pass_ising<true>, g, b, lds_tab_bytes, s, a, tile0, n_tiles,
-                               c, sweep_off, rec_row);
+            hipLaunchKernelGGL(k_stream_pass_ising<true>, g, b, 0, s, a, tile0, n_tiles, c,
+                               sweep_off, rec_row);
         else
-            hipLaunchKernelGGL(k_stream_pass_ising<false>, g, b, lds_tab_bytes, s, a, tile0,
-                               n_tiles, c, sweep_off, rec_row);
+            hipLaunchKernelGGL(k_stream_pass_ising<false>, g, b, 0, s, a, tile0, n_tiles, c,
+                               sweep_off, rec_row);
     } else {
         if (nt)
             hipLaunchKernelGGL(k_stream_pass_potts<true>, g, b, lds_tab_bytes, s, a, tile0, n_tiles,

@@ -16,14 +16,17 @@ constexpr uint32_t kTagFallback = 1u;
 constexpr uint32_t kTagInit = 2u;
 
 constexpr int kIsingClasses = 18;
+// Words of an Ising replica's thresholds in LDS: those of the 18 x 18 pairs of
+// classes, then 18 high and 18 low halves.
+constexpr int kIsingTabWords = 18 * 18 + 2 * 18;
 constexpr int kMaxPottsQ = 128;   // labels fit in 7 bits (SWAR equality test)
 constexpr int kMaxCpmTypes = 4;
 constexpr int kMaxRpb = 16;       // replicas per resident workgroup
 
-// Resident kernel paths: per-site (any model or width), Ising chunks, Potts chunks.
+// Paths of the resident kernel of Potts chunks and sites: per-site (any model or
+// width), Potts chunks.
 constexpr int kResGeneric = 0;
-constexpr int kResIsing = 1;
-constexpr int kResPotts = 2;
+constexpr int kResPotts = 1;
 
 // Per-replica record, device visible.
 struct RepDev {
@@ -68,14 +71,17 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+// The block's words, each xor'ed with X (on two of them free of cost: it joins
+// the last round's keys).
+template <uint32_t X = 0u>
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, r == 9 ? k0 ^ X : k0);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, r == 9 ? k1 ^ X : k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -84,9 +90,9 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
         k1 += 0xBB67AE85u;
     }
     out[0] = c0;
-    out[1] = c1;
+    out[1] = c1 ^ X;
     out[2] = c2;
-    out[3] = c3;
+    out[3] = c3 ^ X;
 }
 
 // Launch parameters common to the lattice kernels.
@@ -114,9 +120,10 @@ struct SweepArgs {
 hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* lat,
                        uint32_t key0, uint32_t key1, int threads, hipStream_t s);
 // Resident groups: chunk groups hold replicas of one model (model selects
-// the path); per-site groups may mix models.
-hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int threads,
-                           size_t lds_bytes, hipStream_t s);
+// the path); per-site groups may mix models.  items: row pairs of 16 columns
+// of a replica (chunk groups); Ising needs at most two a lane.
+hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int items,
+                           int threads, size_t lds_bytes, hipStream_t s);
 // Allow the resident kernels up to lds_bytes of dynamic LDS (call outside capture).
 hipError_t resident_reserve_lds(size_t lds_bytes);
 // nt: own-plane loads and stores nontemporal (lattice sets beyond the cache)

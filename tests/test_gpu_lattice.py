@@ -518,3 +518,38 @@ def test_ising_stream_8192_nontemporal_full_size_sampled(S):
         want, _ = _run_oracle(r, _init_oracle(r, seed), seed, 0, n, 0)
         assert np.array_equal(smp.get_state(i), want), f"replica {i}"
     smp.close()
+
+
+@pytest.mark.parametrize("mode", ["resident", "stream"])
+@pytest.mark.parametrize("beta", [0.0, 1e-6, 0.44, 1.45, 40.0])
+def test_ising_pair_thresholds_at_their_ends(S, beta, mode):
+    """Thresholds of 2^32, high halves of 65535, and of 0, and thresholds of
+    0, with enough attempts that prefixes tie."""
+    reps = [dict(model=0, Lx=256, Ly=128, Jx=1.0, Jy=1.0, h=0.0, beta=beta, rid=1),
+            dict(model=0, Lx=64, Ly=64, Jx=0.7, Jy=-0.4, h=_f32(0.05), beta=beta, rid=2)]
+    _check_batch(S, reps, seed=21, n=40, re=8, schedule=dict(mode=mode))
+
+
+@pytest.mark.parametrize("Lx,Ly,R,sched", [
+    (32, 2, 2, {}),                    # one item, a row above that is the row below
+    (96, 50, 3, {}),                   # three chunks a row, lanes without an item
+    (32, 16, 4099, {}),                # eight replicas in a wave, the last workgroup ragged
+    (64, 32, 2050, {}),                # two replicas a wave
+    (256, 256, 2, {}),                 # 1024 lanes, one item each
+    (512, 256, 1, {}),                 # 1024 lanes, two items each: the largest
+    (256, 130, 2, dict(wg_threads=256)),  # two items, the second ragged
+])
+def test_ising_resident_at_its_limits(S, Lx, Ly, R, sched):
+    seed = 31
+    smp = S([dict(model=0, Lx=Lx, Ly=Ly, Jx=1.0, Jy=0.8, h=_f32(0.02), beta=0.45, rid=r)
+             for r in range(R)], seed, init=True)
+    smp.set_schedule(mode="resident", **sched)
+    smp.sweep(3)
+    st = smp.sweep(4, 2).cpu().numpy()
+    for r in sorted({0, min(1, R - 1), R // 2, R - 1}):
+        a, _ = orc.ising_run(orc.ising_init(Lx, Ly, seed, r), 1.0, 0.8, _f32(0.02), 0.45, seed, r,
+                             0, 3, 0)
+        a, want = orc.ising_run(a, 1.0, 0.8, _f32(0.02), 0.45, seed, r, 3, 4, 2)
+        assert np.array_equal(smp.get_state(r), a), r
+        assert np.array_equal(st[:, r, :], want), r
+    smp.close()
