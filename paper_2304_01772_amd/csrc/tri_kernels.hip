@@ -440,10 +440,10 @@ __global__ void k_tri_observables(TriArgs a, double* obs) {
 // per site.  (In natural order, where a 12- or 8-byte span holds four own
 // sites, the same passes took about 45 lane-instructions a site: 1024 x 96^2
 // triangular, 200 sweeps with every tenth recorded, 2705 us; 256 x 32^3, 100
-// sweeps and one measurement, 1000 us; now 1205 and 568.)
+// sweeps and one measurement, 1000 us; now 982 and 568.)
 //
-// NB = 2 where every row holds an even number of blocks (half the LDS
-// accesses and offsets per site), else 1; NI = 1 up to 1024 items (any number
+// NB = 2 for lattices of more than 1024 blocks a plane whose rows hold an even
+// number of blocks (half the LDS accesses and offsets per site), else 1; NI = 1 up to 1024 items (any number
 // of waves, several workgroups to a CU), else up to 8 / NB.
 template <int NB>
 struct Words {
@@ -796,7 +796,11 @@ const void* plane_resident_fn(bool hc, int nb, int ni) {
 hipError_t launch_plane_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
                                  hipStream_t s) {
     const bool hc = a.model == kModelIsingHC;
-    const int nb = a.even_blocks ? 2 : 1;
+    // one block a lane where the lanes suffice (more waves, shorter chains: 512
+    // sites 0.54 us a sweep against 1.13, 1024 triangular 96 x 96 lattices 4.9
+    // against 6.0), else two, which share half their reads (256 lattices of
+    // 128 x 128: 2.2 us against 2.7)
+    const int nb = a.even_blocks && a.max_blocks > 1024 ? 2 : 1;
     const int items = (a.max_blocks + nb - 1) / nb;
     const int ni = (items + 1023) / 1024;
     if (ni > 8 / nb) return hipErrorInvalidValue;  // lattices above 64 KiB

@@ -56,3 +56,11 @@ def test_chain_square_cubic(Lz, Ly, Lx, beta):
                  beta=beta, rid=50 + r) for r in range(2)]
     _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
                                                         t, n, e))
+
+
+def test_two_blocks_an_item_in_a_ragged_wave():
+    """612 and 594 items of two blocks, one a lane."""
+    reps = [dict(model=3, Lx=144, Ly=102, Jx=1.0, Jy=1.0, h=0.05, beta=0.27, rid=60)]
+    _check(reps, lambda s, d, seed, t, n, e: orc.tri_run(s, 1.0, 0.05, 0.27, seed, 60, t, n, e))
+    reps = [dict(model=4, Lx=144, Ly=66, Lz=1, Jx=1.0, Jy=1.0, h=0.05, beta=0.4, rid=61)]
+    _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, 1.0, 0.05, 0.4, seed, 61, t, n, e))
