@@ -45,6 +45,11 @@ constexpr size_t kAlign = 256;
 constexpr int kResidentMaxBytes = 128 * 1024;  // lattice bytes kept in LDS by the resident kernel
 constexpr int kMaxCpmCells = 1 << 20;
 constexpr int kGraphChunk = 50;  // sweeps per captured graph
+// Sites a colour of all lattices of a resident Ising group up to which a lane
+// takes eight sites instead of a row pair of 16 columns (us a sweep, pairs / eight
+// sites, unrecorded and recorded: 512 lattices of 64 x 64 2.06 / 1.14 and 2.67 /
+// 1.73; 1024 2.74 / 1.74 and 3.45 / 2.51; 2048 2.96 / 2.90 and 3.65 / 4.36).
+constexpr int64_t kIsing8MaxSites = (int64_t)1 << 21;
 constexpr int kSide = 4;         // side streams for concurrent resident groups
 constexpr size_t kResidentLdsBudget = 150 * 1024;
 // Streamed lattice sets beyond this size do not stay in the 256 MB last-level
@@ -149,8 +154,7 @@ struct spinmc_ctx {
     // resident workgroup groups (replicas of one shape packed rpb per workgroup)
     bool nt_ising = false, nt_potts = false;  // nontemporal own-plane access per model
     struct ResGroup {
-        int off, count, rpb, threads, model, items;
-        bool chunk;
+        int off, count, rpb, threads, kind, items;
         size_t slot;
     };
     std::vector<ResGroup> res_groups;
@@ -1592,37 +1596,46 @@ int prepare(spinmc_ctx* c, int mode) {
     c->res_chunk = res_chunk;
     c->res_gen = res_gen;
     c->stream_potts = spotts;
-    // Resident groups: replicas of one shape, packed rpb per workgroup so
-    // that the workgroup's threads cover about one 16-byte chunk (chunk
-    // path) or one site (per-site path) each per pass, while keeping at
-    // least two workgroups per CU when there are enough replicas.
+    // Resident groups: replicas of one kernel and shape, packed rpb per
+    // workgroup so that the workgroup's threads cover about one item each per
+    // pass, while keeping at least two workgroups per CU when there are enough
+    // replicas.
     c->res_groups.clear();
     std::vector<int32_t> buf;
     const int tmax = c->sched.wg_threads > 0 ? c->sched.wg_threads : 512;
     for (int pass = 0; pass < 2; ++pass) {
         const std::vector<int32_t>& L = pass == 0 ? res_chunk : res_gen;
-        // chunk groups: one model and shape each; per-site groups: one shape
         std::map<std::tuple<int, int, int>, std::vector<int32_t>> shapes;
         for (int i : L) {
             const RepDev& d = c->reps[i].dev;
-            shapes[std::make_tuple(pass == 0 ? d.model : 0, d.Lx, d.Ly)].push_back(i);
+            int kind = pass == 0 ? kResPotts : kResGeneric;
+            if (d.model == SPINMC_ISING && pass == 0) kind = kResIsing16;
+            if (d.model == SPINMC_ISING && pass == 1 && d.W >= 8)
+                kind = d.W % 8 == 0 ? kResIsing8 : kResIsing8Any;
+            shapes[std::make_tuple(kind, d.Lx, d.Ly)].push_back(i);
         }
         for (auto& kv : shapes) {
             const HostRep& h = c->reps[kv.second[0]];
-            const int items = pass == 0 ? (h.dev.Ly / 2) * (h.dev.W / 16) : h.dev.Ly * h.dev.W;
-            // Ising chunks: their own table, at most two items a lane (of up to 1024)
-            const bool ising = pass == 0 && h.dev.model == SPINMC_ISING;
+            const int n = (int)kv.second.size();
+            const int plane = h.dev.Ly * h.dev.W;
+            int kind = std::get<0>(kv.first);
+            // row pairs of 16 columns share most; eight sites a lane give four
+            // times the waves
+            if (kind == kResIsing16 && plane <= 8 * 1024 &&
+                (int64_t)n * plane <= kIsing8MaxSites)
+                kind = kResIsing8;
+            const bool ising = kind >= kResIsing16;
+            const int items = kind == kResGeneric ? plane : kind >= kResIsing8 ? (plane + 7) / 8 : plane / 32;
             const size_t slot = (ising ? (size_t)4 * kIsingTabWords
                                        : align_up((size_t)8 * c->max_tab_n, 16)) +
-                                align_up(h.lat_bytes, 16);
-            const int n = (int)kv.second.size();
+                                align_up(kind >= kResIsing8 ? 2 * align_up((size_t)plane + 8, 8) : h.lat_bytes, 16);
             const int tcap = ising && c->sched.wg_threads == 0 ? 1024 : tmax;
             int P = 1;
             if (c->sched.rpb > 0) {
                 // forced packing: at most rpb, within the LDS budget, one
                 // wave per replica at least, and no more than the group holds
                 while (P * 2 <= c->sched.rpb && P * 2 <= kMaxRpb && P * 2 * 64 <= tmax &&
-                       (!ising || P * 2 * items <= 2048) &&
+                       (kind != kResIsing16 || P * 2 * items <= 2048) &&
                        (size_t)(P * 2) * slot <= kResidentLdsBudget && P * 2 <= n)
                     P *= 2;
             } else {
@@ -1633,9 +1646,8 @@ int prepare(spinmc_ctx* c, int mode) {
             // forced packing gives every replica a wave at least (64 P <= tmax)
             int threads = c->sched.rpb > 0 ? 64 * P : 64;
             while (threads < tcap && threads < P * items) threads *= 2;
-            while (ising && 2 * threads < P * items) threads *= 2;
-            c->res_groups.push_back({(int)buf.size(), n, P, threads, std::get<0>(kv.first), items,
-                                     pass == 0, slot});
+            while (kind == kResIsing16 && 2 * threads < P * items) threads *= 2;
+            c->res_groups.push_back({(int)buf.size(), n, P, threads, kind, items, slot});
             buf.insert(buf.end(), kv.second.begin(), kv.second.end());
         }
     }
@@ -1657,11 +1669,9 @@ int prepare(spinmc_ctx* c, int mode) {
         e = hipMemcpy(c->d_tiles, tiles.data(), sizeof(TileDev) * tiles.size(),
                       hipMemcpyHostToDevice);
     c->n_tiles = (int)tiles.size();
-    if (e == hipSuccess && !buf.empty()) {
-        size_t lds = 0;
-        for (const auto& g : c->res_groups) lds = std::max(lds, g.slot * g.rpb);
-        e = resident_reserve_lds(lds);
-    }
+    for (const auto& g : c->res_groups)
+        if (e == hipSuccess)
+            e = resident_reserve_lds(g.kind, g.items, g.threads / g.rpb, g.slot * g.rpb);
     if (e != hipSuccess) return check_dev(c, e, "prepare schedule");
     c->persist = (c->sched.flags & SPINMC_SCHED_PERSIST) != 0 && mode != 1 && !tiles.empty();
     if (c->persist) {
@@ -1713,7 +1723,7 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
         a.rpb = g.rpb;
         a.res_slot_bytes = (int)g.slot;
         e = timed(c, SPINMC_K_RESIDENT, [&] {
-            return launch_resident(a, g.count, g.model, g.chunk, g.items, g.threads, g.slot * g.rpb, side);
+            return launch_resident(a, g.count, g.kind, g.items, g.threads, g.slot * g.rpb, side);
         }, side);
     }
     return e;

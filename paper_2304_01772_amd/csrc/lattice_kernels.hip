@@ -171,11 +171,13 @@ __device__ __forceinline__ void load_ising_table(const uint32_t* tab, const RepD
     }
 }
 
-// The ties of a chunk (bit j of tie: site j), decided by the low halves.
-__device__ __forceinline__ uint32_t ising_ties(uint32_t tie, const uint32_t* tab, uint32_t i0,
-                                            uint32_t i1, uint32_t i2, uint32_t i3, uint32_t kb,
-                                            uint32_t p, uint32_t rid, uint32_t k0, uint32_t k1) {
+// The ties of an item (bit j of tie: site j), decided by the low halves.
+template <int NW>
+__device__ __forceinline__ uint32_t ising_ties(uint32_t tie, const uint32_t* tab,
+                                               const uint32_t (&idx)[NW], uint32_t kb, uint32_t p,
+                                               uint32_t rid, uint32_t k0, uint32_t k1) {
     uint32_t acc = 0u;
+    const uint32_t i0 = idx[0], i1 = idx[1], i2 = idx[NW - 2], i3 = idx[NW - 1];
     while (tie != 0u) {
         const uint32_t j = (uint32_t)__builtin_ctz(tie);
         tie &= tie - 1u;
@@ -193,35 +195,33 @@ __device__ __forceinline__ uint32_t ising_ties(uint32_t tie, const uint32_t* tab
     return acc;
 }
 
-// The new own bytes nv of a 16-site chunk, within-colour index kb of its first
-// site, and the side neighbours sv.  par = (y + c) & 1, a constant at each call.
-// About 165 VALU slots a chunk, 108 of them the two Philox blocks; a lookup and
-// a 32-bit compare for every site took 213.
-__device__ __forceinline__ void ising_core(int par, const uint4& o, const uint4& m, const uint4& U,
-                                           const uint4& D, uint32_t e, uint32_t kb, uint32_t p,
+// The new own bytes nv of 4 NW sites, a whole number of Philox blocks from
+// within-colour index kb on; other plane's bytes at the same place mv, at the
+// side sv, above Uv and below Dv.
+// About 165 VALU slots for 16 sites, 108 of them the two Philox blocks; a lookup
+// and a 32-bit compare for every site took 213.
+template <int NW>
+__device__ __forceinline__ void ising_core(const uint32_t (&ov)[NW], const uint32_t (&mv)[NW],
+                                           const uint32_t (&sv)[NW], const uint32_t (&Uv)[NW],
+                                           const uint32_t (&Dv)[NW], uint32_t kb, uint32_t p,
                                            uint32_t rid, uint32_t k0, uint32_t k1,
-                                           const uint32_t* tab, uint32_t (&nv)[4],
-                                           uint32_t (&sv)[4]) {
-    const uint32_t ov[4] = {o.x, o.y, o.z, o.w};
-    const uint32_t mv[4] = {m.x, m.y, m.z, m.w};
-    const uint32_t Uv[4] = {U.x, U.y, U.z, U.w};
-    const uint32_t Dv[4] = {D.x, D.y, D.z, D.w};
-    side_bytes(par, mv, e, sv);
+                                           const uint32_t* tab, uint32_t (&nv)[NW]) {
     // class 9u + 3nx + ny per byte (< 18)
-    uint32_t idx[4];
+    uint32_t idx[NW];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < NW; ++k) {
         const uint32_t nx = mv[k] + sv[k];
         idx[k] = ((ov[k] << 3) + ov[k]) + ((nx << 1) + nx) + (Uv[k] + Dv[k]);
     }
-    uint32_t w[8];
-    philox4x32_10<0x80008000u>(kb >> 3, p, rid, kTagMain, k0, k1, &w[0]);
-    philox4x32_10<0x80008000u>((kb >> 3) + 1u, p, rid, kTagMain, k0, k1, &w[4]);
+    uint32_t w[2 * NW];
+#pragma unroll
+    for (int b = 0; b < NW / 2; ++b)
+        philox4x32_10<0x80008000u>((kb >> 3) + (uint32_t)b, p, rid, kTagMain, k0, k1, &w[4 * b]);
     const uint32_t base = (uint32_t)(uintptr_t)(lds_u32_t)tab;
-    s16x2_t d[8];
+    s16x2_t d[2 * NW];
     u16x2_t dmin = {0xFFFF, 0xFFFF};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 2 * NW; ++i) {
         const uint32_t at =
             __builtin_amdgcn_udot4(idx[i >> 1], (i & 1) ? 0x04480000u : 0x00000448u, base, false);
         const uint32_t T = *(lds_u32_t)(uintptr_t)at;
@@ -230,7 +230,7 @@ __device__ __forceinline__ void ising_core(int par, const uint4& o, const uint4&
         dmin = __builtin_elementwise_min(dmin, __builtin_bit_cast(u16x2_t, d[i]));
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < NW; ++k) {
         // v_perm_b32 selectors 8 .. 11: the signs of the four 16-bit halves
         const uint32_t f = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, d[2 * k + 1]),
                                                  __builtin_bit_cast(uint32_t, d[2 * k]), 0x0B0A0908u);
@@ -239,24 +239,24 @@ __device__ __forceinline__ void ising_core(int par, const uint4& o, const uint4&
     if (min((uint32_t)dmin.x, (uint32_t)dmin.y) == 0u) {
         uint32_t tie = 0u;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 2 * NW; ++i)
             tie |= (d[i].x == 0 ? 1u << (2 * i) : 0u) | (d[i].y == 0 ? 2u << (2 * i) : 0u);
-        const uint32_t acc =
-            ising_ties(tie, tab, idx[0], idx[1], idx[2], idx[3], kb, p, rid, k0, k1);
+        const uint32_t acc = ising_ties(tie, tab, idx, kb, p, rid, k0, k1);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) nv[j >> 2] ^= ((acc >> j) & 1u) << (8 * (j & 3));
+        for (int j = 0; j < 4 * NW; ++j) nv[j >> 2] ^= ((acc >> j) & 1u) << (8 * (j & 3));
     }
 }
 
-// Adds a chunk of a recorded sweep's colour-1 pass to byte-wise counts: up
+// Adds an item of a recorded sweep's colour-1 pass to byte-wise counts: up
 // spins of both colours, unequal horizontal and vertical bonds (every bond has
-// exactly one colour-1 end).  At most 8 a byte and call.
-__device__ __forceinline__ void ising_count(const uint32_t (&nv)[4], const uint32_t (&mv)[4],
-                                            const uint32_t (&sv)[4], const uint32_t (&Uv)[4],
-                                            const uint32_t (&Dv)[4], uint32_t& up, uint32_t& dx,
+// exactly one colour-1 end).  At most 2 NW a byte and call.
+template <int NW>
+__device__ __forceinline__ void ising_count(const uint32_t (&nv)[NW], const uint32_t (&mv)[NW],
+                                            const uint32_t (&sv)[NW], const uint32_t (&Uv)[NW],
+                                            const uint32_t (&Dv)[NW], uint32_t& up, uint32_t& dx,
                                             uint32_t& dy) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < NW; ++k) {
         up = nv[k] + mv[k] + up;
         dx = (nv[k] ^ mv[k]) + dx;
         dx = (nv[k] ^ sv[k]) + dx;
@@ -265,17 +265,26 @@ __device__ __forceinline__ void ising_count(const uint32_t (&nv)[4], const uint3
     }
 }
 
+__device__ __forceinline__ void arr(const uint4& v, uint32_t (&o)[4]) {
+    o[0] = v.x;
+    o[1] = v.y;
+    o[2] = v.z;
+    o[3] = v.w;
+}
+
 template <int PAR, bool REC, bool NT>
 __device__ __forceinline__ void ising_compute(const ChunkIn& in, uint8_t* own, uint32_t oo,
                                               uint32_t p, uint32_t rid, uint32_t k0, uint32_t k1,
                                               const uint32_t* tab, IsingAcc& acc) {
-    uint32_t nv[4], sv[4];
-    ising_core(PAR, in.o, in.m, in.U, in.D, in.e, oo, p, rid, k0, k1, tab, nv, sv);
+    uint32_t ov[4], mv[4], Uv[4], Dv[4], nv[4], sv[4];
+    arr(in.o, ov);
+    arr(in.m, mv);
+    arr(in.U, Uv);
+    arr(in.D, Dv);
+    side_bytes(PAR, mv, in.e, sv);
+    ising_core(ov, mv, sv, Uv, Dv, oo, p, rid, k0, k1, tab, nv);
     store_own<NT>(own + oo, nv[0], nv[1], nv[2], nv[3]);
     if (REC) {
-        const uint32_t mv[4] = {in.m.x, in.m.y, in.m.z, in.m.w};
-        const uint32_t Uv[4] = {in.U.x, in.U.y, in.U.z, in.U.w};
-        const uint32_t Dv[4] = {in.D.x, in.D.y, in.D.z, in.D.w};
         uint32_t up = 0u, dx = 0u, dy = 0u;
         ising_count(nv, mv, sv, Uv, Dv, up, dx, dy);
         acc.M += 2 * (int)sad_u8(up, 0u) - 32;
@@ -1048,18 +1057,6 @@ __global__ void __launch_bounds__(512) k_resident_generic(SweepArgs a) {
 // ------------------------------------------------ resident Ising chunks
 namespace {
 
-// Sum of v over groups of n lanes (a power of two up to 64, uniform).
-__device__ __forceinline__ int group_sum(int v, int n) {
-    // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
-    if (n > 1) v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
-    if (n > 2) v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
-    if (n > 4) v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
-    if (n > 8) v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
-    if (n > 16) v += __shfl_xor(v, 16, 64);
-    if (n > 32) v += __shfl_xor(v, 32, 64);
-    return v;
-}
-
 // The lanes of one replica meet: a barrier, or where a replica has at most a
 // wave's lanes only an order of its LDS accesses (a wave's are served in order).
 __device__ __forceinline__ void replica_sync(bool waves) {
@@ -1071,12 +1068,68 @@ __device__ __forceinline__ void replica_sync(bool waves) {
     }
 }
 
-__device__ __forceinline__ void arr(const uint4& v, uint32_t (&o)[4]) {
-    o[0] = v.x;
-    o[1] = v.y;
-    o[2] = v.z;
-    o[3] = v.w;
-}
+// Recorded sweeps of a replica: its lanes add their counts in LDS, kRecRows rows
+// at a time, so that no sweep waits for a reduction or for global memory.
+constexpr int kRecRows = 32;
+struct RecRows {
+    int (*l)[3];         // this replica's kRecRows x 3 counts in LDS
+    int next, every;     // sweeps to the next recorded one
+    int row0, n;         // first row and number of rows in LDS
+    __device__ __forceinline__ void start(int (*lds)[3], const SweepArgs& a) {
+        l = lds;
+        every = a.record_every;
+        next = every > 0 ? every - a.sweep_off % every : 0;
+        row0 = every > 0 ? a.sweep_off / every : 0;
+        n = 0;
+    }
+    // true at a recorded sweep
+    __device__ __forceinline__ bool due() {
+        if (every <= 0 || --next > 0) return false;
+        next = every;
+        return true;
+    }
+    // byte-wise counts; sums of 16 lanes (or of the nt < 16
+    // lanes of a replica) by data-parallel-primitive moves, then LDS atomics
+    __device__ __forceinline__ void add(uint32_t up, uint32_t dx, uint32_t dy, int nt) {
+        int u = (int)sad_u8(up, 0u), b = (int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16));
+        // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
+        if (nt > 1) {
+            u += __builtin_amdgcn_update_dpp(0, u, 0xB1, 0xf, 0xf, true);
+            b += __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xf, 0xf, true);
+        }
+        if (nt > 2) {
+            u += __builtin_amdgcn_update_dpp(0, u, 0x4E, 0xf, 0xf, true);
+            b += __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xf, 0xf, true);
+        }
+        if (nt > 4) {
+            u += __builtin_amdgcn_update_dpp(0, u, 0x141, 0xf, 0xf, true);
+            b += __builtin_amdgcn_update_dpp(0, b, 0x141, 0xf, 0xf, true);
+        }
+        if (nt > 8) {
+            u += __builtin_amdgcn_update_dpp(0, u, 0x140, 0xf, 0xf, true);
+            b += __builtin_amdgcn_update_dpp(0, b, 0x140, 0xf, 0xf, true);
+        }
+        if (((int)threadIdx.x & (min(nt, 16) - 1)) == 0) {
+            atomicAdd(&l[n][0], u);
+            atomicAdd(&l[n][1], b & 0xFFFF);
+            atomicAdd(&l[n][2], (int)((uint32_t)b >> 16));
+        }
+    }
+    // stores and clears the rows; the replica's lanes meet before and after
+    __device__ __forceinline__ void flush(const SweepArgs& a, int rep, int N, bool active, int lt,
+                                          int nt) {
+        if (active)
+            for (int i = lt; i < n * a.width; i += nt) {
+                const int r = i / a.width, k = i - r * a.width;
+                const int v = k < 3 ? l[r][k] : 0;
+                a.stats[((size_t)(row0 + r) * a.R + rep) * a.width + k] =
+                    k == 0 ? 2 * v - N : (k < 3 ? N - 2 * v : 0);
+                if (k < 3) l[r][k] = 0;
+            }
+        row0 += n;
+        n = 0;
+    }
+};
 
 }  // namespace
 
@@ -1096,7 +1149,7 @@ template <int NI, bool UNI>
 __global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
     // dynamic LDS: rpb slots of [thresholds (kIsingTabWords) | plane 0 | plane 1]
     extern __shared__ __align__(16) uint8_t dyn[];
-    __shared__ int lsum[kMaxRpb][3];  // per-slot counts of a recorded sweep
+    __shared__ int lrec[kMaxRpb][kRecRows][3];  // counts of recorded sweeps
     const int P = a.rpb;
     const int nt = blockDim.x / P;
     int g = threadIdx.x / nt;
@@ -1140,14 +1193,16 @@ __global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
                 }
         }
     }
-    if (threadIdx.x < 3 * kMaxRpb) (&lsum[0][0])[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < 3 * kRecRows * P; i += blockDim.x) (&lrec[0][0][0])[i] = 0;
     __syncthreads();
     const bool waves = nt > 64;
-    const uint64_t t0 = *a.t_base;
+    RecRows rr;
+    rr.start(lrec[g], a);
+    const uint64_t t0 = *a.t_base + (uint64_t)a.sweep_off;
     for (int i = 0; i < a.n_sweeps; ++i) {
-        const int sw = a.sweep_off + i;  // sweep index within the call
-        const uint64_t t = t0 + (uint64_t)sw;
-        const bool rec = a.record_every > 0 && ((sw + 1) % a.record_every) == 0;
+        const uint64_t t = t0 + (uint64_t)i;
+        const bool rec = rr.due();
+        uint32_t up = 0u, dx = 0u, dy = 0u;  // this lane's counts of a recorded sweep
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
@@ -1163,70 +1218,37 @@ __global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
                     *reinterpret_cast<const uint32_t*>(oth + (c == 0 ? le[k] : re[k]));
                 const uint32_t e1 =
                     *reinterpret_cast<const uint32_t*>(oth + W + (c == 0 ? re[k] : le[k]));
-                uint32_t nv[4], sv[4];
-                ising_core(c, V[c][0][k], V[1 - c][0][k], U, V[1 - c][1][k], e0, oo[k], p, rid,
-                              a.key0, a.key1, tab, nv, sv);
+                uint32_t o0[4], o1[4], m0[4], m1[4], Uv[4], Dv[4], nv[4], sv[4];
+                arr(V[c][0][k], o0);
+                arr(V[c][1][k], o1);
+                arr(V[1 - c][0][k], m0);
+                arr(V[1 - c][1][k], m1);
+                arr(U, Uv);
+                arr(D, Dv);
+                side_bytes(c, m0, e0, sv);
+                ising_core(o0, m0, sv, Uv, m1, oo[k], p, rid, a.key0, a.key1, tab, nv);
+                if (c == 1 && rec) ising_count(nv, m0, sv, Uv, m1, up, dx, dy);
                 V[c][0][k] = make_uint4(nv[0], nv[1], nv[2], nv[3]);
                 *reinterpret_cast<uint4*>(own + oo[k]) = V[c][0][k];
-                ising_core(1 - c, V[c][1][k], V[1 - c][1][k], V[1 - c][0][k], D, e1,
-                                  oo[k] + (uint32_t)W, p, rid, a.key0, a.key1, tab, nv, sv);
+                side_bytes(1 - c, m1, e1, sv);
+                ising_core(o1, m1, sv, m0, Dv, oo[k] + (uint32_t)W, p, rid, a.key0, a.key1, tab,
+                           nv);
+                if (c == 1 && rec) ising_count(nv, m1, sv, m0, Dv, up, dx, dy);
                 V[c][1][k] = make_uint4(nv[0], nv[1], nv[2], nv[3]);
                 *reinterpret_cast<uint4*>(own + oo[k] + W) = V[c][1][k];
             }
             if (c == 0) replica_sync(waves);
         }
         if (rec) {
-            // colour 1 just written, colour 0 (in LDS) before the next pass writes it
-            uint32_t up = 0u, dx = 0u, dy = 0u;
-#pragma unroll
-            for (int k = 0; k < NI; ++k) {
-                if (lt + k * nt >= n_items) continue;
-                uint32_t nv[2][4], mv[2][4], sv[4], Uv[4], Dv[4];
-                arr(V[1][0][k], nv[0]);
-                arr(V[1][1][k], nv[1]);
-                arr(V[0][0][k], mv[0]);
-                arr(V[0][1][k], mv[1]);
-                arr(*reinterpret_cast<const uint4*>(lds + uo[k]), Uv);
-                arr(*reinterpret_cast<const uint4*>(lds + dof[k]), Dv);
-                side_bytes(1, mv[0], *reinterpret_cast<const uint32_t*>(lds + re[k]), sv);
-                ising_count(nv[0], mv[0], sv, Uv, mv[1], up, dx, dy);
-                side_bytes(0, mv[1], *reinterpret_cast<const uint32_t*>(lds + W + le[k]), sv);
-                ising_count(nv[1], mv[1], sv, mv[0], Dv, up, dx, dy);
+            rr.add(up, dx, dy, nt);  // at most 16 NI a byte
+            if (++rr.n == kRecRows) {
+                replica_sync(waves);
+                rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
             }
-            // at most 16 NI a byte, 8192 a wave: the bonds in one word
-            const int n = nt < 64 ? nt : 64;
-            const int su = group_sum((int)sad_u8(up, 0u), n);
-            const int sb = group_sum((int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16)), n);
-            int cu = su, cx = sb & 0xFFFF, cy = (int)((uint32_t)sb >> 16);
-            if (waves) {
-                if ((lt & 63) == 0) {
-                    atomicAdd(&lsum[g][0], cu);
-                    atomicAdd(&lsum[g][1], cx);
-                    atomicAdd(&lsum[g][2], cy);
-                }
-                __syncthreads();
-                if (lt == 0) {  // cleared for the next row, a barrier away
-                    cu = lsum[g][0];
-                    cx = lsum[g][1];
-                    cy = lsum[g][2];
-                    lsum[g][0] = lsum[g][1] = lsum[g][2] = 0;
-                }
-            } else {
-                replica_sync(false);
-            }
-            if (active && lt == 0) {
-                const int N = 2 * (int)plane;
-                int32_t* row =
-                    a.stats + ((size_t)((sw + 1) / a.record_every - 1) * a.R + rep) * a.width;
-                row[0] = 2 * cu - N;
-                row[1] = N - 2 * cx;
-                row[2] = N - 2 * cy;
-                for (int k = 3; k < a.width; ++k) row[k] = 0;
-            }
-        } else {
-            replica_sync(waves);
         }
+        replica_sync(waves);
     }
+    rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
 #pragma unroll
     for (int k = 0; k < NI; ++k)
         if (lt + k * nt < n_items)
@@ -1236,6 +1258,249 @@ __global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
                 for (int o = 0; o < 2; ++o)
                     *reinterpret_cast<uint4*>(gmem + c * plane + oo[k] + (uint32_t)(o * W)) =
                         V[c][o][k];
+}
+
+namespace {
+
+// Eight consecutive sites of a plane, one Philox block, from byte k on.  With AL
+// (W a multiple of 8) they lie in one row; without, they may run on into the
+// next one (W >= 9): e is the byte that ends a row, s the byte that starts one.
+// Offsets wrap around the plane; a plane's first 8 bytes are repeated behind it.
+// The last item may hold fewer sites (Ly W is even): its further bytes are 0 or 1,
+// updated like the others, never stored or counted.
+template <bool AL>
+struct Item8 {
+    uint32_t k, uo, dof;   // this item, the sites above and below
+    uint32_t lo, hi;       // AL: halo dwords left and right; else: bytes ending the row that
+                           // starts here and starting the row that ends here
+    uint32_t left[2];      // bytes whose side neighbour is the left one in colour 0
+    uint32_t end[2], start[2];  // !AL: the bytes e and s
+    __device__ __forceinline__ void init(uint32_t item, uint32_t W, uint32_t plane) {
+        k = 8u * item;
+        const uint32_t y = k / W, j = k - y * W, row = k - j;
+        uo = k < W ? k + plane - W : k - W;
+        dof = k + W >= plane ? k + W - plane : k + W;
+        if (AL) {
+            left[0] = (y & 1u) ? 0u : ~0u;
+            lo = row + (j == 0u ? W : j) - 4u;
+            hi = row + (j + 8u == W ? 0u : j + 8u);
+        } else {
+            const uint32_t b = W - j;  // bytes of row y from here on
+            const uint64_t first = b >= 8u ? ~0ull : (1ull << (8u * b)) - 1ull;
+            const uint64_t lm = (y & 1u) ? ~first : first;
+            const uint64_t em = b <= 8u ? 0xFFull << (8u * (b - 1u)) : 0ull;
+            const uint64_t sm = j == 0u ? 0xFFull : (b < 8u ? 0xFFull << (8u * b) : 0ull);
+            left[0] = (uint32_t)lm;
+            left[1] = (uint32_t)(lm >> 32);
+            end[0] = (uint32_t)em;
+            end[1] = (uint32_t)(em >> 32);
+            start[0] = (uint32_t)sm;
+            start[1] = (uint32_t)(sm >> 32);
+            hi = row;
+            lo = j == 0u ? row + W - 1u : (b < 8u ? row + 2u * W - 1u : row);
+        }
+    }
+};
+
+__device__ __forceinline__ uint32_t lds32(const uint8_t* p) {
+    return *reinterpret_cast<const uint32_t*>(p);
+}
+
+// The first n bytes (even, at most 8) of v to a 2-byte aligned place.
+__device__ __forceinline__ void put_bytes(uint8_t* p, const uint2& v, uint32_t n) {
+    uint16_t* q = reinterpret_cast<uint16_t*>(p);
+    if (n > 0u) q[0] = (uint16_t)v.x;
+    if (n > 2u) q[1] = (uint16_t)(v.x >> 16);
+    if (n > 4u) q[2] = (uint16_t)v.y;
+    if (n > 6u) q[3] = (uint16_t)(v.y >> 16);
+}
+
+// A plane in LDS: stores an item (and, for item 0, the repeat behind the plane).
+template <bool AL>
+__device__ __forceinline__ void store8(uint8_t* own, uint32_t k, uint32_t plane, const uint2& v) {
+    if (AL || (plane & 7u) == 0u) {
+        *reinterpret_cast<uint2*>(own + k) = v;
+        if (!AL && k == 0u) *reinterpret_cast<uint2*>(own + plane) = v;
+    } else {
+        if (k + 8u <= plane)
+            *reinterpret_cast<uint2*>(own + k) = v;
+        else
+            put_bytes(own + k, v, plane - k);
+        if (k == 0u) put_bytes(own + plane, v, 8u);
+    }
+}
+
+// The other plane's neighbours of an item in colour c: side, above, below.
+template <bool AL>
+__device__ __forceinline__ void near8(const Item8<AL>& t, const uint8_t* oth, int c,
+                                      const uint32_t (&m)[2], uint32_t (&sv)[2],
+                                      uint32_t (&Uv)[2], uint32_t (&Dv)[2]) {
+    if (AL) {
+        const uint2 U = *reinterpret_cast<const uint2*>(oth + t.uo);
+        const uint2 D = *reinterpret_cast<const uint2*>(oth + t.dof);
+        const bool lf = (t.left[0] != 0u) == (c == 0);
+        const uint32_t h = lds32(oth + (lf ? t.lo : t.hi));
+        const uint32_t a0 = lf ? h : m[0], a1 = lf ? m[0] : m[1], a2 = lf ? m[1] : h;
+        const uint32_t sh = lf ? 3u : 1u;
+        sv[0] = __builtin_amdgcn_alignbyte(a1, a0, sh);
+        sv[1] = __builtin_amdgcn_alignbyte(a2, a1, sh);
+        Uv[0] = U.x;
+        Uv[1] = U.y;
+        Dv[0] = D.x;
+        Dv[1] = D.y;
+    } else {
+        const uint8_t* u = oth + (t.uo & ~3u);
+        const uint8_t* d = oth + (t.dof & ~3u);
+        const uint32_t u0 = lds32(u), u1 = lds32(u + 4), u2 = lds32(u + 8);
+        const uint32_t d0 = lds32(d), d1 = lds32(d + 4), d2 = lds32(d + 8);
+        const uint32_t pv = lds32(oth + (t.k == 0u ? 0u : t.k - 4u)), nx = lds32(oth + t.k + 8u);
+        const uint32_t eb = oth[t.hi] * 0x01010101u, sb = oth[t.lo] * 0x01010101u;
+        Uv[0] = __builtin_amdgcn_alignbyte(u1, u0, t.uo);
+        Uv[1] = __builtin_amdgcn_alignbyte(u2, u1, t.uo);
+        Dv[0] = __builtin_amdgcn_alignbyte(d1, d0, t.dof);
+        Dv[1] = __builtin_amdgcn_alignbyte(d2, d1, t.dof);
+        const uint32_t L[2] = {__builtin_amdgcn_alignbyte(m[0], pv, 3),
+                               __builtin_amdgcn_alignbyte(m[1], m[0], 3)};
+        const uint32_t R[2] = {__builtin_amdgcn_alignbyte(m[1], m[0], 1),
+                               __builtin_amdgcn_alignbyte(nx, m[1], 1)};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t lf = c == 0 ? t.left[i] : ~t.left[i];
+            const uint32_t fe = t.end[i] & ~lf, fs = t.start[i] & lf;
+            uint32_t v = (lf & L[i]) | (~lf & R[i]);
+            v = (fe & eb) | (~fe & v);
+            sv[i] = (fs & sb) | (~fs & v);
+        }
+    }
+}
+
+}  // namespace
+
+// The resident kernel for items of eight sites: a lane takes one Philox block a
+// pass instead of four, so a small lattice spreads over four times as many lanes
+// and a pass is a quarter of the chain of instructions.  It serves lattices
+// whose waves leave the chip idle (one 32 x 32 lattice, recorded: 1.1 us a sweep
+// against 2.7) and, without AL, every other width from 18 on (k_resident_generic
+// draws a block for every site: 100 lattices of 300 x 300, 20 sweeps and the
+// gradients 2064 us, now 405).
+// ONE: at most one item a lane, its offsets and both planes' bytes in registers;
+// else a lane's items are worked out in every pass.
+template <bool AL, bool ONE, bool UNI>
+__global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
+    // dynamic LDS: rpb slots of [thresholds (kIsingTabWords) | plane 0 and its repeat |
+    // plane 1 and its repeat], each plane in whole 8 bytes
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ int lrec[kMaxRpb][kRecRows][3];
+    const int P = a.rpb;
+    const int nt = blockDim.x / P;
+    int g = threadIdx.x / nt;
+    const int lt = threadIdx.x - g * nt;
+    if (UNI) g = __builtin_amdgcn_readfirstlane(g);
+    const int first = blockIdx.x * P;
+    const bool active = first + g < a.n_list;
+    const int rep = a.rep_list[active ? first + g : first];
+    const RepDev& R = a.reps[rep];
+    const uint32_t W = (uint32_t)R.W, plane = (uint32_t)R.Ly * W, rid = R.rid;
+    const uint32_t stride = (plane + 15u) & ~7u;
+    uint8_t* slot = dyn + (size_t)(active ? g : 0) * a.res_slot_bytes;
+    uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
+    uint8_t* lds = slot + 4 * kIsingTabWords;
+    uint8_t* gmem = a.lat + R.lat_off;
+    const uint32_t n_items = active ? (plane + 7u) >> 3 : 0u;
+    if (active) load_ising_table(a.tab, R, tab, lt, nt);
+    if (AL || (plane & 7u) == 0u) {
+        for (uint32_t i = lt; i < n_items; i += (uint32_t)nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                store8<AL>(lds + c * stride, 8u * i, plane,
+                           *reinterpret_cast<const uint2*>(gmem + c * plane + 8u * i));
+    } else if (active) {  // with the repeated bytes
+        for (uint32_t i = lt; i < plane + 8u; i += (uint32_t)nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                lds[c * stride + i] = gmem[c * plane + (i < plane ? i : i - plane)];
+    }
+    Item8<AL> it1;
+    uint2 V[2];
+    const bool own1 = (uint32_t)lt < n_items;
+    __syncthreads();
+    if (ONE) {
+        it1.init(own1 ? (uint32_t)lt : 0u, W, plane);
+#pragma unroll
+        for (uint32_t c = 0; c < 2u; ++c)
+            if (own1) V[c] = *reinterpret_cast<const uint2*>(lds + c * stride + it1.k);
+    }
+    for (int i = threadIdx.x; i < 3 * kRecRows * P; i += blockDim.x) (&lrec[0][0][0])[i] = 0;
+    __syncthreads();
+    const bool waves = nt > 64;
+    RecRows rr;
+    rr.start(lrec[g], a);
+    const uint64_t t0 = *a.t_base + (uint64_t)a.sweep_off;
+    for (int sw = 0; sw < a.n_sweeps; ++sw) {
+        const uint64_t t = t0 + (uint64_t)sw;
+        const bool rec = rr.due();
+        uint32_t up = 0u, dx = 0u, dy = 0u;  // this lane's counts of a recorded sweep
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
+            uint8_t* own = lds + (uint32_t)c * stride;
+            const uint8_t* oth = lds + (uint32_t)(1 - c) * stride;
+            auto pass = [&](const Item8<AL>& q, uint2& o, const uint2& m2) {
+                const uint32_t ov[2] = {o.x, o.y};
+                uint32_t m[2] = {m2.x, m2.y}, sv[2], Uv[2], Dv[2], nv[2];
+                near8<AL>(q, oth, c, m, sv, Uv, Dv);
+                ising_core(ov, m, sv, Uv, Dv, q.k, p, rid, a.key0, a.key1, tab, nv);
+                o = make_uint2(nv[0], nv[1]);
+                store8<AL>(own, q.k, plane, o);
+                if (c == 1 && rec) {
+                    if (!AL && q.k + 8u > plane) {
+                        const uint64_t in = (1ull << (8u * (plane - q.k))) - 1ull;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const uint32_t w = (uint32_t)(in >> (32 * i));
+                            nv[i] &= w;
+                            m[i] &= w;
+                            sv[i] &= w;
+                            Uv[i] &= w;
+                            Dv[i] &= w;
+                        }
+                    }
+                    ising_count(nv, m, sv, Uv, Dv, up, dx, dy);
+                }
+            };
+            if (ONE) {
+                if (own1) pass(it1, V[c], V[1 - c]);
+            } else {
+                for (uint32_t i = lt; i < n_items; i += (uint32_t)nt) {
+                    Item8<AL> q;
+                    q.init(i, W, plane);
+                    uint2 o = *reinterpret_cast<const uint2*>(own + q.k);
+                    pass(q, o, *reinterpret_cast<const uint2*>(oth + q.k));
+                }
+            }
+            if (c == 0) replica_sync(waves);
+        }
+        if (rec) {  // at most 4 a byte and item
+            rr.add(up, dx, dy, nt);
+            if (++rr.n == kRecRows) {
+                replica_sync(waves);
+                rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
+            }
+        }
+        replica_sync(waves);
+    }
+    rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
+    if (AL || (plane & 7u) == 0u) {
+        for (uint32_t i = lt; i < n_items; i += (uint32_t)nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                *reinterpret_cast<uint2*>(gmem + c * plane + 8u * i) =
+                    *reinterpret_cast<const uint2*>(lds + c * stride + 8u * i);
+    } else if (active) {
+        for (uint32_t i = lt; i < plane; i += (uint32_t)nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c) gmem[c * plane + i] = lds[c * stride + i];
+    }
 }
 
 __global__ void __launch_bounds__(512) k_resident_potts(SweepArgs a) {
@@ -1343,36 +1608,45 @@ hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* 
     return hipGetLastError();
 }
 
-hipError_t resident_reserve_lds(size_t lds_bytes) {
-    const void* fns[] = {(const void*)k_resident_generic, (const void*)k_resident_potts,
-                         (const void*)k_resident_ising<1, false>,
-                         (const void*)k_resident_ising<2, false>,
-                         (const void*)k_resident_ising<1, true>,
-                         (const void*)k_resident_ising<2, true>};
-    hipError_t e = hipSuccess;
-    for (const void* f : fns)
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    return e;
+namespace {
+template <bool AL>
+const void* ising8_fn(bool one, bool uni) {
+    return one ? (uni ? (const void*)k_resident_ising8<AL, true, true>
+                      : (const void*)k_resident_ising8<AL, true, false>)
+               : (uni ? (const void*)k_resident_ising8<AL, false, true>
+                      : (const void*)k_resident_ising8<AL, false, false>);
 }
 
-hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int items,
-                           int threads, size_t lds_bytes, hipStream_t s) {
-    if (n_list <= 0) return hipSuccess;
-    const dim3 g((n_list + a.rpb - 1) / a.rpb), b(threads);
-    if (!chunk) {
-        hipLaunchKernelGGL(k_resident_generic, g, b, lds_bytes, s, a);
-    } else if (model == kModelIsing) {
-        const int nt = threads / a.rpb;
-        if (items > 2 * nt) return hipErrorInvalidValue;
-        auto* k = nt % 64 == 0 ? (items > nt ? k_resident_ising<2, true> : k_resident_ising<1, true>)
-                               : (items > nt ? k_resident_ising<2, false>
-                                             : k_resident_ising<1, false>);
-        hipLaunchKernelGGL(k, g, b, lds_bytes, s, a);
-    } else {
-        hipLaunchKernelGGL(k_resident_potts, g, b, lds_bytes, s, a);
+const void* resident_fn(int kind, int items, int nt) {
+    const bool uni = nt % 64 == 0;
+    switch (kind) {
+        case kResIsing16:
+            return items > nt ? (uni ? (const void*)k_resident_ising<2, true>
+                                     : (const void*)k_resident_ising<2, false>)
+                              : (uni ? (const void*)k_resident_ising<1, true>
+                                     : (const void*)k_resident_ising<1, false>);
+        case kResIsing8: return ising8_fn<true>(items <= nt, uni);
+        case kResIsing8Any: return ising8_fn<false>(items <= nt, uni);
+        case kResPotts: return (const void*)k_resident_potts;
+        default: return (const void*)k_resident_generic;
     }
-    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t resident_reserve_lds(int kind, int items, int nt, size_t lds_bytes) {
+    return hipFuncSetAttribute(resident_fn(kind, items, nt),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+}
+
+hipError_t launch_resident(const SweepArgs& a, int n_list, int kind, int items, int threads,
+                           size_t lds_bytes, hipStream_t s) {
+    if (n_list <= 0) return hipSuccess;
+    const int nt = threads / a.rpb;
+    if (kind == kResIsing16 && items > 2 * nt) return hipErrorInvalidValue;
+    SweepArgs b = a;
+    void* args[] = {&b};
+    return hipLaunchKernel(resident_fn(kind, items, nt), dim3((n_list + a.rpb - 1) / a.rpb),
+                           dim3(threads), args, lds_bytes, s);
 }
 
 hipError_t launch_stream_pass(const SweepArgs& a, int model, int tile0, int n_tiles, int c,

@@ -23,10 +23,14 @@ constexpr int kMaxPottsQ = 128;   // labels fit in 7 bits (SWAR equality test)
 constexpr int kMaxCpmTypes = 4;
 constexpr int kMaxRpb = 16;       // replicas per resident workgroup
 
-// Paths of the resident kernel of Potts chunks and sites: per-site (any model or
-// width), Potts chunks.
-constexpr int kResGeneric = 0;
-constexpr int kResPotts = 1;
+// Resident kernels of the lattice models.
+enum {
+    kResGeneric = 0,    // per site: any model or width
+    kResPotts = 1,      // Potts chunks of 16 sites (W % 16 == 0)
+    kResIsing16 = 2,    // Ising, row pairs of 16 columns a lane (W % 16 == 0)
+    kResIsing8 = 3,     // Ising, 8 sites a lane (W % 8 == 0)
+    kResIsing8Any = 4,  // Ising, 8 sites a lane (W >= 9)
+};
 
 // Per-replica record, device visible.
 struct RepDev {
@@ -119,13 +123,14 @@ struct SweepArgs {
 // Host-side launchers implemented in the kernel translation units.
 hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* lat,
                        uint32_t key0, uint32_t key1, int threads, hipStream_t s);
-// Resident groups: chunk groups hold replicas of one model (model selects
-// the path); per-site groups may mix models.  items: row pairs of 16 columns
-// of a replica (chunk groups); Ising needs at most two a lane.
-hipError_t launch_resident(const SweepArgs& a, int n_list, int model, bool chunk, int items,
-                           int threads, size_t lds_bytes, hipStream_t s);
-// Allow the resident kernels up to lds_bytes of dynamic LDS (call outside capture).
-hipError_t resident_reserve_lds(size_t lds_bytes);
+// Resident groups: replicas of one shape (and, except kResGeneric, of one
+// model).  items: the lanes' units of a replica (row pairs of 16 columns, 8
+// sites or sites); kResIsing16 takes at most two a lane.
+hipError_t launch_resident(const SweepArgs& a, int n_list, int kind, int items, int threads,
+                           size_t lds_bytes, hipStream_t s);
+// Allow a group's kernel (nt lanes a replica) up to lds_bytes of dynamic LDS
+// (call outside capture).
+hipError_t resident_reserve_lds(int kind, int items, int nt, size_t lds_bytes);
 // nt: own-plane loads and stores nontemporal (lattice sets beyond the cache)
 hipError_t launch_stream_pass(const SweepArgs& a, int model, int tile0, int n_tiles, int c,
                               int sweep_off, int rec_row, int threads, size_t lds_tab_bytes,

@@ -553,3 +553,29 @@ def test_ising_resident_at_its_limits(S, Lx, Ly, R, sched):
         assert np.array_equal(smp.get_state(r), a), r
         assert np.array_equal(st[:, r, :], want), r
     smp.close()
+
+
+@pytest.mark.parametrize("Lx,Ly,R", [
+    (18, 2, 3), (18, 10, 2),     # the narrowest rows, a last item of two sites
+    (30, 4, 2), (22, 14, 2),     # last items of four and two sites
+    (20, 20, 5), (26, 24, 2),    # whole items that run on into the next row
+    (16, 2, 1), (48, 20, 2),     # items within rows (8 and 24 bytes)
+    (128, 128, 3),               # 1024 lanes
+    (18, 4, 4099), (32, 8, 2050),  # several replicas a wave
+    (300, 300, 1), (362, 362, 1),  # several items a lane; the largest, ragged
+    (16, 8192, 1),               # eight items within rows a lane
+])
+def test_ising_eight_sites_a_lane(S, Lx, Ly, R):
+    seed, h = 33, _f32(0.02)
+    reps = [dict(model=0, Lx=Lx, Ly=Ly, Jx=1.0, Jy=0.8, h=h, beta=0.45, rid=r) for r in range(R)]
+    reps.append(dict(model=1, Lx=Lx if Lx < 300 else 20, Ly=Ly if Ly < 300 else 20, q=3, Jx=1.0,
+                     Jy=1.0, h=0.0, beta=0.9, rid=R))  # the same shape, another kernel
+    smp = S(reps, seed, init=True)
+    smp.sweep(3)
+    st = smp.sweep(70, 2).cpu().numpy()  # more rows than gather in LDS
+    for r in sorted({0, R // 2, R - 1}):
+        a, _ = orc.ising_run(orc.ising_init(Lx, Ly, seed, r), 1.0, 0.8, h, 0.45, seed, r, 0, 3, 0)
+        a, want = orc.ising_run(a, 1.0, 0.8, h, 0.45, seed, r, 3, 70, 2)
+        assert np.array_equal(smp.get_state(r), a), r
+        assert np.array_equal(st[:, r, :], want), r
+    smp.close()
