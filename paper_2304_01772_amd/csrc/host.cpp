@@ -1705,18 +1705,23 @@ SweepArgs sweep_args(spinmc_ctx* c, int n, int re, int32_t* stats) {
 
 int ensure_side_streams(spinmc_ctx* c);
 
+// A single resident group with nothing streamed beside it needs no fork (the
+// events cost a short call about 15 us).
+bool resident_alone(const spinmc_ctx* c) { return c->res_groups.size() == 1 && c->n_tiles == 0; }
+
 // Resident kernels for the call's sweeps: each group on its own side stream,
 // forked from and joined back into stream s (so they overlap one another and
 // whatever s runs meanwhile).  With join = false the caller joins later via
 // join_resident.
 hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
     if (c->res_groups.empty()) return hipSuccess;
-    if (ensure_side_streams(c) != SPINMC_OK) return hipErrorOutOfMemory;
-    hipError_t e = hipEventRecord(c->cap_ev[0], s);
+    const bool alone = resident_alone(c);
+    if (!alone && ensure_side_streams(c) != SPINMC_OK) return hipErrorOutOfMemory;
+    hipError_t e = alone ? hipSuccess : hipEventRecord(c->cap_ev[0], s);
     for (size_t k = 0; k < c->res_groups.size() && e == hipSuccess; ++k) {
         const auto& g = c->res_groups[k];
-        hipStream_t side = c->cap[1 + k % kSide];
-        if (k < (size_t)kSide) e = hipStreamWaitEvent(side, c->cap_ev[0], 0);
+        hipStream_t side = alone ? s : c->cap[1 + k % kSide];
+        if (!alone && k < (size_t)kSide) e = hipStreamWaitEvent(side, c->cap_ev[0], 0);
         if (e != hipSuccess) break;
         a.rep_list = c->d_lists + c->off_res_chunk + g.off;
         a.n_list = g.count;
@@ -1731,6 +1736,7 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
 
 hipError_t join_resident(spinmc_ctx* c, hipStream_t s) {
     hipError_t e = hipSuccess;
+    if (resident_alone(c)) return e;
     const size_t used = std::min(c->res_groups.size(), (size_t)kSide);
     for (size_t k = 0; k < used && e == hipSuccess; ++k) {
         e = hipEventRecord(c->cap_ev[1 + k], c->cap[1 + k]);
@@ -1842,15 +1848,16 @@ int enqueue_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     int rc = prepare(c, mode);
     if (rc) return rc;
     hipError_t e = hipSuccess;
-    // Unrecorded, untimed calls replay cached graphs of whole chunks.  When
+    // Unrecorded, untimed calls with streamed passes replay cached graphs of
+    // whole chunks (resident groups alone are one launch each).  When
     // both resident groups and streamed tiles exist, the resident kernels
     // run outside the graphs, one launch per group for all n sweeps on side
     // streams forked from the call's stream (their start counter copied to
     // d_t[1] first, since the graphs advance d_t[0] meanwhile), so that they
     // overlap the streamed graph replays for the whole call rather than
     // meeting them at every chunk boundary.
-    if (re == 0 && !c->prof && c->use_graphs) {
-        const bool split = c->n_tiles > 0 && !c->res_groups.empty();
+    if (re == 0 && !c->prof && c->use_graphs && c->n_tiles > 0) {
+        const bool split = !c->res_groups.empty();
         const int G = std::min(n, kGraphChunk);
         const int full = n / G, rest = n - full * G;
         hipGraphExec_t ex = nullptr, ex_rest = nullptr;
