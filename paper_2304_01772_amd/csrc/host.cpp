@@ -108,6 +108,7 @@ struct HostRep {
     RepDev dev{};
     bool chunk = false;     // W % 16 == 0: 16-byte SWAR path
     bool resident = false;  // fits the resident kernel's LDS
+    int slab_rows = 0, slab_halo = 0;  // resident in slabs of rows (0: not), set by plan_slabs
     size_t lat_bytes = 0;
 };
 
@@ -156,8 +157,15 @@ struct spinmc_ctx {
     struct ResGroup {
         int off, count, rpb, threads, kind, items;
         size_t slot;
+        bool whole;  // fits a workgroup whole
+        // slabs of rows (0: whole lattices only): tiles d_slabs[slab0 ..], halo rows
+        // either side, items and lanes of a workgroup and dynamic LDS
+        int n_slabs, slab0, halo, slab_items, slab_threads;
+        size_t slab_lds;
     };
     std::vector<ResGroup> res_groups;
+    TileDev* d_slabs = nullptr;
+    uint8_t* d_lat2 = nullptr;  // the other lattices of slab launches (as d_lat; null: no slabs)
     // persistent streamed passes (schedule flag SPINMC_SCHED_PERSIST): one
     // plan per model (Ising, Potts) over the streamed replicas
     struct PersistPlan {
@@ -258,6 +266,8 @@ void free_all(spinmc_ctx* c) {
     hipFree(c->d_t);
     hipFree(c->d_hist);
     hipFree(c->d_lists);
+    hipFree(c->d_slabs);
+    hipFree(c->d_lat2);
     hipFree(c->d_tiles);
     hipFree(c->d_ctype);
     hipFree(c->d_target);
@@ -296,6 +306,8 @@ void free_all(spinmc_ctx* c) {
     c->d_t = nullptr;
     c->d_hist = nullptr;
     c->d_lists = nullptr;
+    c->d_slabs = nullptr;
+    c->d_lat2 = nullptr;
     c->d_tiles = nullptr;
 }
 
@@ -484,6 +496,14 @@ int cpm_prepare_tables(const spinmc_replica_desc* d, int n) {
 int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
                spinmc_ctx** out);
 
+// Lattices of the resident kernels (whole or in slabs) under a resolved mode.
+bool is_resident(const HostRep& h, int mode) {
+    return mode == 1 || !h.chunk || (mode == 3 && h.resident) || h.slab_rows > 0;
+}
+
+void plan_slabs(spinmc_ctx* c, int mode);
+int effective_mode(const spinmc_ctx* c);
+
 size_t resident_lds(const spinmc_ctx* c, const HostRep& r) {
     return align_up((size_t)8 * c->max_tab_n, 16) + r.lat_bytes;
 }
@@ -625,6 +645,7 @@ int spinmc_create(const spinmc_replica_desc* d, int32_t n, uint64_t seed, int32_
         if (r.model == SPINMC_POTTS) c->potts_list.push_back(i);
     }
     c->lat_bytes = lat_off + 64;
+    plan_slabs(c, effective_mode(c));
     // host threshold words: hi16 | lo16 halves
     std::vector<uint32_t> tab(std::max<size_t>(tab_off, 1));
     for (int i = 0; i < n; ++i) {
@@ -823,7 +844,7 @@ int spinmc_schedule_sites(const spinmc_ctx* c, int64_t streamed[3], int64_t resi
     } else {
         const int mode = effective_mode(c);
         for (const HostRep& h : c->reps) {
-            const bool res = (mode == 1) || !h.chunk || (mode == 3 && h.resident);
+            const bool res = is_resident(h, mode);
             (res ? resident : streamed)[h.dev.model] += (int64_t)h.dev.Lx * h.dev.Ly;
         }
     }
@@ -860,6 +881,7 @@ int spinmc_set_schedule(spinmc_ctx* c, const spinmc_schedule* s) {
             if (!h.resident)
                 return fail(SPINMC_E_INVALID, "set_schedule: a lattice exceeds the resident LDS budget");
     c->sched = *s;
+    if (!c->cpm && !c->tri && !c->msc) plan_slabs(c, effective_mode(c));
     c->prepared = false;  // new tiles, resident lists and graphs on the next sweep
     return SPINMC_OK;
 }
@@ -1464,7 +1486,7 @@ int plan_persist(spinmc_ctx* c, int mode) {
     std::vector<int> by_model[2];
     for (int i = 0; i < c->R; ++i) {
         const HostRep& h = c->reps[i];
-        const bool resident = (mode == 1) || !h.chunk || (mode == 3 && h.resident);
+        const bool resident = is_resident(h, mode);
         if (!resident) by_model[h.dev.model == SPINMC_ISING ? 0 : 1].push_back(i);
     }
     int n_cu = 0;
@@ -1553,6 +1575,65 @@ int persist_check(spinmc_ctx* c) {
     return SPINMC_OK;
 }
 
+// Slabs of n Ising lattices of one shape (W % 8 == 0): rows of a slab and halo
+// rows either side of it, of the plan that takes least by this account in
+// microseconds a sweep, if that is well below that of whole or streamed lattices.
+// Whole: a compute unit's VALU time for a lattice (10.2 slots a site of 153.6e9 a
+// second), at least 2.2.  Streamed: two launches of 2.7, and the chip's time for
+// all.  Slabs: 6 for a launch of halo / 2 sweeps, and for the rows and the halo's
+// average 16 slots a site where a unit has one workgroup, 19 where it has several,
+// at least 1.3 (one item a lane) or 1.7 (two).  Measured, whole and in slabs:
+// 1, 32, 64 lattices of 256 x 256 4.3, 4.4, 4.4 and 1.4, 2.1, 2.7; 64 of 512 x 256
+// 8.6 and 5.9; 96 of 256 x 256 stay whole.
+bool best_slabs(const RepDev& d, int n, bool streamed, int* rows, int* halo) {
+    if (d.W % 8 != 0 || n >= 256) return false;
+    const double us = 1.0 / 153.6e3, sites = (double)d.Lx * d.Ly;
+    double best = 0.9 * (streamed ? 2.0 * std::max(2.7, n * sites * 5.1 * us / 256.0)
+                                  : std::max(2.2, 10.2 * us * sites));
+    bool found = false;
+    for (int S = 2; S <= 256 && 2 * S <= d.Ly; ++S) {
+        const int own = ((d.Ly + S - 1) / S + 1) & ~1;
+        for (int k = 1; k <= 16; ++k) {
+            const int window = own + 4 * k;
+            const int items = window * d.W / 8;
+            if (window > d.Ly || items > 2048) break;
+            const double turns = std::ceil((double)n * S / 256.0);
+            const double valu = turns * (turns > 1.0 ? 19.0 : 16.0) * us * d.Lx * (own + 2 * k);
+            const double t = 6.0 / k + std::max(items > 1024 ? 1.7 : 1.3, valu);
+            if (t < best) {
+                best = t;
+                *rows = own;
+                *halo = 2 * k;
+                found = true;
+            }
+        }
+    }
+    return found;
+}
+
+// Marks the replicas that run in slabs under the current schedule (a choice of
+// the automatic modes: none where tiles or packing are given).
+void plan_slabs(spinmc_ctx* c, int mode) {
+    std::map<std::pair<int, int>, std::vector<int>> shapes;
+    for (int i = 0; i < (int)c->reps.size(); ++i) {
+        HostRep& h = c->reps[i];
+        h.slab_rows = h.slab_halo = 0;
+        if (h.dev.model == SPINMC_ISING) shapes[{h.dev.Lx, h.dev.Ly}].push_back(i);
+    }
+    const spinmc_schedule& sc = c->sched;
+    if (sc.mode > 1 || sc.rpb != 0 || sc.wg_threads != 0 || sc.tile_rows != 0 || sc.flags != 0)
+        return;
+    for (auto& kv : shapes) {
+        const HostRep& h = c->reps[kv.second[0]];
+        int rows = 0, halo = 0;
+        if (best_slabs(h.dev, (int)kv.second.size(), !is_resident(h, mode), &rows, &halo))
+            for (int i : kv.second) {
+                c->reps[i].slab_rows = rows;
+                c->reps[i].slab_halo = halo;
+            }
+    }
+}
+
 // (Re)build the tile table and the resident lists for a schedule.
 //   mode 1: every replica resident;
 //   mode 2: every replica with the chunk layout streamed (others resident);
@@ -1563,11 +1644,18 @@ int prepare(spinmc_ctx* c, int mode) {
                      ((long)(c->sched.wg_threads >> 8) << 40) | ((long)c->sched.flags << 32) |
                      (long)(unsigned)tr;
     if (c->prepared && c->prepared_key == key) return SPINMC_OK;
+    plan_slabs(c, mode);
+    bool any_slab = false;
+    for (const HostRep& h : c->reps) any_slab = any_slab || h.slab_rows > 0;
+    if (any_slab && !c->d_lat2 && hipMalloc((void**)&c->d_lat2, c->lat_bytes) != hipSuccess) {
+        (void)hipGetLastError();  // no memory for a second set of lattices: no slabs
+        for (HostRep& h : c->reps) h.slab_rows = 0;
+    }
     std::vector<int32_t> res_chunk, res_gen, spotts;
     std::vector<TileDev> tiles, ptiles;  // Ising tiles first, then Potts tiles
     for (int i = 0; i < c->R; ++i) {
         const HostRep& h = c->reps[i];
-        const bool resident = (mode == 1) || !h.chunk || (mode == 3 && h.resident);
+        const bool resident = is_resident(h, mode);
         if (resident) {
             (h.chunk ? res_chunk : res_gen).push_back(i);
             continue;
@@ -1584,7 +1672,7 @@ int prepare(spinmc_ctx* c, int mode) {
         size_t bi = 0, bp = 0;
         for (int i = 0; i < c->R; ++i) {
             const HostRep& h = c->reps[i];
-            const bool resident = (mode == 1) || !h.chunk || (mode == 3 && h.resident);
+            const bool resident = is_resident(h, mode);
             if (!resident) (h.dev.model == SPINMC_ISING ? bi : bp) += h.lat_bytes;
         }
         const int f = c->sched.flags & (SPINMC_SCHED_NT_ON | SPINMC_SCHED_NT_OFF);
@@ -1602,6 +1690,7 @@ int prepare(spinmc_ctx* c, int mode) {
     // replicas.
     c->res_groups.clear();
     std::vector<int32_t> buf;
+    std::vector<TileDev> slabs;
     const int tmax = c->sched.wg_threads > 0 ? c->sched.wg_threads : 512;
     for (int pass = 0; pass < 2; ++pass) {
         const std::vector<int32_t>& L = pass == 0 ? res_chunk : res_gen;
@@ -1621,7 +1710,7 @@ int prepare(spinmc_ctx* c, int mode) {
             int kind = std::get<0>(kv.first);
             // row pairs of 16 columns share most; eight sites a lane give four
             // times the waves
-            if (kind == kResIsing16 && plane <= 8 * 1024 &&
+            if (kind == kResIsing16 && plane <= 16 * 1024 &&
                 (int64_t)n * plane <= kIsing8MaxSites)
                 kind = kResIsing8;
             const bool ising = kind >= kResIsing16;
@@ -1647,7 +1736,23 @@ int prepare(spinmc_ctx* c, int mode) {
             int threads = c->sched.rpb > 0 ? 64 * P : 64;
             while (threads < tcap && threads < P * items) threads *= 2;
             while (kind == kResIsing16 && 2 * threads < P * items) threads *= 2;
-            c->res_groups.push_back({(int)buf.size(), n, P, threads, kind, items, slot});
+            c->res_groups.push_back(
+                {(int)buf.size(), n, P, threads, kind, items, slot, true, 0, 0, 0, 0, 0, 0});
+            if (h.slab_rows > 0) {
+                auto& g = c->res_groups.back();
+                const int rows = h.slab_rows;
+                g.whole = h.resident;
+                g.slab0 = (int)slabs.size();
+                for (int i : kv.second)
+                    for (int y = 0; y < h.dev.Ly; y += rows)
+                        slabs.push_back(TileDev{i, y, std::min(rows, h.dev.Ly - y), 0});
+                g.n_slabs = (int)slabs.size() - g.slab0;
+                g.halo = h.slab_halo;
+                const size_t window = (size_t)(rows + 2 * g.halo) * h.dev.W;
+                g.slab_items = (int)(window / 8);
+                g.slab_threads = (int)std::min<size_t>(1024, align_up(window / 8, 64));
+                g.slab_lds = (size_t)4 * kIsingTabWords + 2 * align_up(window + 8, 8);
+            }
             buf.insert(buf.end(), kv.second.begin(), kv.second.end());
         }
     }
@@ -1669,9 +1774,20 @@ int prepare(spinmc_ctx* c, int mode) {
         e = hipMemcpy(c->d_tiles, tiles.data(), sizeof(TileDev) * tiles.size(),
                       hipMemcpyHostToDevice);
     c->n_tiles = (int)tiles.size();
-    for (const auto& g : c->res_groups)
+    hipFree(c->d_slabs);
+    c->d_slabs = nullptr;
+    if (e == hipSuccess && !slabs.empty()) {
+        e = hipMalloc((void**)&c->d_slabs, sizeof(TileDev) * slabs.size());
         if (e == hipSuccess)
+            e = hipMemcpy(c->d_slabs, slabs.data(), sizeof(TileDev) * slabs.size(),
+                          hipMemcpyHostToDevice);
+    }
+    for (const auto& g : c->res_groups) {
+        if (e == hipSuccess && g.whole)
             e = resident_reserve_lds(g.kind, g.items, g.threads / g.rpb, g.slot * g.rpb);
+        if (e == hipSuccess && g.n_slabs > 0)
+            e = resident_reserve_lds(kResIsingSlab, g.slab_items, g.slab_threads, g.slab_lds);
+    }
     if (e != hipSuccess) return check_dev(c, e, "prepare schedule");
     c->persist = (c->sched.flags & SPINMC_SCHED_PERSIST) != 0 && mode != 1 && !tiles.empty();
     if (c->persist) {
@@ -1723,6 +1839,30 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
         hipStream_t side = alone ? s : c->cap[1 + k % kSide];
         if (!alone && k < (size_t)kSide) e = hipStreamWaitEvent(side, c->cap_ev[0], 0);
         if (e != hipSuccess) break;
+        // slabs write the other lattices: an even number of launches (one without a
+        // sweep if there is but one) ends in d_lat
+        if (g.n_slabs > 0 && (a.n_sweeps >= 2 || !g.whole)) {
+            const int k = g.halo / 2;
+            const int m = std::max(2, ((a.n_sweeps + k - 1) / k + 1) & ~1);
+            SweepArgs b = a;
+            b.tiles = c->d_slabs + g.slab0;
+            b.n_list = g.n_slabs;
+            b.rpb = 1;
+            b.halo = g.halo;
+            for (int i = 0; i < m && e == hipSuccess; ++i) {
+                const int i0 = (int)((int64_t)a.n_sweeps * i / m);
+                const int i1 = (int)((int64_t)a.n_sweeps * (i + 1) / m);
+                b.sweep_off = a.sweep_off + i0;
+                b.n_sweeps = i1 - i0;
+                b.lat = i % 2 == 0 ? c->d_lat2 : c->d_lat;
+                b.lat_src = i % 2 == 0 ? c->d_lat : c->d_lat2;
+                e = timed(c, SPINMC_K_RESIDENT, [&] {
+                    return launch_resident(b, g.n_slabs, kResIsingSlab, g.slab_items,
+                                           g.slab_threads, g.slab_lds, side);
+                }, side);
+            }
+            continue;
+        }
         a.rep_list = c->d_lists + c->off_res_chunk + g.off;
         a.n_list = g.count;
         a.rpb = g.rpb;
@@ -1848,16 +1988,16 @@ int enqueue_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     int rc = prepare(c, mode);
     if (rc) return rc;
     hipError_t e = hipSuccess;
-    // Unrecorded, untimed calls with streamed passes replay cached graphs of
-    // whole chunks (resident groups alone are one launch each).  When
+    // Unrecorded, untimed calls replay cached graphs of whole chunks (a single
+    // resident group is one launch, or a few of slabs).  When
     // both resident groups and streamed tiles exist, the resident kernels
     // run outside the graphs, one launch per group for all n sweeps on side
     // streams forked from the call's stream (their start counter copied to
     // d_t[1] first, since the graphs advance d_t[0] meanwhile), so that they
     // overlap the streamed graph replays for the whole call rather than
     // meeting them at every chunk boundary.
-    if (re == 0 && !c->prof && c->use_graphs && c->n_tiles > 0) {
-        const bool split = !c->res_groups.empty();
+    if (re == 0 && !c->prof && c->use_graphs && !resident_alone(c)) {
+        const bool split = c->n_tiles > 0 && !c->res_groups.empty();
         const int G = std::min(n, kGraphChunk);
         const int full = n / G, rest = n - full * G;
         hipGraphExec_t ex = nullptr, ex_rest = nullptr;
@@ -1880,9 +2020,11 @@ int enqueue_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     }
     SweepArgs a = sweep_args(c, n, re, stats);
     const int n_rec = re > 0 ? n / re : 0;
-    if (n_rec > 0 && c->n_tiles > 0) {
-        // stream-pass statistics accumulate with atomics: clear their rows
-        // first (resident replicas overwrite theirs)
+    bool adds = c->n_tiles > 0;
+    for (const auto& g : c->res_groups) adds = adds || g.n_slabs > 0;
+    if (n_rec > 0 && adds) {
+        // statistics of stream passes and slabs accumulate with atomics: clear
+        // their rows first (whole resident replicas overwrite theirs)
         e = launch_fill_i32(stats, (size_t)n_rec * c->R * c->width, 0, c->stream);
     }
     // resident groups on side streams, one launch per group for all n

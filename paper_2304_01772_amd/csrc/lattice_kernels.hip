@@ -1115,15 +1115,22 @@ struct RecRows {
             atomicAdd(&l[n][2], (int)((uint32_t)b >> 16));
         }
     }
-    // stores and clears the rows; the replica's lanes meet before and after
+    // stores (SLAB: adds, the rows hold zeros or other slabs' shares) and clears
+    // the rows; the replica's lanes meet before and after.  N: the sites counted.
+    template <bool SLAB>
     __device__ __forceinline__ void flush(const SweepArgs& a, int rep, int N, bool active, int lt,
                                           int nt) {
         if (active)
             for (int i = lt; i < n * a.width; i += nt) {
                 const int r = i / a.width, k = i - r * a.width;
                 const int v = k < 3 ? l[r][k] : 0;
-                a.stats[((size_t)(row0 + r) * a.R + rep) * a.width + k] =
-                    k == 0 ? 2 * v - N : (k < 3 ? N - 2 * v : 0);
+                const int share = k == 0 ? 2 * v - N : N - 2 * v;
+                int32_t* at = a.stats + ((size_t)(row0 + r) * a.R + rep) * a.width + k;
+                if (SLAB) {
+                    if (k < 3) atomicAdd(at, share);
+                } else {
+                    *at = k < 3 ? share : 0;
+                }
                 if (k < 3) l[r][k] = 0;
             }
         row0 += n;
@@ -1243,12 +1250,12 @@ __global__ void __launch_bounds__(1024) k_resident_ising(SweepArgs a) {
             rr.add(up, dx, dy, nt);  // at most 16 NI a byte
             if (++rr.n == kRecRows) {
                 replica_sync(waves);
-                rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
+                rr.flush<false>(a, rep, 2 * (int)plane, active, lt, nt);
             }
         }
         replica_sync(waves);
     }
-    rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
+    rr.flush<false>(a, rep, 2 * (int)plane, active, lt, nt);
 #pragma unroll
     for (int k = 0; k < NI; ++k)
         if (lt + k * nt < n_items)
@@ -1383,9 +1390,17 @@ __device__ __forceinline__ void near8(const Item8<AL>& t, const uint8_t* oth, in
 // against 2.7) and, without AL, every other width from 18 on (k_resident_generic
 // draws a block for every site: 100 lattices of 300 x 300, 20 sweeps and the
 // gradients 2064 us, now 405).
-// ONE: at most one item a lane, its offsets and both planes' bytes in registers;
-// else a lane's items are worked out in every pass.
-template <bool AL, bool ONE, bool UNI>
+// NI = 1, 2: at most NI items a lane, their offsets and both planes' bytes in
+// registers; NI = 0: a lane's items are worked out in every pass.
+//
+// SLAB (with AL, NI > 0 and UNI): a few large lattices are cut into slabs of rows, a
+// workgroup each, where whole ones would leave most of the chip idle.  A
+// workgroup reads its slab with a.halo rows on either side from a.lat_src, runs
+// n_sweeps <= a.halo / 2 sweeps on that window and writes its own rows to a.lat:
+// the window's outermost valid row moves inwards by one a pass, since every
+// site's draws depend on its place alone, so the slabs need no exchange between
+// launches (64 lattices of 256 x 256: @S1@ us a sweep in 512 slabs, @S0@ whole).
+template <bool AL, int NI, bool UNI, bool SLAB>
 __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     // dynamic LDS: rpb slots of [thresholds (kIsingTabWords) | plane 0 and its repeat |
     // plane 1 and its repeat], each plane in whole 8 bytes
@@ -1398,14 +1413,24 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     if (UNI) g = __builtin_amdgcn_readfirstlane(g);
     const int first = blockIdx.x * P;
     const bool active = first + g < a.n_list;
-    const int rep = a.rep_list[active ? first + g : first];
+    const TileDev T = SLAB ? a.tiles[blockIdx.x] : TileDev{};
+    const int rep = SLAB ? T.rep : a.rep_list[active ? first + g : first];
     const RepDev& R = a.reps[rep];
-    const uint32_t W = (uint32_t)R.W, plane = (uint32_t)R.Ly * W, rid = R.rid;
+    // the window: the whole lattice, or a slab and its halo rows
+    const int rows = SLAB ? T.rows + 2 * a.halo : R.Ly;
+    const uint32_t W = (uint32_t)R.W, plane = (uint32_t)rows * W, rid = R.rid;
+    const uint32_t gplane = (uint32_t)R.Ly * W;
     const uint32_t stride = (plane + 15u) & ~7u;
     uint8_t* slot = dyn + (size_t)(active ? g : 0) * a.res_slot_bytes;
     uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
     uint8_t* lds = slot + 4 * kIsingTabWords;
     uint8_t* gmem = a.lat + R.lat_off;
+    // place in the lattice of a window's byte k
+    auto place = [&](uint32_t k) {
+        if (!SLAB) return k;
+        const int at = (T.y0 - a.halo) * (int)W + (int)k;
+        return (uint32_t)(at < 0 ? at + (int)gplane : at >= (int)gplane ? at - (int)gplane : at);
+    };
     const uint32_t n_items = active ? (plane + 7u) >> 3 : 0u;
     if (active) load_ising_table(a.tab, R, tab, lt, nt);
     if (AL || (plane & 7u) == 0u) {
@@ -1413,22 +1438,34 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
 #pragma unroll
             for (uint32_t c = 0; c < 2u; ++c)
                 store8<AL>(lds + c * stride, 8u * i, plane,
-                           *reinterpret_cast<const uint2*>(gmem + c * plane + 8u * i));
+                           *reinterpret_cast<const uint2*>((SLAB ? a.lat_src + R.lat_off : gmem) +
+                                                           c * gplane + place(8u * i)));
     } else if (active) {  // with the repeated bytes
         for (uint32_t i = lt; i < plane + 8u; i += (uint32_t)nt)
 #pragma unroll
             for (uint32_t c = 0; c < 2u; ++c)
                 lds[c * stride + i] = gmem[c * plane + (i < plane ? i : i - plane)];
     }
-    Item8<AL> it1;
-    uint2 V[2];
-    const bool own1 = (uint32_t)lt < n_items;
+    constexpr int NR = NI > 0 ? NI : 1;
+    Item8<AL> it[NR];
+    uint2 V[2][NR];
+    uint32_t kb[NR];  // within-colour index
+    int row[NR];      // SLAB: the window's row, -1 without an item
+    auto held = [&](int n) { return (uint32_t)(lt + n * nt) < n_items; };
+    // not a halo row
+    auto mine = [&](int n) {
+        return !SLAB || (row[n] >= a.halo && row[n] < a.halo + T.rows);
+    };
+    const int sites = SLAB ? 2 * T.rows * (int)W : 2 * (int)plane;  // counted here
     __syncthreads();
-    if (ONE) {
-        it1.init(own1 ? (uint32_t)lt : 0u, W, plane);
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+        it[n].init(held(n) ? (uint32_t)(lt + n * nt) : 0u, W, plane);
+        kb[n] = place(it[n].k);
+        row[n] = SLAB ? (held(n) ? (int)(it[n].k / W) : -1) : 0;
 #pragma unroll
         for (uint32_t c = 0; c < 2u; ++c)
-            if (own1) V[c] = *reinterpret_cast<const uint2*>(lds + c * stride + it1.k);
+            if (held(n)) V[c][n] = *reinterpret_cast<const uint2*>(lds + c * stride + it[n].k);
     }
     for (int i = threadIdx.x; i < 3 * kRecRows * P; i += blockDim.x) (&lrec[0][0][0])[i] = 0;
     __syncthreads();
@@ -1445,14 +1482,14 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
             const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
             uint8_t* own = lds + (uint32_t)c * stride;
             const uint8_t* oth = lds + (uint32_t)(1 - c) * stride;
-            auto pass = [&](const Item8<AL>& q, uint2& o, const uint2& m2) {
+            auto pass = [&](const Item8<AL>& q, uint32_t k0, bool cnt, uint2& o, const uint2& m2) {
                 const uint32_t ov[2] = {o.x, o.y};
                 uint32_t m[2] = {m2.x, m2.y}, sv[2], Uv[2], Dv[2], nv[2];
                 near8<AL>(q, oth, c, m, sv, Uv, Dv);
-                ising_core(ov, m, sv, Uv, Dv, q.k, p, rid, a.key0, a.key1, tab, nv);
+                ising_core(ov, m, sv, Uv, Dv, k0, p, rid, a.key0, a.key1, tab, nv);
                 o = make_uint2(nv[0], nv[1]);
                 store8<AL>(own, q.k, plane, o);
-                if (c == 1 && rec) {
+                if (c == 1 && rec && cnt) {
                     if (!AL && q.k + 8u > plane) {
                         const uint64_t in = (1ull << (8u * (plane - q.k))) - 1ull;
 #pragma unroll
@@ -1468,14 +1505,19 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
                     ising_count(nv, m, sv, Uv, Dv, up, dx, dy);
                 }
             };
-            if (ONE) {
-                if (own1) pass(it1, V[c], V[1 - c]);
+            if (NI > 0) {
+                // after pass j the rows j + 1 .. rows - 2 - j are valid
+                const int j = 2 * sw + c;
+#pragma unroll
+                for (int n = 0; n < NI; ++n)
+                    if (SLAB ? row[n] > j && row[n] < rows - 1 - j : held(n))
+                        pass(it[n], kb[n], mine(n), V[c][n], V[1 - c][n]);
             } else {
                 for (uint32_t i = lt; i < n_items; i += (uint32_t)nt) {
                     Item8<AL> q;
                     q.init(i, W, plane);
                     uint2 o = *reinterpret_cast<const uint2*>(own + q.k);
-                    pass(q, o, *reinterpret_cast<const uint2*>(oth + q.k));
+                    pass(q, q.k, true, o, *reinterpret_cast<const uint2*>(oth + q.k));
                 }
             }
             if (c == 0) replica_sync(waves);
@@ -1484,13 +1526,20 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
             rr.add(up, dx, dy, nt);
             if (++rr.n == kRecRows) {
                 replica_sync(waves);
-                rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
+                rr.flush<SLAB>(a, rep, sites, active, lt, nt);
             }
         }
         replica_sync(waves);
     }
-    rr.flush(a, rep, 2 * (int)plane, active, lt, nt);
-    if (AL || (plane & 7u) == 0u) {
+    rr.flush<SLAB>(a, rep, sites, active, lt, nt);
+    if (SLAB) {
+#pragma unroll
+        for (int n = 0; n < NI; ++n)
+            if (mine(n))
+#pragma unroll
+                for (uint32_t c = 0; c < 2u; ++c)
+                    *reinterpret_cast<uint2*>(gmem + c * gplane + kb[n]) = V[c][n];
+    } else if (AL || (plane & 7u) == 0u) {
         for (uint32_t i = lt; i < n_items; i += (uint32_t)nt)
 #pragma unroll
             for (uint32_t c = 0; c < 2u; ++c)
@@ -1609,12 +1658,11 @@ hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* 
 }
 
 namespace {
-template <bool AL>
-const void* ising8_fn(bool one, bool uni) {
-    return one ? (uni ? (const void*)k_resident_ising8<AL, true, true>
-                      : (const void*)k_resident_ising8<AL, true, false>)
-               : (uni ? (const void*)k_resident_ising8<AL, false, true>
-                      : (const void*)k_resident_ising8<AL, false, false>);
+template <bool AL, bool UNI>
+const void* ising8_fn(int items, int nt) {
+    return items <= nt       ? (const void*)k_resident_ising8<AL, 1, UNI, false>
+           : items <= 2 * nt ? (const void*)k_resident_ising8<AL, 2, UNI, false>
+                             : (const void*)k_resident_ising8<AL, 0, UNI, false>;
 }
 
 const void* resident_fn(int kind, int items, int nt) {
@@ -1625,8 +1673,12 @@ const void* resident_fn(int kind, int items, int nt) {
                                      : (const void*)k_resident_ising<2, false>)
                               : (uni ? (const void*)k_resident_ising<1, true>
                                      : (const void*)k_resident_ising<1, false>);
-        case kResIsing8: return ising8_fn<true>(items <= nt, uni);
-        case kResIsing8Any: return ising8_fn<false>(items <= nt, uni);
+        case kResIsing8: return uni ? ising8_fn<true, true>(items, nt) : ising8_fn<true, false>(items, nt);
+        case kResIsing8Any:
+            return uni ? ising8_fn<false, true>(items, nt) : ising8_fn<false, false>(items, nt);
+        case kResIsingSlab:
+            return items <= nt ? (const void*)k_resident_ising8<true, 1, true, true>
+                               : (const void*)k_resident_ising8<true, 2, true, true>;
         case kResPotts: return (const void*)k_resident_potts;
         default: return (const void*)k_resident_generic;
     }
@@ -1642,7 +1694,7 @@ hipError_t launch_resident(const SweepArgs& a, int n_list, int kind, int items, 
                            size_t lds_bytes, hipStream_t s) {
     if (n_list <= 0) return hipSuccess;
     const int nt = threads / a.rpb;
-    if (kind == kResIsing16 && items > 2 * nt) return hipErrorInvalidValue;
+    if ((kind == kResIsing16 || kind == kResIsingSlab) && items > 2 * nt) return hipErrorInvalidValue;
     SweepArgs b = a;
     void* args[] = {&b};
     return hipLaunchKernel(resident_fn(kind, items, nt), dim3((n_list + a.rpb - 1) / a.rpb),

@@ -30,6 +30,7 @@ enum {
     kResIsing16 = 2,    // Ising, row pairs of 16 columns a lane (W % 16 == 0)
     kResIsing8 = 3,     // Ising, 8 sites a lane (W % 8 == 0)
     kResIsing8Any = 4,  // Ising, 8 sites a lane (W >= 9)
+    kResIsingSlab = 5,  // Ising, 8 sites a lane (W % 8 == 0), a slab of rows a workgroup
 };
 
 // Per-replica record, device visible.
@@ -118,6 +119,10 @@ struct SweepArgs {
     // resident kernels: replicas per workgroup, LDS bytes per replica slot,
     // and the number of entries of rep_list
     int32_t rpb, res_slot_bytes, n_list;
+    // kResIsingSlab: one tile a workgroup (n_list of them), rows either side of
+    // it that its window holds (even), and the lattices read (lat is written)
+    int32_t halo;
+    const uint8_t* lat_src;
 };
 
 // Host-side launchers implemented in the kernel translation units.
@@ -125,7 +130,7 @@ hipError_t launch_init(const RepDev* reps, const int32_t* list, int n, uint8_t* 
                        uint32_t key0, uint32_t key1, int threads, hipStream_t s);
 // Resident groups: replicas of one shape (and, except kResGeneric, of one
 // model).  items: the lanes' units of a replica (row pairs of 16 columns, 8
-// sites or sites); kResIsing16 takes at most two a lane.
+// sites or sites); kResIsing16 and kResIsingSlab take at most two a lane.
 hipError_t launch_resident(const SweepArgs& a, int n_list, int kind, int items, int threads,
                            size_t lds_bytes, hipStream_t s);
 // Allow a group's kernel (nt lanes a replica) up to lds_bytes of dynamic LDS

@@ -579,3 +579,33 @@ def test_ising_eight_sites_a_lane(S, Lx, Ly, R):
         assert np.array_equal(smp.get_state(r), a), r
         assert np.array_equal(st[:, r, :], want), r
     smp.close()
+
+
+@pytest.mark.parametrize("Lx,Ly,R,slabs", [
+    (256, 256, 2, True),          # several slabs of equal height
+    (512, 250, 1, True),          # the last slab shorter
+    (96, 1024, 3, True),          # narrow and high
+    (512, 512, 2, True),          # too large for a workgroup: slabs instead of passes
+    (1024, 600, 1, True),
+    (256, 256, 200, False),       # enough lattices: whole
+])
+def test_ising_slabs(S, Lx, Ly, R, slabs):
+    """A few large lattices cut into slabs with halo rows: calls of one sweep,
+    of an odd number, and recorded rows across launches; the schedule that
+    forces whole or streamed lattices gives the same chain."""
+    seed, h = 35, _f32(0.02)
+    reps = [dict(model=0, Lx=Lx, Ly=Ly, Jx=1.0, Jy=0.8, h=h, beta=0.45, rid=r) for r in range(R)]
+    smp, ref = S(reps, seed, init=True), S(reps, seed, init=True)
+    ref.set_schedule(mode="stream")
+    streamed, resident = smp.schedule_sites()
+    assert resident == R * Lx * Ly and streamed == 0 if slabs else True
+    for n, re in ((1, 0), (3, 1), (13, 4), (2, 0), (37, 3)):
+        got, want = smp.sweep(n, re), ref.sweep(n, re)
+        if re:
+            assert torch.equal(got, want), n
+    for r in {0, R - 1}:
+        assert np.array_equal(smp.get_state(r), ref.get_state(r)), r
+    a, _ = orc.ising_run(orc.ising_init(Lx, Ly, seed, 0), 1.0, 0.8, h, 0.45, seed, 0, 0, 56, 0)
+    assert np.array_equal(smp.get_state(0), a)
+    smp.close()
+    ref.close()
