@@ -156,6 +156,7 @@ struct spinmc_ctx {
     bool nt_ising = false, nt_potts = false;  // nontemporal own-plane access per model
     struct ResGroup {
         int off, count, rpb, threads, kind, items;
+        int tab_bytes;  // thresholds in LDS
         size_t slot;
         bool whole;  // fits a workgroup whole
         // slabs of rows (0: whole lattices only): tiles d_slabs[slab0 ..], halo rows
@@ -200,6 +201,7 @@ struct spinmc_ctx {
     // multispin-coded Ising: reps holds the G groups, R = 32 G
     bool msc = false;
     int msc_mode = kMscAny;
+    size_t stream_tab_bytes = 0;  // LDS of the streamed Potts passes' thresholds
     RepDev* d_reps_obs = nullptr;  // one square-lattice Ising entry per replica
     long long* d_cov_part = nullptr;  // chunk sums of the split covariance estimator
     size_t cov_part_n = 0;
@@ -497,6 +499,16 @@ int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
                spinmc_ctx** out);
 
 // Lattices of the resident kernels (whole or in slabs) under a resolved mode.
+// LDS bytes of the thresholds of the per-site kernel, and of Potts items of the
+// listed replicas.
+size_t generic_tab_bytes(const spinmc_ctx* c) { return align_up((size_t)8 * c->max_tab_n, 16); }
+size_t potts_tab_bytes(const spinmc_ctx* c, const std::vector<int>& list) {
+    size_t n = 0;
+    for (int i : list)
+        if (c->reps[i].dev.h != 0.0f) n = std::max(n, (size_t)c->reps[i].dev.tab_n);
+    return (size_t)4 * kPottsTabWords + align_up(8 * n, 16);
+}
+
 bool is_resident(const HostRep& h, int mode) {
     return mode == 1 || !h.chunk || (mode == 3 && h.resident) || h.slab_rows > 0;
 }
@@ -1501,7 +1513,7 @@ int plan_persist(spinmc_ctx* c, int mode) {
         auto& P = c->pplan[m];
         P = spinmc_ctx::PersistPlan{};
         if (by_model[m].empty()) continue;
-        P.slot_words = m == 0 ? kIsingTabWords : (int)align_up((size_t)2 * c->max_tab_n + 18, 4);
+        P.slot_words = m == 0 ? kIsingTabWords : (int)(potts_tab_bytes(c, by_model[m]) / 4);
         const int items_cap = std::max(1, std::min(16, 8192 / (4 * P.slot_words)));
         P.lds = (size_t)items_cap * P.slot_words * 4;
         const bool nt = m == 0 ? c->nt_ising : c->nt_potts;
@@ -1684,6 +1696,7 @@ int prepare(spinmc_ctx* c, int mode) {
     c->res_chunk = res_chunk;
     c->res_gen = res_gen;
     c->stream_potts = spotts;
+    c->stream_tab_bytes = potts_tab_bytes(c, spotts);
     // Resident groups: replicas of one kernel and shape, packed rpb per
     // workgroup so that the workgroup's threads cover about one item each per
     // pass, while keeping at least two workgroups per CU when there are enough
@@ -1697,10 +1710,12 @@ int prepare(spinmc_ctx* c, int mode) {
         std::map<std::tuple<int, int, int>, std::vector<int32_t>> shapes;
         for (int i : L) {
             const RepDev& d = c->reps[i].dev;
-            int kind = pass == 0 ? kResPotts : kResGeneric;
-            if (d.model == SPINMC_ISING && pass == 0) kind = kResIsing16;
-            if (d.model == SPINMC_ISING && pass == 1 && d.W >= 8)
-                kind = d.W % 8 == 0 ? kResIsing8 : kResIsing8Any;
+            const bool ising = d.model == SPINMC_ISING;
+            int kind = kResGeneric;
+            if (d.W % 8 == 0)
+                kind = !ising ? kResPotts8 : d.W % 16 == 0 ? kResIsing16 : kResIsing8;
+            else if (d.W >= 9)
+                kind = ising ? kResIsing8Any : kResPotts8Any;
             shapes[std::make_tuple(kind, d.Lx, d.Ly)].push_back(i);
         }
         for (auto& kv : shapes) {
@@ -1713,12 +1728,15 @@ int prepare(spinmc_ctx* c, int mode) {
             if (kind == kResIsing16 && plane <= 16 * 1024 &&
                 (int64_t)n * plane <= kIsing8MaxSites)
                 kind = kResIsing8;
-            const bool ising = kind >= kResIsing16;
-            const int items = kind == kResGeneric ? plane : kind >= kResIsing8 ? (plane + 7) / 8 : plane / 32;
-            const size_t slot = (ising ? (size_t)4 * kIsingTabWords
-                                       : align_up((size_t)8 * c->max_tab_n, 16)) +
-                                align_up(kind >= kResIsing8 ? 2 * align_up((size_t)plane + 8, 8) : h.lat_bytes, 16);
-            const int tcap = ising && c->sched.wg_threads == 0 ? 1024 : tmax;
+            const bool ising = kind >= kResIsing16 && kind <= kResIsing8Any;
+            const bool eights = kind != kResGeneric && kind != kResIsing16;
+            const int items = kind == kResGeneric ? plane : eights ? (plane + 7) / 8 : plane / 32;
+            size_t tab = ising ? (size_t)4 * kIsingTabWords : generic_tab_bytes(c);
+            if (kind >= kResPotts8) tab = potts_tab_bytes(c, kv.second);
+            const size_t slot =
+                tab + align_up(eights ? 2 * align_up((size_t)plane + 8, 8) : h.lat_bytes, 16);
+            const int tcap =
+                kind != kResGeneric && c->sched.wg_threads == 0 ? 1024 : tmax;
             int P = 1;
             if (c->sched.rpb > 0) {
                 // forced packing: at most rpb, within the LDS budget, one
@@ -1737,7 +1755,7 @@ int prepare(spinmc_ctx* c, int mode) {
             while (threads < tcap && threads < P * items) threads *= 2;
             while (kind == kResIsing16 && 2 * threads < P * items) threads *= 2;
             c->res_groups.push_back(
-                {(int)buf.size(), n, P, threads, kind, items, slot, true, 0, 0, 0, 0, 0, 0});
+                {(int)buf.size(), n, P, threads, kind, items, (int)tab, slot, true, 0, 0, 0, 0, 0, 0});
             if (h.slab_rows > 0) {
                 auto& g = c->res_groups.back();
                 const int rows = h.slab_rows;
@@ -1815,7 +1833,7 @@ SweepArgs sweep_args(spinmc_ctx* c, int n, int re, int32_t* stats) {
     a.n_sweeps = n;
     a.record_every = re;
     a.n_units = c->n_tiles;
-    a.tab_lds_bytes = (int)align_up((size_t)8 * c->max_tab_n, 16);
+    a.tab_lds_bytes = (int)c->stream_tab_bytes;  // streamed Potts passes
     return a;
 }
 
@@ -1866,6 +1884,7 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
         a.rep_list = c->d_lists + c->off_res_chunk + g.off;
         a.n_list = g.count;
         a.rpb = g.rpb;
+        a.tab_lds_bytes = g.tab_bytes;
         a.res_slot_bytes = (int)g.slot;
         e = timed(c, SPINMC_K_RESIDENT, [&] {
             return launch_resident(a, g.count, g.kind, g.items, g.threads, g.slot * g.rpb, side);

@@ -294,8 +294,43 @@ __device__ __forceinline__ void ising_compute(const ChunkIn& in, uint8_t* own, u
 }
 
 // ---------------------------------------------------------------- Potts
+// Thresholds of a replica in LDS: the high halves by pattern (kPottsFast), then
+// 9 high and 9 low halves by dn + 4 (h = 0), then, for the others, the whole
+// table [tab_n hi | tab_n lo].
+constexpr int kPatternWords = 256;
+static_assert(kPottsTabWords == kPatternWords + 20, "table layout");
+
+// The rule of a replica: labels of three bits and no field; no field; any.
+enum { kPottsFast = 0, kPottsNoField = 1, kPottsAny = 2 };
+__device__ __forceinline__ int potts_path(const RepDev& R) {
+    return R.h != 0.0f ? kPottsAny : (R.q <= 8 ? kPottsFast : kPottsNoField);
+}
+
+// Lanes tid = 0 .. nthr - 1 fill l; no other lane reads before they meet.
+__device__ __forceinline__ void load_potts_table(const uint32_t* tab, const RepDev& R, uint32_t* l,
+                                                 int tid, int nthr) {
+    const uint32_t* t = tab + R.tab_off;
+    const int wq = 2 * R.q - 1;  // h = 0: the column s' = s stands for all
+    if (R.h == 0.0f) {
+        for (int i = tid; i < (R.q <= 8 ? kPatternWords : 0); i += nthr)
+            l[i] = t[(__popc(i & 15) + 4 - __popc(i >> 4)) * wq + R.q - 1];
+        for (int i = tid; i < 18; i += nthr) {
+            const int k = i % 9, half = i / 9;
+            l[kPatternWords + i] = t[half * R.tab_n + k * wq + R.q - 1];
+        }
+    } else {
+        for (int i = tid; i < 2 * R.tab_n; i += nthr) l[kPottsTabWords + i] = t[i];
+    }
+}
+
 struct PottsAcc {
     int Nx, Ny, S;
+    int n[8];  // labels 0 .. 7 (q <= 8)
+    __device__ __forceinline__ void clear() {
+        Nx = Ny = S = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) n[k] = 0;
+    }
 };
 
 // Byte-wise "not equal" flags (bit 7 of each byte) for labels < 128.
@@ -303,194 +338,294 @@ __device__ __forceinline__ uint32_t ne_hi(uint32_t a, uint32_t b) {
     return ((a ^ b) + 0x7F7F7F7Fu) & 0x80808080u;
 }
 
-// 16-site Potts chunk.  thr: LDS [n hi | n lo], n = 9(2q-1); thr9: LDS
-// [9 hi | 9 lo] by dn + 4 (used when HZ, i.e. h = 0).
-// Byte offsets within a plane: oo of the chunk (own row and the other
-// plane's same row), uo / dof of the rows above / below, eo of the halo dword.
-template <int PAR, bool REC, bool HZ, bool NT>
-__device__ __forceinline__ void potts_chunk(uint8_t* own, const uint8_t* oth, uint32_t oo,
-                                            uint32_t uo, uint32_t dof, uint32_t eo, uint32_t p,
-                                            uint32_t rid, uint32_t k0, uint32_t k1,
-                                            const uint32_t* thr, const uint32_t* thr9, int q,
-                                            int ntab, uint32_t lem_thr, PottsAcc& acc,
-                                            int* lhist) {
-    const uint4 o = load_own<NT>(own + oo);
-    const uint4 m = *reinterpret_cast<const uint4*>(oth + oo);
-    const uint4 U = *reinterpret_cast<const uint4*>(oth + uo);
-    const uint4 D = *reinterpret_cast<const uint4*>(oth + dof);
-    const uint32_t e = *reinterpret_cast<const uint32_t*>(oth + eo);
-    const uint32_t ov[4] = {o.x, o.y, o.z, o.w};
-    const uint32_t mv[4] = {m.x, m.y, m.z, m.w};
-    const uint32_t Uv[4] = {U.x, U.y, U.z, U.w};
-    const uint32_t Dv[4] = {D.x, D.y, D.z, D.w};
-    uint32_t sv[4];
-    if (PAR == 0) {
-        sv[0] = __builtin_amdgcn_alignbyte(mv[0], e, 3);
-        sv[1] = __builtin_amdgcn_alignbyte(mv[1], mv[0], 3);
-        sv[2] = __builtin_amdgcn_alignbyte(mv[2], mv[1], 3);
-        sv[3] = __builtin_amdgcn_alignbyte(mv[3], mv[2], 3);
-    } else {
-        sv[0] = __builtin_amdgcn_alignbyte(mv[1], mv[0], 1);
-        sv[1] = __builtin_amdgcn_alignbyte(mv[2], mv[1], 1);
-        sv[2] = __builtin_amdgcn_alignbyte(mv[3], mv[2], 1);
-        sv[3] = __builtin_amdgcn_alignbyte(e, mv[3], 1);
-    }
-    const uint32_t kb = oo;
-    uint32_t w[16];
+// a where m, b elsewhere.
+__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
+}
+
+// Word j >> 2 of NW (2 or 4), by value.
+template <int NW>
+__device__ __forceinline__ uint32_t word_of(const uint32_t (&v)[NW], uint32_t j) {
+    const uint32_t a = v[0], b = v[1], c = v[NW - 2], d = v[NW - 1];
+    return j < 8u ? (j < 4u ? a : b) : (j < 12u ? c : d);
+}
+
+// 4 NW sites, a whole number of Philox blocks from within-colour index kb on;
+// neighbours as in ising_core.  About 430 VALU slots for 16 sites (kPottsFast), 220
+// of them the four Philox blocks; counting neighbours flag by flag takes 520.  Passes
+// over lattices in memory gain little (64 of 1024 x 1024: 29 us, 100 MB at 3.5 TB/s), but
+// recorded ones do: 59 -> 35 us a pass for q = 4, the labels counted from bit planes.
+template <int NW, int PATH>
+__device__ __forceinline__ void potts_core(const uint32_t (&ov)[NW], const uint32_t (&mv)[NW],
+                                           const uint32_t (&sv)[NW], const uint32_t (&Uv)[NW],
+                                           const uint32_t (&Dv)[NW], uint32_t kb, uint32_t p,
+                                           uint32_t rid, uint32_t k0, uint32_t k1,
+                                           const uint32_t* tab, int q, int ntab, uint32_t lem_thr,
+                                           uint32_t (&nv)[NW]) {
+    constexpr int NS = 4 * NW;
+    uint32_t w[NS];
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NW; ++b)
         philox4x32_10((kb >> 2) + (uint32_t)b, p, rid, kTagMain, k0, k1, &w[4 * b]);
     const uint32_t mq = (uint32_t)(q - 1);
     // proposals s' = s + 1 + off (mod q), off uniform in [0, q-1): off is
     // byte 2 of the 16-bit Lemire product (< 2^24), and the smallest low half
     // of the products flags a rejection anywhere
-    uint32_t pr[16];
+    uint32_t pr[NS];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) pr[j] = __umul24(w[j] & 0xFFFFu, mq);  // full-rate 24-bit multiply
+    for (int j = 0; j < NS; ++j) pr[j] = __umul24(w[j] & 0xFFFFu, mq);  // full-rate 24-bit multiply
     // Bytewise: t = s + 1 + off <= 2q - 2 < 256; u = t + (128 - q) has bit 7
     // set iff t >= q (and stays below 256); those bytes take t - q.
     const uint32_t Cb = (uint32_t)(128 - q) * 0x01010101u;
     const uint32_t Cb1 = Cb + 0x01010101u;
-    uint32_t s2v[4];
-    if (q <= 64) {
-        // t < 128: the bytes with t >= q take the low seven bits of u
-        // (u - 128 = t - q), the others u - (128 - q) = t, in one select
+    uint32_t s2v[NW];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t offs = __builtin_amdgcn_perm(pr[4 * k + 1], pr[4 * k], 0x0C0C0602u) |
-                                  __builtin_amdgcn_perm(pr[4 * k + 3], pr[4 * k + 2], 0x06020C0Cu);
-            const uint32_t u = ov[k] + offs + Cb1;
-            const uint32_t G = u & 0x80808080u;
-            const uint32_t M = G - (G >> 7);  // 0x7F in the bytes with t >= q
-            s2v[k] = (u & M) | ((u - Cb) & ~M);
-        }
-    } else {
-        const uint32_t Qb = (uint32_t)q * 0x01010101u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t offs = __builtin_amdgcn_perm(pr[4 * k + 1], pr[4 * k], 0x0C0C0602u) |
-                                  __builtin_amdgcn_perm(pr[4 * k + 3], pr[4 * k + 2], 0x06020C0Cu);
-            const uint32_t u = ov[k] + offs + Cb1;
-            const uint32_t ge = u & 0x80808080u;
-            const uint32_t wrap = ((ge << 1) - (ge >> 7)) & Qb;  // q in the bytes with t >= q
-            s2v[k] = u - Cb - wrap;
+    for (int k = 0; k < NW; ++k) {
+        const uint32_t offs = __builtin_amdgcn_perm(pr[4 * k + 1], pr[4 * k], 0x0C0C0602u) |
+                              __builtin_amdgcn_perm(pr[4 * k + 3], pr[4 * k + 2], 0x06020C0Cu);
+        const uint32_t u = ov[k] + offs + Cb1;
+        const uint32_t G = u & 0x80808080u;
+        if (PATH == kPottsFast || q <= 64) {
+            // t < 128: the bytes with t >= q take the low seven bits of u
+            // (u - 128 = t - q), the others u - (128 - q) = t, in one select
+            s2v[k] = bfi(G - (G >> 7), u, u - Cb);
+        } else {
+            const uint32_t Qb = (uint32_t)q * 0x01010101u;
+            s2v[k] = u - Cb - (((G << 1) - (G >> 7)) & Qb);
         }
     }
     // a rejected 16-bit Lemire draw (low half of the product below
     // 2^16 mod (q - 1)) is redrawn from the fallback stream; none are
     // rejected when q - 1 divides 2^16
-    uint32_t lmin = 0xFFFFFFFFu;
     if (lem_thr != 0u) {
-        // low halves compared in pairs (one word-select min per pair)
+        uint16_t lmin = 0xFFFF;
 #pragma unroll
-        for (int j = 0; j < 16; j += 2) lmin = min(lmin, min(pr[j] & 0xFFFFu, pr[j + 1] & 0xFFFFu));
-    }
-    if (lmin < lem_thr) {
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t prod = __umul24(w[j] & 0xFFFFu, mq);
-            if ((prod & 0xFFFFu) >= lem_thr) continue;
-            uint32_t f[4];
-            philox4x32_10(kb + (uint32_t)j, p, rid, kTagFallback, k0, k1, f);
-            const uint32_t s = (ov[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-            const uint32_t off = (uint32_t)(((uint64_t)f[1] * (uint64_t)mq) >> 32);
-            const uint32_t s2 = s + 1u + off;
-            const int sh = 8 * (j & 3);
-            s2v[j >> 2] = (s2v[j >> 2] & ~(0xFFu << sh)) | (min(s2, s2 - (uint32_t)q) << sh);
+        for (int j = 0; j < NS; ++j) lmin = min(lmin, (uint16_t)pr[j]);
+        if (lmin < lem_thr) {
+            uint32_t redo = 0u;
+#pragma unroll
+            for (int j = 0; j < NS; ++j) redo |= (pr[j] & 0xFFFFu) < lem_thr ? 1u << j : 0u;
+            while (redo != 0u) {
+                const uint32_t j = (uint32_t)__builtin_ctz(redo), sh = 8u * (j & 3u);
+                redo &= redo - 1u;
+                uint32_t f[4];
+                philox4x32_10(kb + j, p, rid, kTagFallback, k0, k1, f);
+                const uint32_t off = (uint32_t)(((uint64_t)f[1] * (uint64_t)mq) >> 32);
+                const uint32_t t = ((word_of(ov, j) >> sh) & 0xFFu) + 1u + off;
+                const uint32_t x = min(t, t - (uint32_t)q) << sh;
+#pragma unroll
+                for (int k = 0; k < NW; ++k)
+                    s2v[k] = bfi((j >> 2) == (uint32_t)k ? 0xFFu << sh : 0u, x, s2v[k]);
+            }
         }
     }
-    // dn + 4 = #ne(s) - #ne(s') + 4 = #ne(s) + #eq(s') per byte.  Labels
-    // below 2^b (b <= 4): ((a ^ c) + (2^b - 1)) has bit b set iff a != c;
-    // the eight flags (unequal to s, equal to s') sum to (4 + dn) 2^b < 256
-    // in each byte, so no per-flag shift is needed.
-    uint32_t dn4[4];
-    if (q <= 16) {
+    // The class of a site by dn + 4 = #ne(s) + #eq(s'), per byte of cls.
+    uint32_t cls[NW];
+    if (PATH == kPottsFast) {
+        // s and s' side by side in the nibbles of a byte, compared with a
+        // neighbour at once: bit 3 of each nibble of (x ^ c) + 7 is set iff they
+        // differ.  The four neighbours' flags gather in a nibble each: the
+        // pattern of a site, whose threshold the table holds.
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const uint32_t x = ov[k] | (s2v[k] << 4);
+            const uint32_t t0 = (x ^ (mv[k] | (mv[k] << 4))) + 0x77777777u;
+            const uint32_t t1 = (x ^ (sv[k] | (sv[k] << 4))) + 0x77777777u;
+            const uint32_t t2 = (x ^ (Uv[k] | (Uv[k] << 4))) + 0x77777777u;
+            const uint32_t t3 = (x ^ (Dv[k] | (Dv[k] << 4))) + 0x77777777u;
+            const uint32_t a = bfi(0x88888888u, t0, t1 >> 1), b = bfi(0x88888888u, t2, t3 >> 1);
+            cls[k] = bfi(0xCCCCCCCCu, a, b >> 2);
+        }
+    } else if (q <= 16) {
+        // Labels below 2^b (b <= 4): ((a ^ c) + (2^b - 1)) has bit b set iff
+        // a != c; the eight flags (unequal to s, equal to s') sum to
+        // (4 + dn) 2^b < 256 in each byte, so no per-flag shift is needed.
         const int b = q <= 2 ? 1 : 32 - __clz(q - 1);
         const uint32_t F = 0x01010101u << b, A = F - 0x01010101u;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NW; ++k) {
             const uint32_t neo = (((ov[k] ^ mv[k]) + A) & F) + (((ov[k] ^ sv[k]) + A) & F) +
                                  (((ov[k] ^ Uv[k]) + A) & F) + (((ov[k] ^ Dv[k]) + A) & F);
             const uint32_t eqn = (~((s2v[k] ^ mv[k]) + A) & F) + (~((s2v[k] ^ sv[k]) + A) & F) +
                                  (~((s2v[k] ^ Uv[k]) + A) & F) + (~((s2v[k] ^ Dv[k]) + A) & F);
-            dn4[k] = (neo + eqn) >> b;
+            cls[k] = (neo + eqn) >> b;
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NW; ++k) {
             const uint32_t neo = (ne_hi(ov[k], mv[k]) >> 7) + (ne_hi(ov[k], sv[k]) >> 7) +
                                  (ne_hi(ov[k], Uv[k]) >> 7) + (ne_hi(ov[k], Dv[k]) >> 7);
             const uint32_t nen = (ne_hi(s2v[k], mv[k]) >> 7) + (ne_hi(s2v[k], sv[k]) >> 7) +
                                  (ne_hi(s2v[k], Uv[k]) >> 7) + (ne_hi(s2v[k], Dv[k]) >> 7);
-            dn4[k] = neo + 0x04040404u - nen;
+            cls[k] = neo + 0x04040404u - nen;
         }
     }
-    // Class: (dn+4)(2q-1) + (s'-s+q-1); with h = 0 the threshold depends on dn
-    // only and thr9 holds the 9 (hi | lo) entries.  d = r - T_hi unsigned:
-    // bit 31 set iff the prefix accepts, 0 iff it ties.
+    // Threshold of pattern or dn + 4, or (with a field) of (dn + 4)(2q - 1) +
+    // (s' - s + q - 1).  d = r - T_hi unsigned: bit 31 set iff the prefix
+    // accepts, 0 iff it ties.
     const uint32_t wq = (uint32_t)(2 * q - 1);
-    uint32_t d[16];
+    const uint32_t* t9 = tab + kPatternWords;
+    const uint32_t* thr = tab + kPottsTabWords;
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_u32_t)(PATH == kPottsFast ? tab : t9);
+    uint32_t d[NS];
     uint32_t dmin = 0xFFFFFFFFu;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
+    for (int j = 0; j < NS; ++j) {
         const int sh = 8 * (j & 3);
-        const uint32_t d4 = (dn4[j >> 2] >> sh) & 0xFFu;
         uint32_t th;
-        if (HZ) {
-            th = thr9[d4];
+        if (PATH != kPottsAny) {
+            const uint32_t at = __builtin_amdgcn_udot4(cls[j >> 2], 4u << sh, base, false);
+            th = *(lds_u32_t)(uintptr_t)at;
         } else {
             const uint32_t s = (ov[j >> 2] >> sh) & 0xFFu;
             const uint32_t s2 = (s2v[j >> 2] >> sh) & 0xFFu;
-            th = thr[__umul24(d4, wq) + s2 + (uint32_t)(q - 1) - s];
+            th = thr[__umul24((cls[j >> 2] >> sh) & 0xFFu, wq) + s2 + (uint32_t)(q - 1) - s];
         }
         d[j] = (w[j] >> 16) - th;
         dmin = min(dmin, d[j]);
     }
-    uint32_t acc_sel[4];  // 0xFF in bytes that accept
+    uint32_t acc_sel[NW];  // 0xFF in bytes that accept
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < NW; ++k)
         acc_sel[k] = sign_bytes(d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]);
     if (dmin == 0u) {
         // a prefix equals the threshold's high half: the low halves decide
-        for (int j = 0; j < 16; ++j) {
-            if (d[j] != 0u) continue;
-            const int sh = 8 * (j & 3);
-            const uint32_t d4 = (dn4[j >> 2] >> sh) & 0xFFu;
+        uint32_t tie = 0u;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) tie |= d[j] == 0u ? 1u << j : 0u;
+        while (tie != 0u) {
+            const uint32_t j = (uint32_t)__builtin_ctz(tie), sh = 8u * (j & 3u);
+            tie &= tie - 1u;
+            const uint32_t c = (word_of(cls, j) >> sh) & 0xFFu;
             uint32_t lo;
-            if (HZ) {
-                lo = thr9[9 + d4];
+            if (PATH == kPottsFast) {
+                lo = t9[9u + __popc(c & 15u) + 4u - __popc(c >> 4)];
+            } else if (PATH == kPottsNoField) {
+                lo = t9[9u + c];
             } else {
-                const uint32_t s = (ov[j >> 2] >> sh) & 0xFFu;
-                const uint32_t s2 = (s2v[j >> 2] >> sh) & 0xFFu;
-                lo = thr[ntab + __umul24(d4, wq) + s2 + (uint32_t)(q - 1) - s];
+                const uint32_t s = (word_of(ov, j) >> sh) & 0xFFu;
+                const uint32_t s2 = (word_of(s2v, j) >> sh) & 0xFFu;
+                lo = thr[(uint32_t)ntab + __umul24(c, wq) + s2 + (uint32_t)(q - 1) - s];
             }
             if (lo == 0u) continue;
             uint32_t f[4];
-            philox4x32_10(kb + (uint32_t)j, p, rid, kTagFallback, k0, k1, f);
-            if ((f[0] & 0xFFFFu) < lo) acc_sel[j >> 2] |= 0xFFu << sh;
+            philox4x32_10(kb + j, p, rid, kTagFallback, k0, k1, f);
+            if ((f[0] & 0xFFFFu) < lo) {
+#pragma unroll
+                for (int k = 0; k < NW; ++k)
+                    acc_sel[k] |= (j >> 2) == (uint32_t)k ? 0xFFu << sh : 0u;
+            }
         }
     }
-    uint32_t nv[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) nv[k] = (s2v[k] & acc_sel[k]) | (ov[k] & ~acc_sel[k]);
-    store_own<NT>(own + oo, nv[0], nv[1], nv[2], nv[3]);
-    if (REC) {
-        uint32_t nex = 0u, ney = 0u, ssum = 0u;
+    for (int k = 0; k < NW; ++k) nv[k] = bfi(acc_sel[k], s2v[k], ov[k]);
+}
+
+// Labels 0 .. 7 of two planes' words counted from bit planes: the labels of 8 NW
+// sites as nibbles, one word a bit, and a population count for each label.
+template <int NW>
+__device__ __forceinline__ void count_labels8(const uint32_t (&a)[NW], const uint32_t (&b)[NW],
+                                              int (&n)[8]) {
+    uint32_t B[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            nex = sad_u8((ne_hi(nv[k], mv[k]) >> 7) + (ne_hi(nv[k], sv[k]) >> 7), nex);
-            ney = sad_u8((ne_hi(nv[k], Uv[k]) >> 7) + (ne_hi(nv[k], Dv[k]) >> 7), ney);
-            ssum = sad_u8(nv[k], ssum);
-            ssum = sad_u8(mv[k], ssum);
+    for (int k = 0; k < NW; ++k) {
+        const uint32_t x = a[k] | (b[k] << 4);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t m = 0x11111111u << k;
+            B[i] = bfi(m, k >= i ? x << (k - i) : x >> (i - k), B[i]);
         }
-        acc.Nx += 32 - (int)nex;
-        acc.Ny += 32 - (int)ney;
-        acc.S += (int)ssum;
+    }
+    constexpr uint32_t all = NW == 4 ? ~0u : 0x33333333u;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+    for (int l = 0; l < 8; ++l)
+        n[l] += __popc(((l & 1) ? B[0] : ~B[0]) & ((l & 2) ? B[1] : ~B[1]) &
+                       ((l & 4) ? B[2] : (~B[2] & all)));
+}
+
+// Adds an item of a recorded sweep's colour-1 pass (every bond has one colour-1
+// end): equal bonds, label sum and the labels of both colours, those of q > 8 by
+// atomics in lhist.
+template <int NW>
+__device__ __forceinline__ void potts_count(const uint32_t (&nv)[NW], const uint32_t (&mv)[NW],
+                                            const uint32_t (&sv)[NW], const uint32_t (&Uv)[NW],
+                                            const uint32_t (&Dv)[NW], int q, PottsAcc& acc,
+                                            int* lhist) {
+    uint32_t nex = 0u, ney = 0u, ssum = 0u;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        nex = sad_u8((ne_hi(nv[k], mv[k]) >> 7) + (ne_hi(nv[k], sv[k]) >> 7), nex);
+        ney = sad_u8((ne_hi(nv[k], Uv[k]) >> 7) + (ne_hi(nv[k], Dv[k]) >> 7), ney);
+        ssum = sad_u8(nv[k], ssum);
+        ssum = sad_u8(mv[k], ssum);
+    }
+    acc.Nx += 8 * NW - (int)nex;
+    acc.Ny += 8 * NW - (int)ney;
+    acc.S += (int)ssum;
+    if (q <= 8) {
+        count_labels8(nv, mv, acc.n);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4 * NW; ++j) {
             atomicAdd(&lhist[(nv[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1);
             atomicAdd(&lhist[(mv[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1);
         }
     }
+}
+
+// Sum over the 16 lanes of a row (the n < 16 lanes of a group, a power of two).
+__device__ __forceinline__ int row_sum(int v, int n) {
+    // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
+    if (n > 1) v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
+    if (n > 2) v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
+    if (n > 4) v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
+    if (n > 8) v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
+    return v;
+}
+
+// Adds acc's labels (q <= 8) to lhist and (SUM) its sums to sum[3];
+// groups of n lanes (at least 16: any).  A group's lanes add one count each.
+template <bool SUM>
+__device__ __forceinline__ void add_counts(const PottsAcc& acc, int q, int n, int* lhist, int* sum) {
+    const int m = min(n, 16), lane = (int)threadIdx.x & (m - 1);
+    int v[11];
+#pragma unroll
+    for (int l = 0; l < 8; ++l) v[l] = q <= 8 ? row_sum(acc.n[l], n) : 0;
+    v[8] = row_sum(acc.Nx, n);
+    v[9] = row_sum(acc.Ny, n);
+    v[10] = row_sum(acc.S, n);
+    for (int k0 = 0; k0 < 11; k0 += m) {  // once where a group has 16 lanes
+        const int k = k0 + lane;
+        int x = v[0];
+#pragma unroll
+        for (int l = 1; l < 11; ++l) x = k == l ? v[l] : x;
+        if (k < 8) {
+            if (q <= 8) atomicAdd(&lhist[k], x);
+        } else if (k < 11 && SUM) {
+            atomicAdd(&sum[k - 8], x);
+        }
+    }
+}
+
+// 16-site Potts chunk of a plane in global memory.
+// Byte offsets within a plane: oo of the chunk (own row and the other
+// plane's same row), uo / dof of the rows above / below, eo of the halo dword.
+template <int PAR, bool REC, int PATH, bool NT>
+__device__ __forceinline__ void potts_chunk(uint8_t* own, const uint8_t* oth, uint32_t oo,
+                                            uint32_t uo, uint32_t dof, uint32_t eo, uint32_t p,
+                                            uint32_t rid, uint32_t k0, uint32_t k1,
+                                            const uint32_t* tab, int q, int ntab, uint32_t lem_thr,
+                                            PottsAcc& acc, int* lhist) {
+    const ChunkIn in = chunk_load<NT>(own, oth, oo, uo, dof, eo);
+    uint32_t ov[4], mv[4], Uv[4], Dv[4], nv[4], sv[4];
+    arr(in.o, ov);
+    arr(in.m, mv);
+    arr(in.U, Uv);
+    arr(in.D, Dv);
+    side_bytes(PAR, mv, in.e, sv);
+    potts_core<4, PATH>(ov, mv, sv, Uv, Dv, oo, p, rid, k0, k1, tab, q, ntab, lem_thr, nv);
+    store_own<NT>(own + oo, nv[0], nv[1], nv[2], nv[3]);
+    if (REC) potts_count(nv, mv, sv, Uv, Dv, q, acc, lhist);
 }
 
 // ------------------------------------------------- tile-level iteration
@@ -498,11 +633,10 @@ __device__ __forceinline__ void potts_chunk(uint8_t* own, const uint8_t* oth, ui
 // tid = 0..nthr-1 (a whole workgroup, or the share of one replica when a
 // workgroup holds several).  Rows are visited by parity so that PAR is
 // uniform across a wave.
-template <bool REC, bool HZ, bool NT>
+template <bool REC, int PATH, bool NT>
 __device__ __forceinline__ void run_tile_potts(uint8_t* planes, int W, int Ly, int y0, int rows,
                                                int c, uint32_t p, uint32_t rid, uint32_t k0,
-                                               uint32_t k1, const uint32_t* thr,
-                                               const uint32_t* thr9, int q, int ntab,
+                                               uint32_t k1, const uint32_t* tab, int q, int ntab,
                                                uint32_t lem_thr, PottsAcc& pa, int* lhist,
                                                int tid, int nthr) {
     uint8_t* own = planes + (size_t)c * Ly * W;
@@ -526,12 +660,12 @@ __device__ __forceinline__ void run_tile_potts(uint8_t* planes, int W, int Ly, i
         for (; ro < ro_end;) {
             if (par == 0) {
                 const ChunkOff<0> f(ro, j0, Wb, last);
-                potts_chunk<0, REC, HZ, NT>(own, oth, f.oo, f.uo, f.dof, f.eo, p, rid, k0, k1, thr,
-                                        thr9, q, ntab, lem_thr, pa, lhist);
+                potts_chunk<0, REC, PATH, NT>(own, oth, f.oo, f.uo, f.dof, f.eo, p, rid, k0, k1,
+                                              tab, q, ntab, lem_thr, pa, lhist);
             } else {
                 const ChunkOff<1> f(ro, j0, Wb, last);
-                potts_chunk<1, REC, HZ, NT>(own, oth, f.oo, f.uo, f.dof, f.eo, p, rid, k0, k1, thr,
-                                        thr9, q, ntab, lem_thr, pa, lhist);
+                potts_chunk<1, REC, PATH, NT>(own, oth, f.oo, f.uo, f.dof, f.eo, p, rid, k0, k1,
+                                              tab, q, ntab, lem_thr, pa, lhist);
             }
             ro += dro;
             j0 += dj0;
@@ -596,31 +730,23 @@ __device__ __forceinline__ uint32_t lemire_threshold(int q) {
     return 65536u % (uint32_t)(q - 1);
 }
 
-// The 9 Potts thresholds of the dn classes (hi | lo) for h = 0, where the
-// class no longer depends on s' - s (column s' = s of the full table).
-__device__ __forceinline__ void load_table9(const uint32_t* tab, const RepDev& R, uint32_t* t9,
-                                            int tid) {
-    if (R.model != kModelPotts) return;
-    const int wq = 2 * R.q - 1;
-    if (tid < 18) {
-        const int i = tid % 9, half = tid / 9;
-        t9[tid] = tab[R.tab_off + half * R.tab_n + i * wq + R.q - 1];
-    }
-}
-
-// Potts tile with the h = 0 specialisation chosen per replica.
+// Potts tile with the rule chosen per replica.
 template <bool REC, bool NT>
 __device__ __forceinline__ void potts_tile(const RepDev& R, uint8_t* planes, int y0, int rows,
                                            int c, uint32_t p, uint32_t k0, uint32_t k1,
-                                           const uint32_t* thr, const uint32_t* thr9,
-                                           PottsAcc& pa, int* lhist, int tid, int nthr) {
+                                           const uint32_t* tab, PottsAcc& pa, int* lhist, int tid,
+                                           int nthr) {
     const uint32_t lt = lemire_threshold(R.q);
-    if (R.h == 0.0f)
-        run_tile_potts<REC, true, NT>(planes, R.W, R.Ly, y0, rows, c, p, R.rid, k0, k1, thr, thr9, R.q,
-                                  R.tab_n, lt, pa, lhist, tid, nthr);
+    const int path = potts_path(R);
+    if (path == kPottsFast)
+        run_tile_potts<REC, kPottsFast, NT>(planes, R.W, R.Ly, y0, rows, c, p, R.rid, k0, k1, tab,
+                                            R.q, R.tab_n, lt, pa, lhist, tid, nthr);
+    else if (path == kPottsNoField)
+        run_tile_potts<REC, kPottsNoField, NT>(planes, R.W, R.Ly, y0, rows, c, p, R.rid, k0, k1,
+                                               tab, R.q, R.tab_n, lt, pa, lhist, tid, nthr);
     else
-        run_tile_potts<REC, false, NT>(planes, R.W, R.Ly, y0, rows, c, p, R.rid, k0, k1, thr, thr9,
-                                   R.q, R.tab_n, lt, pa, lhist, tid, nthr);
+        run_tile_potts<REC, kPottsAny, NT>(planes, R.W, R.Ly, y0, rows, c, p, R.rid, k0, k1, tab,
+                                           R.q, R.tab_n, lt, pa, lhist, tid, nthr);
 }
 
 // XCD-aware block order: consecutive logical units land on one XCD (blocks
@@ -642,24 +768,24 @@ __device__ __forceinline__ int logical_block(int n) {
 template <int MODEL, bool NT>
 __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, int n, int c,
                                                  int sweep_off, int rec_row, uint32_t* lthr,
-                                                 uint32_t* lthr9, int* lhist, int* lred) {
+                                                 int* lhist, int* lred) {
     const TileDev T = a.tiles[tile0 + logical_block(n)];
     const RepDev R = a.reps[T.rep];
     if (MODEL == kModelPotts) {
-        load_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
-        load_table9(a.tab, R, lthr9, threadIdx.x);
+        load_potts_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
     } else {
         load_ising_table(a.tab, R, lthr, threadIdx.x, blockDim.x);
     }
     const bool rec = (rec_row >= 0) && (c == 1);
     if (MODEL == kModelPotts && rec)
-        for (int i = threadIdx.x; i < R.q; i += blockDim.x) lhist[i] = 0;
+        for (int i = threadIdx.x; i < max(R.q, 8); i += blockDim.x) lhist[i] = 0;
     __syncthreads();
     const uint64_t t = *a.t_base + (uint64_t)sweep_off;
     const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
     uint8_t* planes = a.lat + R.lat_off;
     IsingAcc ia{0, 0, 0};
-    PottsAcc pa{0, 0, 0};
+    PottsAcc pa;
+    pa.clear();
     if (MODEL == kModelIsing) {
         if (rec)
             run_tile_ising<true, NT>(planes, R.W, R.Ly, T.y0, T.rows, c, p, R.rid, a.key0, a.key1,
@@ -669,11 +795,11 @@ __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, 
                                   lthr, ia, threadIdx.x, blockDim.x);
     } else {
         if (rec)
-            potts_tile<true, NT>(R, planes, T.y0, T.rows, c, p, a.key0, a.key1, lthr, lthr9, pa,
-                             lhist, threadIdx.x, blockDim.x);
+            potts_tile<true, NT>(R, planes, T.y0, T.rows, c, p, a.key0, a.key1, lthr, pa, lhist,
+                                 threadIdx.x, blockDim.x);
         else
-            potts_tile<false, NT>(R, planes, T.y0, T.rows, c, p, a.key0, a.key1, lthr, lthr9, pa,
-                              lhist, threadIdx.x, blockDim.x);
+            potts_tile<false, NT>(R, planes, T.y0, T.rows, c, p, a.key0, a.key1, lthr, pa, lhist,
+                                  threadIdx.x, blockDim.x);
     }
     if (rec) {
         int v[3];
@@ -682,6 +808,7 @@ __device__ __forceinline__ void stream_pass_body(const SweepArgs& a, int tile0, 
         } else {
             v[0] = pa.Nx; v[1] = pa.Ny; v[2] = pa.S;
         }
+        if (MODEL == kModelPotts && R.q <= 8) add_counts<false>(pa, R.q, 64, lhist, nullptr);
         block_sum<3>(v, lred);
         int32_t* row = a.stats + ((size_t)rec_row * a.R + T.rep) * a.width;
         if (threadIdx.x == 0) {
@@ -704,18 +831,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6, 8))
 k_stream_pass_ising(SweepArgs a, int tile0, int n, int c, int sweep_off, int rec_row) {
     __shared__ uint32_t tab[kIsingTabWords];  // thresholds of this tile's replica
     __shared__ int lred[64];
-    stream_pass_body<kModelIsing, NT>(a, tile0, n, c, sweep_off, rec_row, tab, nullptr, nullptr,
-                                      lred);
+    stream_pass_body<kModelIsing, NT>(a, tile0, n, c, sweep_off, rec_row, tab, nullptr, lred);
 }
 
 template <bool NT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 8)))
 k_stream_pass_potts(SweepArgs a, int tile0, int n, int c, int sweep_off, int rec_row) {
-    extern __shared__ uint32_t lthr[];
-    __shared__ uint32_t lthr9[18];
+    extern __shared__ uint32_t lthr[];  // kPottsTabWords, with fields the whole table too
     __shared__ int lhist[kMaxPottsQ];
     __shared__ int lred[64];
-    stream_pass_body<kModelPotts, NT>(a, tile0, n, c, sweep_off, rec_row, lthr, lthr9, lhist, lred);
+    stream_pass_body<kModelPotts, NT>(a, tile0, n, c, sweep_off, rec_row, lthr, lhist, lred);
 }
 
 // ------------------------------------------------- persistent streamed passes
@@ -779,14 +904,12 @@ __device__ __forceinline__ void persist_body(const SweepArgs& a, const PersistIt
                                              uint32_t* abort_flag, int slot_words, uint32_t* lds,
                                              int* go) {
     const int i0 = item_off[blockIdx.x], i1 = item_off[blockIdx.x + 1];
-    // threshold tables of the items' replicas (Potts: the h = 0 table of 9
-    // entries in the last 18 words of the slot)
+    // threshold tables of the items' replicas
     for (int k = i0; k < i1; ++k) {
         const RepDev R = a.reps[items[k].rep];
         uint32_t* t = lds + (k - i0) * slot_words;
         if (MODEL == kModelPotts) {
-            load_table(a.tab, R, t, threadIdx.x, blockDim.x);
-            load_table9(a.tab, R, t + slot_words - 18, threadIdx.x);
+            load_potts_table(a.tab, R, t, threadIdx.x, blockDim.x);
         } else {
             load_ising_table(a.tab, R, t, threadIdx.x, blockDim.x);
         }
@@ -813,10 +936,10 @@ __device__ __forceinline__ void persist_body(const SweepArgs& a, const PersistIt
                                                     a.key0, a.key1, tab, ia, threadIdx.x,
                                                     blockDim.x);
                 } else {
-                    PottsAcc pa{0, 0, 0};
-                    potts_tile<false, NT>(R, planes, it.y0, it.rows, c, p, a.key0, a.key1, tab,
-                                          tab + slot_words - 18, pa, nullptr, threadIdx.x,
-                                          blockDim.x);
+                    PottsAcc pa;
+                    pa.clear();
+                    potts_tile<false, NT>(R, planes, it.y0, it.rows, c, p, a.key0, a.key1, tab, pa,
+                                          nullptr, threadIdx.x, blockDim.x);
                 }
                 if (it.slab >= 0) {
                     wait_stores();
@@ -956,15 +1079,11 @@ __device__ __forceinline__ void lattice_stats(int model, const uint8_t* planes, 
 // Resident kernel: a workgroup owns a.rpb replicas of one shape for the
 // whole call, each with its thresholds and both planes in LDS, and
 // blockDim/rpb threads; colour passes are separated by workgroup barriers.
-// KIND selects the path: kResPotts runs the 16-byte SWAR chunks (W % 16 == 0,
-// every replica of the launch of that model), kResGeneric the per-site code for
-// any model and width.  Ising chunks have k_resident_ising.
-template <int KIND>
-__device__ __forceinline__ void resident_body(const SweepArgs& a) {
-    constexpr bool CHUNK = KIND != kResGeneric;
+// Site by site for any model and width: lattices narrower than 16 (plane rows
+// below 8 bytes); all others have the kernels of items below.
+__global__ void __launch_bounds__(512) k_resident_generic(SweepArgs a) {
     // dynamic LDS: rpb slots of [thresholds (tab_lds_bytes) | plane 0 | plane 1]
     extern __shared__ __align__(16) uint8_t dyn[];
-    __shared__ uint32_t lthr9[kMaxRpb][18];
     __shared__ int lhist[kMaxPottsQ];
     __shared__ int lred[64];
     const int P = a.rpb;
@@ -988,7 +1107,6 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
             for (int i = lt; i < bytes; i += nt) lds[i] = gmem[i];
         }
         load_table(a.tab, R, lthr, lt, nt);
-        load_table9(a.tab, R, lthr9[g], lt);
     }
     __syncthreads();
     const uint64_t t0 = *a.t_base;
@@ -999,15 +1117,9 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
         for (int c = 0; c < 2; ++c) {
             const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
             if (active) {
-                if (KIND == kResPotts) {
-                    PottsAcc pa{0, 0, 0};
-                    potts_tile<false, false>(R, lds, 0, R.Ly, c, p, a.key0, a.key1, lthr, lthr9[g], pa,
-                                      lhist, lt, nt);
-                } else {
-                    for (int k = lt; k < plane; k += nt)
-                        generic_site(R.model, lds, R.W, R.Ly, c, k, p, R.rid, a.key0, a.key1,
-                                     lthr, R.q, R.tab_n);
-                }
+                for (int k = lt; k < plane; k += nt)
+                    generic_site(R.model, lds, R.W, R.Ly, c, k, p, R.rid, a.key0, a.key1, lthr,
+                                 R.q, R.tab_n);
             }
             __syncthreads();
         }
@@ -1050,11 +1162,7 @@ __device__ __forceinline__ void resident_body(const SweepArgs& a) {
     }
 }
 
-__global__ void __launch_bounds__(512) k_resident_generic(SweepArgs a) {
-    resident_body<kResGeneric>(a);
-}
-
-// ------------------------------------------------ resident Ising chunks
+// ------------------------------------------------------ resident items
 namespace {
 
 // The lanes of one replica meet: a barrier, or where a replica has at most a
@@ -1067,6 +1175,8 @@ __device__ __forceinline__ void replica_sync(bool waves) {
         __builtin_amdgcn_wave_barrier();
     }
 }
+
+constexpr int kPottsRecRows = 16;  // as kRecRows, of the Potts kernel
 
 // Recorded sweeps of a replica: its lanes add their counts in LDS, kRecRows rows
 // at a time, so that no sweep waits for a reduction or for global memory.
@@ -1091,28 +1201,16 @@ struct RecRows {
     // byte-wise counts; sums of 16 lanes (or of the nt < 16
     // lanes of a replica) by data-parallel-primitive moves, then LDS atomics
     __device__ __forceinline__ void add(uint32_t up, uint32_t dx, uint32_t dy, int nt) {
-        int u = (int)sad_u8(up, 0u), b = (int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16));
-        // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
-        if (nt > 1) {
-            u += __builtin_amdgcn_update_dpp(0, u, 0xB1, 0xf, 0xf, true);
-            b += __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xf, 0xf, true);
-        }
-        if (nt > 2) {
-            u += __builtin_amdgcn_update_dpp(0, u, 0x4E, 0xf, 0xf, true);
-            b += __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xf, 0xf, true);
-        }
-        if (nt > 4) {
-            u += __builtin_amdgcn_update_dpp(0, u, 0x141, 0xf, 0xf, true);
-            b += __builtin_amdgcn_update_dpp(0, b, 0x141, 0xf, 0xf, true);
-        }
-        if (nt > 8) {
-            u += __builtin_amdgcn_update_dpp(0, u, 0x140, 0xf, 0xf, true);
-            b += __builtin_amdgcn_update_dpp(0, b, 0x140, 0xf, 0xf, true);
-        }
-        if (((int)threadIdx.x & (min(nt, 16) - 1)) == 0) {
-            atomicAdd(&l[n][0], u);
-            atomicAdd(&l[n][1], b & 0xFFFF);
-            atomicAdd(&l[n][2], (int)((uint32_t)b >> 16));
+        const int u = row_sum((int)sad_u8(up, 0u), nt);
+        const int b = row_sum((int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16)), nt);
+        // lanes 0, 1, 2 of a group add one count each (sub-groups below four lanes:
+        // their first lane all)
+        const int lane = (int)threadIdx.x & (min(nt, 16) - 1);
+        const int v[3] = {u, b & 0xFFFF, (int)((uint32_t)b >> 16)};
+        if (nt >= 4) {
+            if (lane < 3) atomicAdd(&l[n][lane], lane == 0 ? v[0] : lane == 1 ? v[1] : v[2]);
+        } else if (lane == 0) {
+            for (int k = 0; k < 3; ++k) atomicAdd(&l[n][k], v[k]);
         }
     }
     // stores (SLAB: adds, the rows hold zeros or other slabs' shares) and clears
@@ -1282,9 +1380,12 @@ struct Item8 {
                            // starts here and starting the row that ends here
     uint32_t left[2];      // bytes whose side neighbour is the left one in colour 0
     uint32_t end[2], start[2];  // !AL: the bytes e and s
-    __device__ __forceinline__ void init(uint32_t item, uint32_t W, uint32_t plane) {
+    // inv = 1 / W: k <= 2^16 and W >= 8, so (k + 1/2) inv is off by less than its
+    // distance from a whole number, 1 / (2 W)
+    __device__ __forceinline__ void init(uint32_t item, uint32_t W, float inv, uint32_t plane) {
         k = 8u * item;
-        const uint32_t y = k / W, j = k - y * W, row = k - j;
+        const uint32_t y = (uint32_t)(((float)k + 0.5f) * inv), j = k - __umul24(y, W);
+        const uint32_t row = k - j;
         uo = k < W ? k + plane - W : k - W;
         dof = k + W >= plane ? k + W - plane : k + W;
         if (AL) {
@@ -1381,12 +1482,47 @@ __device__ __forceinline__ void near8(const Item8<AL>& t, const uint8_t* oth, in
     }
 }
 
+// Both planes of a lattice between memory and LDS (with their repeats), by lanes
+// lt = 0 .. nt - 1.
+template <bool AL>
+__device__ __forceinline__ void load_planes8(uint8_t* lds, const uint8_t* gmem, uint32_t plane,
+                                             uint32_t stride, uint32_t lt, uint32_t nt) {
+    if (AL || (plane & 7u) == 0u) {
+        for (uint32_t k = 8u * lt; k < plane; k += 8u * nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                store8<AL>(lds + c * stride, k, plane,
+                           *reinterpret_cast<const uint2*>(gmem + c * plane + k));
+    } else {
+        for (uint32_t i = lt; i < plane + 8u; i += nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                lds[c * stride + i] = gmem[c * plane + (i < plane ? i : i - plane)];
+    }
+}
+
+template <bool AL>
+__device__ __forceinline__ void store_planes8(uint8_t* gmem, const uint8_t* lds, uint32_t plane,
+                                              uint32_t stride, uint32_t lt, uint32_t nt) {
+    if (AL || (plane & 7u) == 0u) {
+        for (uint32_t k = 8u * lt; k < plane; k += 8u * nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c)
+                *reinterpret_cast<uint2*>(gmem + c * plane + k) =
+                    *reinterpret_cast<const uint2*>(lds + c * stride + k);
+    } else {
+        for (uint32_t i = lt; i < plane; i += nt)
+#pragma unroll
+            for (uint32_t c = 0; c < 2u; ++c) gmem[c * plane + i] = lds[c * stride + i];
+    }
+}
+
 }  // namespace
 
 // The resident kernel for items of eight sites: a lane takes one Philox block a
 // pass instead of four, so a small lattice spreads over four times as many lanes
 // and a pass is a quarter of the chain of instructions.  It serves lattices
-// whose waves leave the chip idle (one 32 x 32 lattice, recorded: 1.1 us a sweep
+// whose waves leave the chip idle (one 32 x 32 lattice, recorded: 0.9 us a sweep
 // against 2.7) and, without AL, every other width from 18 on (k_resident_generic
 // draws a block for every site: 100 lattices of 300 x 300, 20 sweeps and the
 // gradients 2064 us, now 405).
@@ -1399,7 +1535,7 @@ __device__ __forceinline__ void near8(const Item8<AL>& t, const uint8_t* oth, in
 // n_sweeps <= a.halo / 2 sweeps on that window and writes its own rows to a.lat:
 // the window's outermost valid row moves inwards by one a pass, since every
 // site's draws depend on its place alone, so the slabs need no exchange between
-// launches (64 lattices of 256 x 256: @S1@ us a sweep in 512 slabs, @S0@ whole).
+// launches (64 lattices of 256 x 256: 2.7 us a sweep in slabs, 4.4 whole).
 template <bool AL, int NI, bool UNI, bool SLAB>
 __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     // dynamic LDS: rpb slots of [thresholds (kIsingTabWords) | plane 0 and its repeat |
@@ -1420,6 +1556,7 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     const int rows = SLAB ? T.rows + 2 * a.halo : R.Ly;
     const uint32_t W = (uint32_t)R.W, plane = (uint32_t)rows * W, rid = R.rid;
     const uint32_t gplane = (uint32_t)R.Ly * W;
+    const float inv = 1.0f / (float)W;
     const uint32_t stride = (plane + 15u) & ~7u;
     uint8_t* slot = dyn + (size_t)(active ? g : 0) * a.res_slot_bytes;
     uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
@@ -1433,18 +1570,15 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     };
     const uint32_t n_items = active ? (plane + 7u) >> 3 : 0u;
     if (active) load_ising_table(a.tab, R, tab, lt, nt);
-    if (AL || (plane & 7u) == 0u) {
+    if (SLAB) {
         for (uint32_t i = lt; i < n_items; i += (uint32_t)nt)
 #pragma unroll
             for (uint32_t c = 0; c < 2u; ++c)
-                store8<AL>(lds + c * stride, 8u * i, plane,
-                           *reinterpret_cast<const uint2*>((SLAB ? a.lat_src + R.lat_off : gmem) +
-                                                           c * gplane + place(8u * i)));
-    } else if (active) {  // with the repeated bytes
-        for (uint32_t i = lt; i < plane + 8u; i += (uint32_t)nt)
-#pragma unroll
-            for (uint32_t c = 0; c < 2u; ++c)
-                lds[c * stride + i] = gmem[c * plane + (i < plane ? i : i - plane)];
+                *reinterpret_cast<uint2*>(lds + c * stride + 8u * i) =
+                    *reinterpret_cast<const uint2*>(a.lat_src + R.lat_off + c * gplane +
+                                                    place(8u * i));
+    } else if (active) {
+        load_planes8<AL>(lds, gmem, plane, stride, (uint32_t)lt, (uint32_t)nt);
     }
     constexpr int NR = NI > 0 ? NI : 1;
     Item8<AL> it[NR];
@@ -1460,7 +1594,7 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
-        it[n].init(held(n) ? (uint32_t)(lt + n * nt) : 0u, W, plane);
+        it[n].init(held(n) ? (uint32_t)(lt + n * nt) : 0u, W, inv, plane);
         kb[n] = place(it[n].k);
         row[n] = SLAB ? (held(n) ? (int)(it[n].k / W) : -1) : 0;
 #pragma unroll
@@ -1515,7 +1649,7 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
             } else {
                 for (uint32_t i = lt; i < n_items; i += (uint32_t)nt) {
                     Item8<AL> q;
-                    q.init(i, W, plane);
+                    q.init(i, W, inv, plane);
                     uint2 o = *reinterpret_cast<const uint2*>(own + q.k);
                     pass(q, q.k, true, o, *reinterpret_cast<const uint2*>(oth + q.k));
                 }
@@ -1539,24 +1673,181 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
 #pragma unroll
                 for (uint32_t c = 0; c < 2u; ++c)
                     *reinterpret_cast<uint2*>(gmem + c * gplane + kb[n]) = V[c][n];
-    } else if (AL || (plane & 7u) == 0u) {
-        for (uint32_t i = lt; i < n_items; i += (uint32_t)nt)
-#pragma unroll
-            for (uint32_t c = 0; c < 2u; ++c)
-                *reinterpret_cast<uint2*>(gmem + c * plane + 8u * i) =
-                    *reinterpret_cast<const uint2*>(lds + c * stride + 8u * i);
     } else if (active) {
-        for (uint32_t i = lt; i < plane; i += (uint32_t)nt)
-#pragma unroll
-            for (uint32_t c = 0; c < 2u; ++c) gmem[c * plane + i] = lds[c * stride + i];
+        store_planes8<AL>(gmem, lds, plane, stride, (uint32_t)lt, (uint32_t)nt);
     }
 }
 
-__global__ void __launch_bounds__(512) k_resident_potts(SweepArgs a) {
-    resident_body<kResPotts>(a);
+// A recorded sweep of a replica: adds the lanes' counts (labels of q > 8 are in
+// lhist already) to its row in LDS, (Nx, Ny, S, the most frequent label's count),
+// and clears lhist.  The replica's lanes meet in it, and meet again before lhist
+// or the row is next used.
+__device__ __forceinline__ void potts_record(const PottsAcc& pa, int q, int lt, int nt, int* lhist,
+                                             int* row) {
+    add_counts<true>(pa, q, nt, lhist, row);
+    replica_sync(nt > 64);
+    if (q <= 8 && nt >= 8) {
+        int mx = 0;
+        if (lt < 8) {
+            mx = lhist[lt];
+            lhist[lt] = 0;
+        }
+        mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xf, 0xf, true));
+        mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x4E, 0xf, 0xf, true));
+        mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x141, 0xf, 0xf, true));
+        if (lt == 0) row[3] = mx;
+    } else if (lt < q) {
+        int mx = 0;
+        for (int k = lt; k < q; k += nt) {
+            mx = max(mx, lhist[k]);
+            lhist[k] = 0;
+        }
+        int at = 3;
+        asm volatile("" : "+v"(at));  // a plain atomic, not a reduction over the wave first
+        atomicMax(&row[at], mx);
+    }
 }
 
-// Initial state from the init stream: natural index n, block n >> 2, word n & 3.
+// Stores and clears the n rows behind row0.
+__device__ __forceinline__ void potts_flush(const SweepArgs& a, int rep, int row0, int n,
+                                            bool active, int lt, int nt, int (*rows)[4]) {
+    if (!active) return;
+    for (int i = lt; i < n * a.width; i += nt) {
+        const int r = i / a.width, k = i - r * a.width;
+        a.stats[((size_t)(row0 + r) * a.R + rep) * a.width + k] = k < 4 ? rows[r][k] : 0;
+        if (k < 4) rows[r][k] = 0;
+    }
+}
+
+// Resident Potts lattices by items of eight sites, two Philox blocks a lane and
+// pass, for every width from 16 on (AL, NI, UNI as for k_resident_ising8, NI = 0
+// or 1).  Bound by VALU operations (about 27 slots a site in lattices of three-bit
+// labels without a field) or by a wave's latency: 1024 lattices of 64 x 64 take 1.9 us
+// a pass (3.6 by chunks of 16 sites) and 3.0 with every sweep recorded (12.5 when
+// that read every site with its neighbours).
+template <bool AL, int NI, bool UNI>
+__global__ void __launch_bounds__(1024) k_resident_potts8(SweepArgs a) {
+    // dynamic LDS: rpb slots of [thresholds (tab_lds_bytes) | plane 0 and its repeat |
+    // plane 1 and its repeat]
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ int lhist[kMaxRpb][kMaxPottsQ];
+    __shared__ int lrow[kMaxRpb][kPottsRecRows][4];
+    const int P = a.rpb;
+    const int nt = blockDim.x / P;
+    int g = threadIdx.x / nt;
+    const int lt = threadIdx.x - g * nt;
+    if (UNI) g = __builtin_amdgcn_readfirstlane(g);
+    const int first = blockIdx.x * P;
+    const bool active = first + g < a.n_list;
+    const int rep = a.rep_list[active ? first + g : first];
+    const RepDev& R = a.reps[rep];
+    const uint32_t W = (uint32_t)R.W, plane = (uint32_t)R.Ly * W, rid = R.rid;
+    const uint32_t stride = (plane + 15u) & ~7u;
+    const float inv = 1.0f / (float)W;
+    const int q = R.q, ntab = R.tab_n, path = potts_path(R);
+    const uint32_t lem = lemire_threshold(q);
+    uint8_t* slot = dyn + (size_t)(active ? g : 0) * a.res_slot_bytes;
+    uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
+    uint8_t* lds = slot + a.tab_lds_bytes;
+    uint8_t* gmem = a.lat + R.lat_off;
+    const uint32_t n_items = active ? (plane + 7u) >> 3 : 0u;
+    if (active) {
+        load_potts_table(a.tab, R, tab, lt, nt);
+        load_planes8<AL>(lds, gmem, plane, stride, (uint32_t)lt, (uint32_t)nt);
+    }
+    for (int i = threadIdx.x; i < P * kMaxPottsQ; i += blockDim.x) (&lhist[0][0])[i] = 0;
+    for (int i = threadIdx.x; i < P * kPottsRecRows * 4; i += blockDim.x) (&lrow[0][0][0])[i] = 0;
+    __syncthreads();
+    Item8<AL> it;
+    const bool held = NI > 0 && (uint32_t)lt < n_items;
+    uint2 vo, vm;  // NI = 1: the item's bytes in the colour at work and in the other
+    if (NI > 0) {
+        it.init(held ? (uint32_t)lt : 0u, W, inv, plane);
+        vo = *reinterpret_cast<const uint2*>(lds + it.k);
+        vm = *reinterpret_cast<const uint2*>(lds + stride + it.k);
+    }
+    const bool waves = nt > 64;
+    const uint64_t t0 = *a.t_base + (uint64_t)a.sweep_off;
+    int next = a.record_every > 0 ? a.record_every - a.sweep_off % a.record_every : 0;
+    int row0 = a.record_every > 0 ? a.sweep_off / a.record_every : 0, n_rows = 0;
+    for (int sw = 0; sw < a.n_sweeps; ++sw) {
+        const uint64_t t = t0 + (uint64_t)sw;
+        bool rec = false;
+        if (a.record_every > 0 && --next == 0) {
+            next = a.record_every;
+            rec = true;
+        }
+        PottsAcc pa;
+        pa.clear();
+#pragma nounroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
+            uint8_t* own = lds + (uint32_t)c * stride;
+            const uint8_t* oth = lds + (uint32_t)(1 - c) * stride;
+            auto pass = [&](const Item8<AL>& e, uint2& o, const uint2& m2) {
+                const uint32_t ov[2] = {o.x, o.y}, m[2] = {m2.x, m2.y};
+                uint32_t sv[2], Uv[2], Dv[2], nv[2];
+                near8<AL>(e, oth, c, m, sv, Uv, Dv);
+                if (path == kPottsFast)
+                    potts_core<2, kPottsFast>(ov, m, sv, Uv, Dv, e.k, p, rid, a.key0, a.key1, tab,
+                                              q, ntab, lem, nv);
+                else if (path == kPottsNoField)
+                    potts_core<2, kPottsNoField>(ov, m, sv, Uv, Dv, e.k, p, rid, a.key0, a.key1,
+                                                 tab, q, ntab, lem, nv);
+                else
+                    potts_core<2, kPottsAny>(ov, m, sv, Uv, Dv, e.k, p, rid, a.key0, a.key1, tab,
+                                             q, ntab, lem, nv);
+                o = make_uint2(nv[0], nv[1]);
+                store8<AL>(own, e.k, plane, o);
+                if (c == 1 && rec) {
+                    if (AL || e.k + 8u <= plane) {
+                        potts_count(nv, m, sv, Uv, Dv, q, pa, lhist[g]);
+                    } else {  // the last item's sites
+                        for (uint32_t j = 0; j < plane - e.k; ++j) {
+                            const uint32_t sh = 8u * (j & 3u);
+                            auto at = [&](const uint32_t (&v)[2]) {
+                                return ((j < 4u ? v[0] : v[1]) >> sh) & 0xFFu;
+                            };
+                            const uint32_t s = at(nv), x = at(m);
+                            pa.Nx += (s == x) + (s == at(sv));
+                            pa.Ny += (s == at(Uv)) + (s == at(Dv));
+                            pa.S += (int)(s + x);
+                            atomicAdd(&lhist[g][s], 1);
+                            atomicAdd(&lhist[g][x], 1);
+                        }
+                    }
+                }
+            };
+            if (NI > 0) {
+                if (held) pass(it, vo, vm);
+                const uint2 v = vo;
+                vo = vm;
+                vm = v;
+            } else {
+                for (uint32_t i = lt; i < n_items; i += (uint32_t)nt) {
+                    Item8<AL> e;
+                    e.init(i, W, inv, plane);
+                    uint2 o = *reinterpret_cast<const uint2*>(own + e.k);
+                    pass(e, o, *reinterpret_cast<const uint2*>(oth + e.k));
+                }
+            }
+            if (c == 0) replica_sync(waves);
+        }
+        if (rec) {
+            potts_record(pa, q, lt, nt, lhist[g], lrow[g][n_rows]);
+            if (++n_rows == kPottsRecRows) {
+                replica_sync(waves);
+                potts_flush(a, rep, row0, n_rows, active, lt, nt, lrow[g]);
+                row0 += n_rows;
+                n_rows = 0;
+            }
+        }
+        replica_sync(waves);
+    }
+    potts_flush(a, rep, row0, n_rows, active, lt, nt, lrow[g]);
+    if (active) store_planes8<AL>(gmem, lds, plane, stride, (uint32_t)lt, (uint32_t)nt);
+}
+
 __global__ void k_init(const RepDev* reps, const int32_t* list, uint8_t* lat, uint32_t k0,
                        uint32_t k1) {
     const RepDev R = reps[list[blockIdx.y]];
@@ -1665,6 +1956,12 @@ const void* ising8_fn(int items, int nt) {
                              : (const void*)k_resident_ising8<AL, 0, UNI, false>;
 }
 
+template <bool AL, bool UNI>
+const void* potts8_fn(int items, int nt) {
+    return items <= nt ? (const void*)k_resident_potts8<AL, 1, UNI>
+                       : (const void*)k_resident_potts8<AL, 0, UNI>;
+}
+
 const void* resident_fn(int kind, int items, int nt) {
     const bool uni = nt % 64 == 0;
     switch (kind) {
@@ -1679,7 +1976,9 @@ const void* resident_fn(int kind, int items, int nt) {
         case kResIsingSlab:
             return items <= nt ? (const void*)k_resident_ising8<true, 1, true, true>
                                : (const void*)k_resident_ising8<true, 2, true, true>;
-        case kResPotts: return (const void*)k_resident_potts;
+        case kResPotts8: return uni ? potts8_fn<true, true>(items, nt) : potts8_fn<true, false>(items, nt);
+        case kResPotts8Any:
+            return uni ? potts8_fn<false, true>(items, nt) : potts8_fn<false, false>(items, nt);
         default: return (const void*)k_resident_generic;
     }
 }

@@ -19,6 +19,9 @@ constexpr int kIsingClasses = 18;
 // Words of an Ising replica's thresholds in LDS: those of the 18 x 18 pairs of
 // classes, then 18 high and 18 low halves.
 constexpr int kIsingTabWords = 18 * 18 + 2 * 18;
+// Those of a Potts replica without a field (256 patterns, 9 high and 9 low halves,
+// two words of padding); with a field the whole table follows.
+constexpr int kPottsTabWords = 256 + 20;
 constexpr int kMaxPottsQ = 128;   // labels fit in 7 bits (SWAR equality test)
 constexpr int kMaxCpmTypes = 4;
 constexpr int kMaxRpb = 16;       // replicas per resident workgroup
@@ -26,11 +29,12 @@ constexpr int kMaxRpb = 16;       // replicas per resident workgroup
 // Resident kernels of the lattice models.
 enum {
     kResGeneric = 0,    // per site: any model or width
-    kResPotts = 1,      // Potts chunks of 16 sites (W % 16 == 0)
-    kResIsing16 = 2,    // Ising, row pairs of 16 columns a lane (W % 16 == 0)
-    kResIsing8 = 3,     // Ising, 8 sites a lane (W % 8 == 0)
-    kResIsing8Any = 4,  // Ising, 8 sites a lane (W >= 9)
-    kResIsingSlab = 5,  // Ising, 8 sites a lane (W % 8 == 0), a slab of rows a workgroup
+    kResIsing16 = 1,    // Ising, row pairs of 16 columns a lane (W % 16 == 0)
+    kResIsing8 = 2,     // Ising, 8 sites a lane (W % 8 == 0)
+    kResIsing8Any = 3,  // Ising, 8 sites a lane (W >= 9)
+    kResIsingSlab = 4,  // Ising, 8 sites a lane (W % 8 == 0), a slab of rows a workgroup
+    kResPotts8 = 5,     // Potts, 8 sites a lane (W % 8 == 0)
+    kResPotts8Any = 6,  // Potts, 8 sites a lane (W >= 9)
 };
 
 // Per-replica record, device visible.
@@ -115,7 +119,8 @@ struct SweepArgs {
     int32_t n_sweeps, record_every;
     int32_t sweep_off;            // resident kernels: first sweep of the launch within the call
     int32_t n_units;
-    int32_t tab_lds_bytes;        // bytes of LDS reserved for thresholds (multiple of 16)
+    int32_t tab_lds_bytes;        // bytes of LDS reserved for thresholds (multiple of 16;
+                                  // Ising items: kIsingTabWords)
     // resident kernels: replicas per workgroup, LDS bytes per replica slot,
     // and the number of entries of rep_list
     int32_t rpb, res_slot_bytes, n_list;

@@ -609,3 +609,35 @@ def test_ising_slabs(S, Lx, Ly, R, slabs):
     assert np.array_equal(smp.get_state(0), a)
     smp.close()
     ref.close()
+
+
+_EIGHT = [(18, 2), (18, 10), (30, 4),        # last items of two, two and four sites
+          (20, 20), (16, 2), (48, 20),
+          (128, 128), (160, 136)]            # one item a lane at its most, then several
+_RULE = [(2, 0.0), (7, 0.0), (8, 0.0), (8, 0.1), (9, 0.0), (16, 0.0), (17, -0.1), (65, 0.0),
+         (128, 0.02)]
+
+
+@pytest.mark.parametrize("Lx,Ly,n,q,h", [(Lx, Ly, 1, q, h) for Lx, Ly in _EIGHT for q, h in _RULE]
+                         + [(32, 4, 1030, q, h) for q, h in _RULE[2:7:2]])  # several a wave
+def test_potts_eight_sites_a_lane(S, Lx, Ly, n, q, h):
+    """The three rules (three-bit labels, no field, any), labels counted from bit
+    planes and by atomics, more recorded rows than gather in LDS."""
+    seed, h = 51, _f32(h)
+    rep = dict(model=1, Lx=Lx, Ly=Ly, q=q, Jx=1.0, Jy=1.0, h=h, beta=1.1)
+    smp = S([dict(rep, rid=r) for r in range(n)], seed, init=True)
+    smp.sweep(2)
+    st = smp.sweep(37, 2).cpu().numpy()
+    for r in sorted({0, n // 2, n - 1}):
+        a, _ = _run_oracle(dict(rep, rid=r), _init_oracle(dict(rep, rid=r), seed), seed, 0, 2, 0)
+        a, want = _run_oracle(dict(rep, rid=r), a, seed, 2, 37, 2)
+        assert np.array_equal(smp.get_state(r), a), r
+        assert np.array_equal(st[:, r, :], want), r
+    smp.close()
+
+
+@pytest.mark.parametrize("q,h", [(3, 0.0), (8, 0.0), (11, 0.0), (6, 0.1)])
+def test_potts_streamed_rules(S, q, h):
+    reps = [dict(model=1, Lx=64, Ly=34, q=q, Jx=1.0, Jy=1.0, h=_f32(h), beta=1.0, rid=1),
+            dict(model=1, Lx=32, Ly=16, q=5, Jx=1.0, Jy=1.0, h=0.0, beta=40.0, rid=2)]
+    _check_batch(S, reps, seed=52, n=30, re=4, schedule=dict(mode="stream"))
