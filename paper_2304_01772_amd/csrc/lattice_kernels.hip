@@ -21,6 +21,8 @@
 // threshold T = ceil(2^32 exp(-beta dE)).
 #include "spinmc_internal.hpp"
 
+#include <algorithm>
+
 namespace spinmc {
 
 namespace {
@@ -1872,24 +1874,79 @@ __global__ void k_init(const RepDev* reps, const int32_t* list, uint8_t* lat, ui
 }
 
 // Statistics of the current state: grid (tiles of natural sites, replicas).
-__global__ void k_measure(const RepDev* reps, const int32_t* list, const uint8_t* lat,
-                          int32_t* stats, int32_t* hist, int width) {
+// Statistics of every lattice.  Rows of whole 16-site chunks count as a recorded
+// colour-1 pass does, other widths site by site; Potts labels gather in LDS (one
+// atomic a site in memory took 9 ms for 512 lattices of up to 1024 x 1024, now
+// about 100 us).
+__global__ void __launch_bounds__(256) k_measure(const RepDev* reps, const int32_t* list,
+                                                 const uint8_t* lat, int32_t* stats, int32_t* hist,
+                                                 int width) {
     __shared__ int lred[64];
+    __shared__ int lhist[kMaxPottsQ];
     const int r = list[blockIdx.y];
     const RepDev R = reps[r];
-    const int N = R.Lx * R.Ly;
-    const int per = 4096;
-    const int n0 = blockIdx.x * per;
-    if (n0 >= N) return;
-    const int n1 = min(N, n0 + per);
+    const uint8_t* p0 = lat + R.lat_off;
+    const bool potts = R.model == kModelPotts;
+    const int n_items = (R.W & 15) == 0 ? (R.Ly >> 1) * (R.W >> 4) : R.Lx * R.Ly;
+    if ((int)(blockIdx.x * blockDim.x) >= n_items) return;
+    for (int i = threadIdx.x; i < kMaxPottsQ; i += blockDim.x) lhist[i] = 0;
+    __syncthreads();
+    PottsAcc pa;
+    pa.clear();
     int v[3] = {0, 0, 0};
-    lattice_stats(R.model, lat + R.lat_off, R.Lx, R.Ly, R.W, n0, n1, v, hist + R.hist_off);
-    block_sum<3>(v, lred);
+    const int stride = gridDim.x * blockDim.x;
+    if ((R.W & 15) == 0) {
+        const uint32_t W = (uint32_t)R.W, last = (uint32_t)(R.Ly - 1) * W, cpr = W >> 4;
+        const uint8_t* p1 = p0 + (size_t)R.Ly * W;
+#pragma unroll
+        for (int par = 0; par < 2; ++par)  // rows of parity (y + 1) & 1 = par
+            for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_items; i += stride) {
+                const uint32_t y = (uint32_t)i / cpr, j0 = ((uint32_t)i - y * cpr) << 4;
+                const uint32_t ro = (2u * y + (par ? 0u : 1u)) * W;
+                ChunkIn in;
+                if (par == 0) {
+                    const ChunkOff<0> f(ro, j0, W, last);
+                    in = chunk_load<false>(p1, p0, f.oo, f.uo, f.dof, f.eo);
+                } else {
+                    const ChunkOff<1> f(ro, j0, W, last);
+                    in = chunk_load<false>(p1, p0, f.oo, f.uo, f.dof, f.eo);
+                }
+                uint32_t ov[4], mv[4], Uv[4], Dv[4], sv[4];
+                arr(in.o, ov);
+                arr(in.m, mv);
+                arr(in.U, Uv);
+                arr(in.D, Dv);
+                side_bytes(par, mv, in.e, sv);
+                if (potts) {
+                    potts_count(ov, mv, sv, Uv, Dv, R.q, pa, lhist);
+                } else {
+                    uint32_t up = 0u, dx = 0u, dy = 0u;
+                    ising_count(ov, mv, sv, Uv, Dv, up, dx, dy);
+                    v[0] += 2 * (int)sad_u8(up, 0u) - 32;
+                    v[1] += 32 - 2 * (int)sad_u8(dx, 0u);
+                    v[2] += 32 - 2 * (int)sad_u8(dy, 0u);
+                }
+            }
+        if (potts) {
+            v[0] = pa.Nx;
+            v[1] = pa.Ny;
+            v[2] = pa.S;
+            if (R.q <= 8) add_counts<false>(pa, R.q, 64, lhist, nullptr);
+        }
+    } else {
+        for (int n0 = blockIdx.x * blockDim.x; n0 < n_items; n0 += stride)
+            lattice_stats(R.model, p0, R.Lx, R.Ly, R.W, n0, min(n_items, n0 + (int)blockDim.x), v,
+                          lhist);
+    }
+    block_sum<3>(v, lred);  // its barriers order the labels too
     if (threadIdx.x == 0) {
         atomicAdd(&stats[(size_t)r * width + 0], v[0]);
         atomicAdd(&stats[(size_t)r * width + 1], v[1]);
         atomicAdd(&stats[(size_t)r * width + 2], v[2]);
     }
+    if (potts)
+        for (int i = threadIdx.x; i < R.q; i += blockDim.x)
+            if (lhist[i]) atomicAdd(&hist[R.hist_off + i], lhist[i]);
 }
 
 __global__ void k_fill_i32(int32_t* p, size_t n, int32_t v) {
@@ -2099,8 +2156,9 @@ hipError_t launch_measure(const RepDev* reps, const int32_t* list, int n, int ma
                           const uint8_t* lat, int32_t* stats, int32_t* hist, int width,
                           hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    // grid.x covers the largest replica in 4096-site tiles; extra blocks exit
-    const int gx = (max_sites + 4095) / 4096;
+    // about 16384 sites a workgroup, at most 64 workgroups a replica; those past a
+    // smaller replica's items exit
+    const int gx = std::min(64, (max_sites + 16383) / 16384);
     hipLaunchKernelGGL(k_measure, dim3(gx, n), dim3(256), 0, s, reps, list, lat, stats, hist,
                        width);
     return hipGetLastError();

@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(256) k_tri_pass4(TriArgs a, int c, int sweep_o
     }
 }
 
-// [M, Bh, Bv, Bd]: wave sums of each lane's sites, one atomic per wave and
+// [M, Bh, Bv, Bd] of any width: wave sums of each lane's sites, one atomic per wave and
 // statistic (integers, so the order does not matter).
 __global__ void __launch_bounds__(256) k_tri_stats(TriArgs a, int rec_row) {
     const int r = blockIdx.y;
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(256) k_hc_pass4(TriArgs a, int c, int sweep_of
     }
 }
 
-// [M, Bx, By, Bz] of the chain / square / cubic lattices.
+// [M, Bx, By, Bz] of the chain / square / cubic lattices of any width.
 __global__ void __launch_bounds__(256) k_hc_stats(TriArgs a, int rec_row) {
     const int r = blockIdx.y;
     const RepDev D = a.reps[r];
@@ -603,6 +603,79 @@ __device__ __forceinline__ void hc_words(const int8_t* oth, int c, const PlaneIt
     }
 }
 
+// Adds to cnt an item's -1 spins and unequal bonds in each direction, from
+// bytes whose bits MASK tell the spins apart: triangular from every site's three
+// forward bonds, chain / cubic from both ends' directions of the colour-1 sites
+// (every bond has one colour-1 end) and the spins of both colours.
+template <int MODEL, int NB, uint32_t MASK>
+__device__ __forceinline__ void count_item(const int8_t* ls, uint32_t psz, const PlaneItem& q,
+                                           int Ly, int Lz, int (&cnt)[4]) {
+    if (MODEL == kModelIsingTri) {
+        for (int c = 0; c < 3; ++c) {
+            const TriWords<NB> w = tri_words<NB, false>(ls, psz, c, q);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const uint32_t s = w.S.v[b];
+                cnt[0] += __popc(s & MASK);
+                cnt[1] += __popc((s ^ w.sa.v[b]) & MASK);
+                cnt[2] += __popc((s ^ w.fe.v[b]) & MASK);
+                cnt[3] += __popc((s ^ w.sc.v[b]) & MASK);
+            }
+        }
+    } else {
+        Words<NB> M, H;
+        hc_words<NB>(ls, 1, q, M, H);
+        const Words<NB> S = ldw<NB>(ls + psz + q.off);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            cnt[0] += __popc(S.v[b] & MASK) + __popc(M.v[b] & MASK);
+            cnt[1] += __popc((S.v[b] ^ M.v[b]) & MASK) + __popc((S.v[b] ^ H.v[b]) & MASK);
+        }
+        if (Ly > 1) {
+            const Words<NB> u = ldw<NB>(ls + q.ou), d = ldw<NB>(ls + q.od);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                cnt[2] += __popc((S.v[b] ^ u.v[b]) & MASK) + __popc((S.v[b] ^ d.v[b]) & MASK);
+        }
+        if (Lz > 1) {
+            const Words<NB> u = ldw<NB>(ls + q.ozu), d = ldw<NB>(ls + q.ozd);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                cnt[3] += __popc((S.v[b] ^ u.v[b]) & MASK) + __popc((S.v[b] ^ d.v[b]) & MASK);
+        }
+    }
+}
+
+// [M, B1, B2, B3] of lattices in memory, rows of whole Philox blocks (Lx % 12 == 0
+// triangular, % 8 == 0 chain / cubic): items of 4 NB sites as in the resident
+// kernel, one atomic a wave and statistic.  Bound by its loads: 256 lattices of
+// 32^3 take 8 us (site by site 129).
+template <int MODEL, int NB>
+__global__ void __launch_bounds__(256) k_plane_stats(TriArgs a, int rec_row) {
+    constexpr bool TRI = MODEL == kModelIsingTri;
+    const int r = blockIdx.y;
+    const RepDev D = a.reps[r];
+    const int Lx = D.Lx, Ly = D.Ly, Lz = TRI ? 1 : D.q;
+    const uint32_t psz = (uint32_t)(Lx * Ly * Lz / (TRI ? 3 : 2));
+    const int items = (int)(psz / (4 * NB));
+    const int8_t* lat = a.lat + D.lat_off;
+    int cnt[4] = {0, 0, 0, 0}, n = 0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < items; i += gridDim.x * blockDim.x) {
+        // spins +-1 as bytes 01 and FF
+        count_item<MODEL, NB, 0x02020202u>(lat, psz, plane_item<MODEL, NB>(i, Lx, Ly, Lz), Ly, Lz,
+                                           cnt);
+        n += (TRI ? 12 : 8) * NB;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool has = TRI || k < 2 || (k == 2 ? Ly > 1 : Lz > 1);
+        int v = has ? n - 2 * cnt[k] : 0;
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if ((threadIdx.x & 63) == 0)
+            atomicAdd(&a.stats[((size_t)rec_row * a.R + r) * a.width + k], v);
+    }
+}
+
 // Four sites of one Philox block: own bytes S, neighbour counts N (-1
 // neighbours per byte); lt holds T - 1 by n + 8 [s = -1] (W < T as a 32-bit
 // compare), zero the bits of the entries with T = 0, which never accept.
@@ -627,9 +700,7 @@ __device__ __forceinline__ uint32_t plane_decide(uint32_t S, uint32_t N, const u
 // re > 0: after sweep sw0 + sw + 1 = k re of the call the statistics of the
 // lattice go to stats row k - 1 (columns 0..3; the caller zeroes the rows).
 // They are counts of unequal bonds (and of -1 spins) from the planes, four
-// sites a word: triangular from every site's three forward bonds, chain /
-// cubic from both ends' directions of the colour-1 sites (every bond has one
-// colour-1 end).  The counts of the launch's rows gather in LDS behind the
+// sites a word.  The counts of the launch's rows gather in LDS behind the
 // lattice and are stored once at its end, so no sweep waits for global
 // memory.
 template <int MODEL, int NB, int NI>
@@ -723,40 +794,7 @@ __global__ void __launch_bounds__(1024) k_plane_resident(TriArgs a, int n_sweeps
             for (int k = 0; k < NI; ++k) {
                 if (tid + k * nthr >= items) break;
                 const PlaneItem q = NI == 1 ? it0 : unpack_item(itp[k]);
-                if (TRI) {
-                    for (int c = 0; c < 3; ++c) {
-                        const TriWords<NB> w = tri_words<NB, false>(ls, psz, c, q);
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            const uint32_t s = w.S.v[b];
-                            cnt[0] += __popc(s);
-                            cnt[1] += __popc(s ^ w.sa.v[b]);
-                            cnt[2] += __popc(s ^ w.fe.v[b]);
-                            cnt[3] += __popc(s ^ w.sc.v[b]);
-                        }
-                    }
-                } else {
-                    Words<NB> M, H;
-                    hc_words<NB>(ls, 1, q, M, H);
-                    const Words<NB> S = ldw<NB>(ls + psz + q.off);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        cnt[0] += __popc(S.v[b]) + __popc(M.v[b]);
-                        cnt[1] += __popc(S.v[b] ^ M.v[b]) + __popc(S.v[b] ^ H.v[b]);
-                    }
-                    if (Ly > 1) {
-                        const Words<NB> u = ldw<NB>(ls + q.ou), d = ldw<NB>(ls + q.od);
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-                            cnt[2] += __popc(S.v[b] ^ u.v[b]) + __popc(S.v[b] ^ d.v[b]);
-                    }
-                    if (Lz > 1) {
-                        const Words<NB> u = ldw<NB>(ls + q.ozu), d = ldw<NB>(ls + q.ozd);
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-                            cnt[3] += __popc(S.v[b] ^ u.v[b]) + __popc(S.v[b] ^ d.v[b]);
-                    }
-                }
+                count_item<MODEL, NB, ~0u>(ls, psz, q, Ly, Lz, cnt);
             }
             // wave sums (every wave is full and has reconverged)
             int* row = lrec + 4 * ((sw0 + sw + 1) / re - rec0);
@@ -846,7 +884,21 @@ hipError_t launch_tri_pass(const TriArgs& a, int c, int sweep_off, hipStream_t s
 
 hipError_t launch_tri_stats(const TriArgs& a, int rec_row, hipStream_t s) {
     const int per = (a.max_sites + 255) / 256;
-    if (a.model == kModelIsingHC)
+    const bool hc = a.model == kModelIsingHC;
+    if (hc ? a.all_lx8 : a.all_lx12) {
+        // four items a lane, as many workgroups as that gives up to 64 a lattice
+        const int nb = a.even_blocks ? 2 : 1;
+        const int gx = std::min(64, (a.max_blocks / nb + 1023) / 1024);
+        const dim3 g(gx, a.R), b(256);
+        if (hc && nb == 2)
+            hipLaunchKernelGGL((k_plane_stats<kModelIsingHC, 2>), g, b, 0, s, a, rec_row);
+        else if (hc)
+            hipLaunchKernelGGL((k_plane_stats<kModelIsingHC, 1>), g, b, 0, s, a, rec_row);
+        else if (nb == 2)
+            hipLaunchKernelGGL((k_plane_stats<kModelIsingTri, 2>), g, b, 0, s, a, rec_row);
+        else
+            hipLaunchKernelGGL((k_plane_stats<kModelIsingTri, 1>), g, b, 0, s, a, rec_row);
+    } else if (hc)
         hipLaunchKernelGGL(k_hc_stats, dim3(per < 64 ? per : 64, a.R), dim3(256), 0, s, a, rec_row);
     else
         hipLaunchKernelGGL(k_tri_stats, dim3(per < 64 ? per : 64, a.R), dim3(256), 0, s, a,

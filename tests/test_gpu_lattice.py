@@ -641,3 +641,20 @@ def test_potts_streamed_rules(S, q, h):
     reps = [dict(model=1, Lx=64, Ly=34, q=q, Jx=1.0, Jy=1.0, h=_f32(h), beta=1.0, rid=1),
             dict(model=1, Lx=32, Ly=16, q=5, Jx=1.0, Jy=1.0, h=0.0, beta=40.0, rid=2)]
     _check_batch(S, reps, seed=52, n=30, re=4, schedule=dict(mode="stream"))
+
+
+@pytest.mark.parametrize("Lx,Ly", [(32, 2), (32, 16), (96, 50), (20, 18), (14, 6), (512, 66),
+                                   (1024, 256)])
+def test_measured_statistics_equal_recorded_ones(S, Lx, Ly):
+    """measure() after a recorded sweep: whole chunks and other widths, labels
+    counted from bit planes and by atomics, lattices of different size."""
+    reps = [dict(model=0, Lx=Lx, Ly=Ly, Jx=1.0, Jy=0.7, h=0.0, beta=0.4, rid=1)]
+    reps += [dict(model=1, Lx=Lx, Ly=Ly, q=q, Jx=1.0, Jy=1.0, h=0.0, beta=0.9, rid=q)
+             for q in (2, 8, 9, 128)]
+    reps.append(dict(model=0, Lx=32, Ly=4, Jx=1.0, Jy=0.7, h=0.0, beta=0.4, rid=3))
+    smp = S(reps, 61, init=True)
+    st = smp.sweep(3, 1)[-1]
+    got, _ = smp.measure()
+    again, _ = smp.measure()
+    assert torch.equal(got, st) and torch.equal(again, st)
+    smp.close()

@@ -64,3 +64,26 @@ def test_two_blocks_an_item_in_a_ragged_wave():
     _check(reps, lambda s, d, seed, t, n, e: orc.tri_run(s, 1.0, 0.05, 0.27, seed, 60, t, n, e))
     reps = [dict(model=4, Lx=144, Ly=66, Lz=1, Jx=1.0, Jy=1.0, h=0.05, beta=0.4, rid=61)]
     _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, 1.0, 0.05, 0.4, seed, 61, t, n, e))
+
+
+@pytest.mark.parametrize("dims", [
+    dict(model=3, Lx=12, Ly=3), dict(model=3, Lx=36, Ly=9), dict(model=3, Lx=120, Ly=102),
+    dict(model=4, Lx=8, Ly=1, Lz=1), dict(model=4, Lx=48, Ly=1, Lz=1),
+    dict(model=4, Lx=16, Ly=2, Lz=1), dict(model=4, Lx=24, Ly=2, Lz=2),
+    dict(model=4, Lx=32, Ly=34, Lz=6), dict(model=4, Lx=4, Ly=6, Lz=4),
+])
+def test_measured_statistics_equal_recorded_ones(dims):
+    """measure() after a recorded sweep: one and two blocks an item, absent
+    dimensions, a lattice whose rows are no whole blocks."""
+    from paper_2304_01772_amd.sampler import Sampler
+    reps = [dict(dims, Jx=1.0, Jy=1.0, h=0.0, beta=0.3, rid=r) for r in range(3)]
+    smp = Sampler(reps, 62, init=True)
+    st = smp.sweep(2, 1)[-1]
+    got, _ = smp.measure()
+    assert torch.equal(got, st)
+    smp.set_schedule(mode="stream")
+    st = smp.sweep(2, 2)[-1]
+    smp.set_schedule(mode="auto")
+    got, _ = smp.measure()
+    assert torch.equal(got, st)
+    smp.close()
