@@ -489,6 +489,19 @@ int spinmc_dmc_backward(const spinmc_dmc_params *p, void *dev_s, const void *dev
                         const void *dev_Jy, const void *dev_save, void *dev_gs, void *dev_gJx,
                         void *dev_gJy, void *dev_work, void *hip_stream);
 
+/* The same with separate outputs (new arrays, none of them an input): the
+ * forward writes the final spins to dev_out and, if it is not null, to
+ * dev_copy; the backward takes the final spins dev_s and dev_g = dL/ds_final and
+ * writes dL/ds_initial, dL/dJx and dL/dJy.  dev_work: spinmc_dmc_work_floats
+ * + R Ly Lx floats.                                                         */
+int spinmc_dmc_forward_to(const spinmc_dmc_params *p, const void *dev_s, const void *dev_Jx,
+                          const void *dev_Jy, void *dev_save, void *dev_out, void *dev_copy,
+                          void *hip_stream);
+int spinmc_dmc_backward_to(const spinmc_dmc_params *p, const void *dev_s, const void *dev_Jx,
+                           const void *dev_Jy, const void *dev_save, const void *dev_g,
+                           void *dev_gs, void *dev_gJx, void *dev_gJy, void *dev_work,
+                           void *hip_stream);
+
 /* ------------------------------------------------------------------------
  * Spin-value optimisation (Results, optimisation of the spin values): the
  * energy the methods minimise and the quantised update.

@@ -24,6 +24,7 @@ bool valid(const spinmc_dmc_params* p) {
 DmcArgs args(const spinmc_dmc_params* p, float* s, const float* Jx, const float* Jy) {
     DmcArgs a{};
     a.s = s;
+    a.s_in = s;
     a.Jx = Jx;
     a.Jy = Jy;
     a.R = p->R;
@@ -71,9 +72,39 @@ int spinmc_dmc_backward(const spinmc_dmc_params* p, void* dev_s, const void* dev
     if (p->n_sweeps == 0) return SPINMC_OK;
     return status(launch_dmc_backward(args(p, (float*)dev_s, (const float*)dev_Jx,
                                            (const float*)dev_Jy),
-                                      p->t0, p->n_sweeps, (const float*)dev_save, (float*)dev_gs,
-                                      (float*)dev_gJx, (float*)dev_gJy, (float*)dev_work,
+                                      p->t0, p->n_sweeps, (const float*)dev_save,
+                                      (const float*)dev_gs, (float*)dev_gs, (float*)dev_gJx,
+                                      (float*)dev_gJy, (float*)dev_work, false,
                                       (hipStream_t)stream));
+}
+
+int spinmc_dmc_forward_to(const spinmc_dmc_params* p, const void* dev_s, const void* dev_Jx,
+                          const void* dev_Jy, void* dev_save, void* dev_out, void* dev_copy,
+                          void* stream) {
+    if (!valid(p) || !dev_s || !dev_Jx || !dev_Jy || !dev_out || dev_out == dev_s ||
+        dev_copy == dev_s || dev_copy == dev_out || (p->n_sweeps > 0 && !dev_save))
+        return SPINMC_E_INVALID;
+    DmcArgs a = args(p, (float*)dev_out, (const float*)dev_Jx, (const float*)dev_Jy);
+    a.s_in = (const float*)dev_s;
+    a.s_copy = (float*)dev_copy;
+    return status(launch_dmc_forward(a, p->t0, p->n_sweeps, (float*)dev_save,
+                                     (hipStream_t)stream));
+}
+
+int spinmc_dmc_backward_to(const spinmc_dmc_params* p, const void* dev_s, const void* dev_Jx,
+                           const void* dev_Jy, const void* dev_save, const void* dev_g,
+                           void* dev_gs, void* dev_gJx, void* dev_gJy, void* dev_work,
+                           void* stream) {
+    if (!valid(p) || !dev_s || !dev_Jx || !dev_Jy || !dev_g || !dev_gs || dev_gs == dev_g ||
+        !dev_gJx || !dev_gJy || !dev_work || (p->n_sweeps > 0 && !dev_save))
+        return SPINMC_E_INVALID;
+    float* work = (float*)dev_work;
+    DmcArgs a = args(p, work + spinmc_dmc_work_floats(p), (const float*)dev_Jx,
+                     (const float*)dev_Jy);
+    a.s_in = (const float*)dev_s;
+    return status(launch_dmc_backward(a, p->t0, p->n_sweeps, (const float*)dev_save,
+                                      (const float*)dev_g, (float*)dev_gs, (float*)dev_gJx,
+                                      (float*)dev_gJy, work, true, (hipStream_t)stream));
 }
 
 int spinmc_dmc_energy(const spinmc_dmc_params* p, const void* dev_s, const void* dev_Jx,

@@ -7,6 +7,8 @@ namespace spinmc {
 
 struct DmcArgs {
     float* s;              // spins [R][Ly][Lx]
+    const float* s_in;     // forward / backward: the spins to start from (may be s)
+    float* s_copy;         // forward: a second copy of the final spins, or null
     const float* Jx;       // couplings of the bonds (y,x)-(y,x+1) [R][Ly][Lx]
     const float* Jy;       // couplings of the bonds (y,x)-(y+1,x) [R][Ly][Lx]
     int32_t R, Lx, Ly;
@@ -15,14 +17,17 @@ struct DmcArgs {
 };
 
 // n_sweeps sweeps from sweep counter t0; save receives the pre-pass spins of
-// the updated colour, [2 n_sweeps][R][Ly Lx/2].
+// the updated colour, [2 n_sweeps][R][Ly Lx/2]; the final spins go to a.s (and
+// a.s_copy).
 hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float* save,
                               hipStream_t s);
-// Reverse replay: a.s holds the final spins on entry and the initial spins on
-// exit; gs holds dL/ds_final on entry and dL/ds_initial on exit; gJx, gJy
-// accumulate; work is [2][R][Ly Lx/2].
+// Reverse replay: a.s_in holds the final spins and g dL/ds_final; gs receives
+// dL/ds_initial (gs may be g).  fresh: gJx and gJy are written, a.s_in and g stay as
+// they are and a.s (scratch) must be another array; else gJx and gJy accumulate,
+// a.s_in is a.s and holds the initial spins on exit.  work is [2][R][Ly Lx/2].
 hipError_t launch_dmc_backward(const DmcArgs& a, uint64_t t0, int n_sweeps, const float* save,
-                               float* gs, float* gJx, float* gJy, float* work, hipStream_t s);
+                               const float* g, float* gs, float* gJx, float* gJy, float* work,
+                               bool fresh, hipStream_t s);
 
 // Energy H per replica (FP64, e_out[R]) and optionally dH/ds (FP32,
 // [R][Ly][Lx]) of the spins a.s with the couplings a.Jx, a.Jy and field a.h.

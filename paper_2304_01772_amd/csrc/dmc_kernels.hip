@@ -771,7 +771,7 @@ __global__ void __launch_bounds__(1024) k_dmc_resident_fwd(DmcArgs a, uint32_t p
     float jx[NI][9], jy[NI + 1][8];
     res_jx<NI>(a, L, off, jx);
     res_jy<NI>(a, L, off, jy);
-    if (L.in) res_load<NI>(a.s + off, a.Lx, L, lds, plane);
+    if (L.in) res_load<NI>(a.s_in + off, a.Lx, L, lds, plane);
     __syncthreads();
     float* sv = save + (size_t)r * plane;
     for (int i = 0; i < n_sweeps; ++i) {
@@ -782,15 +782,19 @@ __global__ void __launch_bounds__(1024) k_dmc_resident_fwd(DmcArgs a, uint32_t p
         __syncthreads();
         sv += 2 * step;
     }
-    if (L.in) res_store<NI>(a.s + off, a.Lx, L, lds, plane);
+    if (L.in) {
+        res_store<NI>(a.s + off, a.Lx, L, lds, plane);
+        if (a.s_copy) res_store<NI>(a.s_copy + off, a.Lx, L, lds, plane);
+    }
 }
 
 // Dynamic LDS: two planes of the spins, two of the vertical couplings, one of
 // t = dL/dhloc.
 template <int NI>
 __global__ void __launch_bounds__(512) k_dmc_resident_bwd(DmcArgs a, uint32_t p0, int n_sweeps,
-                                                          const float* save, float* gs, float* gJx,
-                                                          float* gJy) {
+                                                          const float* save, const float* g,
+                                                          float* gs, float* gJx, float* gJy,
+                                                          int fresh) {
     extern __shared__ __align__(16) float lds[];
     const int plane = a.Ly * (a.Lx >> 1), Lx = a.Lx;
     float* jp = lds + 2 * plane;
@@ -805,14 +809,19 @@ __global__ void __launch_bounds__(512) k_dmc_resident_bwd(DmcArgs a, uint32_t p0
     for (int q = 0; q < NI; ++q) {
         const uint32_t o = (uint32_t)(L.y0 + q) * Lx + 8 * L.j;
         S.gx[q][0] = 0.f;
-        unpack8(ld8(gJx + off + o), &S.gx[q][1]);
-        unpack8(ld8(gJy + off + o), &S.gy[q + 1][0]);
-        unpack8(ld8(gs + off + o), &S.g[q][0]);
+        if (fresh) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) S.gx[q][1 + x] = S.gy[q + 1][x] = 0.f;
+        } else {
+            unpack8(ld8(gJx + off + o), &S.gx[q][1]);
+            unpack8(ld8(gJy + off + o), &S.gy[q + 1][0]);
+        }
+        unpack8(ld8(g + off + o), &S.g[q][0]);
     }
 #pragma unroll
     for (int x = 0; x < 8; ++x) S.gy[0][x] = 0.f;
     if (L.in) {
-        res_load<NI>(a.s + off, Lx, L, lds, plane);
+        res_load<NI>(a.s_in + off, Lx, L, lds, plane);
         res_load<NI>(a.Jy + off, Lx, L, jp, plane);
     }
     const float* sv = save + (size_t)(2 * n_sweeps - 1) * step + (size_t)r * plane;
@@ -843,7 +852,7 @@ __global__ void __launch_bounds__(512) k_dmc_resident_bwd(DmcArgs a, uint32_t p0
             res_gather_row<NI, 2>(a, L, jp, tp, plane, S);
             res_gather_row<NI, 3>(a, L, jp, tp, plane, S);
         }
-        res_store<NI>(a.s + off, Lx, L, lds, plane);
+        if (!fresh) res_store<NI>(a.s + off, Lx, L, lds, plane);
     }
     __syncthreads();  // the planes are free: shares of other lanes' bonds
     const int lane = (int)threadIdx.x;
@@ -881,7 +890,9 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // 24 replicas on (128 x 128, 10 sweeps: 213 us against 314 for a launch per
 // pass at 64 replicas, 203 against 198 at 16).  256 replicas of 128 x 128, 10
 // sweeps: forward 297 -> 95 us, backward 811 -> 203; 64 x 64, 4 replicas,
-// with the calls around it: forward 126 -> 60, backward 212 -> 103.
+// with the calls around it: forward 126 -> 60, backward 212 -> 103.  Separate inputs
+// and outputs spare the caller four copies and two fills of its arrays (16 MB each
+// there: 40 us).
 int res_lanes(const DmcArgs& a, int NI, int max_lanes) {
     if (a.Ly % NI != 0) return 0;
     const int64_t lanes = (int64_t)(a.Ly / NI) * (a.Lx >> 3);
@@ -901,8 +912,9 @@ hipError_t res_launch(F fn, const DmcArgs& a, int lanes, size_t lds, void** args
 hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float* save,
                               hipStream_t s) {
     const int n_sites = a.Ly * (a.Lx >> 1);
-    const bool v8 = (a.Lx & 7) == 0 && aligned16(a.s) && aligned16(a.Jx) && aligned16(a.Jy) &&
-                    aligned16(save);
+    const bool v8 = (a.Lx & 7) == 0 && aligned16(a.s) && aligned16(a.s_in) &&
+                    aligned16(a.s_copy) && aligned16(a.Jx) && aligned16(a.Jy) && aligned16(save);
+    const size_t bytes = sizeof(float) * a.R * a.Lx * a.Ly;
     const int n_blocks = (n_sites + 3) >> 2;
     if (const int lanes = v8 ? res_lanes(a, 2, 1024) : 0) {
         DmcArgs b = a;
@@ -910,6 +922,9 @@ hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float
         void* args[] = {&b, &p0, &n_sweeps, &save};
         return res_launch(k_dmc_resident_fwd<2>, a, lanes, (size_t)8 * n_sites, args, s);
     }
+    hipError_t e = hipSuccess;
+    if (a.s_in != a.s) e = hipMemcpyAsync(a.s, a.s_in, bytes, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return e;
     const dim3 grid((n_blocks + 255) / 256, a.R), block(256);
     for (int i = 0; i < n_sweeps; ++i)
         for (int c = 0; c < 2; ++c) {
@@ -920,15 +935,19 @@ hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float
             else
                 hipLaunchKernelGGL(k_dmc_pass, grid, block, 0, s, a, c, p, sv);
         }
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (e == hipSuccess && a.s_copy)
+        e = hipMemcpyAsync(a.s_copy, a.s, bytes, hipMemcpyDeviceToDevice, s);
+    return e;
 }
 
 hipError_t launch_dmc_backward(const DmcArgs& a, uint64_t t0, int n_sweeps, const float* save,
-                               float* gs, float* gJx, float* gJy, float* work, hipStream_t s) {
+                               const float* g, float* gs, float* gJx, float* gJy, float* work,
+                               bool fresh, hipStream_t s) {
     const int n_sites = a.Ly * (a.Lx >> 1);
     const size_t plane = (size_t)a.R * n_sites;
-    const bool v8 = (a.Lx & 7) == 0 && aligned16(a.s) && aligned16(a.Jx) && aligned16(a.Jy) &&
-                    aligned16(save) && aligned16(gs) && aligned16(gJx) && aligned16(gJy) &&
+    const bool v8 = (a.Lx & 7) == 0 && aligned16(a.s) && aligned16(a.s_in) && aligned16(a.Jx) &&
+                    aligned16(a.Jy) && aligned16(save) && aligned16(g) && aligned16(gs) && aligned16(gJx) && aligned16(gJy) &&
                     aligned16(work);
     const int n_blocks = (n_sites + 3) >> 2;
     {
@@ -936,9 +955,20 @@ hipError_t launch_dmc_backward(const DmcArgs& a, uint64_t t0, int n_sweeps, cons
         const int l4 = v8 && n_sweeps > 0 && l2 == 0 && a.R >= 24 ? res_lanes(a, 4, 512) : 0;
         DmcArgs b = a;
         uint32_t p0 = (uint32_t)(2 * t0);
-        void* args[] = {&b, &p0, &n_sweeps, &save, &gs, &gJx, &gJy};
+        int fr = fresh ? 1 : 0;
+        void* args[] = {&b, &p0, &n_sweeps, &save, &g, &gs, &gJx, &gJy, &fr};
         if (l2) return res_launch(k_dmc_resident_bwd<2>, a, l2, (size_t)20 * n_sites, args, s);
         if (l4) return res_launch(k_dmc_resident_bwd<4>, a, l4, (size_t)20 * n_sites, args, s);
+    }
+    hipError_t e = hipSuccess;
+    if (fresh) {  // the passes below work in place
+        const size_t n = 2 * plane;
+        e = hipMemcpyAsync(a.s, a.s_in, sizeof(float) * n, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess && gs != g)
+            e = hipMemcpyAsync(gs, g, sizeof(float) * n, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(gJx), n, 0, s);
+        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(gJy), n, 0, s);
+        if (e != hipSuccess) return e;
     }
     const dim3 grid((n_blocks + 255) / 256, a.R), gridg((n_sites + 255) / 256, a.R), block(256);
     // pass m = 2 i + c writes its t to plane m & 1 and folds in the t of

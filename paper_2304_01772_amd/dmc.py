@@ -1,9 +1,9 @@
 """Differentiable Monte Carlo (Methods, Algorithm 2) on the library's kernels.
 
 ``RelaxedIsing`` is a ``torch.autograd.Function``: its forward runs the
-relaxed checkerboard chain (``spinmc_dmc_forward``) on continuous spins with
+relaxed checkerboard chain (``spinmc_dmc_forward_to``) on continuous spins with
 one coupling per bond, its backward replays the chain in reverse
-(``spinmc_dmc_backward``) and returns the gradients with respect to the
+(``spinmc_dmc_backward_to``) and returns the gradients with respect to the
 initial spins and the two coupling fields.  ``optimise_couplings`` is the
 paper's spin-pattern optimisation (Results): Adam (``spinmc_adam``) on the
 couplings so that the relaxed chain drives the lattice to a target pattern,
@@ -49,28 +49,28 @@ class RelaxedIsing(torch.autograd.Function):
         n_save = L.spinmc_dmc_save_floats(C.byref(p))
         if n_save < 0:
             check(n_save)
-        s = s0.detach().to(torch.float32).contiguous().clone()
+        s_in = s0.detach().to(torch.float32).contiguous()
         jx = Jx.detach().to(torch.float32).contiguous()
         jy = Jy.detach().to(torch.float32).contiguous()
-        save = torch.empty(max(n_save, 1), dtype=torch.float32, device=s.device)
-        check(L.spinmc_dmc_forward(C.byref(p), _p(s), _p(jx), _p(jy), _p(save), _stream()))
+        save = torch.empty(max(n_save, 1), dtype=torch.float32, device=s_in.device)
+        s, out = torch.empty_like(s_in), torch.empty_like(s_in)  # kept for the replay; returned
+        check(L.spinmc_dmc_forward_to(C.byref(p), _p(s_in), _p(jx), _p(jy), _p(save), _p(s),
+                                      _p(out), _stream()))
         ctx.p = p
         ctx.save_for_backward(s, jx, jy, save)
-        return s.clone()
+        return out
 
     @staticmethod
     def backward(ctx, g):
         s_final, jx, jy, save = ctx.saved_tensors
         p = ctx.p
         L = lib()
-        s = s_final.clone()
-        gs = g.to(torch.float32).contiguous().clone()
-        gjx = torch.zeros_like(jx)
-        gjy = torch.zeros_like(jy)
-        work = torch.empty(max(L.spinmc_dmc_work_floats(C.byref(p)), 1), dtype=torch.float32,
-                           device=s.device)
-        check(L.spinmc_dmc_backward(C.byref(p), _p(s), _p(jx), _p(jy), _p(save), _p(gs),
-                                    _p(gjx), _p(gjy), _p(work), _stream()))
+        g = g.to(torch.float32).contiguous()
+        gs, gjx, gjy = torch.empty_like(s_final), torch.empty_like(jx), torch.empty_like(jy)
+        n_work = L.spinmc_dmc_work_floats(C.byref(p)) + s_final.numel()
+        work = torch.empty(n_work, dtype=torch.float32, device=s_final.device)
+        check(L.spinmc_dmc_backward_to(C.byref(p), _p(s_final), _p(jx), _p(jy), _p(save), _p(g),
+                                       _p(gs), _p(gjx), _p(gjy), _p(work), _stream()))
         return gs, gjx, gjy, None, None, None, None, None, None, None
 
 

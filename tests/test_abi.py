@@ -162,3 +162,28 @@ def test_cpm_neighbourhood_validation_without_a_device(L):
                   ((12, 12, 2), (12, 12, 1))]:
         assert L.spinmc_create(descs(*specs), len(specs), 1, 0, None, C.byref(ctx)) == -1, specs
         assert not ctx.value
+
+
+def test_dmc_separate_outputs_reject_bad_arguments(L):
+    """Null, overlapping and missing buffers, before anything is enqueued."""
+    p = _dmc()
+    fwd = [1, 2, 3, 4, 5, 6]  # s, Jx, Jy, save, out, copy
+    for i in range(5):
+        bad = list(fwd)
+        bad[i] = None
+        assert L.spinmc_dmc_forward_to(C.byref(p), *bad, None) == -1, i
+    for i, j in ((4, 0), (5, 0), (5, 4)):
+        bad = list(fwd)
+        bad[i] = bad[j]
+        assert L.spinmc_dmc_forward_to(C.byref(p), *bad, None) == -1, (i, j)
+    bwd = [1, 2, 3, 4, 5, 6, 7, 8, 9]  # s, Jx, Jy, save, g, gs, gJx, gJy, work
+    for i in range(9):
+        bad = list(bwd)
+        bad[i] = None
+        assert L.spinmc_dmc_backward_to(C.byref(p), *bad, None) == -1, i
+    bad = list(bwd)
+    bad[5] = bad[4]
+    assert L.spinmc_dmc_backward_to(C.byref(p), *bad, None) == -1
+    p.Lx = 7
+    assert L.spinmc_dmc_forward_to(C.byref(p), *fwd, None) == -1
+    assert L.spinmc_dmc_backward_to(C.byref(p), *bwd, None) == -1
