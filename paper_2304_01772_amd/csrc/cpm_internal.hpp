@@ -6,18 +6,18 @@ namespace spinmc {
 
 // LDS bytes of the resident kernel: thresholds, five per-cell arrays of
 // cell_cap entries, the waves' queues, and the ids with their halo (max_padded
-// sites for the largest replica); SIZE_MAX where a queue entry cannot hold a
-// within-colour index.
+// sites for the largest replica).
 size_t cpm_resident_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int max_sites,
                               int max_padded);
 
 // n_steps Monte Carlo steps of every replica in one launch, one workgroup per
-// replica (range 1 with every Lx % 8 == 0, or range 2); the device step
-// counter is not advanced.  The launch holds steps sw0 .. sw0 + n_steps - 1 of
+// replica (rows: range 1 with every Lx % 8 == 0); the device step counter is
+// not advanced.  The launch holds steps sw0 .. sw0 + n_steps - 1 of
 // a call; with re > 0, step k re of the call stores its statistics (the whole
 // row) in stats row k - 1.
-hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int sw0, int re, int tab_lds_bytes,
-                               int cell_cap, int max_sites, int max_padded, hipStream_t s);
+hipError_t launch_cpm_resident(const CpmArgs& a, bool rows, int n_steps, int sw0, int re,
+                               int tab_lds_bytes, int cell_cap, int max_sites, int max_padded,
+                               hipStream_t s);
 
 // A tile of the streamed two-phase pass: rows y0 .. y0 + rows - 1 (even), columns
 // x0 .. x0 + cols - 1 (multiples of 8) of the replica whose record it carries
@@ -28,10 +28,18 @@ struct CpmTile {
 };
 size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols);
 hipError_t cpm_tile_reserve_lds(size_t lds_bytes);
-// One colour pass (range 1, every Lx % 8 == 0; at most 8192 sites of a colour
-// per tile, rows x cols / 4; cell_cap a multiple of 16; threads a multiple of
-// 64 up to 512; lds_bytes for the largest tile).
+// One colour pass (range 1, every Lx % 8 == 0; cell_cap a multiple of 16; threads
+// a multiple of 64 up to 512; lds_bytes for the largest tile).
 hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
+                                int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
+                                size_t lds_bytes, hipStream_t s);
+
+// The same over bands of whole rows: x0 0, cols Lx, y0 and rows multiples of 3
+// (range 2) or 2.
+size_t cpm_band_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int threads, int rows,
+                          int Lx);
+hipError_t cpm_band_reserve_lds(int range, size_t lds_bytes);
+hipError_t launch_cpm_pass_band(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
                                 int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
                                 size_t lds_bytes, hipStream_t s);
 

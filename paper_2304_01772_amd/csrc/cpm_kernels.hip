@@ -604,16 +604,18 @@ __global__ void __launch_bounds__(1024) k_cpm_pass_site(CpmArgs a, int c, int sw
 // site through the whole decision and computed each block four times.)
 namespace {
 
-// Queue entry: the attempt's accept prefix (bits 16..31), its within-colour
-// index and the chosen neighbour (range 1: index in bits 3..15, neighbour in
-// 0..2; range 2: index in bits 5..15, neighbour in 0..4).
+// Queue entry: the attempt's accept prefix (bits 16..31), its place (up to 11 bits:
+// four times the lane plus the word; where a pass is one round of up to 512 blocks,
+// its within-colour index) and the chosen neighbour (range 1: 3 bits, range 2: 5).
 template <int RANGE>
 struct Entry {
     static constexpr int kShift = RANGE == 1 ? 3 : 5;
-    static __device__ __forceinline__ uint32_t make(uint32_t word, uint32_t k, uint32_t jn) {
-        return (word & 0xFFFF0000u) | (k << kShift) | jn;
+    static __device__ __forceinline__ uint32_t make(uint32_t word, uint32_t place, uint32_t jn) {
+        return (word & 0xFFFF0000u) | (place << kShift) | jn;
     }
-    static __device__ __forceinline__ uint32_t k(uint32_t e) { return (e & 0xFFFFu) >> kShift; }
+    static __device__ __forceinline__ int place(uint32_t e) { return (int)((e & 0xFFFFu) >> kShift); }
+    static __device__ __forceinline__ int lane(uint32_t e) { return (int)(e >> (kShift + 2)) & 63; }
+    static __device__ __forceinline__ int word(uint32_t e) { return (int)(e >> kShift) & 3; }
     static __device__ __forceinline__ uint32_t jn(uint32_t e) { return e & ((1u << kShift) - 1u); }
 };
 
@@ -776,10 +778,10 @@ namespace {
 
 // The four attempts of block b in pass p from their random words: queue
 // entries e and the chosen neighbours' offsets off in the padded lattice,
-// from the window's first id.
+// from the window's first id; place of the first.
 template <int RANGE>
 __device__ __forceinline__ void cpm_draw(const CpmArgs& a, const RepDev& R, const MooreTab& moore,
-                                         int st, int b, uint32_t p, uint32_t (&e)[4],
+                                         int st, int b, int place, uint32_t p, uint32_t (&e)[4],
                                          uint32_t (&off)[4]) {
     uint32_t w[4];
     philox4x32_10((uint32_t)b, p, R.rid, kTagMain, a.key0, a.key1, w);
@@ -802,7 +804,7 @@ __device__ __forceinline__ void cpm_draw(const CpmArgs& a, const RepDev& R, cons
             }
             off[u] = (uint32_t)offset5(jn, st);
         }
-        e[u] = Entry<RANGE>::make(w[u], k, jn);
+        e[u] = Entry<RANGE>::make(w[u], (uint32_t)(place + u), jn);
     }
 }
 
@@ -811,9 +813,8 @@ __device__ __forceinline__ void cpm_draw(const CpmArgs& a, const RepDev& R, cons
 // All n_steps Monte Carlo steps of every replica in one launch: one workgroup
 // per replica with its ids (with a halo of the neighbourhood's width, so that
 // no neighbour wraps), areas, cell tables and thresholds in LDS, one barrier a
-// pass.  Range 1 (Lx % 8 == 0): a block's four sites are consecutive
-// same-colour sites of a row; range 2 (5x5, nine colours): four consecutive
-// within-colour indices; groups of eight blocks go round the waves, so that
+// pass.  A block's four sites are consecutive within-colour indices; ROWS (range 1,
+// Lx % 8 == 0): all of one row; groups of eight blocks go round the waves, so that
 // the cells' boundaries spread over them.  Areas minus targets rotate as in
 // the streamed passes: pass P reads S[P & 1] + D[(P - 1) % 3] and adds its
 // changes into D[P % 3] with LDS atomics, S and D of pass P + 1 are prepared
@@ -827,7 +828,7 @@ __device__ __forceinline__ void cpm_draw(const CpmArgs& a, const RepDev& R, cons
 // with one attempt per lane decided in place, 6.7 with two phases around a
 // barrier and a branch per site, 6.0 without those, 5.6 with the drawing
 // waves.
-template <int RANGE, bool GEN>
+template <int RANGE, bool GEN, bool ROWS>
 __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, int sw0, int re,
                                                        int tab_lds_bytes, int cell_cap,
                                                        int queue_words) {
@@ -879,14 +880,15 @@ __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, i
     const MooreTab moore = moore_tab(st);
     // block of the lane in round j: eight consecutive ones per eight lanes,
     // the groups of eight dealt out to the waves
-    const int b0 = ((lane >> 3) * nw + wave) * 8 + (lane & 7);
+    const auto block_of = [=](int l) { return ((l >> 3) * nw + wave) * 8 + (l & 7); };
+    const int b0 = block_of(lane);
     uint32_t e[4], off[4];
     const auto put = [&](int buf) {
         gE[buf * ndec + dt] = make_uint4(e[0], e[1], e[2], e[3]);
         gO[buf * ndec + dt] = make_uint2(off[0] | (off[1] << 16), off[2] | (off[3] << 16));
     };
     if (gen) {
-        cpm_draw<RANGE>(a, R, moore, st, b0, (uint32_t)(ncol * t0), e, off);
+        cpm_draw<RANGE>(a, R, moore, st, b0, 4 * b0, (uint32_t)(ncol * t0), e, off);
         put(sp);
     }
     __syncthreads();
@@ -906,7 +908,7 @@ __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, i
                 }
             }
             if (gen) {
-                cpm_draw<RANGE>(a, R, moore, st, b0, p + 1u, e, off);
+                cpm_draw<RANGE>(a, R, moore, st, b0, 4 * b0, p + 1u, e, off);
                 put(sp ^ 1);
             }
             // offset of the colour's site (0, 0), one row and column up-left
@@ -922,26 +924,28 @@ __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, i
                     off[0] = ov.x & 0xFFFFu; off[1] = ov.x >> 16;
                     off[2] = ov.y & 0xFFFFu; off[3] = ov.y >> 16;
                 } else {
-                    cpm_draw<RANGE>(a, R, moore, st, b, p, e, off);
+                    cpm_draw<RANGE>(a, R, moore, st, b, 4 * lane, p, e, off);
                 }
                 bool act[4];
                 int r = mdiv(4 * b, mW), i = 4 * b - (int)__umul24((uint32_t)r, (uint32_t)Wc);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const bool in = RANGE == 1 ? b < n_blk : 4 * b + u < n_sites;
+                    const bool in = ROWS ? b < n_blk : 4 * b + u < n_sites;
                     const int o = in ? P * ((int)__umul24((uint32_t)r, (uint32_t)st) + i) : 0;
                     // (no branch around the reads: all of the block's together)
                     act[u] = (lids[oc + o] != lids[on + o + (int)off[u]]) & in;
-                    // the block's next site (range 1: of the same row)
-                    ++i;
-                    if (RANGE == 2 && i == Wc) {
+                    ++i;  // the block's next site
+                    if (!ROWS && i == Wc) {
                         i = 0;
                         ++r;
                     }
                 }
                 const int cnt_q = queue_put(queue, act, e);
                 for (int q = lane; q < cnt_q; q += 64) {
-                    const uint32_t v = queue[q], k = Entry<RANGE>::k(v), jn = Entry<RANGE>::jn(v);
+                    const uint32_t v = queue[q], jn = Entry<RANGE>::jn(v);
+                    const uint32_t k = (uint32_t)(
+                        GEN ? Entry<RANGE>::place(v)
+                            : 4 * (g + block_of(Entry<RANGE>::lane(v))) + Entry<RANGE>::word(v));
                     const int r2 = mdiv((int)k, mW);
                     const int i2 = (int)k - (int)__umul24((uint32_t)r2, (uint32_t)Wc);
                     const int o = P * ((int)__umul24((uint32_t)r2, (uint32_t)st) + i2);
@@ -1116,14 +1120,15 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
             // (no branch around the reads: all of the quad's together)
             act[u] = (lids[oc + o + 2 * u] !=
                       lids[on + o + 2 * u + moore_offset(moore, w[u])]) & in;
-            e[u] = Entry<1>::make(w[u], (uint32_t)(4 * b + u) & 0x1FFFu, w[u] & 7u);
+            e[u] = Entry<1>::make(w[u], (uint32_t)(4 * lane + u), w[u] & 7u);
         }
         const int cnt_q = queue_put(queue, act, e);
         for (int q = lane; q < cnt_q; q += 64) {
-            const uint32_t ev = queue[q], kl = Entry<1>::k(ev), jn = Entry<1>::jn(ev);
-            const int b2 = (int)(kl >> 2), r2 = qrow(b2);
+            const uint32_t ev = queue[q], jn = Entry<1>::jn(ev);
+            const uint32_t kl = (uint32_t)Entry<1>::word(ev);
+            const int b2 = g + (tid & ~63) + Entry<1>::lane(ev), r2 = qrow(b2);
             const int j2 = b2 - (int)__umul24((uint32_t)r2, (uint32_t)Gt);
-            const int o2 = 2 * (int)__umul24((uint32_t)r2, (uint32_t)st) + 8 * j2 + 2 * (int)(kl & 3u);
+            const int o2 = 2 * (int)__umul24((uint32_t)r2, (uint32_t)st) + 8 * j2 + 2 * (int)kl;
             const uint32_t* nb = lids + on + o2;
             const uint32_t s = nb[st + 1], tg = nb[moore_offset(moore, jn)];
             uint32_t cnt = 0u;
@@ -1139,10 +1144,10 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
                     ns += m == s;
                 }
             const uint32_t k = 4u * ((uint32_t)((y0 >> 1) + r2) * (uint32_t)G +
-                                     (uint32_t)((x0 >> 3) + j2)) + (kl & 3u);
+                                     (uint32_t)((x0 >> 3) + j2)) + kl;
             if (cpm_accept(a, R, s | ((uint32_t)lty[s] << 24), tg | ((uint32_t)lty[tg] << 24), cnt, nt,
                            ns, &pairs, lsa[tg], lsa[s], qthr, ev >> 16, k, p)) {
-                gids[(size_t)(y0 + 2 * r2 + cy) * Lx + x0 + 8 * j2 + 2 * (int)(kl & 3u) + cx] = (int)tg;
+                gids[(size_t)(y0 + 2 * r2 + cy) * Lx + x0 + 8 * j2 + 2 * (int)kl + cx] = (int)tg;
                 atomicAdd(&ldel[tg], 1);
                 atomicAdd(&ldel[s], -1);
             }
@@ -1156,6 +1161,172 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
         const int d = ldel[i];
         if (d != 0) atomicAdd(&pa.d_wr[i], d);
     }
+}
+
+// The same pass over bands of whole rows, for every other lattice: range 2 (5x5,
+// nine colours), and range 1 where Lx is not a multiple of 8.  T.rows (a multiple
+// of the colouring's period) by T.cols = Lx; the ids come in dword by dword, a
+// block's four sites may run on into the band's next row, and blocks at the band's
+// ends belong to both bands, each deciding its own sites.  Bound as above; with two
+// or more bands a compute unit by the staging of ids (about 12 dwords a lane).
+// Range 2, 3 x 378^2, 364 cells: 7.1 us a pass with one attempt per lane deciding
+// in place, 6.3 now; 8 x 510^2, 648 cells: 14.4 and 9.3; range 1, 430^2, 450 cells:
+// 12.1 and 6.1; 8 x 510^2: 16.0 and 8.4.
+template <int RANGE>
+__global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile* tiles, int c,
+                                                       int sweep_off, int tab_lds_bytes,
+                                                       int cell_cap) {
+    // dynamic LDS as above; ids: (rows + 2 h) x (Lx + 2 h), h = RANGE
+    extern __shared__ __align__(16) uint8_t dyn[];
+    __shared__ PairTab pairs;
+    constexpr int ncol = RANGE == 2 ? 9 : 4, P = RANGE == 2 ? 3 : 2, h = RANGE;
+    const CpmTile& T = tiles[blockIdx.x];
+    const RepDev R = T.R;
+    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x, lane = tid & 63;
+    uint32_t* qthr = reinterpret_cast<uint32_t*>(dyn);
+    int32_t* lsa = reinterpret_cast<int32_t*>(dyn + tab_lds_bytes);
+    int32_t* ldel = lsa + cell_cap;
+    uint8_t* lty = reinterpret_cast<uint8_t*>(ldel + cell_cap);
+    uint32_t* queue0 = reinterpret_cast<uint32_t*>(lty + cell_cap);
+    uint32_t* queue = queue0 + 256 * (tid >> 6);
+    uint32_t* lids = queue0 + 4 * nthr;
+    const int Lx = R.Lx, Ly = R.Ly, y0 = T.y0, rows = T.rows;
+    const int st = Lx + 2 * h, nd = (rows + 2 * h) * st;
+    int32_t* gids = a.lat + R.lat_off;
+    const uint64_t PP = (uint64_t)ncol * (*a.t_base + (uint64_t)sweep_off) + (uint64_t)c;
+    const uint32_t p = (uint32_t)PP;
+    const PassAreas pa = pass_areas(a, PP, R.cell_off);
+    const int ncell = R.q + 1, ntab = 2 * R.tab_n;
+    const uint32_t mS = mdiv_of(st);
+    // every thread's first loads of each kind before any is used
+    constexpr int kU = 12;
+    int32_t v[kU];
+    const auto load = [&](int i) {
+        const int r = mdiv(i, mS);
+        return gids[(size_t)wrapc(y0 + r - h, Ly) * Lx + wrapc(i - r * st - h, Lx)];
+    };
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+        if (tid + u * nthr < nd) v[u] = load(tid + u * nthr);
+    constexpr int kC = 2;
+    int32_t sv[kC], av[kC];
+    uint8_t tv[kC];
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+        const int i = tid + u * nthr;
+        if (i < ncell) {
+            sv[u] = pa.s_rd[i] + pa.d_rd[i];
+            av[u] = a.target[R.cell_off + i];
+            tv[u] = (uint8_t)a.ctype[R.cell_off + i];
+        }
+    }
+    for (int i = tid; i < ntab; i += nthr) qthr[i] = a.tab[R.tab_off + i];
+    stage_pairs(a, R, &pairs, tid);
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+        const int i = tid + u * nthr;
+        if (i < ncell) {
+            lsa[i] = sv[u] - av[u];
+            lty[i] = (uint8_t)(8 * tv[u]);
+            ldel[i] = 0;
+        }
+    }
+    for (int i = tid + kC * nthr; i < ncell; i += nthr) {
+        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - a.target[R.cell_off + i];
+        lty[i] = (uint8_t)(8 * a.ctype[R.cell_off + i]);
+        ldel[i] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+        if (tid + u * nthr < nd) lids[tid + u * nthr] = (uint32_t)v[u];
+    for (int i = tid + kU * nthr; i < nd; i += nthr) lids[i] = (uint32_t)load(i);
+    pass_rotate(a, PP);
+    __syncthreads();
+    const int cy = c / P, cx = c - P * cy;
+    const int Wc = Lx / P, k0 = y0 / P * Wc, n = rows / P * Wc;  // the band's sites k0 .. k0 + n - 1
+    const int blk0 = k0 >> 2, n_blk = ((k0 + n + 3) >> 2) - blk0;
+    const uint32_t mW = mdiv_of(Wc);
+    const MooreTab moore = moore_tab(st);
+    const int oc = (cy + h) * st + cx + h, on = oc - h * st - h;
+    // every lane takes part (ballots); sites outside the band queue nothing
+    for (int g = 0; g < n_blk; g += nthr) {
+        const int b = blk0 + g + tid;
+        uint32_t e[4], off[4];
+        cpm_draw<RANGE>(a, R, moore, st, b, 4 * lane, p, e, off);
+        const int f = 4 * b - k0, f0 = max(f, 0);  // first site within the band
+        int r = mdiv(f0, mW), i = f0 - r * Wc;
+        bool act[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = f + u >= 0 && f + u < n;
+            const int o = in ? P * ((int)__umul24((uint32_t)r, (uint32_t)st) + i) : 0;
+            // (no branch around the reads: all of the block's together)
+            act[u] = (lids[oc + o] != lids[on + o + (int)off[u]]) & in;
+            if (f + u >= 0 && ++i == Wc) {
+                i = 0;
+                ++r;
+            }
+        }
+        const int cnt_q = queue_put(queue, act, e);
+        for (int q = lane; q < cnt_q; q += 64) {
+            const uint32_t ev = queue[q], jn = Entry<RANGE>::jn(ev);
+            const int k = 4 * (blk0 + g + (tid & ~63) + Entry<RANGE>::lane(ev)) + Entry<RANGE>::word(ev);
+            const int r2 = mdiv(k - k0, mW), i2 = k - k0 - (int)__umul24((uint32_t)r2, (uint32_t)Wc);
+            const uint32_t* nb = lids + on + P * ((int)__umul24((uint32_t)r2, (uint32_t)st) + i2);
+            const uint32_t s = nb[h * st + h];
+            const uint32_t tg = nb[RANGE == 1 ? moore_offset(moore, jn) : offset5(jn, st)];
+            uint32_t cnt = 0u;
+            int nt = 0, ns = 0;
+#pragma unroll
+            for (int dy = 0; dy <= 2 * h; ++dy)
+#pragma unroll
+                for (int dx = 0; dx <= 2 * h; ++dx) {
+                    if (dy == h && dx == h) continue;  // the site itself
+                    const uint32_t m = nb[dy * st + dx];
+                    cnt += 1u << lty[m];
+                    nt += m == tg;
+                    ns += m == s;
+                }
+            if (cpm_accept(a, R, s | ((uint32_t)lty[s] << 24), tg | ((uint32_t)lty[tg] << 24), cnt, nt,
+                           ns, &pairs, lsa[tg], lsa[s], qthr, ev >> 16, (uint32_t)k, p)) {
+                gids[(size_t)(y0 + P * r2 + cy) * Lx + P * i2 + cx] = (int)tg;
+                atomicAdd(&ldel[tg], 1);
+                atomicAdd(&ldel[s], -1);
+            }
+        }
+        // the queue is read before the next round's entries
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (int i = tid; i < ncell; i += nthr) {
+        const int d = ldel[i];
+        if (d != 0) atomicAdd(&pa.d_wr[i], d);
+    }
+}
+
+size_t cpm_band_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int threads, int rows,
+                          int Lx) {
+    return (size_t)tab_lds_bytes + (size_t)9 * cell_cap + (size_t)16 * threads +
+           (size_t)4 * (rows + 2 * range) * (Lx + 2 * range);
+}
+
+hipError_t cpm_band_reserve_lds(int range, size_t lds_bytes) {
+    return hipFuncSetAttribute(range == 2 ? (const void*)k_cpm_pass_band<2>
+                                          : (const void*)k_cpm_pass_band<1>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+}
+
+hipError_t launch_cpm_pass_band(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
+                                int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
+                                size_t lds_bytes, hipStream_t s) {
+    if (a.range == 2)
+        hipLaunchKernelGGL(k_cpm_pass_band<2>, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles,
+                           c, sweep_off, tab_lds_bytes, cell_cap);
+    else
+        hipLaunchKernelGGL(k_cpm_pass_band<1>, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles,
+                           c, sweep_off, tab_lds_bytes, cell_cap);
+    return hipGetLastError();
 }
 
 size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols) {
@@ -1389,22 +1560,25 @@ int cpm_resident_lanes(int range, int max_sites) {
 
 size_t cpm_resident_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int max_sites,
                               int max_padded) {
-    if (max_sites / (range == 2 ? 9 : 4) > (range == 2 ? 2048 : 8192)) return SIZE_MAX;
     const int lanes = cpm_resident_lanes(range, max_sites);
     return (size_t)tab_lds_bytes + (size_t)20 * cell_cap +
            (size_t)(lanes <= 512 ? 16 + 48 : 16) * lanes + (size_t)4 * max_padded;
 }
 
-hipError_t launch_cpm_resident(const CpmArgs& a, int n_steps, int sw0, int re, int tab_lds_bytes,
-                               int cell_cap, int max_sites, int max_padded, hipStream_t s) {
+hipError_t launch_cpm_resident(const CpmArgs& a, bool rows, int n_steps, int sw0, int re,
+                               int tab_lds_bytes, int cell_cap, int max_sites, int max_padded,
+                               hipStream_t s) {
     const size_t lds =
         cpm_resident_lds_bytes(a.range, tab_lds_bytes, cell_cap, max_sites, max_padded);
     const int lanes = cpm_resident_lanes(a.range, max_sites);
     const bool gen = lanes <= 512;
-    const void* fn = a.range == 2 ? (gen ? (const void*)k_cpm_resident<2, true>
-                                         : (const void*)k_cpm_resident<2, false>)
-                                  : (gen ? (const void*)k_cpm_resident<1, true>
-                                         : (const void*)k_cpm_resident<1, false>);
+    const void* fn =
+        a.range == 2 ? (gen ? (const void*)k_cpm_resident<2, true, false>
+                            : (const void*)k_cpm_resident<2, false, false>)
+        : rows       ? (gen ? (const void*)k_cpm_resident<1, true, true>
+                            : (const void*)k_cpm_resident<1, false, true>)
+                     : (gen ? (const void*)k_cpm_resident<1, true, false>
+                            : (const void*)k_cpm_resident<1, false, false>);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int queue_words = 4 * lanes;

@@ -2110,27 +2110,48 @@ int cpm_pass_threads(const spinmc_ctx* c) {
 // per lane), 4096 where that leaves compute units without a tile (8 x 256^2:
 // 5.3 against 5.8 us a pass; 8 x 512^2: 6.5 with 8192, 7.2 with 4096; in
 // workgroups of 256 lanes 8.1 at best); fewer where the LDS asks for it.
+// Bands (every other lattice): the fewest rows, of 2048 sites or more, that leave
+// no compute unit two bands (range 2, 3 x 378^2: 6 rows, 189 bands, 6.3 us a pass,
+// 3 rows 7.2, 9 rows 6.5; 8 x 510^2: 18 rows, 232 bands, 9.1, 15 rows, 272 bands,
+// 10.3; range 1, 8 x 510^2: 16 rows, 256 bands, 8.3, 12 rows 9.5; 256 lanes are
+// slower in each), 8192 sites where these would pass 9216.
 int cpm_build_ctiles(spinmc_ctx* c) {
     hipFree(c->d_ctiles);
     c->d_ctiles = nullptr;
     c->n_ctiles = 0;
-    if (c->cpm_range != 1 || !c->cpm_quad || c->sched.wg_threads != 0) return SPINMC_OK;
+    if (c->sched.wg_threads != 0) return SPINMC_OK;
     const int tab = (int)align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
-    const int threads = 512;
+    const int threads = 512, P = c->cpm_range == 2 ? 3 : 2;
     std::vector<CpmTile> tiles;
     size_t lds = 0, sites = 0;
     for (const HostRep& h : c->reps) sites += (size_t)h.dev.Lx * h.dev.Ly;
-    const int per = sites / 8192 < 256 ? 4096 : 8192;
+    int per = sites / 8192 < 256 ? 4096 : 8192;
+    const auto band_rows = [&](const HostRep& h) {  // whole periods, per sites or more
+        return std::max(P, ((per + h.dev.Lx - 1) / h.dev.Lx + P - 1) / P * P);
+    };
+    if (!c->cpm_quad) {
+        for (per = 2048;; per += 512) {
+            size_t bands = 0;
+            for (const HostRep& h : c->reps)
+                bands += (size_t)((h.dev.Ly + band_rows(h) - 1) / band_rows(h));
+            if (bands <= 256 || per > 9216) break;
+        }
+        if (per > 9216) per = 8192;
+    }
     for (const HostRep& h : c->reps) {
         const int Lx = h.dev.Lx, Ly = h.dev.Ly;
-        const int cols = std::min(Lx, 512);
-        int rows = c->sched.tile_rows > 0 ? c->sched.tile_rows & ~1 : per / cols & ~1;
-        rows = std::max(2, std::min(rows, Ly));
-        while (rows > 2 &&
-               (rows * cols > 4 * 8192 ||
-                cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols) > kCpmResidentLdsMax))
-            rows -= 2;
-        const size_t need = cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols);
+        const int cols = c->cpm_quad ? std::min(Lx, 512) : Lx;
+        const auto bytes = [&](int rows) {
+            return c->cpm_quad ? cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols)
+                               : cpm_band_lds_bytes(c->cpm_range, tab, c->cpm_cell_cap, threads,
+                                                    rows, Lx);
+        };
+        int rows = std::min(c->sched.tile_rows > 0 ? c->sched.tile_rows
+                                                   : (c->cpm_quad ? per / cols : band_rows(h)),
+                            Ly);
+        rows = std::max(P, rows / P * P);
+        while (rows > P && bytes(rows) > kCpmResidentLdsMax) rows -= P;
+        const size_t need = bytes(rows);
         if (need > kCpmResidentLdsMax) return SPINMC_OK;
         lds = std::max(lds, need);
         for (int y0 = 0; y0 < Ly; y0 += rows)
@@ -2142,7 +2163,8 @@ int cpm_build_ctiles(spinmc_ctx* c) {
     if (e == hipSuccess)
         e = hipMemcpy(c->d_ctiles, tiles.data(), sizeof(CpmTile) * tiles.size(),
                       hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = cpm_tile_reserve_lds(lds);
+    if (e == hipSuccess)
+        e = c->cpm_quad ? cpm_tile_reserve_lds(lds) : cpm_band_reserve_lds(c->cpm_range, lds);
     c->n_ctiles = (int)tiles.size();
     c->ctile_threads = threads;
     c->ctile_lds = lds;
@@ -2410,6 +2432,9 @@ hipError_t cpm_enqueue_pass(spinmc_ctx* c, const CpmArgs& a, int i, int col, hip
     const size_t tab_bytes = align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
     const int threads = cpm_pass_threads(c);
     return timed(c, SPINMC_K_CPM_PASS, [&] {
+        if (c->d_ctiles && !c->cpm_quad)
+            return launch_cpm_pass_band(a, c->d_ctiles, c->n_ctiles, col, i, c->ctile_threads,
+                                        (int)tab_bytes, c->cpm_cell_cap, c->ctile_lds, s);
         if (c->cpm_range == 2)
             return launch_cpm_pass5(a, c->n_tiles, col, i, threads, tab_bytes, s);
         if (c->d_ctiles)
@@ -2470,22 +2495,24 @@ int cpm_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     }
     hipError_t e = hipSuccess;
     // steps of lattices whose ids, tables and queue fit the LDS of a compute
-    // unit (the 3x3 neighbourhood with every Lx % 8 == 0, or the 5x5 one),
-    // recorded or not: the resident kernel, one launch per chunk of at most
-    // 500 steps (the step counter advances after each), unless streamed passes
-    // or, for lattices above 64 KiB of ids, tiled ones are requested
+    // unit, recorded or not: the resident kernel, one launch per chunk of at
+    // most 500 steps (the step counter advances after each), unless streamed
+    // passes or, for lattices above 64 KiB of ids, tiled ones are requested.
+    // Also for one large lattice, which then has one compute unit: the barrier
+    // of a pass costs less than its launch (us a pass, streamed and resident:
+    // range 2, 1 x 180^2 5.9 and 3.5; range 1, 1 x 164^2 5.3 and 5.0)
     const bool tiled = re == 0 && (c->sched.flags & SPINMC_SCHED_PERSIST) && c->cpm_range == 1 &&
                        (size_t)4 * c->max_sites > 64 * 1024;
     int max_padded = 0;
     for (const HostRep& h : c->reps)
         max_padded = std::max(max_padded, (h.dev.Lx + 2 * c->cpm_range) * (h.dev.Ly + 2 * c->cpm_range));
-    if (!c->prof && (c->cpm_quad || c->cpm_range == 2) && c->sched.mode != 2 && !tiled &&
+    if (!c->prof && c->sched.mode != 2 && !tiled &&
         cpm_resident_lds_bytes(c->cpm_range, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
                                max_padded) <= kCpmResidentLdsMax) {
         for (int done = 0; done < n && e == hipSuccess;) {
             const int k = std::min(500, n - done);
-            e = launch_cpm_resident(a, k, done, re, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
-                                    max_padded, c->stream);
+            e = launch_cpm_resident(a, c->cpm_quad, k, done, re, (int)tab_bytes, c->cpm_cell_cap,
+                                    c->max_sites, max_padded, c->stream);
             if (e == hipSuccess) e = launch_advance(c->d_t, (uint64_t)k, c->stream);
             done += k;
         }

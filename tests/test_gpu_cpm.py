@@ -487,3 +487,49 @@ def test_streamed_tile_pass_matches_oracle(S, shape, n_cells, n_types, tile_rows
         assert np.array_equal(smp.get_state(r), want), r
         assert np.array_equal(st[:, r], ost), r
     smp.close()
+
+
+# the streamed pass over bands of rows: the smallest lattices, blocks across
+# rows and bands, a ragged last band, more blocks than lanes, cell tables and a
+# width that leave no room for a band (one attempt per lane)
+@pytest.mark.parametrize("cpm_range,shape,n_cells,n_types,tile_rows", [
+    (1, (2, 2), 2, 2, 0), (1, (6, 10), 5, 3, 2), (1, (34, 42), 30, 3, 32), (1, (66, 420), 200, 4, 0),
+    (1, (70, 134), 60, 3, 70), (1, (32, 36), 17300, 3, 0), (1, (4, 12006), 300, 3, 0),
+    (2, (6, 6), 3, 2, 4), (2, (12, 18), 8, 3, 10), (2, (66, 60), 40, 3, 0), (2, (126, 150), 90, 4, 126),
+    (2, (36, 30), 17300, 3, 0), (2, (6, 8004), 300, 3, 0)])
+def test_streamed_band_pass_matches_oracle(S, cpm_range, shape, n_cells, n_types, tile_rows):
+    rng = np.random.default_rng(n_cells)
+    J = rng.integers(0, 17, size=(n_types, n_types)).astype(np.float32)
+    J = np.triu(J) + np.triu(J, 1).T
+    cases = [_random_case(520 + r, shape, n_cells, n_types) for r in range(2)]
+    reps = [dict(_rep(ids, J, ct, A, 1.0, 12.0, 40 + r), cpm_range=cpm_range)
+            for r, (ids, ct, A) in enumerate(cases)]
+    smp = S(reps, 29, init=False)
+    smp.set_schedule(mode="stream", tile_rows=tile_rows)
+    for r, (ids, _, _) in enumerate(cases):
+        smp.set_state(r, ids)
+    smp.sweep(2)
+    st = smp.sweep(2, 1).cpu().numpy()
+    for r, (ids, ct, A) in enumerate(cases):
+        s1, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 29, 40 + r, 0, 2, nrange=cpm_range)
+        want, _, ost = orc.cpm_run(s1, J, ct, A, 1.0, 12.0, 29, 40 + r, 2, 2, 1, nrange=cpm_range)
+        assert np.array_equal(smp.get_state(r), want), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
+
+
+# resident lattices whose blocks cross rows (range 1) or whose within-colour
+# index passes 2048 (range 2): the smallest, both forms of the kernel, the largest
+@pytest.mark.parametrize("cpm_range,shape,n_cells", [
+    (1, (2, 2), 2), (1, (18, 30), 9), (1, (90, 90), 40), (1, (90, 94), 40), (1, (186, 186), 90),
+    (2, (138, 138), 60), (2, (186, 180), 90)])
+def test_resident_blocks_across_rows_match_oracle(S, cpm_range, shape, n_cells):
+    J = JS["sorting"]
+    ids, ct, A = _random_case(540 + n_cells, shape, n_cells)
+    smp = S([dict(_rep(ids, J, ct, A, 1.0, 12.0, 50), cpm_range=cpm_range)], 31, init=False)
+    smp.set_state(0, ids)
+    st = smp.sweep(3, 1).cpu().numpy()
+    want, _, ost = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 31, 50, 0, 3, 1, nrange=cpm_range)
+    assert np.array_equal(smp.get_state(0), want)
+    assert np.array_equal(st[:, 0], ost)
+    smp.close()
