@@ -2780,17 +2780,33 @@ int tri_get_state(spinmc_ctx* c, int r, void* host, size_t bytes) {
     return check_dev(c, e, "get_state");
 }
 
-// Resident schedule (recorded sweeps too): every lattice in LDS (<= 64 KiB,
-// so that two workgroups fit a compute unit) and the span alignment.
-bool tri_resident_ok(const spinmc_ctx* c, const TriArgs& a, int* lds) {
+// Resident schedule (recorded sweeps too, every re-th): every lattice in LDS,
+// up to 64 KiB (two workgroups fit a compute unit) where the rows are whole
+// Philox blocks, else up to 140 KiB, rows of a block's four sites or more, and
+// where that is the faster: a compute unit takes about 1.85 ns a block, streamed
+// passes 3.6 us each and 14 ps a block, and 25 us more for a recorded sweep
+// (us a sweep, resident and streamed: triangular 75^2 4.0 and 13.3 with 64
+// lattices, 249^2 27.3 and 13.4 with 4, 28.8 and 81.6 with 256, recorded 34.0 and
+// 40.6 with 4; cubic 18^3 4.3 and 13.5 with 256, 38^3 27.0 and 21.2 with 64).
+bool tri_resident_ok(const spinmc_ctx* c, const TriArgs& a, int re, int* lds) {
     if (c->sched.mode == 2) return false;  // streamed passes requested
+    const bool hc = a.model == kModelIsingHC;
+    const bool whole = hc ? a.all_lx8 : a.all_lx12;
+    const int n_col = hc ? 2 : 3;
     size_t mx = 0;
+    double blocks = 0.0, most = 0.0;
     for (const HostRep& h : c->reps) {
         mx = std::max(mx, h.lat_bytes);
-        if (a.model == kModelIsingHC ? h.dev.Lx % 8 : h.dev.Lx % 12) return false;
-        if (h.lat_bytes % 4) return false;
+        const size_t W = (size_t)h.dev.Lx / n_col;
+        // the kernel's quotients of within-colour indices by W are exact below 2^32
+        if (!whole && (W < 4 || h.lat_bytes / n_col * W >= ((size_t)1 << 32))) return false;
+        blocks += h.lat_bytes * 0.25;
+        most = std::max(most, h.lat_bytes * 0.25);
     }
-    if (mx > 64 * 1024) return false;
+    if (mx > (whole ? 64 : 140) * (size_t)1024) return false;
+    if (!whole && 1.85e-3 * most * ((c->R + 255) / 256) >
+                      3.6 * n_col + 14e-6 * blocks + (re > 0 ? 25.0 / re : 0.0))
+        return false;
     *lds = (int)align_up(mx, 16);
     return true;
 }
@@ -2801,7 +2817,7 @@ int tri_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     int lds = 0;
     const int n_rec = re > 0 ? n / re : 0;
     if (n_rec > 0) e = launch_fill_i32(stats, (size_t)n_rec * c->R * c->width, 0, c->stream);
-    if (tri_resident_ok(c, a, &lds)) {
+    if (tri_resident_ok(c, a, re, &lds)) {
         // chunks of at most 1000 sweeps per launch (statistics recorded inside);
         // the counter advances after each
         for (int done = 0; done < n && e == hipSuccess;) {

@@ -817,6 +817,163 @@ __global__ void __launch_bounds__(1024) k_plane_resident(TriArgs a, int n_sweeps
         lat[i] = reinterpret_cast<const uint32_t*>(ls)[i] * 0xFEu + 0x01010101u;
 }
 
+// The same launch for every other width (a plane row of W >= 4 sites): a Philox
+// block's four sites may run on into the next row, so a lane works site by site,
+// on the lattice in natural order -- a site's partners are then at the same
+// distances in every colour, but for the wraps, which depend on the row (worked out
+// for the block's two rows) and on x.  The statistics of a recorded sweep come from
+// its passes: a bond is counted with its later end, whose partner is final.
+// About 270 lane-instructions a block, 60 of them Philox, which bound a full chip:
+// 512 triangular 75^2 take 6.4 us a sweep and 7.9 a recorded one (streamed site by
+// site 23.8 and 66.1), 256 x 30^3 15.0 and 16.2 (35.7 and 158.9).
+namespace {
+struct RowAt {
+    int base, up, dn, zu, zd;  // row's first site; from a site to its partners in y and z
+    int ph;                    // x of the colour's first site
+};
+
+template <int MODEL>
+__device__ __forceinline__ RowAt row_at(int row, int c, int Lx, int Ly, int Lz, uint32_t mY) {
+    RowAt r;
+    const int z = MODEL == kModelIsingTri || Lz == 1 ? 0 : (Ly == 1 ? row : (int)__umulhi((uint32_t)row, mY));
+    const int y = row - z * Ly, slab = Lx * Ly;
+    r.base = row * Lx;
+    r.up = y == 0 ? slab - Lx : -Lx;
+    r.dn = y + 1 == Ly ? Lx - slab : Lx;
+    r.zu = z == 0 ? slab * (Lz - 1) : -slab;
+    r.zd = z + 1 == Lz ? slab * (1 - Lz) : slab;
+    r.ph = MODEL == kModelIsingTri ? (c + y) % 3 : (c + y + z) & 1;
+    return r;
+}
+}  // namespace
+
+template <int MODEL>
+__global__ void __launch_bounds__(1024) k_plane_resident_any(TriArgs a, int n_sweeps, int sw0,
+                                                             int re) {
+    extern __shared__ __align__(16) uint8_t lsn[];  // a spin a byte (1 for -1) | recorded rows
+    __shared__ uint32_t lt[16];
+    __shared__ uint32_t lzero;
+    constexpr bool TRI = MODEL == kModelIsingTri;
+    constexpr int ncol = TRI ? 3 : 2;
+    const int r = blockIdx.x, tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+    const RepDev D = a.reps[r];
+    const int Lx = D.Lx, Ly = D.Ly, Lz = TRI ? 1 : D.q, W = Lx / ncol, rows = Ly * Lz;
+    const int n = Lx * rows, nk = n / ncol;
+    const bool hy = TRI || Ly > 1, hz = !TRI && Lz > 1;
+    // exact quotients b / d for b d < 2^32, d > 1
+    const uint32_t mW = 0xFFFFFFFFu / (uint32_t)W + 1u, mY = 0xFFFFFFFFu / (uint32_t)Ly + 1u;
+    int8_t* lat = a.lat + D.lat_off;
+    if (tid == 0) lzero = 0u;
+    __syncthreads();
+    if (tid < 16) {
+        const int k = TRI ? 6 : 2 + 2 * (Ly > 1) + 2 * (Lz > 1);
+        const uint64_t T = keyed_threshold(a.tab + (size_t)r * kTriClasses, tid, k);
+        lt[tid] = (uint32_t)(T - 1u);
+        if (T == 0u && (tid & 7) <= k) atomicOr(&lzero, 1u << tid);
+    }
+    // place in natural order of site k of colour c
+    const auto place = [&](int c, int k) {
+        const int row = (int)__umulhi((uint32_t)k, mW);
+        return row * Lx + ncol * (k - row * W) + row_at<MODEL>(row, c, Lx, Ly, Lz, mY).ph;
+    };
+    for (int c = 0; c < ncol; ++c)
+#pragma unroll 4
+        for (int k = tid; k < nk; k += nthr) lsn[place(c, k)] = ((uint8_t)lat[c * nk + k] >> 1) & 1u;
+    int* lrec = reinterpret_cast<int*>(lsn + ((n + 15) & ~15));
+    const int rec0 = re > 0 ? sw0 / re + 1 : 0;
+    const int n_rows = re > 0 ? (sw0 + n_sweeps) / re - sw0 / re : 0;
+    for (int i = tid; i < 4 * n_rows; i += nthr) lrec[i] = 0;
+    __syncthreads();
+    const uint32_t zero = __builtin_amdgcn_readfirstlane(lzero);
+    const uint64_t t0 = *a.t_base;
+    int next = re > 0 ? rec0 * re - sw0 : 0;  // sweeps to the next recorded one
+    for (int sw = 0; sw < n_sweeps; ++sw) {
+        const bool rec = re > 0 && sw + 1 == next;
+        int cnt[4] = {0, 0, 0, 0};
+        for (int c = 0; c < ncol; ++c) {
+            const uint32_t p = (uint32_t)((uint64_t)ncol * (t0 + (uint64_t)sw) + (uint64_t)c);
+            for (int b = tid; 4 * b < nk; b += nthr) {
+                const int row = (int)__umulhi((uint32_t)(4 * b), mW), j0 = 4 * b - row * W;
+                const RowAt ra = row_at<MODEL>(row, c, Lx, Ly, Lz, mY);
+                const RowAt rb = row_at<MODEL>(min(row + 1, rows - 1), c, Lx, Ly, Lz, mY);
+                int at[4], s[4], N[4], nx[4], ny[4], nz[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool nr = j0 + u >= W;  // in the block's second row
+                    const int x = ncol * (nr ? j0 + u - W : j0 + u) + (nr ? rb.ph : ra.ph);
+                    const int o = (nr ? rb.base : ra.base) + x;
+                    const int ol = x == 0 ? o + Lx - 1 : o - 1, orr = x + 1 == Lx ? o + 1 - Lx : o + 1;
+                    at[u] = o;
+                    s[u] = lsn[o];
+                    if (TRI) {
+                        // nx the partners of the next colour, ny those of the one before
+                        const int up = nr ? rb.up : ra.up, dn = nr ? rb.dn : ra.dn;
+                        const int l = lsn[ol], d = lsn[o + dn], ur = lsn[orr + up];
+                        const int R = lsn[orr], U = lsn[o + up], dl = lsn[ol + dn];
+                        N[u] = l + d + ur + R + U + dl;
+                        // by colour: c - 1 (bit fields l, d, ur), all (sums by direction)
+                        nx[u] = l | (d << 8) | (ur << 16);
+                        ny[u] = (l + R) | ((d + U) << 8) | ((ur + dl) << 16);
+                    } else {
+                        nx[u] = lsn[ol] + lsn[orr];
+                        ny[u] = nz[u] = 0;
+                        if (hy) ny[u] = lsn[o + (nr ? rb.up : ra.up)] + lsn[o + (nr ? rb.dn : ra.dn)];
+                        if (hz) nz[u] = lsn[o + (nr ? rb.zu : ra.zu)] + lsn[o + (nr ? rb.zd : ra.zd)];
+                        N[u] = nx[u] + ny[u] + nz[u];
+                    }
+                }
+                uint32_t w[4];
+                philox4x32_10((uint32_t)b, p, D.rid, kTriTagMain, a.key0, a.key1, w);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int K = N[u] + 8 * s[u];
+                    const bool in = 4 * b + u < nk;
+                    bool f = w[u] <= lt[K];
+                    if (zero != 0u) f = f && ((zero >> K) & 1u) == 0u;  // uniform
+                    s[u] ^= f ? 1 : 0;
+                    if (in) lsn[at[u]] = (uint8_t)s[u];
+                    if (rec && in) {  // rec uniform
+                        cnt[0] += s[u];
+                        if (TRI) {
+                            // unequal bonds of a -1 spin: partners less those of -1
+                            const int m = c == 0 ? 0 : (c == 1 ? nx[u] : ny[u]);
+                            const int full = c == 0 ? 0 : (c == 1 ? 0x010101 : 0x020202);
+                            const int e = s[u] ? full - m : m;
+                            cnt[1] += e & 0xFF;
+                            cnt[2] += (e >> 8) & 0xFF;
+                            cnt[3] += e >> 16;
+                        } else if (c == 1) {
+                            cnt[1] += s[u] ? 2 - nx[u] : nx[u];
+                            cnt[2] += s[u] ? 2 - ny[u] : ny[u];
+                            cnt[3] += s[u] ? 2 - nz[u] : nz[u];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        if (rec) {
+            int* row = lrec + 4 * ((sw0 + sw + 1) / re - rec0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                cnt[j] = __ockl_wfred_add_i32(cnt[j]);
+                if ((tid & 63) == 0) atomicAdd(&row[j], cnt[j]);
+            }
+            next += re;
+        }
+    }
+    __syncthreads();
+    // counts to sums: n - 2 x (-1 spins, unequal bonds); 0 for an absent dimension
+    for (int i = tid; i < 4 * n_rows; i += nthr) {
+        const int j = i & 3;
+        const bool has = j < 2 || (j == 2 ? hy : TRI || hz);
+        a.stats[((size_t)(rec0 - 1 + (i >> 2)) * a.R + r) * a.width + j] = has ? n - 2 * lrec[i] : 0;
+    }
+    for (int c = 0; c < ncol; ++c)
+#pragma unroll 4
+        for (int k = tid; k < nk; k += nthr) lat[c * nk + k] = lsn[place(c, k)] ? (int8_t)-1 : (int8_t)1;
+}
+
 namespace {
 const void* plane_resident_fn(bool hc, int nb, int ni) {
     if (hc)
@@ -834,6 +991,16 @@ const void* plane_resident_fn(bool hc, int nb, int ni) {
 hipError_t launch_plane_resident(const TriArgs& a, int n_sweeps, int sw0, int re, int lds_bytes,
                                  hipStream_t s) {
     const bool hc = a.model == kModelIsingHC;
+    if (!(hc ? a.all_lx8 : a.all_lx12)) {
+        const void* fn = hc ? (const void*)k_plane_resident_any<kModelIsingHC>
+                            : (const void*)k_plane_resident_any<kModelIsingTri>;
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (e != hipSuccess) return e;
+        TriArgs b = a;
+        void* args[] = {&b, &n_sweeps, &sw0, &re};
+        return hipLaunchKernel(fn, dim3(a.R), dim3(std::min(1024, (a.max_blocks + 63) & ~63)), args,
+                               lds_bytes, s);
+    }
     // one block a lane where the lanes suffice (more waves, shorter chains: 512
     // sites 0.54 us a sweep against 1.13, 1024 triangular 96 x 96 lattices 4.9
     // against 6.0), else two, which share half their reads (256 lattices of

@@ -87,3 +87,42 @@ def test_measured_statistics_equal_recorded_ones(dims):
     got, _ = smp.measure()
     assert torch.equal(got, st)
     smp.close()
+
+
+@pytest.mark.parametrize("Ly,Lx,n_rep,beta", [
+    (3, 15, 1, 0.27), (6, 21, 2, 0.27), (27, 33, 3, 0.27),  # blocks across rows
+    (102, 123, 2, 0.27), (243, 267, 1, 0.27), (3, 21843, 1, 0.27),  # rounds of blocks; the limit
+    (12, 27, 2, 90.0),  # T = 0 for the largest energy changes
+])
+def test_triangular_blocks_across_rows(Ly, Lx, n_rep, beta):
+    reps = [dict(model=3, Lx=Lx, Ly=Ly, Jx=1.0 - 0.5 * r, Jy=1.0 - 0.5 * r, h=0.05, beta=beta,
+                 rid=70 + r) for r in range(n_rep)]
+    reps.append(dict(reps[0], Lx=12, Ly=3, rid=79))  # whole blocks beside the others
+    _check(reps, lambda s, d, seed, t, n, e: orc.tri_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
+                                                         t, n, e), every=3 if Lx * Ly < 20000 else 1)
+
+
+@pytest.mark.parametrize("Lz,Ly,Lx,beta", [
+    (1, 1, 10, 0.4), (1, 1, 4098, 0.4), (1, 1, 65534, 0.4), (1, 2, 14, 0.4), (2, 2, 10, 0.3),
+    (1, 66, 70, 0.4), (4, 1, 18, 0.3), (34, 30, 34, 0.22), (40, 38, 42, 0.22),
+    (2, 4, 10, 130.0),  # T = 0 for the largest energy changes
+])
+def test_chain_square_cubic_blocks_across_rows(Lz, Ly, Lx, beta):
+    reps = [dict(model=4, Lx=Lx, Ly=Ly, Lz=Lz, Jx=1.0 - 0.7 * r, Jy=1.0 - 0.7 * r, h=-0.03,
+                 beta=beta, rid=80 + r) for r in range(2)]
+    _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
+                                                        t, n, e), every=3 if Lx * Ly * Lz < 20000 else 1)
+
+
+def test_large_lattices_in_numbers_across_rows():
+    """Lattices above 64 KiB of which every compute unit has one."""
+    from paper_2304_01772_amd.sampler import Sampler
+    reps = [dict(model=3, Lx=375, Ly=375, Jx=1.0, Jy=1.0, h=0.02, beta=0.27, rid=r)
+            for r in range(128)]
+    smp = Sampler(reps, 63, init=True)
+    init = smp.get_state(127)
+    st = smp.sweep(3, 1).cpu().numpy()
+    want, ost = orc.tri_run(init, 1.0, 0.02, 0.27, 63, 127, 0, 3, 1)
+    assert np.array_equal(smp.get_state(127), want)
+    assert np.array_equal(st[:, 127], ost)
+    smp.close()
