@@ -2783,11 +2783,12 @@ int tri_get_state(spinmc_ctx* c, int r, void* host, size_t bytes) {
 // Resident schedule (recorded sweeps too, every re-th): every lattice in LDS,
 // up to 64 KiB (two workgroups fit a compute unit) where the rows are whole
 // Philox blocks, else up to 140 KiB, rows of a block's four sites or more, and
-// where that is the faster: a compute unit takes about 1.85 ns a block, streamed
-// passes 3.6 us each and 14 ps a block, and 25 us more for a recorded sweep
-// (us a sweep, resident and streamed: triangular 75^2 4.0 and 13.3 with 64
-// lattices, 249^2 27.3 and 13.4 with 4, 28.8 and 81.6 with 256, recorded 34.0 and
-// 40.6 with 4; cubic 18^3 4.3 and 13.5 with 256, 38^3 27.0 and 21.2 with 64).
+// where that is the faster (mode 0; mode 3 asks for it): a compute unit takes about
+// 1.85 ns a block and a fifth more in a recorded sweep, streamed passes 3.6 us each
+// and 14 ps a block, and 6 us and 10 ps a block more for a recorded sweep
+// (us a sweep, resident and streamed: triangular 75^2 4.0 and 11.4 with 64
+// lattices, 249^2 27.3 and 11.4 with 4, 28.8 and 69 with 256, recorded 34.0 and
+// 17.7 with 4; cubic 18^3 4.3 and 12.0 with 256, 38^3 27.0 and 20.7 with 64).
 bool tri_resident_ok(const spinmc_ctx* c, const TriArgs& a, int re, int* lds) {
     if (c->sched.mode == 2) return false;  // streamed passes requested
     const bool hc = a.model == kModelIsingHC;
@@ -2804,8 +2805,10 @@ bool tri_resident_ok(const spinmc_ctx* c, const TriArgs& a, int re, int* lds) {
         most = std::max(most, h.lat_bytes * 0.25);
     }
     if (mx > (whole ? 64 : 140) * (size_t)1024) return false;
-    if (!whole && 1.85e-3 * most * ((c->R + 255) / 256) >
-                      3.6 * n_col + 14e-6 * blocks + (re > 0 ? 25.0 / re : 0.0))
+    const double part = re > 0 ? 1.0 / re : 0.0;  // of the sweeps, recorded
+    if (!whole && c->sched.mode == 0 &&
+        (1.0 + 0.2 * part) * 1.85e-3 * most * ((c->R + 255) / 256) >
+            3.6 * n_col + 14e-6 * blocks + part * (6.0 + 10e-6 * blocks))
         return false;
     *lds = (int)align_up(mx, 16);
     return true;

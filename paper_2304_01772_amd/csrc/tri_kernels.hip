@@ -64,38 +64,6 @@ __global__ void __launch_bounds__(256) k_tri_init(TriArgs a) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_tri_pass(TriArgs a, int c, int sweep_off) {
-    __shared__ uint64_t lt[kTriClasses];
-    const int r = blockIdx.y;
-    if (threadIdx.x < kTriClasses) lt[threadIdx.x] = a.tab[(size_t)r * kTriClasses + threadIdx.x];
-    __syncthreads();
-    const RepDev D = a.reps[r];
-    const int Lx = D.Lx, Ly = D.Ly, W3 = Lx / 3;
-    const int nk = Ly * W3;
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (4 * b >= nk) return;
-    const uint64_t t = *a.t_base + (uint64_t)sweep_off;
-    const uint32_t p = (uint32_t)(3 * t + (uint64_t)c);
-    uint32_t w[4];
-    philox4x32_10((uint32_t)b, p, D.rid, kTriTagMain, a.key0, a.key1, w);
-    int8_t* lat = a.lat + D.lat_off;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = 4 * b + u;
-        if (k >= nk) break;
-        const int y = k / W3;
-        const int x = 3 * (k - y * W3) + (c + y) % 3;
-        const int yu = wrapt(y - 1, Ly), yd = wrapt(y + 1, Ly);
-        const int xl = wrapt(x - 1, Lx), xr = wrapt(x + 1, Lx);
-        const int s = lat[(size_t)c * nk + k];
-        const int S6 = lat[tri_byte(y, xl, Lx, Ly)] + lat[tri_byte(y, xr, Lx, Ly)] +
-                       lat[tri_byte(yu, x, Lx, Ly)] + lat[tri_byte(yd, x, Lx, Ly)] +
-                       lat[tri_byte(yu, xr, Lx, Ly)] + lat[tri_byte(yd, xl, Lx, Ly)];
-        const int idx = 7 * (s > 0) + (S6 + 6) / 2;
-        if ((uint64_t)w[u] < lt[idx]) lat[(size_t)c * nk + k] = (int8_t)(-s);
-    }
-}
-
 // Span form of a pass (four sites of one Philox block per lane, byte
 // arithmetic in 32-bit words).  A spin byte is 0x01 (+1) or 0xFF (-1), so
 // v & 0x02020202 flags the -1 bytes of a word as 2 per byte.  Sums of such
@@ -158,6 +126,149 @@ __device__ __forceinline__ uint32_t ld32(const int8_t* p) { return *reinterpret_
 __device__ __forceinline__ uint2 ld64(const int8_t* p) { return *reinterpret_cast<const uint2*>(p); }
 __device__ __forceinline__ uint32_t negflag(const int8_t* p) { return (uint32_t)(uint8_t)*p & 2u; }
 }  // namespace
+
+// Lattices of any width, site by site on the colour planes.  A lane takes the four
+// sites of a Philox block, which may run on into the next rows: one division finds
+// the first, the others follow by steps, and all of the block's bytes are loaded
+// before any is decided.  Bound by its byte loads (28 a block in three dimensions)
+// and their addresses; with one division a site and each site's loads behind the
+// store before it, 4 triangular lattices of 195^2 took 13.1 us a sweep, 8 x 375^2
+// 14.9, now 11.2 and 12.5; a recorded sweep 26 us more, now 6.
+namespace {
+template <int MODEL>
+struct PlaneSite {
+    int W, Ly, Lz, nk;
+    int row, j, y, z;  // the site is byte j of row z Ly + y of its plane
+
+    __device__ __forceinline__ PlaneSite(const RepDev& D, int k) {
+        constexpr bool TRI = MODEL == kModelIsingTri;
+        W = TRI ? D.Lx / 3 : D.Lx >> 1;
+        Ly = D.Ly;
+        Lz = TRI ? 1 : D.q;
+        nk = W * Ly * Lz;
+        const bool small = nk < 1 << 22;
+        row = qdiv(k, W, small);
+        j = k - row * W;
+        z = Lz > 1 ? qdiv(row, Ly, small) : 0;
+        y = row - z * Ly;
+    }
+    __device__ __forceinline__ void step() {  // to the next site, staying on the last
+        const bool last = row * W + j + 1 >= nk;
+        const bool nr = j + 1 == W && !last, ns = nr && y + 1 == Ly;
+        j = nr ? 0 : (last ? j : j + 1);
+        row += nr ? 1 : 0;
+        y = ns ? 0 : (nr ? y + 1 : y);
+        z += ns ? 1 : 0;
+    }
+    // x of the site is (2 or 3) j + phase
+    __device__ __forceinline__ int phase(int c) const {
+        return MODEL == kModelIsingTri ? (c + y) % 3 : (c + y + z) & 1;
+    }
+    // places in the partners' planes of x + 1 and x - 1 in this row, and the steps to
+    // the rows around it
+    __device__ __forceinline__ int right(int ph) const {
+        return row * W + (ph != (MODEL == kModelIsingTri ? 2 : 1) ? j : (j + 1 == W ? 0 : j + 1));
+    }
+    __device__ __forceinline__ int left(int ph) const {
+        return row * W + (ph != 0 ? j : (j == 0 ? W - 1 : j - 1));
+    }
+    __device__ __forceinline__ int up() const { return y == 0 ? (Ly - 1) * W : -W; }
+    __device__ __forceinline__ int down() const { return y + 1 == Ly ? (1 - Ly) * W : W; }
+    __device__ __forceinline__ int zup() const { return (z == 0 ? Lz - 1 : -1) * Ly * W; }
+    __device__ __forceinline__ int zdown() const { return (z + 1 == Lz ? 1 - Lz : 1) * Ly * W; }
+};
+}  // namespace
+
+template <int MODEL>
+__global__ void __launch_bounds__(256) k_plane_pass_any(TriArgs a, int c, int sweep_off) {
+    __shared__ uint64_t lt[kTriClasses];
+    constexpr bool TRI = MODEL == kModelIsingTri;
+    const int r = blockIdx.y;
+    if (threadIdx.x < kTriClasses) lt[threadIdx.x] = a.tab[(size_t)r * kTriClasses + threadIdx.x];
+    __syncthreads();
+    const RepDev D = a.reps[r];
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    const int nk = (TRI ? D.Lx / 3 : D.Lx >> 1) * D.Ly * (TRI ? 1 : D.q);
+    if (4 * b >= nk) return;
+    PlaneSite<MODEL> q(D, 4 * b);
+    int8_t* own = a.lat + D.lat_off + (size_t)c * nk;
+    // the planes of the next colour and of the one before (one plane with two colours)
+    const int8_t* nx = a.lat + D.lat_off + (size_t)(TRI ? (c + 1) % 3 : 1 - c) * nk;
+    const int8_t* pv = a.lat + D.lat_off + (size_t)(TRI ? (c + 2) % 3 : 1 - c) * nk;
+    int s[4], S[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int ph = q.phase(c), o = q.row * q.W + q.j, R = q.right(ph), L = q.left(ph);
+        s[u] = own[o];
+        S[u] = nx[R] + pv[L];
+        if (TRI)
+            S[u] += nx[o + q.up()] + pv[o + q.down()] + pv[R + q.up()] + nx[L + q.down()];
+        else {
+            if (q.Ly > 1) S[u] += nx[o + q.up()] + nx[o + q.down()];
+            if (q.Lz > 1) S[u] += nx[o + q.zup()] + nx[o + q.zdown()];
+        }
+        q.step();
+    }
+    const uint64_t t = *a.t_base + (uint64_t)sweep_off;
+    uint32_t w[4];
+    philox4x32_10((uint32_t)b, (uint32_t)((TRI ? 3 : 2) * t + (uint64_t)c), D.rid, kTriTagMain, a.key0,
+                  a.key1, w);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = 7 * (s[u] > 0) + (S[u] + 6) / 2;
+        if (4 * b + u < nk && (uint64_t)w[u] < lt[idx]) own[4 * b + u] = (int8_t)(-s[u]);
+    }
+}
+
+// A workgroup's sums of v into row, one atomic a statistic (an atomic a wave of 62
+// workgroups of 256 lanes took 25 us, all on one cache line).
+__device__ __forceinline__ void add_sums(int (&v)[4], int32_t* row) {
+    __shared__ int sum[4];
+    if (threadIdx.x < 4) sum[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&sum[k], v[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) atomicAdd(&row[threadIdx.x], sum[threadIdx.x]);
+}
+
+// [M, B1, B2, B3] of any width (integers, so the order does not matter).
+template <int MODEL>
+__global__ void __launch_bounds__(256) k_plane_stats_any(TriArgs a, int rec_row) {
+    constexpr bool TRI = MODEL == kModelIsingTri;
+    constexpr int ncol = TRI ? 3 : 2;
+    const int r = blockIdx.y;
+    const RepDev D = a.reps[r];
+    const int8_t* lat = a.lat + D.lat_off;
+    const int nk = (TRI ? D.Lx / 3 : D.Lx >> 1) * D.Ly * (TRI ? 1 : D.q), nb = (nk + 3) >> 2;
+    int v[4] = {0, 0, 0, 0};
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ncol * nb; i += gridDim.x * blockDim.x) {
+        const int c = (i >= nb ? 1 : 0) + (TRI && i >= 2 * nb ? 1 : 0), b = i - c * nb;
+        const int8_t* own = lat + (size_t)c * nk;
+        const int8_t* nx = lat + (size_t)(TRI ? (c + 1) % 3 : 1 - c) * nk;
+        const int8_t* pv = lat + (size_t)(TRI ? (c + 2) % 3 : 1 - c) * nk;
+        PlaneSite<MODEL> q(D, 4 * b);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int ph = q.phase(c), o = q.row * q.W + q.j;
+            const int s = 4 * b + u < nk ? own[o] : 0;
+            v[0] += s;
+            v[1] += s * nx[q.right(ph)];
+            if (TRI) {
+                v[2] += s * pv[o + q.down()];
+                v[3] += s * nx[q.left(ph) + q.down()];
+            } else {
+                if (q.Ly > 1) v[2] += s * nx[o + q.down()];
+                if (q.Lz > 1) v[3] += s * nx[o + q.zdown()];
+            }
+            q.step();
+        }
+    }
+    add_sums(v, &a.stats[((size_t)rec_row * a.R + r) * a.width]);
+}
 
 // Lx a multiple of 12: the four sites of a Philox block are four consecutive
 // bytes i0 .. i0 + 3 of row y of plane c (planes of W3 = Lx / 3 bytes per
@@ -241,79 +352,6 @@ __global__ void __launch_bounds__(256) k_tri_pass4(TriArgs a, int c, int sweep_o
     }
 }
 
-// [M, Bh, Bv, Bd] of any width: wave sums of each lane's sites, one atomic per wave and
-// statistic (integers, so the order does not matter).
-__global__ void __launch_bounds__(256) k_tri_stats(TriArgs a, int rec_row) {
-    const int r = blockIdx.y;
-    const RepDev D = a.reps[r];
-    const int Lx = D.Lx, Ly = D.Ly, n = Lx * Ly;
-    const int8_t* lat = a.lat + D.lat_off;
-    int M = 0, Bh = 0, Bv = 0, Bd = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int y = i / Lx, x = i - y * Lx;
-        const int yd = wrapt(y + 1, Ly), xr = wrapt(x + 1, Lx), xl = wrapt(x - 1, Lx);
-        const int s = lat[tri_byte(y, x, Lx, Ly)];
-        M += s;
-        Bh += s * lat[tri_byte(y, xr, Lx, Ly)];
-        Bv += s * lat[tri_byte(yd, x, Lx, Ly)];
-        Bd += s * lat[tri_byte(yd, xl, Lx, Ly)];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        M += __shfl_xor(M, o);
-        Bh += __shfl_xor(Bh, o);
-        Bv += __shfl_xor(Bv, o);
-        Bd += __shfl_xor(Bd, o);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        int32_t* row = a.stats + ((size_t)rec_row * a.R + r) * a.width;
-        atomicAdd(&row[0], M);
-        atomicAdd(&row[1], Bh);
-        atomicAdd(&row[2], Bv);
-        atomicAdd(&row[3], Bd);
-    }
-}
-
-// Chain / square / simple cubic (Lz = D.q) on the colour planes: the
-// colour-c site with within-colour index k -- byte k of plane c -- for the
-// four k of a Philox block; neighbours x +- 1 and, where the extent exceeds
-// 1, y +- 1 and z +- 1, all in the other plane.
-__global__ void __launch_bounds__(256) k_hc_pass(TriArgs a, int c, int sweep_off) {
-    __shared__ uint64_t lt[kTriClasses];
-    const int r = blockIdx.y;
-    if (threadIdx.x < kTriClasses) lt[threadIdx.x] = a.tab[(size_t)r * kTriClasses + threadIdx.x];
-    __syncthreads();
-    const RepDev D = a.reps[r];
-    const int Lx = D.Lx, Ly = D.Ly, Lz = D.q, W = Lx >> 1;
-    const int nk = Ly * Lz * W;
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (4 * b >= nk) return;
-    const uint64_t t = *a.t_base + (uint64_t)sweep_off;
-    const uint32_t p = (uint32_t)(2 * t + (uint64_t)c);
-    uint32_t w[4];
-    philox4x32_10((uint32_t)b, p, D.rid, kTriTagMain, a.key0, a.key1, w);
-    int8_t* own = a.lat + D.lat_off + (size_t)c * nk;
-    const int8_t* oth = a.lat + D.lat_off + (size_t)(1 - c) * nk;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = 4 * b + u;
-        if (k >= nk) break;
-        const int row = k / W, j = k - row * W;  // row = z Ly + y
-        const int z = row / Ly, y = row - z * Ly;
-        const int x = 2 * j + ((c + y + z) & 1);
-        const size_t rb = (size_t)row * W;
-        const int s = own[k];
-        int S = oth[rb + (wrapt(x - 1, Lx) >> 1)] + oth[rb + (wrapt(x + 1, Lx) >> 1)];
-        if (Ly > 1)
-            S += oth[(size_t)(z * Ly + wrapt(y - 1, Ly)) * W + j] +
-                 oth[(size_t)(z * Ly + wrapt(y + 1, Ly)) * W + j];
-        if (Lz > 1)
-            S += oth[(size_t)(wrapt(z - 1, Lz) * Ly + y) * W + j] +
-                 oth[(size_t)(wrapt(z + 1, Lz) * Ly + y) * W + j];
-        const int idx = 7 * (s > 0) + (S + 6) / 2;
-        if ((uint64_t)w[u] < lt[idx]) own[k] = (int8_t)(-s);
-    }
-}
-
 // Lx a multiple of 8: the four sites of a Philox block are four consecutive
 // bytes j0 .. j0 + 3 of a row of plane c (plane rows of W = Lx / 2 bytes, so
 // a row holds W / 4 blocks); the other plane's word of the same row plus one
@@ -374,37 +412,6 @@ __global__ void __launch_bounds__(256) k_hc_pass4(TriArgs a, int c, int sweep_of
     for (int k = 0; k < NB; ++k) {
         const uint32_t v = hc_word(S[k], N[k], M[k], hf[k], par[k], w[k], lt);
         if (bt + 256 * k < nb) *reinterpret_cast<uint32_t*>(own + off[k]) = v;
-    }
-}
-
-// [M, Bx, By, Bz] of the chain / square / cubic lattices of any width.
-__global__ void __launch_bounds__(256) k_hc_stats(TriArgs a, int rec_row) {
-    const int r = blockIdx.y;
-    const RepDev D = a.reps[r];
-    const int Lx = D.Lx, Ly = D.Ly, Lz = D.q, n = Lx * Ly * Lz;
-    const int8_t* lat = a.lat + D.lat_off;
-    int M = 0, Bx = 0, By = 0, Bz = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int row = i / Lx, x = i - row * Lx;
-        const int z = row / Ly, y = row - z * Ly;
-        const int s = lat[hc_byte(z, y, x, Lx, Ly, Lz)];
-        M += s;
-        Bx += s * lat[hc_byte(z, y, wrapt(x + 1, Lx), Lx, Ly, Lz)];
-        if (Ly > 1) By += s * lat[hc_byte(z, wrapt(y + 1, Ly), x, Lx, Ly, Lz)];
-        if (Lz > 1) Bz += s * lat[hc_byte(wrapt(z + 1, Lz), y, x, Lx, Ly, Lz)];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        M += __shfl_xor(M, o);
-        Bx += __shfl_xor(Bx, o);
-        By += __shfl_xor(By, o);
-        Bz += __shfl_xor(Bz, o);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        int32_t* rw = a.stats + ((size_t)rec_row * a.R + r) * a.width;
-        atomicAdd(&rw[0], M);
-        atomicAdd(&rw[1], Bx);
-        atomicAdd(&rw[2], By);
-        atomicAdd(&rw[3], Bz);
     }
 }
 
@@ -648,7 +655,7 @@ __device__ __forceinline__ void count_item(const int8_t* ls, uint32_t psz, const
 
 // [M, B1, B2, B3] of lattices in memory, rows of whole Philox blocks (Lx % 12 == 0
 // triangular, % 8 == 0 chain / cubic): items of 4 NB sites as in the resident
-// kernel, one atomic a wave and statistic.  Bound by its loads: 256 lattices of
+// kernel.  Bound by its loads: 256 lattices of
 // 32^3 take 8 us (site by site 129).
 template <int MODEL, int NB>
 __global__ void __launch_bounds__(256) k_plane_stats(TriArgs a, int rec_row) {
@@ -669,11 +676,9 @@ __global__ void __launch_bounds__(256) k_plane_stats(TriArgs a, int rec_row) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const bool has = TRI || k < 2 || (k == 2 ? Ly > 1 : Lz > 1);
-        int v = has ? n - 2 * cnt[k] : 0;
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if ((threadIdx.x & 63) == 0)
-            atomicAdd(&a.stats[((size_t)rec_row * a.R + r) * a.width + k], v);
+        cnt[k] = has ? n - 2 * cnt[k] : 0;
     }
+    add_sums(cnt, &a.stats[((size_t)rec_row * a.R + r) * a.width]);
 }
 
 // Four sites of one Philox block: own bytes S, neighbour counts N (-1
@@ -824,8 +829,8 @@ __global__ void __launch_bounds__(1024) k_plane_resident(TriArgs a, int n_sweeps
 // for the block's two rows) and on x.  The statistics of a recorded sweep come from
 // its passes: a bond is counted with its later end, whose partner is final.
 // About 270 lane-instructions a block, 60 of them Philox, which bound a full chip:
-// 512 triangular 75^2 take 6.4 us a sweep and 7.9 a recorded one (streamed site by
-// site 23.8 and 66.1), 256 x 30^3 15.0 and 16.2 (35.7 and 158.9).
+// 512 triangular 75^2 take 6.4 us a sweep and 7.9 a recorded one (streamed 19.4 and
+// 35.1), 256 x 30^3 14.7 and 16.0 (34.0 and 89.0).
 namespace {
 struct RowAt {
     int base, up, dn, zu, zd;  // row's first site; from a site to its partners in y and z
@@ -1037,14 +1042,14 @@ hipError_t launch_tri_pass(const TriArgs& a, int c, int sweep_off, hipStream_t s
         else
             hipLaunchKernelGGL(k_hc_pass4<1>, g1, dim3(256), 0, s, a, c, sweep_off, gx1);
     } else if (a.model == kModelIsingHC)
-        hipLaunchKernelGGL(k_hc_pass, dim3((a.max_blocks + 255) / 256, a.R), dim3(256), 0, s, a,
+        hipLaunchKernelGGL(k_plane_pass_any<kModelIsingHC>, dim3((a.max_blocks + 255) / 256, a.R), dim3(256), 0, s, a,
                            c, sweep_off);
     else if (a.all_lx12 && two)
         hipLaunchKernelGGL(k_tri_pass4<2>, g2, dim3(256), 0, s, a, c, sweep_off, gx2);
     else if (a.all_lx12)
         hipLaunchKernelGGL(k_tri_pass4<1>, g1, dim3(256), 0, s, a, c, sweep_off, gx1);
     else
-        hipLaunchKernelGGL(k_tri_pass, dim3((a.max_blocks + 255) / 256, a.R), dim3(256), 0, s, a,
+        hipLaunchKernelGGL(k_plane_pass_any<kModelIsingTri>, dim3((a.max_blocks + 255) / 256, a.R), dim3(256), 0, s, a,
                            c, sweep_off);
     return hipGetLastError();
 }
@@ -1066,10 +1071,11 @@ hipError_t launch_tri_stats(const TriArgs& a, int rec_row, hipStream_t s) {
         else
             hipLaunchKernelGGL((k_plane_stats<kModelIsingTri, 1>), g, b, 0, s, a, rec_row);
     } else if (hc)
-        hipLaunchKernelGGL(k_hc_stats, dim3(per < 64 ? per : 64, a.R), dim3(256), 0, s, a, rec_row);
+        hipLaunchKernelGGL(k_plane_stats_any<kModelIsingHC>, dim3(std::min(64, (per + 7) / 8), a.R),
+                           dim3(256), 0, s, a, rec_row);
     else
-        hipLaunchKernelGGL(k_tri_stats, dim3(per < 64 ? per : 64, a.R), dim3(256), 0, s, a,
-                           rec_row);
+        hipLaunchKernelGGL(k_plane_stats_any<kModelIsingTri>, dim3(std::min(64, (per + 7) / 8), a.R),
+                           dim3(256), 0, s, a, rec_row);
     return hipGetLastError();
 }
 

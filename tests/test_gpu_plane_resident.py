@@ -89,6 +89,27 @@ def test_measured_statistics_equal_recorded_ones(dims):
     smp.close()
 
 
+def _check_both(reps, run):
+    """Resident whatever the size, then streamed passes, of one chain."""
+    from paper_2304_01772_amd.sampler import Sampler
+    smp = Sampler(reps, 64, init=True)
+    cur = [smp.get_state(r) for r in range(len(reps))]
+    t = 0
+    for mode, n, every in (("hybrid", 2, 0), ("hybrid", 7, 3), ("stream", 3, 2)):
+        smp.set_schedule(mode=mode)
+        st = smp.sweep(n, every)
+        for r, d in enumerate(reps):
+            cur[r], ost = run(cur[r], d, t, n, every)
+            assert np.array_equal(smp.get_state(r), cur[r]), (r, mode)
+            if every:
+                assert np.array_equal(st[:, r].cpu().numpy(), ost), (r, mode)
+        t += n
+    smp.set_schedule(mode="hybrid")
+    st = smp.sweep(1, 1)[-1]
+    assert torch.equal(smp.measure()[0], st)
+    smp.close()
+
+
 @pytest.mark.parametrize("Ly,Lx,n_rep,beta", [
     (3, 15, 1, 0.27), (6, 21, 2, 0.27), (27, 33, 3, 0.27),  # blocks across rows
     (102, 123, 2, 0.27), (243, 267, 1, 0.27), (3, 21843, 1, 0.27),  # rounds of blocks; the limit
@@ -98,8 +119,7 @@ def test_triangular_blocks_across_rows(Ly, Lx, n_rep, beta):
     reps = [dict(model=3, Lx=Lx, Ly=Ly, Jx=1.0 - 0.5 * r, Jy=1.0 - 0.5 * r, h=0.05, beta=beta,
                  rid=70 + r) for r in range(n_rep)]
     reps.append(dict(reps[0], Lx=12, Ly=3, rid=79))  # whole blocks beside the others
-    _check(reps, lambda s, d, seed, t, n, e: orc.tri_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
-                                                         t, n, e), every=3 if Lx * Ly < 20000 else 1)
+    _check_both(reps, lambda s, d, t, n, e: orc.tri_run(s, d["Jx"], d["h"], beta, 64, d["rid"], t, n, e))
 
 
 @pytest.mark.parametrize("Lz,Ly,Lx,beta", [
@@ -110,8 +130,7 @@ def test_triangular_blocks_across_rows(Ly, Lx, n_rep, beta):
 def test_chain_square_cubic_blocks_across_rows(Lz, Ly, Lx, beta):
     reps = [dict(model=4, Lx=Lx, Ly=Ly, Lz=Lz, Jx=1.0 - 0.7 * r, Jy=1.0 - 0.7 * r, h=-0.03,
                  beta=beta, rid=80 + r) for r in range(2)]
-    _check(reps, lambda s, d, seed, t, n, e: orc.hc_run(s, d["Jx"], d["h"], beta, seed, d["rid"],
-                                                        t, n, e), every=3 if Lx * Ly * Lz < 20000 else 1)
+    _check_both(reps, lambda s, d, t, n, e: orc.hc_run(s, d["Jx"], d["h"], beta, 64, d["rid"], t, n, e))
 
 
 def test_large_lattices_in_numbers_across_rows():
