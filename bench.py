@@ -205,9 +205,10 @@ def cpm_probe(Sampler, torch, mcs):
     smp.sweep(mcs)
     torch.cuda.synchronize()
     kms, nl = smp.profile_read("cpm_pass")
-    site_form = chosen.get("wg_threads", 0) in (0, 512)
-    kind = ("k_cpm_pass_site (one site per lane, one launch per colour pass)" if site_form
-            else "k_cpm_pass_quad (one quad per lane, one launch per colour pass)")
+    kind = {0: "k_cpm_pass_tile (two phases on LDS tiles, one launch per colour pass)",
+            512: "k_cpm_pass_site (one site per lane, one launch per colour pass)"}.get(
+                chosen.get("wg_threads", 0),
+                "k_cpm_pass_quad (one quad per lane, one launch per colour pass)")
     per_launch = ids.size // 4
     if nl == 0:  # the tiled persistent passes: one launch for all passes of the call
         kms, nl = smp.profile_read("cpm_tiled")
@@ -524,12 +525,11 @@ def surrogate_probe(torch, n_points=100_000):
 def dmc_probe(torch, R=256, L=128, sweeps=10):
     """Differentiable Monte Carlo (relaxed chain of Algorithm 2): R replicas
     of L x L with per-bond couplings, `sweeps` sweeps forward and the reverse
-    replay, timed with HIP events (best of five calls); algorithmic HBM bytes of a forward pass
-    are 32 per attempt (spins of both colours 8, the four bond couplings 16,
-    the updated spin 4 and its saved value 4), of a backward pass 76 (reads:
-    saved spin 4, neighbour spins 4, couplings 16, adjoint 4, neighbour t 4,
-    coupling gradients 16; writes: adjoint 4, restored spin 4, t 4, coupling
-    gradients 16)."""
+    replay, timed with HIP events (best of five calls); algorithmic HBM bytes with the
+    lattices resident: forward 4 per attempt (the saved spin) and 16 per site
+    and call (spin and two couplings read, spin written), backward 4 per
+    attempt and 28 per site and call (output spin and its gradient, two
+    couplings read; three gradients written)."""
     from paper_2304_01772_amd.dmc import relaxed_ising
     g = torch.Generator(device="cpu").manual_seed(0)
     s0 = (torch.rand((R, L, L), generator=g) * 2 - 1).cuda()
@@ -551,15 +551,16 @@ def dmc_probe(torch, R=256, L=128, sweeps=10):
         torch.cuda.synchronize()
         fwd_ms, bwd_ms = min(fwd_ms, e0.elapsed_time(e1)), min(bwd_ms, e2.elapsed_time(e3))
     att = R * L * L * sweeps
+    fwd_b, bwd_b = 4 + 16 / sweeps, 4 + 28 / sweeps
     return {"config": f"{R} Ising replicas of {L}x{L}, per-bond couplings, {sweeps} sweeps, "
                       "alpha 10, beta 0.5",
-            "kernel": "k_dmc_pass8 / k_dmc_back8 (+ one k_dmc_gather)", "bound": "hbm",
+            "kernel": "k_dmc_resident_fwd / k_dmc_resident_bwd", "bound": "alu",
             "forward_attempts_per_ns": round(att / (fwd_ms * 1e6), 1),
             "backward_attempts_per_ns": round(att / (bwd_ms * 1e6), 1),
-            "forward_GBs_algorithmic": round(32 * att / (fwd_ms * 1e-3) / 1e9, 1),
-            "forward_frac": round(32 * att / (fwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-            "backward_GBs_algorithmic": round(76 * att / (bwd_ms * 1e-3) / 1e9, 1),
-            "backward_frac": round(76 * att / (bwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
+            "forward_GBs_algorithmic": round(fwd_b * att / (fwd_ms * 1e-3) / 1e9, 1),
+            "forward_frac": round(fwd_b * att / (fwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+            "backward_GBs_algorithmic": round(bwd_b * att / (bwd_ms * 1e-3) / 1e9, 1),
+            "backward_frac": round(bwd_b * att / (bwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
 
 
 def dmc_vs_covariance_probe(torch, R=4096, L=4):

@@ -87,8 +87,9 @@ enum spinmc_status {
  * dE = 2 s (J S6 + h) (always when dE <= 0).  Initial state as for Ising.
  * A context holds only triangular replicas.  Sweeps, recorded or not, run
  * resident in LDS (one workgroup per replica) when every lattice holds at
- * most 64 KiB and every Lx is a multiple of 12, unless the schedule's mode
- * is 2 (streamed passes); tile_rows and wg_threads are ignored, and
+ * most 64 KiB (with an Lx that is no multiple of 12: 140 KiB, every Lx at
+ * least 12, and unless a few large lattices are faster streamed), unless the
+ * schedule's mode is 2 (streamed passes); tile_rows and wg_threads are ignored, and
  * spinmc_autotune returns the schedule unchanged.  spinmc_grad is not
  * available.
  *
@@ -100,8 +101,7 @@ enum spinmc_status {
  * p = 2t + c; the colour-c site of the pair (2k, 2k + 1) takes word k & 3 of
  * Philox block (k >> 2, p, rid, 0) whole as W; flip iff
  * W < ceil(2^32 exp(-beta 2 s (J S + h))), S the neighbour sum.  States are
- * int8 [Lz][Ly][Lx]; contexts as for the triangular lattice (resident when
- * every lattice holds at most 64 KiB and every Lx is a multiple of 8).
+ * int8 [Lz][Ly][Lx]; contexts as for the triangular lattice (for 12 read 8).
  *
  * Multispin-coded square-lattice Ising (1-bit spins; SPINMC_ISING_MSC): one
  * descriptor is a group of 32 replicas with its Lx (a multiple of 8), Ly
@@ -261,17 +261,21 @@ int spinmc_thresholds(const spinmc_ctx *ctx, int32_t replica, uint64_t *host_T, 
 /* Execution schedule of spinmc_sweep (the batched scheduler).
  * mode 1 resident: one persistent launch per group of replicas (one model
  *   and shape) for all sweeps of the call; each workgroup owns 1 to 16
- *   replicas whose lattices live in LDS for the whole call (lattices up to
- *   128 KiB); groups run concurrently on side streams.
+ *   replicas whose lattices live in registers or LDS for the whole call
+ *   (lattices up to 128 KiB); groups run concurrently on side streams.
  * mode 2 stream: one launch per colour pass over (replica, row-tile) units of
  *   every replica whose Lx/2 is a multiple of 16 (others go resident).
  * mode 3 hybrid: resident where the lattice fits the LDS budget, streamed
  *   otherwise; both run concurrently.
  * mode 0 auto: resident if every lattice fits, else hybrid.
- * Calls without recording replay cached hipGraphs of 50-sweep chunks of
- * the streamed passes; resident groups run one launch per group for all
- * sweeps of a call on side streams forked from and joined into the call's
- * stream, concurrently with the streamed work.
+ * In modes 0 and 1 with no other field set, sweeps (recorded or not) of Ising
+ * lattices too few to fill the chip cut them into slabs of rows that carry a
+ * halo, one workgroup a slab, a few sweeps a launch.
+ * Streamed calls without recording replay cached hipGraphs of 50-sweep
+ * chunks of the streamed passes; resident groups beside them run one launch
+ * per group for all sweeps of a call on side streams forked from and joined
+ * into the call's stream.  A call of one resident group alone launches it on
+ * the call's stream.
  * tile_rows: rows of a plane per streamed unit (even; 0 = about 16 KiB);
  * wg_threads: 256 or 512 (0 = default; a resident Ising workgroup takes up to
  * 1024 lanes by default and never fewer than half its row pairs of 16 columns);
@@ -313,8 +317,10 @@ int spinmc_thresholds(const spinmc_ctx *ctx, int32_t replica, uint64_t *host_T, 
  * decided, in workgroups of 512 (where the cells' tables leave no room for a
  * tile: one site per lane, workgroups of 1024); 512 = one site per lane in
  * workgroups of 512, 256 = four same-colour sites per lane in workgroups of
- * 256 (tiles of about 4096 sites); the same decisions either way.  Other CPM passes use at most 256 threads.  spinmc_autotune tries
- * both forms of the 3x3 pass, and for Ising and Potts contexts also the
+ * 256 (tiles of about 4096 sites); the same decisions either way.  Other CPM
+ * passes: 0 = bands of whole rows in LDS, in workgroups of 512 (where a band
+ * does not fit: one site per lane); else one site per lane, at most 256
+ * threads.  spinmc_autotune tries both forms of the 3x3 pass, and for Ising and Potts contexts also the
  * best streaming schedule with NT forced on and off.                        */
 enum { SPINMC_SCHED_NT_ON = 1, SPINMC_SCHED_NT_OFF = 2, SPINMC_SCHED_PERSIST = 4 };
 typedef struct spinmc_schedule {

@@ -447,7 +447,7 @@ __global__ void k_tri_observables(TriArgs a, double* obs) {
 // per site.  (In natural order, where a 12- or 8-byte span holds four own
 // sites, the same passes took about 45 lane-instructions a site: 1024 x 96^2
 // triangular, 200 sweeps with every tenth recorded, 2705 us; 256 x 32^3, 100
-// sweeps and one measurement, 1000 us; now 982 and 568.)
+// sweeps and one measurement, 1000 us; now 982 and 437.)
 //
 // NB = 2 for lattices of more than 1024 blocks a plane whose rows hold an even
 // number of blocks (half the LDS accesses and offsets per site), else 1; NI = 1 up to 1024 items (any number
