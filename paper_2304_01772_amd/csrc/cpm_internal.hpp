@@ -35,10 +35,11 @@ hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_ti
                                 size_t lds_bytes, hipStream_t s);
 
 // The same over bands of whole rows: x0 0, cols Lx, y0 and rows multiples of 3
-// (range 2) or 2.
+// (range 2) or 2.  cell_cap 0 (always with
+// range 2): the cells' tables stay in global memory.
 size_t cpm_band_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int threads, int rows,
                           int Lx);
-hipError_t cpm_band_reserve_lds(int range, size_t lds_bytes);
+hipError_t cpm_band_reserve_lds(int range, int cell_cap, size_t lds_bytes);
 hipError_t launch_cpm_pass_band(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
                                 int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
                                 size_t lds_bytes, hipStream_t s);

@@ -1169,14 +1169,17 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
 // block's four sites may run on into the band's next row, and blocks at the band's
 // ends belong to both bands, each deciding its own sites.  Bound as above; with two
 // or more bands a compute unit by the staging of ids (about 12 dwords a lane).
+// Without TAB the cells' tables stay in global memory, for the decided attempts alone.
 // Range 2, 3 x 378^2, 364 cells: 7.1 us a pass with one attempt per lane deciding
-// in place, 6.3 now; 8 x 510^2, 648 cells: 14.4 and 9.3; range 1, 430^2, 450 cells:
-// 12.1 and 6.1; 8 x 510^2: 16.0 and 8.4.
-template <int RANGE>
+// in place, 5.9 now; 8 x 510^2, 648 cells: 14.4 and 9.2; range 1, 430^2, 450 cells:
+// 12.1 and 6.1; 8 x 510^2: 16.0 and 8.4.  (A lattice with nothing left to decide, all
+// one id, is the exception: 3.2 us in place and 4.4 for one of 216^2.)
+template <int RANGE, bool TAB>
 __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile* tiles, int c,
                                                        int sweep_off, int tab_lds_bytes,
                                                        int cell_cap) {
-    // dynamic LDS as above; ids: (rows + 2 h) x (Lx + 2 h), h = RANGE
+    // dynamic LDS as above, cell_cap 0 without TAB; ids: (rows + 2 h) x (Lx + 2 h),
+    // h = RANGE
     extern __shared__ __align__(16) uint8_t dyn[];
     __shared__ PairTab pairs;
     constexpr int ncol = RANGE == 2 ? 9 : 4, P = RANGE == 2 ? 3 : 2, h = RANGE;
@@ -1211,13 +1214,16 @@ __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile*
     constexpr int kC = 2;
     int32_t sv[kC], av[kC];
     uint8_t tv[kC];
+    const int nst = TAB ? ncell : 0;  // cells staged
+    const int32_t* gA = a.target + R.cell_off;
+    const int8_t* gty = a.ctype + R.cell_off;
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
         const int i = tid + u * nthr;
-        if (i < ncell) {
+        if (i < nst) {
             sv[u] = pa.s_rd[i] + pa.d_rd[i];
-            av[u] = a.target[R.cell_off + i];
-            tv[u] = (uint8_t)a.ctype[R.cell_off + i];
+            av[u] = gA[i];
+            tv[u] = (uint8_t)gty[i];
         }
     }
     for (int i = tid; i < ntab; i += nthr) qthr[i] = a.tab[R.tab_off + i];
@@ -1225,17 +1231,21 @@ __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile*
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
         const int i = tid + u * nthr;
-        if (i < ncell) {
+        if (i < nst) {
             lsa[i] = sv[u] - av[u];
             lty[i] = (uint8_t)(8 * tv[u]);
             ldel[i] = 0;
         }
     }
-    for (int i = tid + kC * nthr; i < ncell; i += nthr) {
-        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - a.target[R.cell_off + i];
-        lty[i] = (uint8_t)(8 * a.ctype[R.cell_off + i]);
+    for (int i = tid + kC * nthr; i < nst; i += nthr) {
+        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - gA[i];
+        lty[i] = (uint8_t)(8 * gty[i]);
         ldel[i] = 0;
     }
+    const auto type8 = [&](uint32_t m) { return TAB ? (uint32_t)lty[m] : 8u * (uint32_t)gty[m]; };
+    const auto over = [&](uint32_t m) {  // pass-start area minus target
+        return TAB ? lsa[m] : pa.s_rd[m] + pa.d_rd[m] - gA[m];
+    };
 #pragma unroll
     for (int u = 0; u < kU; ++u)
         if (tid + u * nthr < nd) lids[tid + u * nthr] = (uint32_t)v[u];
@@ -1283,21 +1293,22 @@ __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile*
                 for (int dx = 0; dx <= 2 * h; ++dx) {
                     if (dy == h && dx == h) continue;  // the site itself
                     const uint32_t m = nb[dy * st + dx];
-                    cnt += 1u << lty[m];
+                    cnt += 1u << type8(m);
                     nt += m == tg;
                     ns += m == s;
                 }
-            if (cpm_accept(a, R, s | ((uint32_t)lty[s] << 24), tg | ((uint32_t)lty[tg] << 24), cnt, nt,
-                           ns, &pairs, lsa[tg], lsa[s], qthr, ev >> 16, (uint32_t)k, p)) {
+            if (cpm_accept(a, R, s | (type8(s) << 24), tg | (type8(tg) << 24), cnt, nt, ns, &pairs,
+                           over(tg), over(s), qthr, ev >> 16, (uint32_t)k, p)) {
                 gids[(size_t)(y0 + P * r2 + cy) * Lx + P * i2 + cx] = (int)tg;
-                atomicAdd(&ldel[tg], 1);
-                atomicAdd(&ldel[s], -1);
+                atomicAdd(TAB ? &ldel[tg] : &pa.d_wr[tg], 1);
+                atomicAdd(TAB ? &ldel[s] : &pa.d_wr[s], -1);
             }
         }
         // the queue is read before the next round's entries
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
+    if (!TAB) return;
     __syncthreads();
     for (int i = tid; i < ncell; i += nthr) {
         const int d = ldel[i];
@@ -1311,22 +1322,25 @@ size_t cpm_band_lds_bytes(int range, int tab_lds_bytes, int cell_cap, int thread
            (size_t)4 * (rows + 2 * range) * (Lx + 2 * range);
 }
 
-hipError_t cpm_band_reserve_lds(int range, size_t lds_bytes) {
-    return hipFuncSetAttribute(range == 2 ? (const void*)k_cpm_pass_band<2>
-                                          : (const void*)k_cpm_pass_band<1>,
+namespace {
+const void* band_fn(int range, bool tab) {
+    if (range == 2) return (const void*)k_cpm_pass_band<2, false>;
+    return tab ? (const void*)k_cpm_pass_band<1, true> : (const void*)k_cpm_pass_band<1, false>;
+}
+}  // namespace
+
+hipError_t cpm_band_reserve_lds(int range, int cell_cap, size_t lds_bytes) {
+    return hipFuncSetAttribute(band_fn(range, cell_cap > 0),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 
 hipError_t launch_cpm_pass_band(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
                                 int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
                                 size_t lds_bytes, hipStream_t s) {
-    if (a.range == 2)
-        hipLaunchKernelGGL(k_cpm_pass_band<2>, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles,
-                           c, sweep_off, tab_lds_bytes, cell_cap);
-    else
-        hipLaunchKernelGGL(k_cpm_pass_band<1>, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles,
-                           c, sweep_off, tab_lds_bytes, cell_cap);
-    return hipGetLastError();
+    CpmArgs b = a;
+    void* args[] = {&b, &tiles, &c, &sweep_off, &tab_lds_bytes, &cell_cap};
+    return hipLaunchKernel(band_fn(a.range, cell_cap > 0), dim3(n_tiles), dim3(threads), args,
+                           lds_bytes, s);
 }
 
 size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols) {
