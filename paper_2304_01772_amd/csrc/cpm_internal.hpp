@@ -27,8 +27,9 @@ struct CpmTile {
     int32_t y0, rows, x0, cols;
 };
 size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows, int cols);
-hipError_t cpm_tile_reserve_lds(size_t lds_bytes);
-// One colour pass (range 1, every Lx % 8 == 0; cell_cap a multiple of 16; threads
+hipError_t cpm_tile_reserve_lds(int cell_cap, size_t lds_bytes);
+// One colour pass (range 1, every Lx % 8 == 0; cell_cap a multiple of 16, or 0: the
+// cells' tables stay in global memory; threads
 // a multiple of 64 up to 512; lds_bytes for the largest tile).
 hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
                                 int sweep_off, int threads, int tab_lds_bytes, int cell_cap,

@@ -1022,14 +1022,16 @@ __global__ void __launch_bounds__(1024) k_cpm_resident(CpmArgs a, int n_steps, i
 // waiting for another but for the tile's record -- and the attempts run on the
 // LDS ids in the two phases of the resident kernel.  Accepted ids go straight
 // to the lattice; area changes gather in LDS and go to the pass's change
-// buffer as one atomic per touched cell.  Bound by latencies: launch, the tile
+// buffer as one atomic per touched cell (without TAB: types and areas are read from
+// memory and changed there, by the decided attempts alone).  Bound by latencies: launch, the tile
 // record, the loads, the chain of LDS reads, the stores.  8 x 512^2, 1000
 // cells: 9.0 us a pass with one attempt per lane on a register window,
 // 6.5 now.
+template <bool TAB>
 __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile* tiles, int c,
                                                        int sweep_off, int tab_lds_bytes,
                                                        int cell_cap) {
-    // dynamic LDS: [T hi | T lo] (tab_lds_bytes) | snap - A, area changes (int32
+    // dynamic LDS (cell_cap 0 without TAB): [T hi | T lo] (tab_lds_bytes) | snap - A, area changes (int32
     // [cell_cap] each) | 8 x type (int8 [cell_cap]) | queue (256 words per wave)
     // | ids: (rows + 2) x (cols + 8), four halo columns on either side
     extern __shared__ __align__(16) uint8_t dyn[];
@@ -1067,13 +1069,16 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
     constexpr int kC = 2;
     int32_t sv[kC], av[kC];
     uint8_t tv[kC];
+    const int nst = TAB ? ncell : 0;  // cells staged
+    const int32_t* gA = a.target + R.cell_off;
+    const int8_t* gty = a.ctype + R.cell_off;
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
         const int i = tid + u * nthr;
-        if (i < ncell) {
+        if (i < nst) {
             sv[u] = pa.s_rd[i] + pa.d_rd[i];
-            av[u] = a.target[R.cell_off + i];
-            tv[u] = (uint8_t)a.ctype[R.cell_off + i];
+            av[u] = gA[i];
+            tv[u] = (uint8_t)gty[i];
         }
     }
     for (int i = tid; i < ntab; i += nthr) qthr[i] = a.tab[R.tab_off + i];
@@ -1081,17 +1086,21 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
         const int i = tid + u * nthr;
-        if (i < ncell) {
+        if (i < nst) {
             lsa[i] = sv[u] - av[u];
             lty[i] = (uint8_t)(8 * tv[u]);
             ldel[i] = 0;
         }
     }
-    for (int i = tid + kC * nthr; i < ncell; i += nthr) {
-        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - a.target[R.cell_off + i];
-        lty[i] = (uint8_t)(8 * a.ctype[R.cell_off + i]);
+    for (int i = tid + kC * nthr; i < nst; i += nthr) {
+        lsa[i] = pa.s_rd[i] + pa.d_rd[i] - gA[i];
+        lty[i] = (uint8_t)(8 * gty[i]);
         ldel[i] = 0;
     }
+    const auto type8 = [&](uint32_t m) { return TAB ? (uint32_t)lty[m] : 8u * (uint32_t)gty[m]; };
+    const auto over = [&](uint32_t m) {  // pass-start area minus target
+        return TAB ? lsa[m] : pa.s_rd[m] + pa.d_rd[m] - gA[m];
+    };
 #pragma unroll
     for (int u = 0; u < kU; ++u)
         if (tid + u * nthr < nch) reinterpret_cast<int4*>(lids)[tid + u * nthr] = v[u];
@@ -1139,23 +1148,24 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
                 for (int dx = 0; dx < 3; ++dx) {
                     if (dy == 1 && dx == 1) continue;
                     const uint32_t m = nb[dy * st + dx];
-                    cnt += 1u << lty[m];
+                    cnt += 1u << type8(m);
                     nt += m == tg;
                     ns += m == s;
                 }
             const uint32_t k = 4u * ((uint32_t)((y0 >> 1) + r2) * (uint32_t)G +
                                      (uint32_t)((x0 >> 3) + j2)) + kl;
-            if (cpm_accept(a, R, s | ((uint32_t)lty[s] << 24), tg | ((uint32_t)lty[tg] << 24), cnt, nt,
-                           ns, &pairs, lsa[tg], lsa[s], qthr, ev >> 16, k, p)) {
+            if (cpm_accept(a, R, s | (type8(s) << 24), tg | (type8(tg) << 24), cnt, nt, ns, &pairs,
+                           over(tg), over(s), qthr, ev >> 16, k, p)) {
                 gids[(size_t)(y0 + 2 * r2 + cy) * Lx + x0 + 8 * j2 + 2 * (int)kl + cx] = (int)tg;
-                atomicAdd(&ldel[tg], 1);
-                atomicAdd(&ldel[s], -1);
+                atomicAdd(TAB ? &ldel[tg] : &pa.d_wr[tg], 1);
+                atomicAdd(TAB ? &ldel[s] : &pa.d_wr[s], -1);
             }
         }
         // the queue is read before the next round's entries
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
+    if (!TAB) return;
     __syncthreads();
     for (int i = tid; i < ncell; i += nthr) {
         const int d = ldel[i];
@@ -1348,16 +1358,21 @@ size_t cpm_tile_lds_bytes(int tab_lds_bytes, int cell_cap, int threads, int rows
            (size_t)4 * (rows + 2) * (cols + 8);
 }
 
-hipError_t cpm_tile_reserve_lds(size_t lds_bytes) {
-    return hipFuncSetAttribute((const void*)k_cpm_pass_tile,
+hipError_t cpm_tile_reserve_lds(int cell_cap, size_t lds_bytes) {
+    return hipFuncSetAttribute(cell_cap > 0 ? (const void*)k_cpm_pass_tile<true>
+                                            : (const void*)k_cpm_pass_tile<false>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 
 hipError_t launch_cpm_pass_tile(const CpmArgs& a, const CpmTile* tiles, int n_tiles, int c,
                                 int sweep_off, int threads, int tab_lds_bytes, int cell_cap,
                                 size_t lds_bytes, hipStream_t s) {
-    hipLaunchKernelGGL(k_cpm_pass_tile, dim3(n_tiles), dim3(threads), lds_bytes, s, a, tiles, c,
-                       sweep_off, tab_lds_bytes, cell_cap);
+    if (cell_cap > 0)
+        hipLaunchKernelGGL(k_cpm_pass_tile<true>, dim3(n_tiles), dim3(threads), lds_bytes, s, a,
+                           tiles, c, sweep_off, tab_lds_bytes, cell_cap);
+    else
+        hipLaunchKernelGGL(k_cpm_pass_tile<false>, dim3(n_tiles), dim3(threads), lds_bytes, s, a,
+                           tiles, c, sweep_off, tab_lds_bytes, 0);
     return hipGetLastError();
 }
 

@@ -56,13 +56,6 @@ constexpr size_t kResidentLdsBudget = 150 * 1024;
 // cache between passes: their own-plane traffic goes nontemporal by default.
 constexpr size_t kNtAutoBytes = 192ull << 20;
 constexpr int kCpmLdsCells = 16384;  // cells (medium included) per replica in LDS tables
-// Cells up to which bands of the 3x3 neighbourhood keep the cells' tables in LDS;
-// beyond, and for the 5x5 one, staging them for every band costs more than reading
-// the few that decisions need (fifty steps in us, in LDS and not: 3x3, 8 x 510^2,
-// 648 cells 1688 and 2302, 430^2, 450 and 924 cells 1249 and 1243 against 1615 and
-// 1259, 2040 cells 1532 and 1441; 5x5, 3 x 378^2, 364 cells 2855 and 2645, 510^2,
-// 1300 and 8064 cells 3342 and 5414 against 2759 and 2352).
-constexpr int kCpmBandCells = 1024;
 constexpr size_t kCpmResidentLdsMax = 156 * 1024;  // dynamic LDS of the resident CPM kernel
 constexpr size_t kCpmQuadLdsMax = 160 * 1024;  // LDS of one workgroup of the quad pass
 
@@ -213,7 +206,7 @@ struct spinmc_ctx {
     long long* d_cov_part = nullptr;  // chunk sums of the split covariance estimator
     size_t cov_part_n = 0;
     int cpm_cell_cap = 0;
-    int band_cells = 0;  // as cpm_cell_cap where bands keep the cells' tables in LDS, else 0
+    int tile_cells = 0;  // as cpm_cell_cap where tiles keep the cells' tables in LDS, else 0
     // tiles of the streamed two-phase CPM pass (null where it does not fit)
     CpmTile* d_ctiles = nullptr;
     int n_ctiles = 0, ctile_threads = 0;
@@ -2134,7 +2127,6 @@ int cpm_build_ctiles(spinmc_ctx* c) {
     size_t lds = 0, sites = 0;
     for (const HostRep& h : c->reps) sites += (size_t)h.dev.Lx * h.dev.Ly;
     int per = sites / 8192 < 256 ? 4096 : 8192;
-    c->band_cells = c->cpm_range == 1 && c->cpm_cell_cap <= kCpmBandCells ? c->cpm_cell_cap : 0;
     const auto band_rows = [&](const HostRep& h) {  // whole periods, per sites or more
         return std::max(P, ((per + h.dev.Lx - 1) / h.dev.Lx + P - 1) / P * P);
     };
@@ -2147,12 +2139,21 @@ int cpm_build_ctiles(spinmc_ctx* c) {
         }
         if (per > 9216) per = 8192;
     }
+    // The cells' tables in LDS where there are at most 3 cells to 8 sites of a tile, and
+    // not with the 5x5 neighbourhood: beyond, staging them for every tile costs more
+    // than reading the few that decisions need (fifty steps in us, in LDS and not: 3x3,
+    // tiles of 8192 sites, 8 x 512^2, 3612 cells 2030 and 1879, 8 x 510^2, 1300 cells
+    // 1819 and 1842, 648 cells 1688 and 2302; of 4096, 256^2, 1000 cells 1276 and 1290,
+    // 2000 cells 1554 and 1318; of 2580, 430^2, 924 cells 1243 and 1259; 5x5,
+    // 3 x 378^2, 364 cells 2855 and 2645).
+    c->tile_cells =
+        c->cpm_range == 1 && c->cpm_cell_cap <= per * 3 / 8 ? c->cpm_cell_cap : 0;
     for (const HostRep& h : c->reps) {
         const int Lx = h.dev.Lx, Ly = h.dev.Ly;
         const int cols = c->cpm_quad ? std::min(Lx, 512) : Lx;
         const auto bytes = [&](int rows) {
-            return c->cpm_quad ? cpm_tile_lds_bytes(tab, c->cpm_cell_cap, threads, rows, cols)
-                               : cpm_band_lds_bytes(c->cpm_range, tab, c->band_cells, threads,
+            return c->cpm_quad ? cpm_tile_lds_bytes(tab, c->tile_cells, threads, rows, cols)
+                               : cpm_band_lds_bytes(c->cpm_range, tab, c->tile_cells, threads,
                                                     rows, Lx);
         };
         int rows = std::min(c->sched.tile_rows > 0 ? c->sched.tile_rows
@@ -2173,7 +2174,8 @@ int cpm_build_ctiles(spinmc_ctx* c) {
         e = hipMemcpy(c->d_ctiles, tiles.data(), sizeof(CpmTile) * tiles.size(),
                       hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = c->cpm_quad ? cpm_tile_reserve_lds(lds) : cpm_band_reserve_lds(c->cpm_range, c->band_cells, lds);
+        e = c->cpm_quad ? cpm_tile_reserve_lds(c->tile_cells, lds)
+                        : cpm_band_reserve_lds(c->cpm_range, c->tile_cells, lds);
     c->n_ctiles = (int)tiles.size();
     c->ctile_threads = threads;
     c->ctile_lds = lds;
@@ -2443,12 +2445,12 @@ hipError_t cpm_enqueue_pass(spinmc_ctx* c, const CpmArgs& a, int i, int col, hip
     return timed(c, SPINMC_K_CPM_PASS, [&] {
         if (c->d_ctiles && !c->cpm_quad)
             return launch_cpm_pass_band(a, c->d_ctiles, c->n_ctiles, col, i, c->ctile_threads,
-                                        (int)tab_bytes, c->band_cells, c->ctile_lds, s);
+                                        (int)tab_bytes, c->tile_cells, c->ctile_lds, s);
         if (c->cpm_range == 2)
             return launch_cpm_pass5(a, c->n_tiles, col, i, threads, tab_bytes, s);
         if (c->d_ctiles)
             return launch_cpm_pass_tile(a, c->d_ctiles, c->n_ctiles, col, i, c->ctile_threads,
-                                        (int)tab_bytes, c->cpm_cell_cap, c->ctile_lds, s);
+                                        (int)tab_bytes, c->tile_cells, c->ctile_lds, s);
         if (c->cpm_quad)
             return launch_cpm_pass_quad(a, c->n_tiles, col, i, threads, (int)tab_bytes,
                                         c->cpm_cell_cap, s);

@@ -496,7 +496,7 @@ def test_streamed_tile_pass_matches_oracle(S, shape, n_cells, n_types, tile_rows
 @pytest.mark.parametrize("cpm_range,shape,n_cells,n_types,tile_rows", [
     (1, (2, 2), 2, 2, 0), (1, (6, 10), 5, 3, 2), (1, (34, 42), 30, 3, 32), (1, (66, 420), 200, 4, 0),
     (1, (70, 134), 60, 3, 70), (1, (32, 36), 17300, 3, 0), (1, (4, 12006), 300, 3, 0),
-    (1, (42, 58), 1023, 3, 8), (1, (42, 58), 1024, 3, 8),
+    (1, (42, 58), 767, 3, 8), (1, (42, 58), 768, 3, 8),
     (2, (6, 6), 3, 2, 4), (2, (12, 18), 8, 3, 10), (2, (66, 60), 40, 3, 0), (2, (126, 150), 90, 4, 126),
     (2, (36, 30), 17300, 3, 0), (2, (6, 8004), 300, 3, 0)])
 def test_streamed_band_pass_matches_oracle(S, cpm_range, shape, n_cells, n_types, tile_rows):
