@@ -730,7 +730,8 @@ __device__ __forceinline__ int offset5(uint32_t j, int st) {
     return (int)(__umul24(dy, (uint32_t)st) + jj - __umul24(dy, 5u));
 }
 
-// exact quotient b / d for b < 2^16 from m = floor((2^32 - 1) / d) + 1 (d > 1)
+// exact quotient b / d for b < 2^16 from m = floor((2^32 - 1) / d) + 1; d > 1 (for
+// 1, m wraps to 0), which the host sees to for the widths of a colour's rows
 __device__ __forceinline__ int mdiv(int b, uint32_t m) { return (int)__umulhi((uint32_t)b, m); }
 __device__ __forceinline__ uint32_t mdiv_of(int d) { return 0xFFFFFFFFu / (uint32_t)d + 1u; }
 

@@ -2106,6 +2106,15 @@ int cpm_pass_threads(const spinmc_ctx* c) {
     return w > 0 ? std::min(w, 256) : 256;
 }
 
+// A lattice one site of a colour wide (Lx = 2 with the 3x3 neighbourhood): the
+// two-phase kernels divide by that width through a reciprocal that is exact for
+// divisors above 1, so such a context stays on k_cpm_pass.
+bool cpm_one_column(const spinmc_ctx* c) {
+    for (const HostRep& h : c->reps)
+        if (h.dev.Lx < 2 * (c->cpm_range + 1)) return true;
+    return false;
+}
+
 // Tiles of the streamed two-phase pass (wg_threads 0): up to 512 columns by
 // the schedule's rows or as many as make 8192 sites (a quad of a pass's colour
 // per lane), 4096 where that leaves compute units without a tile (8 x 256^2:
@@ -2120,7 +2129,7 @@ int cpm_build_ctiles(spinmc_ctx* c) {
     hipFree(c->d_ctiles);
     c->d_ctiles = nullptr;
     c->n_ctiles = 0;
-    if (c->sched.wg_threads != 0) return SPINMC_OK;
+    if (c->sched.wg_threads != 0 || cpm_one_column(c)) return SPINMC_OK;
     const int tab = (int)align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
     const int threads = 512, P = c->cpm_range == 2 ? 3 : 2;
     std::vector<CpmTile> tiles;
@@ -2517,7 +2526,7 @@ int cpm_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     int max_padded = 0;
     for (const HostRep& h : c->reps)
         max_padded = std::max(max_padded, (h.dev.Lx + 2 * c->cpm_range) * (h.dev.Ly + 2 * c->cpm_range));
-    if (!c->prof && c->sched.mode != 2 && !tiled &&
+    if (!c->prof && c->sched.mode != 2 && !tiled && !cpm_one_column(c) &&
         cpm_resident_lds_bytes(c->cpm_range, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
                                max_padded) <= kCpmResidentLdsMax) {
         for (int done = 0; done < n && e == hipSuccess;) {

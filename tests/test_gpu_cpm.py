@@ -535,3 +535,25 @@ def test_resident_blocks_across_rows_match_oracle(S, cpm_range, shape, n_cells):
     assert np.array_equal(smp.get_state(0), want)
     assert np.array_equal(st[:, 0], ost)
     smp.close()
+
+
+# lattices two columns wide: one site of a colour in every second row
+@pytest.mark.parametrize("mode,tile_rows", [("auto", 0), ("stream", 0), ("stream", 2)])
+@pytest.mark.parametrize("shapes", [[(4, 2)], [(10, 2)], [(40, 2)], [(1030, 2)],
+                                    [(40, 2), (18, 30)]])
+def test_lattices_two_columns_wide_match_oracle(S, mode, tile_rows, shapes):
+    J = JS["sorting"]
+    cases = [_random_case(600 + r, sh, 5) for r, sh in enumerate(shapes)]
+    reps = [_rep(ids, J, ct, A, 1.0, 12.0, 70 + r) for r, (ids, ct, A) in enumerate(cases)]
+    smp = S(reps, 37, init=False)
+    smp.set_schedule(mode=mode, tile_rows=tile_rows)
+    for r, (ids, _, _) in enumerate(cases):
+        smp.set_state(r, ids)
+    smp.sweep(5)
+    st = smp.sweep(4, 2).cpu().numpy()
+    for r, (ids, ct, A) in enumerate(cases):
+        s1, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 37, 70 + r, 0, 5)
+        want, _, ost = orc.cpm_run(s1, J, ct, A, 1.0, 12.0, 37, 70 + r, 5, 4, 2)
+        assert np.array_equal(smp.get_state(r), want), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
