@@ -308,8 +308,8 @@ int spinmc_thresholds(const spinmc_ctx *ctx, int32_t replica, uint64_t *host_T, 
  * step on streamed passes; any other mode lets the steps, recorded or not, of
  * lattices whose ids (4 bytes a site, with a one- or two-cell halo), tables
  * and attempt queues fit 156 KiB of LDS run resident (one workgroup per
- * replica; contexts with a lattice of Lx = 2 stay on passes of one site per
- * lane); with SPINMC_SCHED_PERSIST unrecorded steps of 3x3 lattices
+ * replica; contexts with a lattice of Lx = 2, or with a target area below
+ * sites - 2^31, stay on passes of one site per lane); with SPINMC_SCHED_PERSIST unrecorded steps of 3x3 lattices
  * above 16384 sites run tiled instead.  tile_rows is rounded down to whole
  * periods of the colouring (2 rows, or 6 with the 5x5 neighbourhood).
  * wg_threads of a streamed 3x3 pass where every Lx is a multiple of 8: 0 =

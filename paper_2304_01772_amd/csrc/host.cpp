@@ -206,6 +206,7 @@ struct spinmc_ctx {
     long long* d_cov_part = nullptr;  // chunk sums of the split covariance estimator
     size_t cov_part_n = 0;
     int cpm_cell_cap = 0;
+    bool cpm_wide_areas = false;  // area minus target may pass 32 bits
     int tile_cells = 0;  // as cpm_cell_cap where tiles keep the cells' tables in LDS, else 0
     // tiles of the streamed two-phase CPM pass (null where it does not fit)
     CpmTile* d_ctiles = nullptr;
@@ -2106,10 +2107,13 @@ int cpm_pass_threads(const spinmc_ctx* c) {
     return w > 0 ? std::min(w, 256) : 256;
 }
 
-// A lattice one site of a colour wide (Lx = 2 with the 3x3 neighbourhood): the
-// two-phase kernels divide by that width through a reciprocal that is exact for
-// divisors above 1, so such a context stays on k_cpm_pass.
-bool cpm_one_column(const spinmc_ctx* c) {
+// Contexts that stay on k_cpm_pass / k_cpm_pass5: with a lattice one site of a
+// colour wide (Lx = 2, 3x3 neighbourhood), since the two-phase kernels divide by that
+// width through a reciprocal that is exact for divisors above 1; and with target
+// areas so far below zero that area minus target passes 32 bits, in which the tables
+// of the other kernels hold it.
+bool cpm_per_site(const spinmc_ctx* c) {
+    if (c->cpm_wide_areas) return true;
     for (const HostRep& h : c->reps)
         if (h.dev.Lx < 2 * (c->cpm_range + 1)) return true;
     return false;
@@ -2129,7 +2133,7 @@ int cpm_build_ctiles(spinmc_ctx* c) {
     hipFree(c->d_ctiles);
     c->d_ctiles = nullptr;
     c->n_ctiles = 0;
-    if (c->sched.wg_threads != 0 || cpm_one_column(c)) return SPINMC_OK;
+    if (c->sched.wg_threads != 0 || cpm_per_site(c)) return SPINMC_OK;
     const int tab = (int)align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
     const int threads = 512, P = c->cpm_range == 2 ? 3 : 2;
     std::vector<CpmTile> tiles;
@@ -2268,9 +2272,12 @@ int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
         r.LS = f.LS;
         r.K1 = f.K1;
         r.K0 = f.K0;
-        r.small_areas = (int64_t)r.Lx * r.Ly <= (1 << 26);
-        for (int32_t t : h.target)
+        const int64_t sites = (int64_t)r.Lx * r.Ly;
+        r.small_areas = sites <= (1 << 26);
+        for (int32_t t : h.target) {
             if (t > (1 << 26) || t < -(1 << 26)) r.small_areas = 0;
+            if (sites - t > INT32_MAX) c->cpm_wide_areas = true;
+        }
         h.lat_bytes = (size_t)r.Lx * r.Ly * 4;
         r.lat_off = (int64_t)(lat_off / 4);  // int32 elements
         lat_off = align_up(lat_off + h.lat_bytes, kAlign);
@@ -2304,7 +2311,7 @@ int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
         }
         c->cpm_cell_cap = (int)align_up((size_t)cap, 16);
         const size_t tab_lds = align_up((size_t)8 * std::max(c->max_tab_n, 1), 16);
-        c->cpm_quad = quad && c->cpm_cell_cap <= kCpmLdsCells &&
+        c->cpm_quad = quad && !c->cpm_wide_areas && c->cpm_cell_cap <= kCpmLdsCells &&
                       cpm_quad_lds_bytes((int)tab_lds, c->cpm_cell_cap) <= kCpmQuadLdsMax;
     }
     std::vector<RepDev> rd(n);
@@ -2526,7 +2533,7 @@ int cpm_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
     int max_padded = 0;
     for (const HostRep& h : c->reps)
         max_padded = std::max(max_padded, (h.dev.Lx + 2 * c->cpm_range) * (h.dev.Ly + 2 * c->cpm_range));
-    if (!c->prof && c->sched.mode != 2 && !tiled && !cpm_one_column(c) &&
+    if (!c->prof && c->sched.mode != 2 && !tiled && !cpm_per_site(c) &&
         cpm_resident_lds_bytes(c->cpm_range, (int)tab_bytes, c->cpm_cell_cap, c->max_sites,
                                max_padded) <= kCpmResidentLdsMax) {
         for (int done = 0; done < n && e == hipSuccess;) {

@@ -557,3 +557,29 @@ def test_lattices_two_columns_wide_match_oracle(S, mode, tile_rows, shapes):
         assert np.array_equal(smp.get_state(r), want), r
         assert np.array_equal(st[:, r], ost), r
     smp.close()
+
+
+# target areas at the ends of 32 bits, where area minus target passes them: a quad
+# width, another one, the 5x5 neighbourhood beyond and within the LDS, and the last
+# target for which the difference still fits
+@pytest.mark.parametrize("cpm_range,shape,low", [
+    (1, (24, 32), -2**31), (1, (24, 32), 24 * 32 - 2**31 + 1), (1, (30, 42), -2**31),
+    (1, (200, 202), -2**31), (2, (18, 30), -2**31), (2, (204, 210), -2**31)])
+@pytest.mark.parametrize("mode", ["auto", "stream"])
+def test_extreme_target_areas_match_oracle(S, cpm_range, shape, low, mode):
+    J = JS["sorting"]
+    ids, ct, A = _random_case(640, shape, 6)
+    A[1::3], A[2::3] = low, 2**31 - 1
+    # the area term alone spans 2^32 lambda: attempts between ordinary cells decide by
+    # adhesion, those with an extreme one by the sign of the difference
+    smp = S([dict(_rep(ids, J, ct, A, 1.0, 12.0, 80), cpm_range=cpm_range)], 41, init=False)
+    smp.set_schedule(mode=mode)
+    smp.set_state(0, ids)
+    smp.sweep(2)
+    got = smp.get_state(0)
+    want, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 41, 80, 0, 2, nrange=cpm_range)
+    assert np.array_equal(got, want)
+    smp.sweep(2, 2)
+    want, _, _ = orc.cpm_run(want, J, ct, A, 1.0, 12.0, 41, 80, 2, 2, nrange=cpm_range)
+    assert np.array_equal(smp.get_state(0), want)
+    smp.close()
