@@ -51,7 +51,11 @@ constexpr int kGraphChunk = 50;  // sweeps per captured graph
 // 1.73; 1024 2.74 / 1.74 and 3.45 / 2.51; 2048 2.96 / 2.90 and 3.65 / 4.36).
 constexpr int64_t kIsing8MaxSites = (int64_t)1 << 21;
 constexpr int kSide = 4;         // side streams for concurrent resident groups
+// Dynamic LDS of the replicas packed into one resident workgroup: what the static
+// arrays of its kernel leave of 160 KiB (Ising and per-site: at most 6 KiB).
 constexpr size_t kResidentLdsBudget = 150 * 1024;
+constexpr size_t kResidentPottsLdsBudget =
+    std::min(kResidentLdsBudget, (size_t)160 * 1024 - kPottsStaticLds);
 // Streamed lattice sets beyond this size do not stay in the 256 MB last-level
 // cache between passes: their own-plane traffic goes nontemporal by default.
 constexpr size_t kNtAutoBytes = 192ull << 20;
@@ -1739,17 +1743,18 @@ int prepare(spinmc_ctx* c, int mode) {
                 tab + align_up(eights ? 2 * align_up((size_t)plane + 8, 8) : h.lat_bytes, 16);
             const int tcap =
                 kind != kResGeneric && c->sched.wg_threads == 0 ? 1024 : tmax;
+            const size_t budget = kind >= kResPotts8 ? kResidentPottsLdsBudget : kResidentLdsBudget;
             int P = 1;
             if (c->sched.rpb > 0) {
                 // forced packing: at most rpb, within the LDS budget, one
                 // wave per replica at least, and no more than the group holds
                 while (P * 2 <= c->sched.rpb && P * 2 <= kMaxRpb && P * 2 * 64 <= tmax &&
                        (kind != kResIsing16 || P * 2 * items <= 2048) &&
-                       (size_t)(P * 2) * slot <= kResidentLdsBudget && P * 2 <= n)
+                       (size_t)(P * 2) * slot <= budget && P * 2 <= n)
                     P *= 2;
             } else {
                 while (P * 2 <= kMaxRpb && P * 2 * items <= tmax &&
-                       (size_t)(P * 2) * slot <= kResidentLdsBudget && n / (P * 2) >= 512)
+                       (size_t)(P * 2) * slot <= budget && n / (P * 2) >= 512)
                     P *= 2;
             }
             // forced packing gives every replica a wave at least (64 P <= tmax)

@@ -1178,11 +1178,9 @@ __device__ __forceinline__ void replica_sync(bool waves) {
     }
 }
 
-constexpr int kPottsRecRows = 16;  // as kRecRows, of the Potts kernel
-
 // Recorded sweeps of a replica: its lanes add their counts in LDS, kRecRows rows
 // at a time, so that no sweep waits for a reduction or for global memory.
-constexpr int kRecRows = 32;
+constexpr int kRecRows = 32;  // 6 KiB for kMaxRpb replicas, beside kResidentLdsBudget
 struct RecRows {
     int (*l)[3];         // this replica's kRecRows x 3 counts in LDS
     int next, every;     // sweeps to the next recorded one
@@ -1734,6 +1732,7 @@ __global__ void __launch_bounds__(1024) k_resident_potts8(SweepArgs a) {
     extern __shared__ __align__(16) uint8_t dyn[];
     __shared__ int lhist[kMaxRpb][kMaxPottsQ];
     __shared__ int lrow[kMaxRpb][kPottsRecRows][4];
+    static_assert(sizeof lhist + sizeof lrow == kPottsStaticLds, "LDS budget");
     const int P = a.rpb;
     const int nt = blockDim.x / P;
     int g = threadIdx.x / nt;

@@ -25,6 +25,10 @@ constexpr int kPottsTabWords = 256 + 20;
 constexpr int kMaxPottsQ = 128;   // labels fit in 7 bits (SWAR equality test)
 constexpr int kMaxCpmTypes = 4;
 constexpr int kMaxRpb = 16;       // replicas per resident workgroup
+constexpr int kPottsRecRows = 16;  // recorded rows a replica of a resident Potts workgroup gathers
+// static LDS of a resident Potts workgroup: labels and recorded rows of every replica
+constexpr size_t kPottsStaticLds =
+    sizeof(int) * (size_t)kMaxRpb * (kMaxPottsQ + 4 * kPottsRecRows);
 
 // Resident kernels of the lattice models.
 enum {

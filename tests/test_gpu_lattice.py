@@ -658,3 +658,25 @@ def test_measured_statistics_equal_recorded_ones(S, Lx, Ly):
     again, _ = smp.measure()
     assert torch.equal(got, st) and torch.equal(again, st)
     smp.close()
+
+
+@pytest.mark.parametrize("n,Lx,Ly,q,h,rpb", [
+    (2, 274, 274, 8, 0.0, 2),     # two slots just past what the static arrays leave
+    (2, 272, 274, 8, 0.0, 2),     # the same with whole blocks a row
+    (4096, 32, 32, 118, 0.25, 0),  # packed by the rule: eight would be past it
+    (1, 512, 256, 128, 0.25, 0),  # the largest lattice with the largest table
+])
+def test_resident_potts_packing_fits_the_lds(S, n, Lx, Ly, q, h, rpb):
+    """Dynamic and static LDS of a resident Potts workgroup together stay
+    within a compute unit's 160 KiB."""
+    reps = [dict(model=1, Lx=Lx, Ly=Ly, q=q, Jx=1.0, Jy=1.0, h=h, beta=0.9, rid=i)
+            for i in range(n)]
+    smp = S(reps, 53, init=True)
+    smp.set_schedule(mode="resident" if rpb else "auto", rpb=rpb)
+    st = smp.sweep(2, 1).cpu().numpy()
+    for i in sorted({0, n // 2, n - 1}):
+        s0 = orc.potts_init(Lx, Ly, q, 53, i)
+        want, ost = orc.potts_run(s0, q, 1.0, h, 0.9, 53, i, 0, 2, 1)
+        assert np.array_equal(smp.get_state(i), want), i
+        assert np.array_equal(st[:, i], ost), i
+    smp.close()
