@@ -144,7 +144,7 @@ struct spinmc_ctx {
     int n_tiles = 0;
     int n_tiles_ising = 0;  // streamed Ising tiles come first in d_tiles
     int tiles_rows = 0;
-    int tiles_threads = 0;  // CPM: pass threads the tiles were sized for
+    int tiles_wg = 0;  // CPM: wg_threads of the schedule the tiles were built for
     spinmc_schedule sched{0, 0, 0, 0};
     bool prepared = false;
     long prepared_key = 0;
@@ -2229,7 +2229,7 @@ int cpm_build_tiles(spinmc_ctx* c) {
                       hipMemcpyHostToDevice);
     c->n_tiles = (int)tiles.size();
     c->tiles_rows = c->sched.tile_rows;
-    c->tiles_threads = cpm_pass_threads(c);
+    c->tiles_wg = c->sched.wg_threads;
     if (e != hipSuccess) return check_dev(c, e, "CPM tiles");
     return cpm_build_ctiles(c);
 }
@@ -2513,7 +2513,9 @@ int cpm_chunk_graph(spinmc_ctx* c, int G, hipGraphExec_t* out) {
 }
 
 int cpm_sweep(spinmc_ctx* c, int n, int re, int32_t* stats) {
-    if (c->tiles_rows != c->sched.tile_rows || c->tiles_threads != cpm_pass_threads(c)) {
+    // both plans depend on the schedule's wg_threads itself: 0 asks for tiles or bands
+    // in LDS, 256 and 512 for one site (or quad) per lane
+    if (c->tiles_rows != c->sched.tile_rows || c->tiles_wg != c->sched.wg_threads) {
         int rc = cpm_build_tiles(c);
         if (rc) return rc;
     }

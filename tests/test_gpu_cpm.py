@@ -583,3 +583,32 @@ def test_extreme_target_areas_match_oracle(S, cpm_range, shape, low, mode):
     want, _, _ = orc.cpm_run(want, J, ct, A, 1.0, 12.0, 41, 80, 2, 2, nrange=cpm_range)
     assert np.array_equal(smp.get_state(0), want)
     smp.close()
+
+
+def _kernels(fn):
+    """Names of the device kernels that fn launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in prof.key_averages())
+
+
+# widths that take no quads: bands with wg_threads 0, one site per lane otherwise
+@pytest.mark.parametrize("cpm_range,shape,per_site", [(1, (24, 42), "k_cpm_pass("),
+                                                      (2, (24, 30), "k_cpm_pass5(")])
+def test_wg_threads_alone_changes_the_passes(S, cpm_range, shape, per_site):
+    J = JS["sorting"]
+    ids, ct, A = _random_case(660, shape, 9)
+    smp = S([dict(_rep(ids, J, ct, A, 1.0, 12.0, 90), cpm_range=cpm_range)], 43, init=False)
+    smp.set_state(0, ids)
+    t = 0
+    for threads in (0, 256, 0, 512, 0):
+        smp.set_schedule(mode="stream", wg_threads=threads)
+        names = _kernels(lambda: smp.sweep(2, 1))
+        assert ("k_cpm_pass_band" in names) == (threads == 0), names
+        assert (per_site in names) == (threads != 0), names
+        smp.sweep(1)  # a cached graph of the same passes
+        ids, _, _ = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 43, 90, t, 3, nrange=cpm_range)
+        t += 3
+        assert np.array_equal(smp.get_state(0), ids), threads
+    smp.close()
