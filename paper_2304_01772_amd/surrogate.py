@@ -88,12 +88,16 @@ class SurrogateMLP:
     def predict(self, x):
         """Physical outputs (<e>, <|m|>, chi) for physical inputs x [B, 4]."""
         tensors = (x, self.params, self.x_lo, self.x_hi, self.y_mu, self.y_sd)
-        if x.dim() == 2 and x.shape[0] > 0 and x.shape[1] == 4 and \
-                all(t.dtype == torch.float32 and t.device == x.device and t.is_contiguous()
-                    and t.device.type == "cuda" for t in tensors):
+        B = x.shape[0] if x.dim() == 2 else 0
+        # the shapes and types that the kernel reads; others broadcast below
+        shapes = ((B, 4), (self.np,), (4,), (4,), (3,), (3,))
+        if B > 0 and all(t.shape == n and t.dtype == torch.float32 and t.device == x.device
+                         and t.is_contiguous() and t.device.type == "cuda"
+                         for t, n in zip(tensors, shapes)) and \
+                not (self.y_mu.requires_grad or self.y_sd.requires_grad):
             # scaling of inputs and outputs inside the network's kernel
-            y = torch.empty((x.shape[0], 3), dtype=torch.float32, device=x.device)
-            check(lib().spinmc_mlp_predict(_p(self.params), _p(x), x.shape[0], _p(self.x_lo),
+            y = torch.empty((B, 3), dtype=torch.float32, device=x.device)
+            check(lib().spinmc_mlp_predict(_p(self.params), _p(x), B, _p(self.x_lo),
                                            _p(self.x_hi), _p(self.y_mu), _p(self.y_sd), _p(y),
                                            self._stream()))
             return y

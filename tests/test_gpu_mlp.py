@@ -241,3 +241,23 @@ def test_train_step_gradient_at_workgroup_edges(L, B):
     Pt, xt = torch.tensor(P, device=dev), torch.tensor(x, device=dev)
     assert L.spinmc_mlp_forward(_p(Pt), _p(xt), B, _p(y), _p(act2), s) == 0
     assert np.array_equal(act2.cpu().numpy(), act)
+
+
+@pytest.mark.parametrize("shapes", [((1,), (4,), (3,), (3,)), ((), (1, 4), (3,), (3,)),
+                                    ((4,), (4,), (1,), ()), ((4,), (4,), (1, 3), (5, 3))])
+def test_predict_with_broadcast_scaling(L, shapes):
+    """Ranges and scales of other shapes than the kernel reads broadcast as
+    the separate tensor operations do, and those that need gradients get
+    them."""
+    from paper_2304_01772_amd.surrogate import SurrogateMLP
+    net = SurrogateMLP(seed=4)
+    g = np.random.default_rng(5)
+    fill = lambda shape, lo: torch.tensor(lo + g.random(shape), dtype=torch.float32).cuda()
+    net.x_lo, net.x_hi, net.y_mu, net.y_sd = (
+        fill(s, lo) for s, lo in zip(shapes, (-2.0, 1.0, 0.0, 0.5)))
+    x = fill((5, 4), 0.0)
+    want = net.forward_normalised(net.normalise_x(x)) * net.y_sd + net.y_mu
+    assert torch.equal(net.predict(x), want)
+    net.y_sd = torch.full((3,), 0.5, device="cuda", requires_grad=True)
+    net.predict(x).sum().backward()
+    assert net.y_sd.grad is not None
