@@ -1,6 +1,13 @@
 // Offsets of a lane's eight sites in the colour planes of a resident lattice (plain
 // arithmetic, so that a host program can check every one against the planes' size).
 #pragma once
+#ifdef __HIPCC__
+#include <hip/hip_runtime.h>
+#else
+#define __device__
+#define __forceinline__ inline
+inline unsigned __umul24(unsigned a, unsigned b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
+#endif
 #include <stdint.h>
 
 namespace spinmc {
