@@ -50,15 +50,31 @@ __device__ __forceinline__ float4v mfma(bf16x8 a, bf16x8 b, float4v c) {
 // --------------------------------------------------------------- forward
 namespace {
 
-// SiLU with the reciprocal as v_rcp_f32 and one Newton step (correct to an
-// ulp, three instructions for the ten of an IEEE division); the maximum turns
-// the step's inf * 0 at an overflowed exponential into the quotient's 0.
-__device__ __forceinline__ float sigm_fast(float z) {
-    const float d = 1.0f + __expf(-z);
-    const float r = __builtin_amdgcn_rcpf(d);
-    return fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), 0.0f);
+// Sigmoids of four values, 1 / d with d = 1 + e^-z >= 1, bit for bit the IEEE
+// division's: as v_rcp_f32 and one Newton step, which give the same for every d up to
+// 2^126 (all 1.06e9 compared on the card) in four instructions for its ten.  Beyond, they
+// give 0: v_rcp_f32 flushes the subnormal result, and the maximum turns the step's
+// inf * 0 at an infinite d into it.  Then the divisions: kChecked behind a branch for the
+// four values, kFast by the caller, who finds the 0 in the products, kDiv at once.
+enum { kFast, kChecked, kDiv };
+template <int HOW>
+__device__ __forceinline__ float4v sigm4(float4v z) {
+    float4v s;
+    if (HOW != kDiv) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float d = 1.0f + __expf(-z[i]), r = __builtin_amdgcn_rcpf(d);
+            s[i] = fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), 0.0f);
+        }
+        if (HOW == kFast ||
+            __builtin_expect(fminf(fminf(s[0], s[1]), fminf(s[2], s[3])) != 0.0f, 1))
+            return s;
+        asm volatile("" : "+v"(z));  // kept behind the branch
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = 1.0f / (1.0f + __expf(-z[i]));
+    return s;
 }
-__device__ __forceinline__ float silu_fast(float z) { return z * sigm_fast(z); }
 
 // two values as BF16 in one word (v_cvt_pk_bf16_f32, nearest even), a low
 __device__ __forceinline__ uint32_t pk_bf(float a, float b) {
@@ -84,6 +100,22 @@ struct FwdWeights {
     uint4 w3[4 * 64];       // k tile kt, rows 0..2, rest 0
     float4 b1[32], b2[32];  // biases by four neurons
 };
+
+// silu(z) as the BF16 words of row tile nt
+template <int HOW>
+__device__ __forceinline__ void put_silu(uint32_t (&h)[16], int nt, const float4v& z) {
+    const float4v v = z * sigm4<HOW>(z);
+    h[2 * nt] = pk_bf(v[0], v[1]);
+    h[2 * nt + 1] = pk_bf(v[2], v[3]);
+}
+
+// Least halves of words, as signed numbers: -0.0, the product of a 0 from sigm4, is the
+// least of all.
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ s16x2 least(s16x2 a, uint32_t u, uint32_t v) {
+    return __builtin_elementwise_min(a, __builtin_elementwise_min(__builtin_bit_cast(s16x2, u),
+                                                                  __builtin_bit_cast(s16x2, v)));
+}
 
 __device__ __forceinline__ uint4 pk8(const float4& u, const float4& v) {
     return make_uint4(pk_bf(u.x, u.y), pk_bf(u.z, u.w), pk_bf(v.x, v.y), pk_bf(v.z, v.w));
@@ -158,15 +190,31 @@ __device__ __forceinline__ float4v plus(const float4v& z, const float4& b) {
     return float4v{z[0] + b.x, z[1] + b.y, z[2] + b.z, z[3] + b.w};
 }
 
+// The lane, and the end of a row tile.  kDiv is a repetition behind a branch that is
+// hardly ever taken: the lane is opaque and the tiles stay in sequence, since otherwise
+// the compiler keeps the first run's operands for it, in twice the registers.
+template <int HOW>
+__device__ __forceinline__ int own_lane() {
+    int l = (int)threadIdx.x & 63;
+    if (HOW == kDiv) asm volatile("" : "+v"(l));
+    return l;
+}
+template <int HOW>
+__device__ __forceinline__ void tile_end() {
+    if (HOW == kDiv) __builtin_amdgcn_sched_barrier(0);
+}
+
 // Both hidden layers for C tiles of 16 samples (lane l of tile c: sample
 // s[c], neurons tile_neuron(nt, l / 16) + i): the pre-activations go to act if it
-// is given, h2 receives the B operands of the output layer.
-template <int C>
-__device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (&xb)[C],
-                                              const size_t (&s)[C], int B, float* act, bool vec,
-                                              uint32_t (&h2)[C][16]) {
-    const int l = (int)threadIdx.x & 63, g = l >> 4;
+// is given, h2 receives the B operands of the output layer.  Returns the activations'
+// least halves (kFast): with a -0.0 in any lane the wave repeats its tiles with kDiv.
+template <int C, int HOW>
+__device__ __forceinline__ s16x2 hidden_layers(const FwdWeights& S, const uint4 (&xb)[C],
+                                               const size_t (&s)[C], int B, float* act, bool vec,
+                                               uint32_t (&h2)[C][16]) {
+    const int l = own_lane<HOW>(), g = l >> 4;
     uint32_t h1[C][16];
+    s16x2 low = {0, 0};
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
         const int n0 = tile_neuron(nt, g);
@@ -176,9 +224,10 @@ __device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (
         for (int c = 0; c < C; ++c) {
             const float4v z = plus(mfma(w, as_frag(xb[c]), float4v{0.f, 0.f, 0.f, 0.f}), b);
             if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + n0, z, vec);
-            h1[c][2 * nt] = pk_bf(silu_fast(z[0]), silu_fast(z[1]));
-            h1[c][2 * nt + 1] = pk_bf(silu_fast(z[2]), silu_fast(z[3]));
+            put_silu<HOW>(h1[c], nt, z);
+            if (HOW == kFast) low = least(low, h1[c][2 * nt], h1[c][2 * nt + 1]);
         }
+        tile_end<HOW>();
     }
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
@@ -199,10 +248,12 @@ __device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (
         for (int c = 0; c < C; ++c) {
             z[c] = plus(z[c], b);
             if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + kH + n0, z[c], vec);
-            h2[c][2 * nt] = pk_bf(silu_fast(z[c][0]), silu_fast(z[c][1]));
-            h2[c][2 * nt + 1] = pk_bf(silu_fast(z[c][2]), silu_fast(z[c][3]));
+            put_silu<HOW>(h2[c], nt, z[c]);
+            if (HOW == kFast) low = least(low, h2[c][2 * nt], h2[c][2 * nt + 1]);
         }
+        tile_end<HOW>();
     }
+    return low;
 }
 
 // The same for one tile with the pre-activations kept.
@@ -214,8 +265,7 @@ __device__ __forceinline__ void hidden_layers_z(const FwdWeights& S, const uint4
     for (int nt = 0; nt < 8; ++nt) {
         z1[nt] = plus(mfma(as_frag(S.w1[nt * 64 + l]), as_frag(xb), float4v{0.f, 0.f, 0.f, 0.f}),
                       S.b1[tile_neuron(nt, g) >> 2]);
-        h1[2 * nt] = pk_bf(silu_fast(z1[nt][0]), silu_fast(z1[nt][1]));
-        h1[2 * nt + 1] = pk_bf(silu_fast(z1[nt][2]), silu_fast(z1[nt][3]));
+        put_silu<kChecked>(h1, nt, z1[nt]);
     }
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
@@ -225,8 +275,7 @@ __device__ __forceinline__ void hidden_layers_z(const FwdWeights& S, const uint4
             z = mfma(as_frag(S.w2[(nt * 4 + kt) * 64 + l]),
                      as_frag(make_uint4(h1[4 * kt], h1[4 * kt + 1], h1[4 * kt + 2], h1[4 * kt + 3])), z);
         z2[nt] = plus(z, S.b2[tile_neuron(nt, g) >> 2]);
-        h2[2 * nt] = pk_bf(silu_fast(z2[nt][0]), silu_fast(z2[nt][1]));
-        h2[2 * nt + 1] = pk_bf(silu_fast(z2[nt][2]), silu_fast(z2[nt][3]));
+        put_silu<kChecked>(h2, nt, z2[nt]);
     }
 }
 
@@ -243,26 +292,19 @@ __device__ __forceinline__ float4v output_layer(const FwdWeights& S, const uint3
 
 }  // namespace
 
-// A wave takes C tiles of 16 samples at a time, tile groups strided over the
-// launch's waves, so that the weights are staged once per workgroup.  Bound
-// by the VALU work of the SiLUs (256 a sample, about 60 lane-cycles each,
-// half of it the quarter-rate exponential and reciprocal); the matrix
-// products take a sixth of that.  10^5 points: 82 us with a
-// workgroup (and its own staging and conversion of the weights) per 64
-// samples, activations through LDS and IEEE divisions; now 20.
-template <int C, bool AFF>
-__global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x, int B, float* y,
-                                                 float* act, Affine af) {
-    __shared__ FwdWeights S;
-    stage_fwd(P, S);
-    const int waves = (int)blockDim.x >> 6, l = (int)threadIdx.x & 63, g = l >> 4;
+namespace {
+
+// The tile groups of a wave, from q on in steps of dq.
+template <int C, bool AFF, int HOW>
+__device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float* P, const float* x,
+                                               int B, float* y, float* act, const Affine& af, int q,
+                                               int dq) {
+    const int l = own_lane<HOW>(), g = l >> 4;
     const bool vec = ((uintptr_t)x & 15u) == 0, avec = ((uintptr_t)act & 15u) == 0;
     const float bo[3] = {P[ob3], P[ob3 + 1], P[ob3 + 2]};
-    __syncthreads();
     const int groups = (B + 16 * C - 1) / (16 * C);
-    // one tile a wave (C = 1) needs no loop: the grid covers the samples
-    int q = (int)blockIdx.x * waves + ((int)threadIdx.x >> 6);
-    if (q >= groups) return;
+    s16x2 low = {0, 0};
+    // the first run of one tile a wave (C = 1) needs no loop: the grid covers the samples
     do {
         uint4 xb[C];
         size_t s[C];
@@ -283,7 +325,7 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x,
             }
         }
         uint32_t h2[C][16];
-        hidden_layers<C>(S, xb, s, B, act, avec, h2);
+        low = __builtin_elementwise_min(low, hidden_layers<C, HOW>(S, xb, s, B, act, avec, h2));
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const float4v o = output_layer(S, h2[c]);
@@ -296,8 +338,33 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x,
                 }
             }
         }
-        q += (int)gridDim.x * waves;
-    } while (C > 1 && q < groups);
+        q += dq;
+    } while ((HOW == kDiv || C > 1) && q < groups);
+    return low;
+}
+
+}  // namespace
+
+// A wave takes C tiles of 16 samples at a time, tile groups strided over the
+// launch's waves, so that the weights are staged once per workgroup.  Bound
+// by the VALU work of the SiLUs (256 a sample, about 60 lane-cycles each,
+// half of it the quarter-rate exponential and reciprocal); the matrix
+// products take a sixth of that.  10^5 points: 82 us with a
+// workgroup (and its own staging and conversion of the weights) per 64
+// samples and activations through LDS; 26.8 with divisions in the SiLUs, 21.9 now.
+template <int C, bool AFF>
+__global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x, int B, float* y,
+                                                 float* act, Affine af) {
+    __shared__ FwdWeights S;
+    stage_fwd(P, S);
+    __syncthreads();
+    const int waves = (int)blockDim.x >> 6;
+    const int q = (int)blockIdx.x * waves + ((int)threadIdx.x >> 6), dq = (int)gridDim.x * waves;
+    if (q >= (B + 16 * C - 1) / (16 * C)) return;
+    const s16x2 low = forward_tiles<C, AFF, kFast>(S, P, x, B, y, act, af, q, dq);
+    if (__any(min(low.x, low.y) == -32768))
+        for (int t = q * C; t < q * C + C && t <= (B - 1) / 16; ++t)
+            forward_tiles<1, AFF, kDiv>(S, P, x, B, y, act, af, t, dq * C);
 }
 
 // -------------------------------------------------------------- backward
@@ -345,8 +412,9 @@ __device__ __forceinline__ void stage_w2t(const float* P, uint4* w2t) {
 __device__ __forceinline__ float bf_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
 
-__device__ __forceinline__ float dsilu_fast(float z) {
-    const float s = sigm_fast(z);
+// silu'(z)
+__device__ __forceinline__ float4v dsilu4(const float4v& z) {
+    const float4v s = sigm4<kChecked>(z);
     return s * (1.0f + z * (1.0f - s));
 }
 
@@ -431,10 +499,8 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
         }
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-            h1[2 * nt] = pk_bf(silu_fast(z1[nt][0]), silu_fast(z1[nt][1]));
-            h1[2 * nt + 1] = pk_bf(silu_fast(z1[nt][2]), silu_fast(z1[nt][3]));
-            h2[2 * nt] = pk_bf(silu_fast(z2[nt][0]), silu_fast(z2[nt][1]));
-            h2[2 * nt + 1] = pk_bf(silu_fast(z2[nt][2]), silu_fast(z2[nt][3]));
+            put_silu<kChecked>(h1, nt, z1[nt]);
+            put_silu<kChecked>(h2, nt, z2[nt]);
         }
     }
     if (!in) {  // samples past B: nothing to add
@@ -468,6 +534,7 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
         float4 v[kOut];
 #pragma unroll
         for (int j = 0; j < kOut; ++j) v[j] = S.w3[j][n0 >> 2];
+        const float4v ds = dsilu4(z2[nt]);
         float4v d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -475,7 +542,7 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
 #pragma unroll
             for (int j = 0; j < kOut; ++j)
                 dh += dY[j] * (i == 0 ? v[j].x : (i == 1 ? v[j].y : (i == 2 ? v[j].z : v[j].w)));
-            d[i] = in ? dh * dsilu_fast(z2[nt][i]) : 0.f;
+            d[i] = in ? dh * ds[i] : 0.f;
         }
         *reinterpret_cast<float4v*>(S.dz + row * kSF + n0) = d;
         dzb[2 * nt] = pk_bf(d[0], d[1]);
@@ -539,8 +606,9 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
             acc = mfma(as_frag(S.w2t[(nt * 4 + kt) * 64 + l]),
                        as_frag(make_uint4(dzb[4 * kt], dzb[4 * kt + 1], dzb[4 * kt + 2],
                                           dzb[4 * kt + 3])), acc);
+        const float4v ds = dsilu4(z1[nt]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) d1[nt][i] = in ? acc[i] * dsilu_fast(z1[nt][i]) : 0.f;
+        for (int i = 0; i < 4; ++i) d1[nt][i] = in ? acc[i] * ds[i] : 0.f;
     }
     if (dx) {
         // each lane its 32 neurons, then the four lanes of the sample

@@ -261,3 +261,44 @@ def test_predict_with_broadcast_scaling(L, shapes):
     net.y_sd = torch.full((3,), 0.5, device="cuda", requires_grad=True)
     net.predict(x).sum().backward()
     assert net.y_sd.grad is not None
+
+
+@pytest.mark.parametrize("B", [3, 40000])
+def test_silu_of_large_negative_pre_activations(L, B):
+    """Pre-activations around -88, where the sigmoid is subnormal but its
+    products are not: outputs and gradients through large output weights
+    against 64 bits (bf16 of the activation: 2^-8; exponential and subnormal
+    sigmoid: below 2^-9), and zero where the exponential overflows."""
+    dev = torch.device("cuda")
+    P = np.zeros(mlp.NP, np.float32)
+    q = mlp.unpack(P)
+    q["b2"] = np.linspace(-88.6, -80.0, 128).astype(np.float32).astype(np.float64)
+    q["b2"][-1] = -200.0
+    q["W3"] = np.zeros((3, 128))
+    for j in range(3):  # one neuron an output: the subnormal range, below it, overflow
+        q["W3"][j, (5, 90, 127)[j]] = 2.0 ** 100
+    P = mlp.pack(q).astype(np.float32)
+    x = np.zeros((B, 4), np.float32)
+    Pt, xt = torch.tensor(P, device=dev), torch.tensor(x, device=dev)
+    s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    y = torch.empty((B, 3), device=dev)
+    act = torch.empty(L.spinmc_mlp_act_floats(B), device=dev)
+    assert L.spinmc_mlp_forward(_p(Pt), _p(xt), B, _p(y), _p(act), s) == 0
+    z = q["b2"][[5, 90, 127]]
+    sg = 1.0 / (1.0 + np.exp(-z))
+    want = z * sg * 2.0 ** 100
+    assert -88.5 < z[0] < -87.5 and 0 < sg[0] < 2.0 ** -126 and z[1] > -87
+    yc = y.cpu().numpy()
+    assert np.all(np.abs(yc[:, :2] - want[:2]) <= 2.0 ** -7 * np.abs(want[:2]))
+    assert np.all(yc[:, 2] == 0)
+    # db2 = sum_b 2 w (y - t) / B W3 silu'(z2), with t chosen so that 2 (y - t) / B is 1 / B
+    t = torch.tensor(yc - 0.5, device=dev)
+    w = torch.ones(3, device=dev)
+    g = torch.empty(mlp.NP, device=dev)
+    loss = torch.empty(1, device=dev)
+    ws = torch.empty(L.spinmc_mlp_workspace_floats(B), device=dev)
+    assert L.spinmc_mlp_backward(_p(Pt), _p(xt), _p(act), _p(t), _p(w), B, _p(g), None, _p(loss),
+                                 _p(ws), s) == 0
+    db2 = mlp.unpack(g.cpu().numpy())["b2"][[5, 90]]
+    ref = (sg * (1.0 + z * (1.0 - sg)))[:2] * 2.0 ** 100
+    assert np.all(np.abs(db2 - ref) <= 2.0 ** -8 * np.abs(ref))
