@@ -59,7 +59,7 @@ HBM_BOUND = ("stream_ising", "persist_ising")
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("lattice_kernels.hip", "spinmc_internal.hpp"):
+    for f in ("lattice_kernels.hip", "item8.hpp", "spinmc_internal.hpp"):
         with open(os.path.join(ROOT, "paper_2304_01772_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -896,6 +896,8 @@ def main():
                          persistent=args.persistent)
     sched = smp.get_schedule()
     mode_name = {v: k for k, v in MODES.items()}[sched["mode"]]
+    if mode_name == "auto":  # what it resolves to
+        mode_name = "hybrid" if smp.schedule_sites()[0] else "resident"
     for w in range(args.warmup):
         smp.sweep(args.sweeps)
         torch.cuda.synchronize()

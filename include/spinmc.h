@@ -349,7 +349,7 @@ int spinmc_schedule_sites(const spinmc_ctx *ctx, int64_t streamed[3], int64_t re
  * measured attempts per ns of every candidate in host_rates (capacity cap,
  * may be NULL; *n_tried receives the count).  If chosen is not NULL and
  * chosen->mode > 0 on entry, only candidates of that mode are tried.
- * The candidates: modes, tile heights, workgroup sizes, persistent passes,
+ * The candidates: the default plan, modes, tile heights, workgroup sizes, persistent passes,
  * then nontemporal access forced on and off for the best streaming
  * candidate and replicas per resident workgroup 1, 2, 4 and 8 for the best
  * candidate with resident groups.  The three fastest then run again, twice

@@ -1179,6 +1179,10 @@ int spinmc_autotune(spinmc_ctx* c, int32_t trial_sweeps, spinmc_schedule* chosen
             any_stream = any_stream || h.chunk;
             if (h.chunk) min_def = std::min(min_def, default_tile_rows(h));
         }
+        // the default plan (of the mode asked for): slabs and resident workgroups of
+        // 1024 lanes belong to schedules that name no wg_threads
+        if (mode_filter == 0 || mode_filter == 3 || (mode_filter == 1 && all_res))
+            cand.push_back(spinmc_schedule{mode_filter, 0, 0, 0});
         if (all_res)
             for (int th : {256, 512}) cand.push_back(spinmc_schedule{1, 0, th, 0});
         if (any_stream) {
@@ -1295,7 +1299,12 @@ int spinmc_autotune(spinmc_ctx* c, int32_t trial_sweeps, spinmc_schedule* chosen
     }
     // the best streaming schedule with nontemporal own-plane access forced
     // on and off (candidates so far use the size rule)
-    if (e == hipSuccess && best >= 0 && !c->cpm && cand[best].mode >= 2) {
+    const auto streams = [&](const spinmc_schedule& sc) {
+        bool fits = true;
+        for (const HostRep& h : c->reps) fits = fits && h.resident;
+        return sc.mode >= 2 || (sc.mode == 0 && !fits);
+    };
+    if (e == hipSuccess && best >= 0 && !c->cpm && streams(cand[best])) {
         const size_t nb = cand.size();
         for (int f : {SPINMC_SCHED_NT_ON, SPINMC_SCHED_NT_OFF}) {
             spinmc_schedule sc = cand[best];

@@ -680,3 +680,18 @@ def test_resident_potts_packing_fits_the_lds(S, n, Lx, Ly, q, h, rpb):
         assert np.array_equal(smp.get_state(i), want), i
         assert np.array_equal(st[:, i], ost), i
     smp.close()
+
+
+def test_autotune_can_choose_the_default_plan(S):
+    """Eight lattices of 512 x 512 run in slabs by default, at twice the speed
+    of the streamed passes: the autotuner times that plan too and keeps it."""
+    reps = [dict(model=0, Lx=512, Ly=512, Jx=1.0, Jy=1.0, h=0.0, beta=0.44, rid=i)
+            for i in range(8)]
+    smp = S(reps, 47, init=True)
+    assert smp.schedule_sites() == (0, 8 * 512 * 512)
+    chosen, rates = smp.autotune(trial_sweeps=100, cache=False)
+    assert chosen == dict(mode=0, tile_rows=0, wg_threads=0, flags=0, rpb=0), rates
+    smp.sweep(3)
+    s0 = _init_oracle(reps[7], 47)
+    assert np.array_equal(smp.get_state(7), _run_oracle(reps[7], s0, 47, 0, 3, 0)[0])
+    smp.close()
