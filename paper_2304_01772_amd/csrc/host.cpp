@@ -504,7 +504,6 @@ int cpm_prepare_tables(const spinmc_replica_desc* d, int n) {
 int create_cpm(const spinmc_replica_desc* d, int n, uint64_t seed, void* stream,
                spinmc_ctx** out);
 
-// Lattices of the resident kernels (whole or in slabs) under a resolved mode.
 // LDS bytes of the thresholds of the per-site kernel, and of Potts items of the
 // listed replicas.
 size_t generic_tab_bytes(const spinmc_ctx* c) { return align_up((size_t)8 * c->max_tab_n, 16); }
@@ -515,12 +514,21 @@ size_t potts_tab_bytes(const spinmc_ctx* c, const std::vector<int>& list) {
     return (size_t)4 * kPottsTabWords + align_up(8 * n, 16);
 }
 
+// Runs in the resident kernels (whole or in slabs) under a resolved mode.
 bool is_resident(const HostRep& h, int mode) {
     return mode == 1 || !h.chunk || (mode == 3 && h.resident) || h.slab_rows > 0;
 }
 
 void plan_slabs(spinmc_ctx* c, int mode);
 int effective_mode(const spinmc_ctx* c);
+
+// The schedule of the next sweeps: their tiles, resident lists and graphs are built
+// then, the slabs, of which schedule_sites tells, are planned here.
+void use_schedule(spinmc_ctx* c, const spinmc_schedule& sc) {
+    c->sched = sc;
+    if (!c->cpm && !c->tri && !c->msc) plan_slabs(c, effective_mode(c));
+    c->prepared = false;
+}
 
 size_t resident_lds(const spinmc_ctx* c, const HostRep& r) {
     return align_up((size_t)8 * c->max_tab_n, 16) + r.lat_bytes;
@@ -898,9 +906,7 @@ int spinmc_set_schedule(spinmc_ctx* c, const spinmc_schedule* s) {
         for (const HostRep& h : c->reps)
             if (!h.resident)
                 return fail(SPINMC_E_INVALID, "set_schedule: a lattice exceeds the resident LDS budget");
-    c->sched = *s;
-    if (!c->cpm && !c->tri && !c->msc) plan_slabs(c, effective_mode(c));
-    c->prepared = false;  // new tiles, resident lists and graphs on the next sweep
+    use_schedule(c, *s);
     return SPINMC_OK;
 }
 
@@ -1148,8 +1154,7 @@ int spinmc_autotune(spinmc_ctx* c, int32_t trial_sweeps, spinmc_schedule* chosen
         tune_load_locked();
         auto it = g_tune.find(key);
         if (it != g_tune.end()) {
-            c->sched = it->second;
-            c->prepared = false;
+            use_schedule(c, it->second);
             if (chosen) *chosen = it->second;
             if (n_tried) *n_tried = 0;
             return SPINMC_OK;
@@ -1255,8 +1260,7 @@ int spinmc_autotune(spinmc_ctx* c, int32_t trial_sweeps, spinmc_schedule* chosen
     // recorded in rates for the first round of candidates
     auto timed_run = [&](const spinmc_schedule& sc, int mult, bool record) -> double {
         const int n = trial_sweeps * mult;
-        c->sched = sc;
-        c->prepared = false;
+        use_schedule(c, sc);
         int rc = c->cpm ? cpm_sweep(c, 1, 0, nullptr) : enqueue_sweep(c, 1, 0, nullptr);
         if (rc == SPINMC_OK) rc = c->cpm ? cpm_sweep(c, n, 0, nullptr)
                                          : enqueue_sweep(c, n, 0, nullptr);
@@ -1370,13 +1374,11 @@ int spinmc_autotune(spinmc_ctx* c, int32_t trial_sweeps, spinmc_schedule* chosen
     hipFree(lat_copy);
     hipFree(area_copy);
     if (e != hipSuccess || er != hipSuccess || best < 0) {
-        c->sched = saved_sched;
-        c->prepared = false;
+        use_schedule(c, saved_sched);
         if (c->poisoned) return SPINMC_E_DEVICE;
         return check_dev(c, e != hipSuccess ? e : er, "autotune");
     }
-    c->sched = cand[best];
-    c->prepared = false;
+    use_schedule(c, cand[best]);
     tune_store(key, cand[best]);
     if (chosen) *chosen = cand[best];
     if (n_tried) *n_tried = tried;

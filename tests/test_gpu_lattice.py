@@ -695,3 +695,19 @@ def test_autotune_can_choose_the_default_plan(S):
     s0 = _init_oracle(reps[7], 47)
     assert np.array_equal(smp.get_state(7), _run_oracle(reps[7], s0, 47, 0, 3, 0)[0])
     smp.close()
+
+
+def test_schedule_sites_after_autotune(S):
+    """The autotuner's choice, timed or from the cache, is what schedule_sites
+    tells of at once, not the slabs of the plan before it."""
+    reps = [dict(model=0, Lx=512, Ly=512, Jx=1.0, Jy=1.0, h=0.0, beta=0.45, rid=i)
+            for i in range(9)]
+    sites = 9 * 512 * 512
+    for _ in range(2):  # the second context takes the first one's choice
+        smp = S(reps, 48, init=True)
+        assert smp.schedule_sites() == (0, sites)
+        chosen, _ = smp.autotune(trial_sweeps=3, mode="stream")
+        assert chosen["mode"] == 2 and smp.schedule_sites() == (sites, 0)
+        smp.set_schedule()
+        assert smp.schedule_sites() == (0, sites)
+        smp.close()
