@@ -170,7 +170,8 @@ struct spinmc_ctx {
     };
     std::vector<ResGroup> res_groups;
     TileDev* d_slabs = nullptr;
-    uint8_t* d_lat2 = nullptr;  // the other lattices of slab launches (as d_lat; null: no slabs)
+    uint8_t* d_lat2 = nullptr;  // the other lattices of slab launches, of their replicas alone
+    size_t lat2_bytes = 0;      // (at 256 times their tiles' lat2)
     // persistent streamed passes (schedule flag SPINMC_SCHED_PERSIST): one
     // plan per model (Ising, Potts) over the streamed replicas
     struct PersistPlan {
@@ -1674,11 +1675,19 @@ int prepare(spinmc_ctx* c, int mode) {
                      (long)(unsigned)tr;
     if (c->prepared && c->prepared_key == key) return SPINMC_OK;
     plan_slabs(c, mode);
-    bool any_slab = false;
-    for (const HostRep& h : c->reps) any_slab = any_slab || h.slab_rows > 0;
-    if (any_slab && !c->d_lat2 && hipMalloc((void**)&c->d_lat2, c->lat_bytes) != hipSuccess) {
-        (void)hipGetLastError();  // no memory for a second set of lattices: no slabs
-        for (HostRep& h : c->reps) h.slab_rows = 0;
+    size_t need2 = 0;  // second lattices of the replicas in slabs
+    for (const HostRep& h : c->reps)
+        if (h.slab_rows > 0) need2 += align_up(h.lat_bytes, kAlign);
+    if (need2 != c->lat2_bytes) {
+        hipFree(c->d_lat2);
+        c->d_lat2 = nullptr;
+        c->lat2_bytes = 0;
+        if (need2 > 0 && hipMalloc((void**)&c->d_lat2, need2) != hipSuccess) {
+            (void)hipGetLastError();  // no memory for them: no slabs
+            for (HostRep& h : c->reps) h.slab_rows = 0;
+        } else {
+            c->lat2_bytes = need2;
+        }
     }
     std::vector<int32_t> res_chunk, res_gen, spotts;
     std::vector<TileDev> tiles, ptiles;  // Ising tiles first, then Potts tiles
@@ -1721,6 +1730,7 @@ int prepare(spinmc_ctx* c, int mode) {
     c->res_groups.clear();
     std::vector<int32_t> buf;
     std::vector<TileDev> slabs;
+    size_t off2 = 0;
     const int tmax = c->sched.wg_threads > 0 ? c->sched.wg_threads : 512;
     for (int pass = 0; pass < 2; ++pass) {
         const std::vector<int32_t>& L = pass == 0 ? res_chunk : res_gen;
@@ -1779,9 +1789,11 @@ int prepare(spinmc_ctx* c, int mode) {
                 const int rows = h.slab_rows;
                 g.whole = h.resident;
                 g.slab0 = (int)slabs.size();
-                for (int i : kv.second)
+                for (int i : kv.second) {
                     for (int y = 0; y < h.dev.Ly; y += rows)
-                        slabs.push_back(TileDev{i, y, std::min(rows, h.dev.Ly - y), 0});
+                        slabs.push_back(TileDev{i, y, std::min(rows, h.dev.Ly - y), (int)(off2 / kAlign)});
+                    off2 += align_up(h.lat_bytes, kAlign);
+                }
                 g.n_slabs = (int)slabs.size() - g.slab0;
                 g.halo = h.slab_halo;
                 const size_t window = (size_t)(rows + 2 * g.halo) * h.dev.W;
@@ -1885,13 +1897,13 @@ hipError_t enqueue_resident(spinmc_ctx* c, SweepArgs a, hipStream_t s) {
             b.n_list = g.n_slabs;
             b.rpb = 1;
             b.halo = g.halo;
+            b.lat2 = c->d_lat2;
             for (int i = 0; i < m && e == hipSuccess; ++i) {
                 const int i0 = (int)((int64_t)a.n_sweeps * i / m);
                 const int i1 = (int)((int64_t)a.n_sweeps * (i + 1) / m);
                 b.sweep_off = a.sweep_off + i0;
                 b.n_sweeps = i1 - i0;
-                b.lat = i % 2 == 0 ? c->d_lat2 : c->d_lat;
-                b.lat_src = i % 2 == 0 ? c->d_lat : c->d_lat2;
+                b.from2 = i % 2;
                 e = timed(c, SPINMC_K_RESIDENT, [&] {
                     return launch_resident(b, g.n_slabs, kResIsingSlab, g.slab_items,
                                            g.slab_threads, g.slab_lds, side);

@@ -1489,8 +1489,8 @@ __device__ __forceinline__ void store_planes8(uint8_t* gmem, const uint8_t* lds,
 //
 // SLAB (with AL, NI > 0 and UNI): a few large lattices are cut into slabs of rows, a
 // workgroup each, where whole ones would leave most of the chip idle.  A
-// workgroup reads its slab with a.halo rows on either side from a.lat_src, runs
-// n_sweeps <= a.halo / 2 sweeps on that window and writes its own rows to a.lat:
+// workgroup reads its slab with a.halo rows on either side from one of two lattices, runs
+// n_sweeps <= a.halo / 2 sweeps on that window and writes its own rows to the other:
 // the window's outermost valid row moves inwards by one a pass, since every
 // site's draws depend on its place alone, so the slabs need no exchange between
 // launches (64 lattices of 256 x 256: 2.7 us a sweep in slabs, 4.4 whole).
@@ -1520,6 +1520,12 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
     uint32_t* tab = reinterpret_cast<uint32_t*>(slot);
     uint8_t* lds = slot + 4 * kIsingTabWords;
     uint8_t* gmem = a.lat + R.lat_off;
+    const uint8_t* gsrc = gmem;
+    if (SLAB) {
+        uint8_t* g2 = a.lat2 + (size_t)T.lat2 * 256u;
+        gsrc = a.from2 ? g2 : gmem;
+        gmem = a.from2 ? gmem : g2;
+    }
     // place in the lattice of a window's byte k
     auto place = [&](uint32_t k) {
         if (!SLAB) return k;
@@ -1533,8 +1539,7 @@ __global__ void __launch_bounds__(1024) k_resident_ising8(SweepArgs a) {
 #pragma unroll
             for (uint32_t c = 0; c < 2u; ++c)
                 *reinterpret_cast<uint2*>(lds + c * stride + 8u * i) =
-                    *reinterpret_cast<const uint2*>(a.lat_src + R.lat_off + c * gplane +
-                                                    place(8u * i));
+                    *reinterpret_cast<const uint2*>(gsrc + c * gplane + place(8u * i));
     } else if (active) {
         load_planes8<AL>(lds, gmem, plane, stride, (uint32_t)lt, (uint32_t)nt);
     }

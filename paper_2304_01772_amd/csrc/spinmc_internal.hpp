@@ -63,7 +63,7 @@ struct RepDev {
 
 // One unit of streamed work: rows [y0, y0 + rows) of both planes of a replica.
 struct TileDev {
-    int32_t rep, y0, rows, pad;
+    int32_t rep, y0, rows, lat2;  // lat2: of a slab, its replica's place in the second lattices
 };
 
 // One unit of a persistent workgroup's work (rows [y0, y0 + rows) of both
@@ -129,9 +129,10 @@ struct SweepArgs {
     // and the number of entries of rep_list
     int32_t rpb, res_slot_bytes, n_list;
     // kResIsingSlab: one tile a workgroup (n_list of them), rows either side of
-    // it that its window holds (even), and the lattices read (lat is written)
-    int32_t halo;
-    const uint8_t* lat_src;
+    // it that its window holds (even), the second lattices (256 bytes times a tile's
+    // lat2), and which are read, lat or (from2) lat2; the others are written
+    int32_t halo, from2;
+    uint8_t* lat2;
 };
 
 // Host-side launchers implemented in the kernel translation units.

@@ -711,3 +711,40 @@ def test_schedule_sites_after_autotune(S):
         smp.set_schedule()
         assert smp.schedule_sites() == (0, sites)
         smp.close()
+
+
+def test_slabs_hold_second_lattices_of_their_replicas_alone(S):
+    """One small Ising shape in slabs beside 1 GiB of streamed Potts lattices:
+    the first sweep allocates far less than a second copy of the context, and
+    a schedule without slabs gives the second lattices back."""
+    reps = [dict(model=1, Lx=4096, Ly=4096, q=3, Jx=1.0, Jy=1.0, h=0.0, beta=0.9, rid=i)
+            for i in range(64)]
+    ising = [dict(model=0, Lx=512, Ly=1024, Jx=1.0, Jy=1.0, h=0.0, beta=0.44, rid=100 + i)
+             for i in range(8)]
+    free = lambda: (torch.cuda.synchronize(), torch.cuda.mem_get_info()[0])[1]
+    warm = S(ising[:2], 51, init=True)  # modules and scratch of the kernels
+    warm.sweep(2)
+    smp = S(reps + ising, 51, init=True)
+    n_ising = sum(r["Lx"] * r["Ly"] for r in ising)
+    assert smp.schedule_sites(by_model=True)[1]["ising"] == n_ising
+    f0 = free()
+    smp.sweep(2)
+    f1 = free()
+    assert f0 - f1 < 128 << 20, (f0, f1)
+    smp.sweep(3)
+    s0 = _init_oracle(ising[5], 51)
+    assert np.array_equal(smp.get_state(69), _run_oracle(ising[5], s0, 51, 0, 5, 0)[0])
+    smp.close()
+    small = S(ising, 52, init=True)
+    for mode in ("stream", "auto", "stream", "auto"):  # the first: streams and graphs too
+        small.set_schedule(mode=mode)
+        small.sweep(2)
+        f1, f2 = f0, free()
+        f0 = f2
+        if mode == "stream":
+            gained = f2 - f1
+    assert gained >= n_ising, gained
+    s0 = _init_oracle(ising[7], 52)
+    assert np.array_equal(small.get_state(7), _run_oracle(ising[7], s0, 52, 0, 8, 0)[0])
+    small.close()
+    warm.close()
