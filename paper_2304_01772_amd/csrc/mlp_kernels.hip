@@ -302,7 +302,7 @@ __device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float*
     const int l = own_lane<HOW>(), g = l >> 4;
     const bool vec = ((uintptr_t)x & 15u) == 0, avec = ((uintptr_t)act & 15u) == 0;
     const float bo[3] = {P[ob3], P[ob3 + 1], P[ob3 + 2]};
-    const int groups = (B + 16 * C - 1) / (16 * C);
+    const int groups = (B - 1) / (16 * C) + 1;  // (no sum that passes 32 bits)
     s16x2 low = {0, 0};
     // the first run of one tile a wave (C = 1) needs no loop: the grid covers the samples
     do {
@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x,
     __syncthreads();
     const int waves = (int)blockDim.x >> 6;
     const int q = (int)blockIdx.x * waves + ((int)threadIdx.x >> 6), dq = (int)gridDim.x * waves;
-    if (q >= (B + 16 * C - 1) / (16 * C)) return;
+    if (q > (B - 1) / (16 * C)) return;
     const s16x2 low = forward_tiles<C, AFF, kFast>(S, P, x, B, y, act, af, q, dq);
     if (__any(min(low.x, low.y) == -32768))
         for (int t = q * C; t < q * C + C && t <= (B - 1) / 16; ++t)

@@ -302,3 +302,26 @@ def test_silu_of_large_negative_pre_activations(L, B):
     db2 = mlp.unpack(g.cpu().numpy())["b2"][[5, 90]]
     ref = (sg * (1.0 + z * (1.0 - sg)))[:2] * 2.0 ** 100
     assert np.all(np.abs(db2 - ref) <= 2.0 ** -8 * np.abs(ref))
+
+
+def test_forward_of_the_largest_batch(L):
+    """The last samples of a batch of 2^31 - 1 (34 GB of inputs) are those of
+    a small batch."""
+    B, n = 2 ** 31 - 1, 100
+    if torch.cuda.mem_get_info()[0] < 80 * 2 ** 30:
+        pytest.skip("needs 60 GB of free device memory")
+    rng = np.random.default_rng(6)
+    dev = torch.device("cuda")
+    Pt = torch.tensor(mlp.init_params(rng), device=dev)
+    tail = torch.tensor(rng.uniform(-1, 1, size=(n, 4)).astype(np.float32), device=dev)
+    x = torch.zeros((B, 4), device=dev)
+    x[-n:] = tail
+    y = torch.full((B, 3), float("nan"), device=dev)
+    want = torch.empty((n, 3), device=dev)
+    s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.spinmc_mlp_forward(_p(Pt), _p(x), B, _p(y), None, s) == 0
+    assert L.spinmc_mlp_forward(_p(Pt), _p(tail), n, _p(want), None, s) == 0
+    assert torch.equal(y[-n:], want)
+    assert not torch.isnan(y[:: 2 ** 20]).any()
+    del x, y
+    torch.cuda.empty_cache()
