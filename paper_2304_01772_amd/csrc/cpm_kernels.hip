@@ -1183,8 +1183,9 @@ __global__ void __launch_bounds__(512) k_cpm_pass_tile(CpmArgs a, const CpmTile*
 // Without TAB the cells' tables stay in global memory, for the decided attempts alone.
 // Range 2, 3 x 378^2, 364 cells: 7.1 us a pass with one attempt per lane deciding
 // in place, 5.9 now; 8 x 510^2, 648 cells: 14.4 and 9.2; range 1, 430^2, 450 cells:
-// 12.1 and 6.1; 8 x 510^2: 16.0 and 8.4.  (A lattice with nothing left to decide, all
-// one id, is the exception: 3.2 us in place and 4.4 for one of 216^2.)
+// 12.1 and 6.1; 8 x 510^2: 16.0 and 8.4.  With range 2 a lattice all of one cell is
+// known by that cell's area and ends before its draws (216^2: 3.2 us, in place 3.1,
+// without that 4.2; it costs the others 0.1).
 template <int RANGE, bool TAB>
 __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile* tiles, int c,
                                                        int sweep_off, int tab_lds_bytes,
@@ -1219,9 +1220,11 @@ __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile*
         const int r = mdiv(i, mS);
         return gids[(size_t)wrapc(y0 + r - h, Ly) * Lx + wrapc(i - r * st - h, Lx)];
     };
+    const int32_t id0 = RANGE == 2 ? gids[(size_t)y0 * Lx] : 0;
 #pragma unroll
     for (int u = 0; u < kU; ++u)
         if (tid + u * nthr < nd) v[u] = load(tid + u * nthr);
+    const int32_t area0 = RANGE == 2 ? pa.s_rd[id0] + pa.d_rd[id0] : 0;
     constexpr int kC = 2;
     int32_t sv[kC], av[kC];
     uint8_t tv[kC];
@@ -1263,6 +1266,8 @@ __global__ void __launch_bounds__(512) k_cpm_pass_band(CpmArgs a, const CpmTile*
     for (int i = tid + kU * nthr; i < nd; i += nthr) lids[i] = (uint32_t)load(i);
     pass_rotate(a, PP);
     __syncthreads();
+    // a lattice all of one cell has nothing to decide
+    if (RANGE == 2 && __builtin_amdgcn_readfirstlane(area0) == Lx * Ly) return;
     const int cy = c / P, cx = c - P * cy;
     const int Wc = Lx / P, k0 = y0 / P * Wc, n = rows / P * Wc;  // the band's sites k0 .. k0 + n - 1
     const int blk0 = k0 >> 2, n_blk = ((k0 + n + 3) >> 2) - blk0;

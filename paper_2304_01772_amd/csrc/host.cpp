@@ -2152,7 +2152,8 @@ bool cpm_per_site(const spinmc_ctx* c) {
 // per lane), 4096 where that leaves compute units without a tile (8 x 256^2:
 // 5.3 against 5.8 us a pass; 8 x 512^2: 6.5 with 8192, 7.2 with 4096; in
 // workgroups of 256 lanes 8.1 at best); fewer where the LDS asks for it.
-// Bands (every other lattice): the fewest rows, of 2048 sites or more, that leave
+// Bands (every other lattice): the fewest rows, of 2048 sites or more (range 2: 1024;
+// 216^2 6 rows 5.6 us a pass, 12 rows 5.8; 300^2 6 rows 5.7, 9 rows 5.9), that leave
 // no compute unit two bands (range 2, 3 x 378^2: 6 rows, 189 bands, 6.3 us a pass,
 // 3 rows 7.2, 9 rows 6.5; 8 x 510^2: 18 rows, 232 bands, 9.1, 15 rows, 272 bands,
 // 10.3; range 1, 8 x 510^2: 16 rows, 256 bands, 8.3, 12 rows 9.5; 256 lanes are
@@ -2172,7 +2173,7 @@ int cpm_build_ctiles(spinmc_ctx* c) {
         return std::max(P, ((per + h.dev.Lx - 1) / h.dev.Lx + P - 1) / P * P);
     };
     if (!c->cpm_quad) {
-        for (per = 2048;; per += 512) {
+        for (per = c->cpm_range == 2 ? 1024 : 2048;; per += 512) {
             size_t bands = 0;
             for (const HostRep& h : c->reps)
                 bands += (size_t)((h.dev.Ly + band_rows(h) - 1) / band_rows(h));

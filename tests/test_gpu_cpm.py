@@ -612,3 +612,28 @@ def test_wg_threads_alone_changes_the_passes(S, cpm_range, shape, per_site):
         t += 3
         assert np.array_equal(smp.get_state(0), ids), threads
     smp.close()
+
+
+# 5x5 lattices of one cell (nothing to decide, and known by its area), of the medium, and
+# of all but one site, beside an ordinary one
+def test_uniform_lattices_in_bands_match_oracle(S):
+    J = JS["sorting"]
+    shape = (30, 42)
+    cases = [_random_case(680 + r, shape, 6) for r in range(4)]
+    cases[0][0][:] = 3
+    cases[1][0][:] = 0
+    cases[2][0][:] = 2
+    cases[2][0][17, 29] = 0
+    reps = [_rep5(ids, J, ct, A, 1.0, 12.0, 95 + r) for r, (ids, ct, A) in enumerate(cases)]
+    smp = S(reps, 59, init=False)
+    smp.set_schedule(mode="stream")
+    for r, (ids, _, _) in enumerate(cases):
+        smp.set_state(r, ids)
+    st = smp.sweep(6, 2).cpu().numpy()
+    smp.sweep(3)
+    for r, (ids, ct, A) in enumerate(cases):
+        s1, _, ost = orc.cpm_run(ids, J, ct, A, 1.0, 12.0, 59, 95 + r, 0, 6, 2, nrange=2)
+        want, _, _ = orc.cpm_run(s1, J, ct, A, 1.0, 12.0, 59, 95 + r, 6, 3, nrange=2)
+        assert np.array_equal(smp.get_state(r), want), r
+        assert np.array_equal(st[:, r], ost), r
+    smp.close()
