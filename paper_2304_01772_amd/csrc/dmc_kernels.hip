@@ -882,20 +882,26 @@ namespace {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Lanes of the resident form with NI rows a lane, or 0 where it does not fit.
-// Lattices up to 2^14 sites (8-column spans; the aligned buffers of the span
-// kernels).  Forward: 2 rows a lane, up to 1024 lanes.  Backward: 2 rows up to
-// 512 lanes (2^13 sites), 4 above, where the state of a lane fills 256
-// registers; that form's passes of one workgroup take 10 us, so it pays from
-// 24 replicas on (128 x 128, 10 sweeps: 213 us against 314 for a launch per
-// pass at 64 replicas, 203 against 198 at 16).  256 replicas of 128 x 128, 10
-// sweeps: forward 297 -> 95 us, backward 811 -> 203; 64 x 64, 4 replicas,
-// with the calls around it: forward 126 -> 60, backward 212 -> 103.  Separate inputs
-// and outputs spare the caller four copies and two fills of its arrays (16 MB each
-// there: 40 us).
-int res_lanes(const DmcArgs& a, int NI, int max_lanes) {
+// Lanes of the resident form with NI rows a lane, or 0 where it does not fit or is the
+// slower.  Lattices up to 2^14 sites (8-column spans; the aligned buffers of the span
+// kernels).  One workgroup a replica, so that few replicas leave the chip to a launch per
+// pass: the forms below take them from a number of sites of all replicas on, where both
+// were measured equal (us of 20 sweeps, resident and a launch per pass).
+// Forward: 2 rows a lane, up to 1024 lanes; beyond 768 (a fourth wave a SIMD) from 2^19
+// sites: 128 x 128, 1 replica 142 and 119, 24 144 and 136, 32 144 and 144, 64 144 and
+// 199; 112 x 128, 32 replicas 147 and 140, 48 146 and 168; 96 x 128 at any number 113 to
+// 118 and 117 to 236.
+// Backward: 2 rows up to 512 lanes (2^13 sites), 4 above, where the state of a lane fills
+// 256 registers, from 400000 sites: 96 x 96, 32 replicas 273 and 244, 48 274 and 280;
+// 128 x 128, 24 replicas 268 and 273, 64 274 and 449.
+// 256 replicas of 128 x 128, 10 sweeps: forward 297 -> 95 us, backward 811 -> 203; 64 x
+// 64, 4 replicas, with the calls around it: forward 126 -> 60, backward 212 -> 103.
+// Separate inputs and outputs spare the caller four copies and two fills of its arrays
+// (16 MB each there: 40 us).
+int res_lanes(const DmcArgs& a, int NI, int max_lanes, int any_lanes, int64_t min_sites) {
     if (a.Ly % NI != 0) return 0;
     const int64_t lanes = (int64_t)(a.Ly / NI) * (a.Lx >> 3);
+    if (lanes > any_lanes && (int64_t)a.R * a.Lx * a.Ly < min_sites) return 0;
     return lanes <= max_lanes ? (int)lanes : 0;
 }
 
@@ -916,7 +922,7 @@ hipError_t launch_dmc_forward(const DmcArgs& a, uint64_t t0, int n_sweeps, float
                     aligned16(a.s_copy) && aligned16(a.Jx) && aligned16(a.Jy) && aligned16(save);
     const size_t bytes = sizeof(float) * a.R * a.Lx * a.Ly;
     const int n_blocks = (n_sites + 3) >> 2;
-    if (const int lanes = v8 ? res_lanes(a, 2, 1024) : 0) {
+    if (const int lanes = v8 ? res_lanes(a, 2, 1024, 768, (int64_t)1 << 19) : 0) {
         DmcArgs b = a;
         uint32_t p0 = (uint32_t)(2 * t0);
         void* args[] = {&b, &p0, &n_sweeps, &save};
@@ -951,8 +957,8 @@ hipError_t launch_dmc_backward(const DmcArgs& a, uint64_t t0, int n_sweeps, cons
                     aligned16(work);
     const int n_blocks = (n_sites + 3) >> 2;
     {
-        const int l2 = v8 && n_sweeps > 0 ? res_lanes(a, 2, 512) : 0;
-        const int l4 = v8 && n_sweeps > 0 && l2 == 0 && a.R >= 24 ? res_lanes(a, 4, 512) : 0;
+        const int l2 = v8 && n_sweeps > 0 ? res_lanes(a, 2, 512, 512, 0) : 0;
+        const int l4 = v8 && n_sweeps > 0 && l2 == 0 ? res_lanes(a, 4, 512, 0, 400000) : 0;
         DmcArgs b = a;
         uint32_t p0 = (uint32_t)(2 * t0);
         int fr = fresh ? 1 : 0;

@@ -212,3 +212,30 @@ def test_resident_chain_at_its_limits(R, Ly, Lx, n):
         assert np.all(np.isfinite(got))
         scale = max(1.0, float(np.abs(ref).max()))
         np.testing.assert_allclose(got[pick], ref, rtol=0, atol=2e-4 * scale)
+
+
+# the resident forms' rules at their edges: lanes of a replica, sites of all
+@pytest.mark.parametrize("R,Ly,Lx,fwd,bwd", [
+    (1, 64, 128, True, True), (1, 64, 192, True, False), (1, 66, 192, False, False),
+    (1, 128, 128, False, False), (24, 128, 128, False, False), (25, 128, 128, False, True),
+    (31, 128, 128, False, True), (32, 128, 128, True, True), (45, 64, 136, True, False),
+    (46, 64, 136, True, True)])
+def test_resident_chain_where_it_is_the_faster(R, Ly, Lx, fwd, bwd):
+    from paper_2304_01772_amd.dmc import relaxed_ising
+    s0, Jx, Jy, g = _case(R * 5 + Lx + Ly, R, Ly, Lx)
+    beta, alpha, h = 0.5, 6.0, float(np.float32(0.02))
+    s0t, jx, jy = (torch.tensor(v, device="cuda", requires_grad=True) for v in (s0, Jx, Jy))
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        s = relaxed_ising(s0t, jx, jy, beta, alpha, h, 2, 98, 3, 5)
+        (s * torch.tensor(g, device="cuda")).sum().backward()
+        torch.cuda.synchronize()
+    names = " ".join(e.key for e in prof.key_averages())
+    assert ("k_dmc_resident_fwd" in names) == fwd and ("k_dmc_pass8" in names) != fwd, names
+    assert ("k_dmc_resident_bwd" in names) == bwd and ("k_dmc_back8" in names) != bwd, names
+    pick = sorted({0, R - 1})
+    want, gs0, gJx, gJy, _ = odmc.forward_backward(s0[pick], Jx[pick], Jy[pick], h, beta, alpha, 98,
+                                                   [5 + r for r in pick], 3, 2, g[pick])
+    np.testing.assert_allclose(s.detach().cpu().numpy()[pick], want, rtol=0, atol=2e-5)
+    for got, ref in ((s0t.grad, gs0), (jx.grad, gJx), (jy.grad, gJy)):
+        scale = max(1.0, float(np.abs(ref).max()))
+        np.testing.assert_allclose(got.cpu().numpy()[pick], ref, rtol=0, atol=2e-4 * scale)
