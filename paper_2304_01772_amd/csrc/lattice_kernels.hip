@@ -576,11 +576,11 @@ __device__ __forceinline__ void potts_count(const uint32_t (&nv)[NW], const uint
     }
 }
 
-// Sum over the 16 lanes of a row (the n < 16 lanes of a group, a power of two).
+// Sum over the 16 lanes of a row (the n = 4 or 8 lanes of a group).
 __device__ __forceinline__ int row_sum(int v, int n) {
     // quad_perm 1 0 3 2, quad_perm 2 3 0 1, row_half_mirror, row_mirror
-    if (n > 1) v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
-    if (n > 2) v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
     if (n > 4) v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
     if (n > 8) v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
     return v;
@@ -1199,20 +1199,15 @@ struct RecRows {
         next = every;
         return true;
     }
-    // byte-wise counts; sums of 16 lanes (or of the nt < 16
-    // lanes of a replica) by data-parallel-primitive moves, then LDS atomics
+    // byte-wise counts; sums of 16 lanes (or of the 4 or 8 lanes of a replica: 64 lanes
+    // hold at most 16) by data-parallel-primitive moves, then LDS atomics
     __device__ __forceinline__ void add(uint32_t up, uint32_t dx, uint32_t dy, int nt) {
         const int u = row_sum((int)sad_u8(up, 0u), nt);
         const int b = row_sum((int)(sad_u8(dx, 0u) | (sad_u8(dy, 0u) << 16)), nt);
-        // lanes 0, 1, 2 of a group add one count each (sub-groups below four lanes:
-        // their first lane all)
+        // lanes 0, 1, 2 of a group add one count each
         const int lane = (int)threadIdx.x & (min(nt, 16) - 1);
         const int v[3] = {u, b & 0xFFFF, (int)((uint32_t)b >> 16)};
-        if (nt >= 4) {
-            if (lane < 3) atomicAdd(&l[n][lane], lane == 0 ? v[0] : lane == 1 ? v[1] : v[2]);
-        } else if (lane == 0) {
-            for (int k = 0; k < 3; ++k) atomicAdd(&l[n][k], v[k]);
-        }
+        if (lane < 3) atomicAdd(&l[n][lane], lane == 0 ? v[0] : lane == 1 ? v[1] : v[2]);
     }
     // stores (SLAB: adds, the rows hold zeros or other slabs' shares) and clears
     // the rows; the replica's lanes meet before and after.  N: the sites counted.
