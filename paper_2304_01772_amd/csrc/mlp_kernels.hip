@@ -50,30 +50,26 @@ __device__ __forceinline__ float4v mfma(bf16x8 a, bf16x8 b, float4v c) {
 // --------------------------------------------------------------- forward
 namespace {
 
-// Sigmoids of four values, 1 / d with d = 1 + e^-z >= 1, bit for bit the IEEE
-// division's: as v_rcp_f32 and one Newton step, which give the same for every d up to
-// 2^126 (all 1.06e9 compared on the card) in four instructions for its ten.  Beyond, they
-// give 0: v_rcp_f32 flushes the subnormal result, and the maximum turns the step's
-// inf * 0 at an infinite d into it.  Then the divisions: kChecked behind a branch for the
-// four values, kFast by the caller, who finds the 0 in the products, kDiv at once.
-enum { kFast, kChecked, kDiv };
-template <int HOW>
-__device__ __forceinline__ float4v sigm4(float4v z) {
-    float4v s;
-    if (HOW != kDiv) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float d = 1.0f + __expf(-z[i]), r = __builtin_amdgcn_rcpf(d);
-            s[i] = fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), 0.0f);
-        }
-        if (HOW == kFast ||
-            __builtin_expect(fminf(fminf(s[0], s[1]), fminf(s[2], s[3])) != 0.0f, 1))
-            return s;
-        asm volatile("" : "+v"(z));  // kept behind the branch
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] = 1.0f / (1.0f + __expf(-z[i]));
-    return s;
+// Four times the sigmoid, 1 / a with a = (1 + e^-z) / 4, as v_rcp_f32 and one Newton
+// step: bit for bit the IEEE division's for every a from 1/4 to 2^126 (all 1.08e9
+// compared on the card) in three instructions for its ten, and never subnormal, which
+// v_rcp_f32 would flush.  At an infinite a, where the sigmoid is 0, the step is 0 * inf:
+// GUARD takes the maximum with 0; without, a NaN that reaches the outputs tells.
+template <bool GUARD>
+__device__ __forceinline__ float sigm_x4(float z) {
+    const float a = __builtin_fmaf(__expf(-z), 0.25f, 0.25f);
+    const float r = __builtin_amdgcn_rcpf(a);
+    const float s = __builtin_fmaf(__builtin_fmaf(-a, r, 1.0f), r, r);
+    return GUARD ? fmaxf(s, 0.0f) : s;
+}
+// z / 4 first: exact, where the sigmoid alone would be subnormal
+template <bool GUARD>
+__device__ __forceinline__ float silu(float z) {
+    return 0.25f * z * sigm_x4<GUARD>(z);
+}
+__device__ __forceinline__ float dsilu(float z) {
+    const float s = sigm_x4<true>(z);
+    return 0.25f * (1.0f + z * (1.0f - 0.25f * s)) * s;
 }
 
 // two values as BF16 in one word (v_cvt_pk_bf16_f32, nearest even), a low
@@ -102,19 +98,10 @@ struct FwdWeights {
 };
 
 // silu(z) as the BF16 words of row tile nt
-template <int HOW>
+template <bool GUARD>
 __device__ __forceinline__ void put_silu(uint32_t (&h)[16], int nt, const float4v& z) {
-    const float4v v = z * sigm4<HOW>(z);
-    h[2 * nt] = pk_bf(v[0], v[1]);
-    h[2 * nt + 1] = pk_bf(v[2], v[3]);
-}
-
-// Least halves of words, as signed numbers: -0.0, the product of a 0 from sigm4, is the
-// least of all.
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ s16x2 least(s16x2 a, uint32_t u, uint32_t v) {
-    return __builtin_elementwise_min(a, __builtin_elementwise_min(__builtin_bit_cast(s16x2, u),
-                                                                  __builtin_bit_cast(s16x2, v)));
+    h[2 * nt] = pk_bf(silu<GUARD>(z[0]), silu<GUARD>(z[1]));
+    h[2 * nt + 1] = pk_bf(silu<GUARD>(z[2]), silu<GUARD>(z[3]));
 }
 
 __device__ __forceinline__ uint4 pk8(const float4& u, const float4& v) {
@@ -190,31 +177,29 @@ __device__ __forceinline__ float4v plus(const float4v& z, const float4& b) {
     return float4v{z[0] + b.x, z[1] + b.y, z[2] + b.z, z[3] + b.w};
 }
 
-// The lane, and the end of a row tile.  kDiv is a repetition behind a branch that is
+// The lane, and the end of a row tile.  GUARD is a repetition behind a branch that is
 // hardly ever taken: the lane is opaque and the tiles stay in sequence, since otherwise
 // the compiler keeps the first run's operands for it, in twice the registers.
-template <int HOW>
+template <bool GUARD>
 __device__ __forceinline__ int own_lane() {
     int l = (int)threadIdx.x & 63;
-    if (HOW == kDiv) asm volatile("" : "+v"(l));
+    if (GUARD) asm volatile("" : "+v"(l));
     return l;
 }
-template <int HOW>
+template <bool GUARD>
 __device__ __forceinline__ void tile_end() {
-    if (HOW == kDiv) __builtin_amdgcn_sched_barrier(0);
+    if (GUARD) __builtin_amdgcn_sched_barrier(0);
 }
 
 // Both hidden layers for C tiles of 16 samples (lane l of tile c: sample
 // s[c], neurons tile_neuron(nt, l / 16) + i): the pre-activations go to act if it
-// is given, h2 receives the B operands of the output layer.  Returns the activations'
-// least halves (kFast): with a -0.0 in any lane the wave repeats its tiles with kDiv.
-template <int C, int HOW>
-__device__ __forceinline__ s16x2 hidden_layers(const FwdWeights& S, const uint4 (&xb)[C],
-                                               const size_t (&s)[C], int B, float* act, bool vec,
-                                               uint32_t (&h2)[C][16]) {
-    const int l = own_lane<HOW>(), g = l >> 4;
+// is given, h2 receives the B operands of the output layer.
+template <int C, bool GUARD>
+__device__ __forceinline__ void hidden_layers(const FwdWeights& S, const uint4 (&xb)[C],
+                                              const size_t (&s)[C], int B, float* act, bool vec,
+                                              uint32_t (&h2)[C][16]) {
+    const int l = own_lane<GUARD>(), g = l >> 4;
     uint32_t h1[C][16];
-    s16x2 low = {0, 0};
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
         const int n0 = tile_neuron(nt, g);
@@ -224,10 +209,9 @@ __device__ __forceinline__ s16x2 hidden_layers(const FwdWeights& S, const uint4 
         for (int c = 0; c < C; ++c) {
             const float4v z = plus(mfma(w, as_frag(xb[c]), float4v{0.f, 0.f, 0.f, 0.f}), b);
             if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + n0, z, vec);
-            put_silu<HOW>(h1[c], nt, z);
-            if (HOW == kFast) low = least(low, h1[c][2 * nt], h1[c][2 * nt + 1]);
+            put_silu<GUARD>(h1[c], nt, z);
         }
-        tile_end<HOW>();
+        tile_end<GUARD>();
     }
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
@@ -248,12 +232,10 @@ __device__ __forceinline__ s16x2 hidden_layers(const FwdWeights& S, const uint4 
         for (int c = 0; c < C; ++c) {
             z[c] = plus(z[c], b);
             if (act && s[c] < (size_t)B) store_act(act + s[c] * 2 * kH + kH + n0, z[c], vec);
-            put_silu<HOW>(h2[c], nt, z[c]);
-            if (HOW == kFast) low = least(low, h2[c][2 * nt], h2[c][2 * nt + 1]);
+            put_silu<GUARD>(h2[c], nt, z[c]);
         }
-        tile_end<HOW>();
+        tile_end<GUARD>();
     }
-    return low;
 }
 
 // The same for one tile with the pre-activations kept.
@@ -265,7 +247,7 @@ __device__ __forceinline__ void hidden_layers_z(const FwdWeights& S, const uint4
     for (int nt = 0; nt < 8; ++nt) {
         z1[nt] = plus(mfma(as_frag(S.w1[nt * 64 + l]), as_frag(xb), float4v{0.f, 0.f, 0.f, 0.f}),
                       S.b1[tile_neuron(nt, g) >> 2]);
-        put_silu<kChecked>(h1, nt, z1[nt]);
+        put_silu<true>(h1, nt, z1[nt]);
     }
 #pragma unroll
     for (int nt = 0; nt < 8; ++nt) {
@@ -275,7 +257,7 @@ __device__ __forceinline__ void hidden_layers_z(const FwdWeights& S, const uint4
             z = mfma(as_frag(S.w2[(nt * 4 + kt) * 64 + l]),
                      as_frag(make_uint4(h1[4 * kt], h1[4 * kt + 1], h1[4 * kt + 2], h1[4 * kt + 3])), z);
         z2[nt] = plus(z, S.b2[tile_neuron(nt, g) >> 2]);
-        put_silu<kChecked>(h2, nt, z2[nt]);
+        put_silu<true>(h2, nt, z2[nt]);
     }
 }
 
@@ -294,16 +276,17 @@ __device__ __forceinline__ float4v output_layer(const FwdWeights& S, const uint3
 
 namespace {
 
-// The tile groups of a wave, from q on in steps of dq.
-template <int C, bool AFF, int HOW>
-__device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float* P, const float* x,
-                                               int B, float* y, float* act, const Affine& af, int q,
-                                               int dq) {
-    const int l = own_lane<HOW>(), g = l >> 4;
+// The tile groups of a wave, from q on in steps of dq.  Returns true in a lane whose
+// outputs hold a NaN.
+template <int C, bool AFF, bool GUARD>
+__device__ __forceinline__ bool forward_tiles(const FwdWeights& S, const float* P, const float* x,
+                                              int B, float* y, float* act, const Affine& af, int q,
+                                              int dq) {
+    const int l = own_lane<GUARD>(), g = l >> 4;
     const bool vec = ((uintptr_t)x & 15u) == 0, avec = ((uintptr_t)act & 15u) == 0;
     const float bo[3] = {P[ob3], P[ob3 + 1], P[ob3 + 2]};
     const int groups = (B - 1) / (16 * C) + 1;  // (no sum that passes 32 bits)
-    s16x2 low = {0, 0};
+    float sum = 0.f;  // of the outputs before the scaling: NaN if any is
     // the first run of one tile a wave (C = 1) needs no loop: the grid covers the samples
     do {
         uint4 xb[C];
@@ -325,7 +308,7 @@ __device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float*
             }
         }
         uint32_t h2[C][16];
-        low = __builtin_elementwise_min(low, hidden_layers<C, HOW>(S, xb, s, B, act, avec, h2));
+        hidden_layers<C, GUARD>(S, xb, s, B, act, avec, h2);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const float4v o = output_layer(S, h2[c]);
@@ -333,14 +316,15 @@ __device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float*
 #pragma unroll
                 for (int j = 0; j < kOut; ++j) {
                     float v = o[j] + bo[j];
+                    sum += 0.0f * v;
                     if (AFF) v = v * af.sd[j] + af.mu[j];
                     y[s[c] * kOut + j] = v;
                 }
             }
         }
         q += dq;
-    } while ((HOW == kDiv || C > 1) && q < groups);
-    return low;
+    } while ((GUARD || C > 1) && q < groups);
+    return sum != sum;
 }
 
 }  // namespace
@@ -351,20 +335,21 @@ __device__ __forceinline__ s16x2 forward_tiles(const FwdWeights& S, const float*
 // half of it the quarter-rate exponential and reciprocal); the matrix
 // products take a sixth of that.  10^5 points: 82 us with a
 // workgroup (and its own staging and conversion of the weights) per 64
-// samples and activations through LDS; 26.8 with divisions in the SiLUs, 21.9 now.
+// samples and activations through LDS; 26.8 with divisions in the SiLUs, 21.8 now.
+// Registers for four waves a SIMD: the two workgroups a unit that the grid asks for.
 template <int C, bool AFF>
-__global__ void __launch_bounds__(512) k_mlp_fwd(const float* P, const float* x, int B, float* y,
-                                                 float* act, Affine af) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_mlp_fwd(const float* P, const float* x, int B, float* y, float* act, Affine af) {
     __shared__ FwdWeights S;
     stage_fwd(P, S);
     __syncthreads();
     const int waves = (int)blockDim.x >> 6;
     const int q = (int)blockIdx.x * waves + ((int)threadIdx.x >> 6), dq = (int)gridDim.x * waves;
     if (q > (B - 1) / (16 * C)) return;
-    const s16x2 low = forward_tiles<C, AFF, kFast>(S, P, x, B, y, act, af, q, dq);
-    if (__any(min(low.x, low.y) == -32768))
+    // a wave with a NaN repeats its tiles with the guard
+    if (__any(forward_tiles<C, AFF, false>(S, P, x, B, y, act, af, q, dq)))
         for (int t = q * C; t < q * C + C && t <= (B - 1) / 16; ++t)
-            forward_tiles<1, AFF, kDiv>(S, P, x, B, y, act, af, t, dq * C);
+            forward_tiles<1, AFF, true>(S, P, x, B, y, act, af, t, dq * C);
 }
 
 // -------------------------------------------------------------- backward
@@ -411,12 +396,6 @@ __device__ __forceinline__ void stage_w2t(const float* P, uint4* w2t) {
 
 __device__ __forceinline__ float bf_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
-
-// silu'(z)
-__device__ __forceinline__ float4v dsilu4(const float4v& z) {
-    const float4v s = sigm4<kChecked>(z);
-    return s * (1.0f + z * (1.0f - s));
-}
 
 // Sums over the workgroup's 64 samples of v[sample][neuron] ba[sample][col]
 // for the wave's neuron tile, on FP32 matrix instructions: lane l holds
@@ -499,8 +478,8 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
         }
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-            put_silu<kChecked>(h1, nt, z1[nt]);
-            put_silu<kChecked>(h2, nt, z2[nt]);
+            put_silu<true>(h1, nt, z1[nt]);
+            put_silu<true>(h2, nt, z2[nt]);
         }
     }
     if (!in) {  // samples past B: nothing to add
@@ -534,7 +513,6 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
         float4 v[kOut];
 #pragma unroll
         for (int j = 0; j < kOut; ++j) v[j] = S.w3[j][n0 >> 2];
-        const float4v ds = dsilu4(z2[nt]);
         float4v d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -542,7 +520,7 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
 #pragma unroll
             for (int j = 0; j < kOut; ++j)
                 dh += dY[j] * (i == 0 ? v[j].x : (i == 1 ? v[j].y : (i == 2 ? v[j].z : v[j].w)));
-            d[i] = in ? dh * ds[i] : 0.f;
+            d[i] = in ? dh * dsilu(z2[nt][i]) : 0.f;
         }
         *reinterpret_cast<float4v*>(S.dz + row * kSF + n0) = d;
         dzb[2 * nt] = pk_bf(d[0], d[1]);
@@ -606,9 +584,8 @@ __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x,
             acc = mfma(as_frag(S.w2t[(nt * 4 + kt) * 64 + l]),
                        as_frag(make_uint4(dzb[4 * kt], dzb[4 * kt + 1], dzb[4 * kt + 2],
                                           dzb[4 * kt + 3])), acc);
-        const float4v ds = dsilu4(z1[nt]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) d1[nt][i] = in ? acc[i] * ds[i] : 0.f;
+        for (int i = 0; i < 4; ++i) d1[nt][i] = in ? acc[i] * dsilu(z1[nt][i]) : 0.f;
     }
     if (dx) {
         // each lane its 32 neurons, then the four lanes of the sample
