@@ -526,8 +526,9 @@ def dmc_probe(torch, R=256, L=128, sweeps=10):
     """Differentiable Monte Carlo (relaxed chain of Algorithm 2): R replicas
     of L x L with per-bond couplings, `sweeps` sweeps forward and the reverse
     replay, timed with HIP events (best of five calls); algorithmic HBM bytes with the
-    lattices resident: forward 4 per attempt (the saved spin) and 16 per site
-    and call (spin and two couplings read, spin written), backward 4 per
+    lattices resident: forward 4 per attempt (the saved spin) and 20 per site
+    and call (spin and two couplings read, the final spin written to both
+    outputs, the replay's and the caller's), backward 4 per
     attempt and 28 per site and call (output spin and its gradient, two
     couplings read; three gradients written)."""
     from paper_2304_01772_amd.dmc import relaxed_ising
@@ -551,7 +552,7 @@ def dmc_probe(torch, R=256, L=128, sweeps=10):
         torch.cuda.synchronize()
         fwd_ms, bwd_ms = min(fwd_ms, e0.elapsed_time(e1)), min(bwd_ms, e2.elapsed_time(e3))
     att = R * L * L * sweeps
-    fwd_b, bwd_b = 4 + 16 / sweeps, 4 + 28 / sweeps
+    fwd_b, bwd_b = 4 + 20 / sweeps, 4 + 28 / sweeps
     return {"config": f"{R} Ising replicas of {L}x{L}, per-bond couplings, {sweeps} sweeps, "
                       "alpha 10, beta 0.5",
             "kernel": "k_dmc_resident_fwd / k_dmc_resident_bwd", "bound": "alu",
