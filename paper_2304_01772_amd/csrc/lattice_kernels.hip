@@ -1475,7 +1475,7 @@ __device__ __forceinline__ void store_planes8(uint8_t* gmem, const uint8_t* lds,
 // The resident kernel for items of eight sites: a lane takes one Philox block a
 // pass instead of four, so a small lattice spreads over four times as many lanes
 // and a pass is a quarter of the chain of instructions.  It serves lattices
-// whose waves leave the chip idle (one 32 x 32 lattice, recorded: 0.9 us a sweep
+// whose waves leave the chip idle (one 32 x 32 lattice, recorded: 0.8 us a sweep
 // against 2.7) and, without AL, every other width from 18 on (k_resident_generic
 // draws a block for every site: 100 lattices of 300 x 300, 20 sweeps and the
 // gradients 2064 us, now 405).
@@ -1830,8 +1830,7 @@ __global__ void k_init(const RepDev* reps, const int32_t* list, uint8_t* lat, ui
     }
 }
 
-// Statistics of the current state: grid (tiles of natural sites, replicas).
-// Statistics of every lattice.  Rows of whole 16-site chunks count as a recorded
+// Statistics of every lattice, grid (parts of a lattice, replicas).  Rows of whole 16-site chunks count as a recorded
 // colour-1 pass does, other widths site by site; Potts labels gather in LDS (one
 // atomic a site in memory took 9 ms for 512 lattices of up to 1024 x 1024, now
 // about 100 us).

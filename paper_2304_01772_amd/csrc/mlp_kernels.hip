@@ -331,11 +331,12 @@ __device__ __forceinline__ bool forward_tiles(const FwdWeights& S, const float* 
 
 // A wave takes C tiles of 16 samples at a time, tile groups strided over the
 // launch's waves, so that the weights are staged once per workgroup.  Bound
-// by the VALU work of the SiLUs (256 a sample, about 60 lane-cycles each,
-// half of it the quarter-rate exponential and reciprocal); the matrix
-// products take a sixth of that.  10^5 points: 82 us with a
-// workgroup (and its own staging and conversion of the weights) per 64
-// samples and activations through LDS; 26.8 with divisions in the SiLUs, 21.8 now.
+// by vector issue, most of it the SiLUs (256 a sample): at 10^5 points 391
+// workgroups share 256 units, and a unit with two issues for 12.9 of the 14.1
+// us that its waves live; the matrix instructions take 2.3 of them.  82 us
+// with a workgroup (and its own staging and conversion of the weights) per 64
+// samples and activations through LDS; a call of predict 26.8 with divisions
+// in the SiLUs, 21.3 now.
 // Registers for four waves a SIMD: the two workgroups a unit that the grid asks for.
 template <int C, bool AFF>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
@@ -422,7 +423,7 @@ __device__ __forceinline__ float4v sample_sums(const float* v, const float (&ba)
 // the sums that stay FP32 (dW1, dW3 and the biases) run on FP32 matrix
 // instructions against one [sample][x | 1 | dY] table.  A step of 1024
 // samples is 16 workgroups, one chain of latencies each: forward and backward
-// as two launches with VALU sums and LDS activations 17.2 + 31.9 us, now 19.5.
+// as two launches with VALU sums and LDS activations 17.2 + 31.9 us, now 20.0.
 template <bool FWD>
 __global__ void __launch_bounds__(256) k_mlp_bwd(const float* P, const float* x, float* act,
                                                  const float* t, const float* w, int B,
