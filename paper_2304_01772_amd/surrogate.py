@@ -91,9 +91,10 @@ class SurrogateMLP:
         B = x.shape[0] if x.dim() == 2 else 0
         # the shapes and types that the kernel reads; others broadcast below
         shapes = ((B, 4), (self.np,), (4,), (4,), (3,), (3,))
-        if B > 0 and all(t.shape == n and t.dtype == torch.float32 and t.device == x.device
-                         and t.is_contiguous() and t.device.type == "cuda"
-                         for t, n in zip(tensors, shapes)) and \
+        dev = x.get_device()  # -1 on the CPU
+        if B > 0 and dev >= 0 and all(t.shape == n and t.dtype == torch.float32
+                                      and t.get_device() == dev and t.is_contiguous()
+                                      for t, n in zip(tensors, shapes)) and \
                 not (self.y_mu.requires_grad or self.y_sd.requires_grad):
             # scaling of inputs and outputs inside the network's kernel
             y = torch.empty((B, 3), dtype=torch.float32, device=x.device)
